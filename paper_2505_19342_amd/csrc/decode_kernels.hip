@@ -13,31 +13,14 @@
 //                          streamed from the cache; non-local rows picked from the value codebook, which stays in L2).
 //   decode_reduce_kernel   merges the chunks of every query head (log-sum-exp weights) and normalises.
 // Everything is fp32 except the stored element type; results do not depend on the run (no atomics).
-#include "common.h"
+// bf16 heads of 64 or 128 with codewords of whole 16-byte pieces take decode_stream_kernels.hip instead of the first two.
+#include "decode_common.h"
 
 #include <algorithm>
 #include <mutex>
 #include <type_traits>
 
 namespace astra {
-
-struct DecodeParams {
-    const void* q;
-    const void* k_loc;
-    const void* v_loc;
-    const void* codes_k;
-    const void* codes_v;
-    const unsigned long long* valid_bits;
-    const void* cb_k;
-    const void* cb_v;
-    void* out;
-    float* lse;
-    float* lut;      // [H_kv][n_gh][K][H_q / H_kv]
-    float* part;     // [n_chunks][H_q][dh + 2]: unnormalised o, then m, l
-    int32_t Hq, Hkv, dh, n_local, n_nonlocal, G, K, dg, code16, n_gh, chunk_loc, chunk_nl, n_chunks_loc, n_chunks_nl;
-    int32_t aux_floats;      // floats of the LDS region shared by the query floats, the table slice and the cross-phase sums
-    float scale;
-};
 
 constexpr int kDecThreads = 256;
 constexpr int kDecMaxRep = 8;       // query heads per KV head served by one workgroup
@@ -63,11 +46,6 @@ __device__ __forceinline__ void ld2<uint16_t>(const uint16_t* p, float& a, float
     const uint32_t v = *reinterpret_cast<const uint32_t*>(p);
     a = __uint_as_float(v << 16);
     b = __uint_as_float(v & 0xffff0000u);
-}
-
-__device__ __forceinline__ int load_code(const void* codes, int code16, int64_t i, int K) {
-    const int c = code16 ? (int)((const uint16_t*)codes)[i] : (int)((const uint8_t*)codes)[i];
-    return c < K ? c : K - 1;
 }
 
 // CPL consecutive elements as floats; the address is aligned to the whole segment
@@ -549,7 +527,8 @@ __device__ __forceinline__ void st_elem<uint16_t>(uint16_t* p, float v) { *p = f
 // gridDim.y workgroups per query head, each with its share of the head's channels (a multiple of gridDim.y): the chunks'
 // statistics are combined in parallel (by every workgroup of the head for itself), then thread (c, part) sums output
 // channel c over the chunks part, part + n_part, ... (several loads in flight), parts added in ascending order
-template <typename T>
+// (BASE2: the chunks' maxima are in base-2 units)
+template <typename T, bool BASE2>
 __global__ __launch_bounds__(kDecThreads) void decode_reduce_kernel(const DecodeParams p) {
     extern __shared__ float w_lds[];                 // [n_chunks] weights exp(m_i - M)
     __shared__ float red[kDecRows][kDecMaxRep];
@@ -568,7 +547,7 @@ __global__ __launch_bounds__(kDecThreads) void decode_reduce_kernel(const Decode
     v[0] = 0.f;
     for (int i = tid; i < n_chunks; i += kDecThreads) {
         const float m = w_lds[i];
-        const float w = m == -INFINITY ? 0.f : expf(m - M);
+        const float w = m == -INFINITY ? 0.f : BASE2 ? exp2f(m - M) : expf(m - M);
         w_lds[i] = w;
         v[0] = fmaf(w, base[i * stride + p.dh + 1], v[0]);
     }
@@ -598,10 +577,11 @@ __global__ __launch_bounds__(kDecThreads) void decode_reduce_kernel(const Decode
         for (int q = 0; q < n_part; ++q) t += os[q * dhp + tid];
         st_elem((T*)p.out + (int64_t)h * p.dh + c_lo + tid, L > 0.f ? t / L : 0.f);
     }
-    if (tid == 0 && blockIdx.y == 0 && p.lse) p.lse[h] = L > 0.f ? M + logf(L) : -INFINITY;
+    if (tid == 0 && blockIdx.y == 0 && p.lse) p.lse[h] = L > 0.f ? (BASE2 ? (M + log2f(L)) * 0.6931471805599453f : M + logf(L)) : -INFINITY;
 }
 
 struct DecodePlan {
+    DecodeStreamPlan stream;
     int n_gh, chunk_loc, chunk_nl, n_chunks_loc, n_chunks_nl, aux_floats;
     size_t lds_loc, lds_nl, off_lut, off_part, total;
 };
@@ -643,7 +623,13 @@ static int make_decode_plan(const astra_decode_desc& d, DecodePlan* pl) {
     if (pl->lds_nl > 150 * 1024) return ASTRA_ERR_UNSUPPORTED;
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, 256); return o; };
-    pl->off_lut = take((size_t)d.n_q_heads * n_gh * d.vq.codebook_size * sizeof(float));
+    pl->stream = plan_decode_stream(d.vq.dtype, d.n_q_heads, d.n_kv_heads, d.head_dim, d.n_local, d.n_nonlocal, d.vq.codebook_size, dg);
+    if (pl->stream.applies) {          // one partial result per workgroup and query head
+        pl->n_chunks_loc = pl->stream.wgs_loc;
+        pl->n_chunks_nl = pl->stream.wgs_nl;
+    } else {
+        pl->off_lut = take((size_t)d.n_q_heads * n_gh * d.vq.codebook_size * sizeof(float));
+    }
     pl->off_part = take((size_t)(pl->n_chunks_loc + pl->n_chunks_nl) * d.n_q_heads * (d.head_dim + 2) * sizeof(float));
     pl->total = off > 0 ? off : 256;
     return ASTRA_OK;
@@ -667,18 +653,31 @@ static int launch_partial(const DecodeParams& p, const DecodePlan& pl, hipStream
 
 template <typename T, int REP>
 static int launch_partial_dh(const DecodeParams& p, const DecodePlan& pl, hipStream_t s) {
-    if (p.dg % 8 == 0 && p.dh == 128) return launch_partial<T, 128, REP>(p, pl, s);
-    if (p.dg % 8 == 0 && p.dh == 64) return launch_partial<T, 64, REP>(p, pl, s);
+    if constexpr (sizeof(T) == 4) {         // bf16: decode_stream_kernels.hip
+        if (p.dg % 8 == 0 && p.dh == 128) return launch_partial<T, 128, REP>(p, pl, s);
+        if (p.dg % 8 == 0 && p.dh == 64) return launch_partial<T, 64, REP>(p, pl, s);
+    }
     return launch_partial<T, 0, REP>(p, pl, s);
 }
 
 template <typename T>
 static int run_decode(const DecodeParams& p, const DecodePlan& pl, hipStream_t s) {
+    const int n_chunks = p.n_chunks_loc + p.n_chunks_nl;
+    // long caches: a head's channels over four workgroups, so that each thread walks an eighth of the chunks, not half
+    const int slices = p.dh % 4 == 0 && n_chunks > 64 ? 4 : 1;
+    const dim3 reduce_grid(p.Hq, slices);
+    const size_t reduce_lds = (size_t)std::max(1, n_chunks) * sizeof(float);
+    int rc;
+    if (pl.stream.applies) {
+        rc = launch_decode_stream(p, pl.stream, s);
+        if (rc) return rc;
+        decode_reduce_kernel<T, true><<<reduce_grid, kDecThreads, reduce_lds, s>>>(p);
+        return launch_status();
+    }
     if (p.n_chunks_nl > 0) {
         const int64_t n = (int64_t)p.Hq * p.n_gh * ceil_div(p.K, kDecThreads);
         decode_lut_kernel<T><<<(int)n, kDecThreads, 0, s>>>(p);
     }
-    int rc;
     switch (p.Hq / p.Hkv) {
         case 1: rc = launch_partial_dh<T, 1>(p, pl, s); break;
         case 2: rc = launch_partial_dh<T, 2>(p, pl, s); break;
@@ -687,9 +686,7 @@ static int run_decode(const DecodeParams& p, const DecodePlan& pl, hipStream_t s
         default: return ASTRA_ERR_UNSUPPORTED;
     }
     if (rc) return rc;
-    // long caches: a head's channels over four workgroups, so that each thread walks an eighth of the chunks, not half
-    const int slices = p.dh % 4 == 0 && p.n_chunks_loc + p.n_chunks_nl > 64 ? 4 : 1;
-    decode_reduce_kernel<T><<<dim3(p.Hq, slices), kDecThreads, (size_t)std::max(1, p.n_chunks_loc + p.n_chunks_nl) * sizeof(float), s>>>(p);
+    decode_reduce_kernel<T, false><<<reduce_grid, kDecThreads, reduce_lds, s>>>(p);
     return launch_status();
 }
 
@@ -700,7 +697,7 @@ using namespace astra;
 extern "C" {
 
 size_t astra_decode_attention_workspace_bytes(const astra_decode_desc* desc) {
-    DecodePlan pl;
+    DecodePlan pl{};
     if (!desc || make_decode_plan(*desc, &pl) != ASTRA_OK) return 0;
     return pl.total;
 }
@@ -734,7 +731,7 @@ static int decode_attention_impl(const astra_decode_desc* desc, const void* q, c
                                  const void* codebook_v, void* out, float* lse_out, void* workspace, size_t workspace_bytes,
                                  bool library_scratch, void* stream) {
     if (!desc) return ASTRA_ERR_NULL;
-    DecodePlan pl;
+    DecodePlan pl{};
     int rc = make_decode_plan(*desc, &pl);
     if (rc) return rc;
     if (!q || !out) return ASTRA_ERR_NULL;

@@ -138,3 +138,20 @@ def test_argument_errors():
     odd = B.DecodeDesc(B.vq_desc("bf16", 768, 256, 256), 12, 12, 64, 10, 10, 0.0)      # groups of 3 channels
     with pytest.raises(B.AstraError, match="no kernel"):
         B.astra_decode_attention(odd, t, t, t, t, t, None, t, t, t, None, t)
+
+
+@pytest.mark.parametrize("hq,hkv,dh,groups,K,n_local,n_nonlocal", [
+    (16, 16, 64, 16, 16, 33, 8300),       # score table, one group per head, 16 columns per head
+    (32, 16, 64, 32, 260, 31, 8321),      # score table, two groups; a codebook that is no whole number of 16-codeword tiles
+    (64, 8, 128, 32, 256, 1, 16500),      # score table, eight query heads per KV head: two look-ups per column
+    (32, 8, 128, 16, 1020, 130, 16417),   # score table, two groups of two contraction steps
+    (64, 8, 128, 32, 1024, 65, 97),       # gathered keys, eight query heads per KV head, one token beyond a tile
+    (4, 2, 128, 2, 48, 32, 31),           # gathered keys, one group per head, whole and one-short tiles
+    (6, 3, 64, 12, 20, 161, 33),          # gathered keys, groups of 16 channels: two per contraction step
+    (6, 3, 64, 8, 20, 64, 64),            # groups of 24 channels that straddle contraction steps and heads
+])
+def test_matrix_core_forms(hq, hkv, dh, groups, K, n_local, n_nonlocal):
+    """The bf16 step's tiles of 32 tokens, its two ways to score index rows and its cuts of a head into groups, with a few tokens lost."""
+    cfg = wl.LayerConfig("step", "bf16", 256, hq, hkv, dh, 1024, 4, groups, K, causal=True, seed=31)
+    valid = (np.random.default_rng(n_nonlocal).random(n_nonlocal) > 0.1).astype(np.uint8)
+    run_case(cfg, n_local, n_nonlocal, seed=32, valid=valid, n_groups_kv=groups, real_codes=False)
