@@ -152,18 +152,26 @@ def _check(rc: int, what: str):
 
 
 def _ptr(t):
+    """Device address of a tensor (a plain integer: the functions' argtypes make it a pointer)."""
     if t is None:
         return None
     if not t.is_cuda:
         raise AstraError("device tensor required")
     if not t.is_contiguous():
         raise AstraError("contiguous tensor required")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
+
+
+_torch_c = None
 
 
 def _stream():
-    import torch
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    # the raw handle of torch's current stream; a torch.cuda.Stream object built on every call costs 2.7 us of host time, as much as a launch
+    global _torch_c
+    if _torch_c is None:
+        import torch
+        _torch_c = torch._C
+    return _torch_c._cuda_getCurrentRawStream(_torch_c._cuda_getDevice())
 
 
 def astra_version() -> int:
@@ -255,8 +263,7 @@ def block_weights(**tensors) -> BlockWeights:
         raise AstraError(f"unknown block weight(s): {sorted(unknown)}")
     w = BlockWeights()
     for n in _BLOCK_WEIGHT_NAMES:
-        p = _ptr(tensors.get(n))
-        setattr(w, n, p.value if p is not None else None)
+        setattr(w, n, _ptr(tensors.get(n)))
     return w
 
 
@@ -329,8 +336,7 @@ def astra_navq_forward(desc: VqDesc, codes, n_tokens: int, codebook, mu, lam: fl
 def _ptr_array(tensors):
     arr = (ctypes.c_void_p * len(tensors))()
     for i, t in enumerate(tensors):
-        p = _ptr(t)
-        arr[i] = p.value if p is not None else None
+        arr[i] = _ptr(t)
     return arr
 
 
