@@ -166,8 +166,6 @@ int launch_gemm_batch(int dtype, const GemmProblem* problems, int n_problems, hi
                       bool* enc_fused = nullptr, bool plan_only = false, void* split_ws = nullptr, size_t split_ws_bytes = 0,
                       bool may_cut = true);
 size_t gemm_split_workspace_bytes(int dtype, int64_t M, int64_t N, int64_t K);
-extern int g_gemm_force_cfg;
-extern const int g_gemm_problem_size;
 
 // Row-wise LayerNorm (kind 0) / RMSNorm (kind 1) of the fp32 residual stream x [T, D] into the element type of the layer
 // (out [T, D]); gain, bias fp32 [D], nullable.

@@ -53,15 +53,18 @@ __device__ __forceinline__ int xcd_remap(int wg, int total) {
 __device__ __forceinline__ int swz(int r) { return (r >> 1) & 7; }
 
 // Activations of the position-wise MLP that follows the attention layer inside a block (paper Sec. 3.1), applied in
-// the epilogue.  x * sigmoid(2u) is 0.5 x (1 + tanh u).  FAST uses the hardware exponential (results are rounded to
-// bf16 afterwards); otherwise the library routines.
+// the epilogue.  x * sigmoid(2u) is 0.5 x (1 + tanh u).  FAST uses the hardware exponential and reciprocal (1 ulp; results are rounded
+// to bf16 afterwards); otherwise the library routines.
 template <bool FAST>
-__device__ __forceinline__ float silu(float v) { return v / (1.f + (FAST ? __expf(-v) : expf(-v))); }
+__device__ __forceinline__ float silu(float v) {
+    if (FAST) return v * __builtin_amdgcn_rcpf(1.f + __expf(-v));
+    return v / (1.f + expf(-v));
+}
 template <bool FAST>
 __device__ __forceinline__ float apply_act(float v, int act) {
     if (act == kActGeluTanh) {
         const float u = 0.7978845608028654f * (v + 0.044715f * v * v * v);
-        return FAST ? v / (1.f + __expf(-2.f * u)) : 0.5f * v * (1.f + tanhf(u));
+        return FAST ? v * __builtin_amdgcn_rcpf(1.f + __expf(-2.f * u)) : 0.5f * v * (1.f + tanhf(u));
     }
     if (act == kActGeluErf) return 0.5f * v * (1.f + erff(v * 0.7071067811865476f));
     return v;
@@ -87,7 +90,6 @@ __device__ __forceinline__ FusedId fused_id(int wg, int T, int E) {
 __device__ __forceinline__ int vt_pos(int o) { return 8 * ((o >> 2) & 1) + (o & 3) + 4 * (o >> 3); }
 
 int launch_gemm_mlp(int epi, bool big, const GemmBatch& batch, int grid, hipStream_t s);
-int launch_gemm_mlp_small(int epi, const GemmBatch& batch, int grid, hipStream_t s);
 int launch_split_reduce(const float* part, int n_split, const GemmProblem& p, hipStream_t s);
 int gemm_split_factor(int dtype, int64_t M, int64_t N, int64_t K);
 
@@ -100,20 +102,15 @@ int gemm_split_factor(int dtype, int64_t M, int64_t N, int64_t K);
 //   kEpiSwiGLU       bf16 store of silu(A.gate^T + b_g) * (A.up^T + b_u)
 enum { kEpiLayer = 0, kEpiResidualF32 = 1, kEpiSplit = 2, kEpiGeluTanh = 3, kEpiGeluErf = 4, kEpiSwiGLU = 5 };
 
-// KS = 2: two groups of WM x WN wavefronts work on the same output tile, group g contracting the k ranges
-// [128 t + 64 g, 128 t + 64 g + 64), each with its own operand buffers and the full loop below; their accumulators are
-// added through LDS at the end.  A small tile then keeps its 64 x 64 wave tiles (1 KiB of LDS reads per MFMA) and still
-// has two wavefronts per SIMD to hide each other's staging.
-template <int BM, int BN, int WM, int WN, bool CODE16, bool ENC = false, int EPI = kEpiLayer, int KS = 1>
-__global__ __launch_bounds__(64 * WM * WN * KS) void gemm_nt_bf16_kernel(const GemmBatch batch) {
-    constexpr int THREADS = 64 * WM * WN;                      // threads of one group
+template <int BM, int BN, int WM, int WN, bool CODE16, bool ENC = false, int EPI = kEpiLayer>
+__global__ __launch_bounds__(64 * WM * WN) void gemm_nt_bf16_kernel(const GemmBatch batch) {
+    constexpr int THREADS = 64 * WM * WN;
     constexpr int TM = BM / WM / 32, TN = BN / WN / 32;        // MFMA tiles per wavefront
     constexpr int RPP = THREADS / 8;                           // rows staged per pass
     constexpr int PA = BM / RPP, PB = BN / RPP;                // staging passes per thread
-    static_assert(KS == 1 || KS == 2, "one or two contraction groups");
     static_assert(RPP % 16 == 0, "direct transfers: the row swizzle has to be periodic in the pass stride");
-    __shared__ u32x4 lds_a[2 * KS][BM * kBK / 8];              // [2 * group + buffer]
-    __shared__ u32x4 lds_b[2 * KS][BN * kBK / 8];
+    __shared__ u32x4 lds_a[2][BM * kBK / 8];
+    __shared__ u32x4 lds_b[2][BN * kBK / 8];
 
     int vt;
     if (ENC) {
@@ -129,16 +126,15 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void gemm_nt_bf16_kernel(const G
             u32x4* cb = RING_IN_A ? &lds_a[0][0] : &lds_b[0][0];
             f32x4* cn = reinterpret_cast<f32x4*>(RING_IN_A ? &lds_b[0][0] : &lds_a[0][0]);
             const EncodeJob& job = batch.enc;
-            constexpr int WG_THREADS = THREADS * KS;          // the encode uses every wavefront of the workgroup
             if (vq_encode_fast_needs_zero(job.dg)) {
-                vq_encode_fast_zero_lds<WG_THREADS>(cb);
+                vq_encode_fast_zero_lds<THREADS>(cb);
                 __syncthreads();                           // zero fill done before any transfer lands
             }
             const int n_items = job.G * job.n_tb;
             const int chunk = (n_items + batch.n_enc_wgs - 1) / batch.n_enc_wgs;     // consecutive items share the group
             const int hi = min((id.idx + 1) * chunk, n_items);
             for (int item = id.idx * chunk; item < hi; ++item) {
-                vq_encode_fast_body<WG_THREADS>(job, item / job.n_tb, item % job.n_tb, cb, cn);
+                vq_encode_fast_body<THREADS>(job, item / job.n_tb, item % job.n_tb, cb, cn);
                 __syncthreads();                           // all reads of this item's tiles done before the next item's transfers
             }
             return;
@@ -161,9 +157,7 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void gemm_nt_bf16_kernel(const G
     const int m0 = tm * BM, n0 = tn * BN;
     const int M = P.M, N = P.N, K = P.K;
 
-    const int kgrp = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x / THREADS);      // contraction group (wave-uniform)
-    const int kg2 = 2 * kgrp;
-    const int tid = KS == 1 ? (int)threadIdx.x : (int)threadIdx.x % THREADS;
+    const int tid = (int)threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
     const int i32 = lane & 31, h = lane >> 5;
     const int wm = wave / WN, wn = wave % WN;
@@ -182,13 +176,9 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void gemm_nt_bf16_kernel(const G
     const int dg = gather ? P.dg : 1, Kc = gather ? P.Kc : 1, G = gather ? P.G : 0;
     const uint32_t magic = gather ? (uint32_t)(0x100000000ull / (uint32_t)dg) + 1u : 0u;
     const char* __restrict__ a_base = (const char*)(gather ? P.codebook : P.a);   // plain A advances 128 bytes per tile
-    const int a_step = gather ? 0 : kBK * 2 * KS;
+    const int a_step = gather ? 0 : kBK * 2;
     const uint32_t gmask = gather ? 0xffffffffu : 0u;                           // keeps the gathered offset, or zeroes it
     const char* __restrict__ b_base = (const char*)P.b;
-    if (KS > 1) {                              // this group's first 64 of every 128 along the contraction
-        if (!gather) a_base += kgrp * kBK * 2;
-        b_base += kgrp * kBK * 2;
-    }
     if (EPI == kEpiSplit) {                    // plain A only: both operands start at this copy's slice of the contraction
         a_base += (int64_t)split * batch.k_split * 2;
         b_base += (int64_t)split * batch.k_split * 2;
@@ -217,8 +207,8 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void gemm_nt_bf16_kernel(const G
         }
         boff[it] = ((uint32_t)rb * (uint32_t)(P.ldb ? P.ldb : K) + kc * 8) * 2u;
     }
-    int k_code = kc * 8 + kgrp * kBK; // contraction index of this thread's piece in the tile whose codes are fetched next
-    int k_use = kc * 8 + kgrp * kBK;  // ... in the tile whose operand pieces are fetched next
+    int k_code = kc * 8; // contraction index of this thread's piece in the tile whose codes are fetched next
+    int k_use = kc * 8;  // ... in the tile whose operand pieces are fetched next
     int code[PA];
 
     auto load_codes = [&]() {
@@ -228,7 +218,7 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void gemm_nt_bf16_kernel(const G
             if (CODE16) code[it] = *reinterpret_cast<const uint16_t*>(c_base + (coff[it] + g_));
             else code[it] = *reinterpret_cast<const uint8_t*>(c_base + (coff[it] + g_));
         }
-        k_code += kBK * KS;
+        k_code += kBK;
     };
     // direct transfer of the tile at k_use into LDS buffer buf_: the lanes of a wavefront fill 64 consecutive slots
     // (8 rows of 8 pieces), nothing passes through registers; pass it_ of the A rows, then of the B rows
@@ -242,16 +232,16 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void gemm_nt_bf16_kernel(const G
             asm volatile("" : "+v"(code_here));      // the code is first touched here: an earlier use would wait for the transfers issued before its load
             const uint32_t c_ = (uint32_t)(code_here < Kc ? code_here : Kc - 1);
             const uint32_t goff_ = ((g_ * (uint32_t)Kc + c_) * (uint32_t)dg + j_) * 2u;
-            dma_global_to_lds_16(a_base, (goff_ & gmask) + aoff[it], lds_byte_addr(&lds_a[kg2 + buf_][(wave_rows + RPP * it) * 8]));
+            dma_global_to_lds_16(a_base, (goff_ & gmask) + aoff[it], lds_byte_addr(&lds_a[buf_][(wave_rows + RPP * it) * 8]));
         } else {
             const int it = j_it - PA;
-            dma_global_to_lds_16(b_base, boff[it], lds_byte_addr(&lds_b[kg2 + buf_][(wave_rows + RPP * it) * 8]));
+            dma_global_to_lds_16(b_base, boff[it], lds_byte_addr(&lds_b[buf_][(wave_rows + RPP * it) * 8]));
         }
     };
     auto dma_advance = [&]() {
         a_base += a_step;
-        b_base += kBK * 2 * KS;
-        k_use += kBK * KS;
+        b_base += kBK * 2;
+        k_use += kBK;
     };
 
     f32x16 acc[TM][TN];
@@ -262,7 +252,7 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void gemm_nt_bf16_kernel(const G
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.f;
 
-    if (EPI == kEpiResidualF32 && P.residual != nullptr && kgrp == 0) {
+    if (EPI == kEpiResidualF32 && P.residual != nullptr) {
         // The residual is where the accumulation starts: its loads are issued here, all at once, and land while the first
         // operand tiles are fetched.  (Added in the epilogue, every load would be a round trip to memory in front of a store.)
         // Rows and columns beyond the problem are clamped: those accumulators are never stored.
@@ -294,11 +284,11 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void gemm_nt_bf16_kernel(const G
     // the transfers of tile kt+2.  LDS and global latencies are covered by the MFMAs issued meanwhile.  The workgroup
     // barrier follows step 2, after which step 3 may read the first fragments of tile kt+1 from the other buffer, and
     // the buffer of tile kt (all of whose fragments were requested before the barrier) is free for the transfers.
-    const int n_kt = (EPI == kEpiSplit ? batch.k_split : K) / (kBK * KS);
+    const int n_kt = (EPI == kEpiSplit ? batch.k_split : K) / kBK;
     bf16x8 fa[2][TM], fb[2][TN];
     auto read_frag = [&](int buf_, int ks, int slot, int j) {
-        if (j < TM) fa[slot][j] = __builtin_bit_cast(bf16x8, lds_a[kg2 + buf_][arow[j] * 8 + ((2 * ks + h) ^ swz(arow[j]))]);
-        else fb[slot][j - TM] = __builtin_bit_cast(bf16x8, lds_b[kg2 + buf_][brow[j - TM] * 8 + ((2 * ks + h) ^ swz(brow[j - TM]))]);
+        if (j < TM) fa[slot][j] = __builtin_bit_cast(bf16x8, lds_a[buf_][arow[j] * 8 + ((2 * ks + h) ^ swz(arow[j]))]);
+        else fb[slot][j - TM] = __builtin_bit_cast(bf16x8, lds_b[buf_][brow[j - TM] * 8 + ((2 * ks + h) ^ swz(brow[j - TM]))]);
     };
     constexpr int NR = TM + TN, NM = TM * TN;
     {
@@ -362,29 +352,6 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void gemm_nt_bf16_kernel(const G
             tile_steps_dma(kt + 1, std::integral_constant<int, 1>{});
         }
         for (; kt < n_kt; ++kt) tile_steps_dma(kt, std::integral_constant<int, -1>{});
-    }
-
-    if constexpr (KS == 2) {
-        // the second group hands its accumulators over through the operand buffers (all fragment reads are done)
-        static_assert(KS == 1 || sizeof(lds_a) >= sizeof(float) * BM * BN, "accumulator exchange fits the A buffers");
-        float* xch = reinterpret_cast<float*>(&lds_a[0][0]);
-        __syncthreads();
-        if (kgrp == 1) {
-#pragma unroll
-            for (int a = 0; a < TM; ++a)
-#pragma unroll
-                for (int b = 0; b < TN; ++b)
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) xch[(((wave * TM + a) * TN + b) * 16 + v) * 64 + lane] = acc[a][b][v];
-        }
-        __syncthreads();
-        if (kgrp == 1) return;
-#pragma unroll
-        for (int a = 0; a < TM; ++a)
-#pragma unroll
-            for (int b = 0; b < TN; ++b)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) acc[a][b][v] += xch[(((wave * TM + a) * TN + b) * 16 + v) * 64 + lane];
     }
 
     // epilogue.  acc[a][b][v] is C[m, n] with m = wave row base + 32a + acc_row(v, h), n = wave column base + 32b + lane % 32.

@@ -5,6 +5,9 @@
 // This file holds the layer's instantiations of the bf16 tile kernel, the fp32 kernel and the launcher;
 // the instantiations for the MLP of the surrounding block are compiled in gemm_mlp_kernels.hip.
 #include "gemm_bf16_tile.h"
+#include "gemm_bf16_wave.h"
+
+#include <algorithm>
 
 namespace astra {
 
@@ -122,8 +125,11 @@ __global__ __launch_bounds__(256) void gemm_nt_f32_kernel(const GemmBatch batch)
     }
 }
 
-int g_gemm_force_cfg = -1;      // development override: 0 = 128x128 tiles, 1 = 256x256 tiles
-extern const int g_gemm_problem_size = (int)sizeof(GemmProblem);   // lets a development harness detect a stale header
+
+// row tiles of a problem; a transposed store covers the padded rows too
+static int64_t tile_rows(const GemmProblem& p, int bm) {
+    return ceil_div(p.c_mode == kCTransposedV && p.ldc > p.M ? p.ldc : p.M, bm);
+}
 
 static int fill_batch(GemmBatch& batch, int dtype, const GemmProblem* problems, int n_problems, int bm, int bn, int* total_out) {
     int total = 0, n = 0;
@@ -146,7 +152,7 @@ static int fill_batch(GemmBatch& batch, int dtype, const GemmProblem* problems, 
         } else if (p.c_mode != kCF32) {
             return ASTRA_ERR_UNSUPPORTED;
         }
-        const int64_t tm = ceil_div(p.M, bm), tn = ceil_div(p.N, bn);
+        const int64_t tm = tile_rows(p, bm), tn = ceil_div(p.N, bn);
         const int64_t nt = tm * tn;
         if (nt + total > 0x7fffffff) return ASTRA_ERR_SHAPE;
         batch.p[n] = p;
@@ -165,25 +171,91 @@ static int fill_batch(GemmBatch& batch, int dtype, const GemmProblem* problems, 
 static int64_t count_tiles(const GemmProblem* problems, int n_problems, int bm, int bn) {
     int64_t t = 0;
     for (int i = 0; i < n_problems; ++i)
-        if (problems[i].M > 0 && problems[i].N > 0) t += ceil_div(problems[i].M, bm) * ceil_div(problems[i].N, bn);
+        if (problems[i].M > 0 && problems[i].N > 0) t += tile_rows(problems[i], bm) * ceil_div(problems[i].N, bn);
     return t;
 }
 
-// Rough duration (us) of one bf16 projection launch under the shape rules of launch_gemm_batch: rounds of 256 x 256 tiles
-// (about 105 us per 4096 of contraction), one round of 128 x 256 tiles (70), or 128 x 128 tiles (48 for a single round of
-// one workgroup per unit, 80 per round of two per unit).  Used only to compare ways of cutting a launch in two.
-static double estimate_launch_us(const GemmProblem* problems, int n_problems) {
+// ---- durations (us) by which a launch's form is chosen, fitted to the kernels one by one (MI355X)
+
+static bool plain_layer(const GemmProblem* problems, int n_problems) {
+    for (int i = 0; i < n_problems; ++i)
+        if (problems[i].c_mode == kCSwiGLU || problems[i].act != kActNone || problems[i].residual) return false;
+    return true;
+}
+
+// Tile kernel: rounds of 256 x 256 tiles (about 105 us per 4096 of contraction), one round of 128 x 256 tiles (70), else 128 x 128 tiles
+// on eight wavefronts, two workgroups per unit (80 per round).
+static double tile_launch_us(const GemmProblem* problems, int n_problems, bool can_split) {
     int k_max = 0;
-    for (int i = 0; i < n_problems; ++i) k_max = problems[i].K > k_max ? problems[i].K : k_max;
+    for (int i = 0; i < n_problems; ++i) k_max = std::max(k_max, problems[i].K);
     const double kf = k_max / 4096.0;
     const int64_t big = count_tiles(problems, n_problems, 256, 256);
     if (big == 0) return 0.0;
-    if (big > 128) return (double)ceil_div(big, (int64_t)kCus) * 105.0 * kf + 8.0;
-    const int64_t mid = count_tiles(problems, n_problems, 128, 256);
-    if (mid > kCus / 2 && mid <= kCus) return 70.0 * kf + 8.0;
-    if (big == 128) return 105.0 * kf + 8.0;
-    const int64_t small = count_tiles(problems, n_problems, 128, 128);
-    return (small <= kCus ? 48.0 : (double)ceil_div(small, (int64_t)(2 * kCus)) * 80.0) * kf + 8.0;
+    const bool plain = plain_layer(problems, n_problems);
+    if (plain && big <= 128) {
+        const int64_t mid = count_tiles(problems, n_problems, 128, 256);
+        if (mid > kCus / 2 && mid <= kCus) return 70.0 * kf + 8.0;
+    }
+    if (big >= 128) return (double)ceil_div(big, (int64_t)kCus) * 105.0 * kf + 8.0;
+    const GemmProblem& p0 = problems[0];
+    const int ns = !plain && can_split && p0.c_mode == kCF32 && p0.ldc % 4 == 0 ? gemm_split_factor(ASTRA_BF16, p0.M, p0.N, p0.K) : 1;
+    if (ns > 1) return 105.0 * kf / ns + 8.0 + 4.5 + (ns + 2.0) * p0.M * p0.N * 4.0 / 5.0e6;      // sliced contraction and its reduction
+    return (double)ceil_div(count_tiles(problems, n_problems, 128, 128), (int64_t)(2 * kCus)) * 80.0 * kf + 8.0;
+}
+
+// Wavefront-private kernel: a tile takes its operand bytes at 98 B/ns and its matrix work at 8.4 Gflop/ms (the two add up on four
+// wavefronts; 128 x 64 tiles fall short of that), workgroups beyond the first per unit queue for the same intake; around them the launch, a latency at either end and the
+// reduction through LDS, which two workgroups of a unit hide for each other; never faster than memory delivers the operands.
+static double wave_launch_us(const GemmProblem* problems, int n_problems, int cfg) {
+    const WaveConfig& c = kWaveTable[cfg];
+    int k_max = 0;
+    double bytes = 0.0;
+    for (int i = 0; i < n_problems; ++i) {
+        const GemmProblem& p = problems[i];
+        if (p.M <= 0 || p.N <= 0) continue;
+        k_max = std::max(k_max, p.K);
+        bytes += ((double)p.N + (p.codes ? 0.0 : (double)p.M)) * p.K * 2.0 + (double)p.M * p.N * 2.0;
+    }
+    const int64_t tiles = count_tiles(problems, n_problems, c.bm, c.bn);
+    const double tile = (c.bm == 128 && c.bn == 64 ? 1.1 : 1.0) * k_max * ((c.bm + c.bn) * 2.0 / 98.0e3 + (double)c.bm * c.bn * 2.0 / 8.4e6);
+    const double tail = 3.8 * c.bm * c.bn / 16384.0;
+    const double rounds = (double)ceil_div(tiles, (int64_t)kCus);
+    return std::max(2.2 + tail + rounds * tile + (c.per_cu == 1 ? (rounds - 1.0) * tail : 0.0), 4.0 + bytes / 5.1e6);
+}
+
+// LDS bytes for a tile's codes (the largest of the problems); -1: they do not fit beside the ring
+static int wave_code_bytes(const GemmProblem* problems, int n_problems, int cfg) {
+    int64_t need = 0;
+    for (int i = 0; i < n_problems; ++i)
+        if (problems[i].codes && problems[i].M > 0) need = std::max<int64_t>(need, (int64_t)kWaveTable[cfg].bm * problems[i].G * problems[i].code_bytes);
+    need = (int64_t)align_up((size_t)need, 16);
+    return kWaveTable[cfg].lds + need <= 156 * 1024 ? (int)need : -1;
+}
+
+constexpr double kWaveMargin = 0.97;       // what the fits are good for
+
+// the fastest wavefront-private form of a set of problems, -1: none applies
+static int best_wave(const GemmProblem* problems, int n_problems, double* us) {
+    for (int i = 0; i < n_problems; ++i) {
+        const GemmProblem& p = problems[i];
+        if (p.M > 0 && (p.N % 8 != 0 || p.ldc % 4 != 0)) return -1;          // four consecutive columns per thread
+    }
+    int best = -1;
+    for (int cfg = 0; cfg < kWaveConfigs; ++cfg) {
+        if (wave_code_bytes(problems, n_problems, cfg) < 0) continue;
+        const double t = wave_launch_us(problems, n_problems, cfg);
+        if (best < 0 || t < *us) {
+            best = cfg;
+            *us = t;
+        }
+    }
+    return best;
+}
+
+static double launch_us(const GemmProblem* problems, int n_problems) {
+    const double t = tile_launch_us(problems, n_problems, false);
+    double w = 0.0;
+    return best_wave(problems, n_problems, &w) >= 0 && w < kWaveMargin * t ? w : t;
 }
 
 int launch_gemm_batch(int dtype, const GemmProblem* problems, int n_problems, hipStream_t s, const EncodeJob* enc, bool* enc_fused,
@@ -193,20 +265,17 @@ int launch_gemm_batch(int dtype, const GemmProblem* problems, int n_problems, hi
     // A launch whose last round of 256 x 256 tiles is nearly empty lasts a whole tile longer for a few tiles.  When the
     // problems can be dealt into two launches that are shorter together (say one that fills its rounds and a small one
     // on smaller tiles), run those: the launches are independent and follow each other on the stream.
-    if (dtype == ASTRA_BF16 && may_cut && n_problems >= 2 && g_gemm_force_cfg < 0) {
-        bool plain = true;
-        for (int i = 0; i < n_problems; ++i)
-            plain = plain && problems[i].c_mode != kCSwiGLU && problems[i].act == kActNone && !problems[i].residual;
+    if (dtype == ASTRA_BF16 && may_cut && n_problems >= 2) {
         const int64_t big = count_tiles(problems, n_problems, 256, 256);
-        if (plain && big > kCus && big % kCus != 0 && big % kCus <= 3 * kCus / 8) {
-            const double whole = estimate_launch_us(problems, n_problems);
+        if (plain_layer(problems, n_problems) && big > kCus && big % kCus != 0 && big % kCus <= 3 * kCus / 8) {
+            const double whole = launch_us(problems, n_problems);
             double best = whole - 10.0;        // a second launch has to pay for itself with some margin
             unsigned best_mask = 0;
             GemmProblem a[kMaxGemmProblems], b[kMaxGemmProblems];
             for (unsigned mask = 1; mask + 1 < (1u << n_problems); ++mask) {
                 int na = 0, nb = 0;
                 for (int i = 0; i < n_problems; ++i) ((mask >> i) & 1u ? a[na++] : b[nb++]) = problems[i];
-                const double t = estimate_launch_us(a, na) + estimate_launch_us(b, nb);
+                const double t = launch_us(a, na) + launch_us(b, nb);
                 if (t < best) { best = t; best_mask = mask; }
             }
             if (best_mask != 0) {
@@ -249,16 +318,47 @@ int launch_gemm_batch(int dtype, const GemmProblem* problems, int n_problems, hi
         if (problems[i].codes && problems[i].code_bytes == 2) code16 = true;
         if (problems[i].c_mode == kCSwiGLU || problems[i].act != kActNone || problems[i].residual) mlp = true;
     }
+    int epi = kEpiLayer;
     if (mlp) {
         // the MLP's GEMMs and the residual-adding output projection of a block: plain A rows, one problem per launch
         if (n_problems != 1 || problems[0].codes) return ASTRA_ERR_UNSUPPORTED;
         const GemmProblem& p0 = problems[0];
-        int epi;
         if (p0.c_mode == kCSwiGLU) epi = kEpiSwiGLU;
         else if (p0.c_mode == kCBf16 && p0.act == kActGeluTanh) epi = kEpiGeluTanh;
         else if (p0.c_mode == kCBf16 && p0.act == kActGeluErf) epi = kEpiGeluErf;
         else if (p0.c_mode == kCF32 && p0.act == kActNone) epi = kEpiResidualF32;
         else return ASTRA_ERR_UNSUPPORTED;
+    }
+    double wave_us = 0.0;
+    const int wave_cfg = best_wave(problems, n_problems, &wave_us);
+    if (wave_cfg >= 0 && wave_us < kWaveMargin * tile_launch_us(problems, n_problems, plan_only || split_ws != nullptr)) {
+        const WaveConfig& wc = kWaveTable[wave_cfg];
+        int rc = fill_batch(batch, dtype, problems, n_problems, wc.bm, wc.bn, &total);
+        if (rc) return rc;
+        if (total == 0) return ASTRA_OK;
+        bool gather = false;
+        for (int i = 0; i < batch.n; ++i) gather = gather || batch.p[i].codes != nullptr;
+        // The encode of the local rows rides along (128 tokens of one group an item: about 1 us per 2^20 codeword elements of 256 tokens,
+        // and 2.5 us before its first tile) when the last round has room for its workgroups and they outlast the products by less than
+        // a launch of their own would cost, or when they are short enough to follow the tiles.
+        if (enc && enc_fused && epi == kEpiLayer && enc->n_tokens > 0 && vq_encode_fast_ok(enc->K, enc->dg)) {
+            const int64_t n_tb = ceil_div(enc->n_tokens, kWaveThreads / 2), items = n_tb * enc->G;
+            const int64_t slots = (int64_t)kCus * wc.per_cu, room = (ceil_div(total, slots) * slots - total) & ~(int64_t)7;
+            const int64_t E = std::min<int64_t>(align_up((size_t)items, 8), room > 0 ? std::min<int64_t>(room, kCus) : kCus);
+            const double enc_us = (double)ceil_div(items, E) * 256.0 * enc->K * enc->dg / 1048576.0 + 2.5;
+            if (items <= 0x7fffffff && enc_us <= (room > 0 ? wave_us + 4.0 : 6.0)) {
+                batch.n_enc_wgs = (int)E;
+                batch.enc = *enc;
+                batch.enc.n_tb = (int)n_tb;
+                batch.enc.n_wgs = (int)E;
+                *enc_fused = true;
+            }
+        }
+        if (plan_only) return ASTRA_OK;
+        return launch_gemm_wave(wave_cfg, epi, gather, batch, total + batch.n_enc_wgs, wave_code_bytes(problems, n_problems, wave_cfg), s);
+    }
+    if (mlp) {
+        const GemmProblem& p0 = problems[0];
         int rc = fill_batch(batch, dtype, problems, n_problems, 256, 256, &total);
         if (rc) return rc;
         if (total == 0) return ASTRA_OK;
@@ -276,25 +376,18 @@ int launch_gemm_batch(int dtype, const GemmProblem* problems, int n_problems, hi
         rc = fill_batch(batch, dtype, problems, n_problems, 128, 128, &total);
         if (rc) return rc;
         if (plan_only) return ASTRA_OK;
-        if (total <= kCus / 2 && epi != kEpiSwiGLU && p0.K % (2 * kBK) == 0 && g_gemm_force_cfg < 0) {      // few tiles: see below
-            GemmBatch sb{};
-            int st = 0;
-            rc = fill_batch(sb, dtype, problems, n_problems, 64, 64, &st);
-            if (rc) return rc;
-            if (st <= kCus) return launch_gemm_mlp_small(epi, sb, st, s);
-        }
         return launch_gemm_mlp(epi, false, batch, total, s);
     }
-    // Large tiles quarter the operand traffic per flop; use them once they still fill most of the chip.
+    // Large tiles quarter the operand traffic per flop; use them once they still fill most of the chip.  What is left after the choice above
+    // are launches of many tiles, and cuts into groups whose codes do not fit the wavefront-private kernel's LDS.
     int rc = fill_batch(batch, dtype, problems, n_problems, 256, 256, &total);
     if (rc) return rc;
     bool big = total >= 128;
-    if (g_gemm_force_cfg >= 0) big = g_gemm_force_cfg >= 1;
     // In between, 128 x 256 tiles: when they run as a single round of workgroups that fills more than half of the chip,
     // the launch lasts one such tile (about two thirds of a 256 x 256 one), where 256 x 256 tiles would leave half of
     // the units idle and 128 x 128 tiles would need a second workgroup per unit at a lower rate each.
     bool mid = false;
-    if (g_gemm_force_cfg < 0 && total <= 128) {
+    if (total <= 128) {
         GemmBatch mb{};
         int mt = 0;
         rc = fill_batch(mb, dtype, problems, n_problems, 128, 256, &mt);
@@ -307,7 +400,7 @@ int launch_gemm_batch(int dtype, const GemmProblem* problems, int n_problems, hi
         }
     }
     // Fuse the encode into the launch when the tiles leave a good part of the last round of compute units idle.
-    if ((big || mid) && enc && enc_fused && g_gemm_force_cfg < 0 && vq_encode_fast_ok(enc->K, enc->dg) && enc->n_tokens > 0) {
+    if ((big || mid) && enc && enc_fused && vq_encode_fast_ok(enc->K, enc->dg) && enc->n_tokens > 0) {
         const int rem = total % kCus;
         const int E = rem == 0 ? 0 : ((kCus - rem) & ~7);
         const int64_t n_tb = ceil_div(enc->n_tokens, 256);
@@ -341,12 +434,6 @@ int launch_gemm_batch(int dtype, const GemmProblem* problems, int n_problems, hi
         else gemm_nt_bf16_kernel<128, 256, 2, 4, false><<<total, 512, 0, s>>>(batch);
         return launch_status();
     }
-    if (big && g_gemm_force_cfg == 2) {
-        if (plan_only) return ASTRA_OK;
-        if (code16) gemm_nt_bf16_kernel<256, 256, 2, 2, true><<<total, 256, 0, s>>>(batch);
-        else gemm_nt_bf16_kernel<256, 256, 2, 2, false><<<total, 256, 0, s>>>(batch);
-        return launch_status();
-    }
     if (big) {
         if (total == 0 || plan_only) return ASTRA_OK;
         if (code16) gemm_nt_bf16_kernel<256, 256, 2, 4, true><<<total, 512, 0, s>>>(batch);
@@ -356,95 +443,9 @@ int launch_gemm_batch(int dtype, const GemmProblem* problems, int n_problems, hi
     rc = fill_batch(batch, dtype, problems, n_problems, 128, 128, &total);
     if (rc) return rc;
     if (total == 0) return ASTRA_OK;
-    // one workgroup per compute unit at most: two contraction groups of four wavefronts (when every contraction is a
-    // multiple of 128); more tiles than that: eight wavefronts on one contraction, two workgroups fit a compute unit
-    bool ks2 = total <= kCus;
-    for (int i = 0; i < batch.n; ++i) ks2 = ks2 && batch.p[i].K % (2 * kBK) == 0;
-    if (ks2) {
-        // Half-width tiles (128 x 64) when they still make a single round: a compute unit takes its operands in at 64 bytes per
-        // clock whatever the others do, and a 128 x 64 tile needs three quarters of a 128 x 128 tile's bytes per step
-        // (or 64 x 128, whichever makes fewer tiles: row counts just above a multiple of 128 waste less that way)
-        bool narrow = false, flat = false;
-        if (g_gemm_force_cfg < 0 && total <= kCus / 2) {
-            GemmBatch nb{}, fb{};
-            int nt = 0, ft = 0;
-            rc = fill_batch(nb, dtype, problems, n_problems, 128, 64, &nt);
-            if (rc) return rc;
-            rc = fill_batch(fb, dtype, problems, n_problems, 64, 128, &ft);
-            if (rc) return rc;
-            if (nt <= kCus - 8 && nt <= ft) {
-                narrow = true;
-                batch = nb;
-                total = nt;
-            } else if (ft <= kCus - 8) {
-                narrow = flat = true;
-                batch = fb;
-                total = ft;
-            }
-        }
-        // a single round that leaves compute units idle: they take the encode of the local rows, as in the large-tile launches
-        // (an item = 256 tokens of one group; about 1 us per 2^20 codeword elements; a 128 x 128 tile about 48 us per 4096 of
-        // contraction plus 8 us of fixed cost)
-        if (enc && enc_fused && g_gemm_force_cfg < 0 && vq_encode_fast_ok(enc->K, enc->dg) && enc->n_tokens > 0) {
-            const int E = (kCus - total) & ~7;
-            const int64_t n_tb = ceil_div(enc->n_tokens, 256);
-            int k_max = 0;
-            for (int i = 0; i < batch.n; ++i) k_max = batch.p[i].K > k_max ? batch.p[i].K : k_max;
-            const double tile_us = (narrow ? 36.0 : 48.0) * k_max / 4096.0 + 8.0;
-            const double enc_us = E > 0 ? (double)ceil_div(n_tb * enc->G, (int64_t)E) * 256.0 * enc->K * enc->dg / 1048576.0 + 4.0 : 0.0;
-            if (E >= 8 && n_tb * enc->G <= 0x7fffffff && enc_us <= tile_us) {
-                batch.n_enc_wgs = E;
-                batch.enc = *enc;
-                batch.enc.n_tb = (int)n_tb;
-                batch.enc.n_wgs = E;
-                *enc_fused = true;
-                if (plan_only) return ASTRA_OK;
-                if (flat) {
-                    if (code16) gemm_nt_bf16_kernel<64, 128, 2, 2, true, true, kEpiLayer, 2><<<total + E, 512, 0, s>>>(batch);
-                    else gemm_nt_bf16_kernel<64, 128, 2, 2, false, true, kEpiLayer, 2><<<total + E, 512, 0, s>>>(batch);
-                } else if (narrow) {
-                    if (code16) gemm_nt_bf16_kernel<128, 64, 2, 2, true, true, kEpiLayer, 2><<<total + E, 512, 0, s>>>(batch);
-                    else gemm_nt_bf16_kernel<128, 64, 2, 2, false, true, kEpiLayer, 2><<<total + E, 512, 0, s>>>(batch);
-                } else {
-                    if (code16) gemm_nt_bf16_kernel<128, 128, 2, 2, true, true, kEpiLayer, 2><<<total + E, 512, 0, s>>>(batch);
-                    else gemm_nt_bf16_kernel<128, 128, 2, 2, false, true, kEpiLayer, 2><<<total + E, 512, 0, s>>>(batch);
-                }
-                return launch_status();
-            }
-        }
-        if (plan_only) return ASTRA_OK;
-        // few tiles and no gathered rows (the output projection of a short sequence): a compute unit takes its operands in
-        // at 64 bytes per clock whatever the others do, so the launch is spread over four times as many units on 64 x 64
-        // tiles when those still make a single round
-        bool plain = true;
-        for (int i = 0; i < batch.n; ++i) plain = plain && batch.p[i].codes == nullptr;
-        if (plain && g_gemm_force_cfg < 0) {
-            GemmBatch sb{};
-            int st = 0;
-            rc = fill_batch(sb, dtype, problems, n_problems, 64, 64, &st);
-            if (rc) return rc;
-            if (st <= kCus) {                              // still a single round of workgroups
-                gemm_nt_bf16_kernel<64, 64, 2, 2, false, false, kEpiLayer, 2><<<st, 512, 0, s>>>(sb);
-                return launch_status();
-            }
-        }
-        if (flat) {
-            if (code16) gemm_nt_bf16_kernel<64, 128, 2, 2, true, false, kEpiLayer, 2><<<total, 512, 0, s>>>(batch);
-            else gemm_nt_bf16_kernel<64, 128, 2, 2, false, false, kEpiLayer, 2><<<total, 512, 0, s>>>(batch);
-            return launch_status();
-        }
-        if (narrow) {
-            if (code16) gemm_nt_bf16_kernel<128, 64, 2, 2, true, false, kEpiLayer, 2><<<total, 512, 0, s>>>(batch);
-            else gemm_nt_bf16_kernel<128, 64, 2, 2, false, false, kEpiLayer, 2><<<total, 512, 0, s>>>(batch);
-            return launch_status();
-        }
-        if (code16) gemm_nt_bf16_kernel<128, 128, 2, 2, true, false, kEpiLayer, 2><<<total, 512, 0, s>>>(batch);
-        else gemm_nt_bf16_kernel<128, 128, 2, 2, false, false, kEpiLayer, 2><<<total, 512, 0, s>>>(batch);
-    } else {
-        if (plan_only) return ASTRA_OK;
-        if (code16) gemm_nt_bf16_kernel<128, 128, 4, 2, true><<<total, 512, 0, s>>>(batch);
-        else gemm_nt_bf16_kernel<128, 128, 4, 2, false><<<total, 512, 0, s>>>(batch);
-    }
+    if (plan_only) return ASTRA_OK;
+    if (code16) gemm_nt_bf16_kernel<128, 128, 4, 2, true><<<total, 512, 0, s>>>(batch);
+    else gemm_nt_bf16_kernel<128, 128, 4, 2, false><<<total, 512, 0, s>>>(batch);
     return launch_status();
 }
 

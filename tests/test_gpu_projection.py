@@ -1,0 +1,33 @@
+"""GPU parity of the bf16 product behind the projections, at the edges of its forms: astra_vq_project_codebook with one group is a plain
+C = A . B^T with fp32 output.  Bar: fp32 sums of exact bf16 products in another order, 1e-5 of the largest sum of magnitudes."""
+import numpy as np
+import pytest
+
+from paper_2505_19342_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("m,n,k", [
+    (4, 8, 64),          # one contraction slice: three of the four wavefronts of a workgroup have none
+    (32, 32, 256),       # one tile, one slice per wavefront
+    (33, 40, 320),       # one row and eight columns beyond a tile, five slices over four wavefronts
+    (60, 768, 768),      # ring of two stages, three slices per wavefront
+    (260, 1032, 192),    # several column tiles, the last one of eight columns
+    (256, 4096, 1024),   # larger tiles
+    (516, 4096, 512),    # two workgroups per unit
+    (1024, 4096, 576),   # 128 x 128 tiles, nine slices over four wavefronts
+])
+def test_product_forms(m, n, k):
+    import torch
+    from gpu_util import to_dev, to_host, DEV
+    from paper_2505_19342_amd import binding as B
+    rng = np.random.default_rng(m + n + k)
+    a = wl.round_to_bf16(rng.standard_normal((m, k), dtype=np.float32))
+    b = wl.round_to_bf16(rng.standard_normal((n, k), dtype=np.float32))
+    out = torch.full((1, m, n), float("nan"), dtype=torch.float32, device=DEV)
+    B.astra_vq_project_codebook(B.vq_desc("bf16", k, 1, m), to_dev(a[None], "bf16"), to_dev(b, "bf16"), n, out)
+    torch.cuda.synchronize()
+    ref = a.astype(np.float64) @ b.astype(np.float64).T
+    scale = (np.abs(a).astype(np.float64) @ np.abs(b).astype(np.float64).T).max()
+    assert np.abs(to_host(out)[0] - ref).max() <= 1e-5 * scale
