@@ -130,6 +130,129 @@ __global__ __launch_bounds__(kTrThreads) void sort_place_kernel(const void* __re
     }
 }
 
+// ---- the same sort as one launch, for token counts and codebooks whose counters and sorted sequence fit a compute unit's LDS:
+// one workgroup per group, every one of its 16 wavefronts owning a contiguous run of tokens.  A wavefront ranks its tokens by
+// ballots against counters of its own (no barrier and no atomics: at most one lane per code writes, in program order), one scan over
+// codes and wavefronts turns the counters into first write positions, and the sorted sequence is put together in LDS and
+// leaves as whole lines.  The codes are transposed first: read with their stride they cost one line per token through one
+// compute unit (36.7 us instead of 8.6 + 19.0).  Bound by the vector ALU of that unit (the ballots).  In the three launches
+// above the strided read is repeated, a pass of 256 tokens is four serial turns of its wavefronts, and perm and scode leave as single
+// scattered words.  16384 x 64 codes, K = 1024: 5.4 + 10.6 + 23.0 us there, 8.6 + 19.0 us here.
+constexpr int kSortThreads = 1024, kSortWaves = kSortThreads / kWave, kSortSteps = 16;
+constexpr int kSortMaxTokens = kSortThreads * kSortSteps;         // sorted tokens and codes: 4 bytes each, 64 KB
+constexpr int kSortMaxCodes = kSortThreads;                       // a code per thread in the scan; counters 64 KB
+
+__device__ __forceinline__ void sort_lds_order() {                // LDS accesses of the wavefront's lanes stay in program order
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// out[2 T g + t] = code of (t, g): the codes of a group as one run, in the first half of the group's place in perm.
+// 64 tokens x 64 groups per workgroup.
+__global__ __launch_bounds__(kTrThreads) void code_transpose_kernel(const void* __restrict__ codes, int code16, int T, int G, int K,
+                                                                    uint16_t* __restrict__ out) {
+    __shared__ uint16_t tile[64][66];
+    const int t0 = blockIdx.x * 64, g0 = blockIdx.y * 64, col = threadIdx.x & 63, row = threadIdx.x >> 6;
+#pragma unroll
+    for (int i = row; i < 64; i += kTrThreads / 64)
+        if (t0 + i < T && g0 + col < G) tile[col][i] = (uint16_t)tr_code(codes, code16, (int64_t)(t0 + i) * G + g0 + col, K);
+    __syncthreads();
+#pragma unroll
+    for (int i = row; i < 64; i += kTrThreads / 64)
+        if (t0 + col < T && g0 + i < G) out[(int64_t)(g0 + i) * 2 * T + t0 + col] = tile[i][col];
+}
+
+__global__ __launch_bounds__(kSortThreads) void sort_group_kernel(int T, int K, int steps, int32_t* __restrict__ counts, int32_t* __restrict__ offs,
+                                                                  int32_t* perm, uint16_t* __restrict__ scode) {
+    extern __shared__ int lds_i[];
+    __shared__ int wave_sum[kSortWaves];
+    const int g = blockIdx.x, tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
+    int* mine = lds_i + wave * K;                                                  // [kSortWaves][K] counters
+    uint16_t* l_perm = reinterpret_cast<uint16_t*>(lds_i + kSortWaves * K);        // [T] token of a sorted position
+    uint16_t* l_code = l_perm + T;                                                 // [T] its code
+    const uint16_t* mine_codes = reinterpret_cast<const uint16_t*>(perm + (int64_t)g * T);   // read whole before perm is written
+    const int t0 = wave * steps * kWave + lane;
+    int c[kSortSteps], pos[kSortSteps];
+#pragma unroll
+    for (int i = 0; i < kSortSteps; ++i) {
+        const int t = t0 + i * kWave;
+        c[i] = i < steps && t < T ? (int)mine_codes[t] : -1;
+    }
+    for (int k = lane; k < K; k += kWave) mine[k] = 0;
+    sort_lds_order();
+#pragma unroll
+    for (int i = 0; i < kSortSteps; ++i) {
+        if (i < steps) {
+            uint32_t p_lo = ~0u, p_hi = ~0u;
+#pragma unroll
+            for (int b = 0; b < 11; ++b) {                                         // codes below 1024; all ones: no token
+                const uint32_t same = (uint32_t)(c[i] << (31 - b) >> 31);          // the bit in every position
+                const unsigned long long bal = __builtin_amdgcn_ballot_w64(same != 0);
+                p_lo &= ~((uint32_t)bal ^ same);
+                p_hi &= ~((uint32_t)(bal >> 32) ^ same);
+            }
+            const unsigned long long peers = (unsigned long long)p_hi << 32 | p_lo;
+            const int rank = __popcll(peers & ((1ull << lane) - 1ull));
+            const int before = c[i] >= 0 ? mine[c[i]] : 0;
+            pos[i] = before + rank;
+            sort_lds_order();
+            if (c[i] >= 0 && rank == 0) mine[c[i]] = before + __popcll(peers);
+            sort_lds_order();
+        }
+    }
+    __syncthreads();
+    int total = 0;
+    if (tid < K)
+#pragma unroll
+        for (int w = 0; w < kSortWaves; ++w) total += lds_i[w * K + tid];
+    int incl = total;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+        const int v = __shfl_up(incl, o);
+        if (lane >= o) incl += v;
+    }
+    if (lane == kWave - 1) wave_sum[wave] = incl;
+    __syncthreads();
+    int base = incl - total;
+    for (int w = 0; w < wave; ++w) base += wave_sum[w];
+    if (tid < K) {
+        counts[(int64_t)g * K + tid] = total;
+        offs[(int64_t)g * (K + 1) + tid] = base;
+        if (tid == K - 1) offs[(int64_t)g * (K + 1) + K] = base + total;
+        int run = base;
+#pragma unroll
+        for (int w = 0; w < kSortWaves; ++w) {
+            const int n = lds_i[w * K + tid];
+            lds_i[w * K + tid] = run;                                              // first write position of (wavefront, code)
+            run += n;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kSortSteps; ++i)
+        if (i < steps && c[i] >= 0) {
+            const int p = mine[c[i]] + pos[i];
+            l_perm[p] = (uint16_t)(t0 + i * kWave);
+            l_code[p] = (uint16_t)c[i];
+        }
+    __syncthreads();
+    for (int i = tid; i < T; i += kSortThreads) {
+        perm[(int64_t)g * T + i] = l_perm[i];
+        scode[(int64_t)g * T + i] = l_code[i];
+    }
+}
+
+static int launch_sort_group(const void* codes, int code16, int T, int G, int K, int32_t* counts, int32_t* offs, int32_t* perm,
+                             uint16_t* scode, hipStream_t s) {
+    static const hipError_t raised = hipFuncSetAttribute((const void*)sort_group_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                         kSortWaves * kSortMaxCodes * 4 + kSortMaxTokens * 4);
+    if (raised != hipSuccess) return ASTRA_ERR_HIP;
+    const size_t lds = (size_t)kSortWaves * K * sizeof(int) + (size_t)T * 4;
+    if (T > 0) code_transpose_kernel<<<dim3((int)ceil_div(T, 64), (int)ceil_div(G, 64)), kTrThreads, 0, s>>>(codes, code16, T, G, K, (uint16_t*)perm);
+    sort_group_kernel<<<G, kSortThreads, lds, s>>>(T, K, (int)ceil_div(T, kSortThreads), counts, offs, perm, scode);
+    return ASTRA_OK;
+}
+
 // ---- sums of the rows of every codeword and the squared distances to the codeword, for element types and group widths
 // without whole 16-byte pieces (fp32, unaligned bf16 slices).  grid (blocks of codewords, G), a channel per thread.
 // PH threads share a (codeword, channel) pair: thread ph adds the rows at positions lo + ph, lo + ph + PH, ... of the
@@ -452,10 +575,18 @@ int astra_codebook_stats(const astra_vq_desc* desc, const void* x, const void* c
     int32_t* hist = (int32_t*)(ws + pl.off_hist);
     uint16_t* scode = (uint16_t*)(ws + pl.off_scode);
     float* part = (float*)(ws + pl.off_part);
-    const dim3 sgrid(pl.n_seg, G);
-    sort_count_kernel<<<sgrid, kTrThreads, (size_t)K * sizeof(int), s>>>(codes, code16, T, G, K, pl.seg_len, hist);
-    sort_scan_kernel<<<G, kTrThreads, (size_t)K * sizeof(int), s>>>(hist, pl.n_seg, K, counts_out, offs);
-    sort_place_kernel<<<sgrid, kTrThreads, (size_t)K * sizeof(int), s>>>(codes, code16, T, G, K, pl.seg_len, hist, perm, scode);
+    // the single launch wherever a group fits a unit's LDS (16384 tokens of 1024 codewords in 64
+    // groups: 28 us against 39); longer batches and larger codebooks
+    // take the three launches, whose segments of tokens spread a group over many units
+    if (T <= kSortMaxTokens && K <= kSortMaxCodes) {
+        rc = launch_sort_group(codes, code16, T, G, K, counts_out, offs, perm, scode, s);
+        if (rc) return rc;
+    } else {
+        const dim3 sgrid(pl.n_seg, G);
+        sort_count_kernel<<<sgrid, kTrThreads, (size_t)K * sizeof(int), s>>>(codes, code16, T, G, K, pl.seg_len, hist);
+        sort_scan_kernel<<<G, kTrThreads, (size_t)K * sizeof(int), s>>>(hist, pl.n_seg, K, counts_out, offs);
+        sort_place_kernel<<<sgrid, kTrThreads, (size_t)K * sizeof(int), s>>>(codes, code16, T, G, K, pl.seg_len, hist, perm, scode);
+    }
     if (pl.units) {
         if (pl.n_blocks > 0) {
             const size_t lds = (size_t)(2 * pl.units_per_wg * kUnitRows + 2) * sizeof(int);

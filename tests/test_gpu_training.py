@@ -113,6 +113,33 @@ def test_stats_edge_cases():
         np.testing.assert_allclose(sqerr, q_ref, rtol=1e-5, atol=1e-6)
 
 
+@pytest.mark.parametrize("T,K", [(1, 3), (63, 1024), (1023, 256), (1024, 1024), (1025, 255), (16383, 1024), (16384, 3), (16384, 1024),
+                                 (16385, 1024), (2000, 1025)])
+def test_stats_sort_edges(T, K):
+    """Both forms of the sort on either side of their limits (16384 tokens, 1024 codewords).  The rows are small whole numbers, so
+    that every sum is exact in fp32 whatever its order: the results are equal to the reference's, not near them."""
+    import torch
+    from gpu_util import codes_to_dev, to_dev, DEV
+    from paper_2505_19342_amd import binding as B
+    G, dg = 3, 16
+    rng = np.random.default_rng(T + K)
+    x = rng.integers(-4, 5, (T, G * dg)).astype(np.float32)
+    cb = rng.integers(-4, 5, (G, K, dg)).astype(np.float32)
+    codes = (K * rng.random((T, G)) ** 1.5).astype(np.int64)
+    desc = B.vq_desc("bf16", G * dg, G, K)
+    dev = dict(x=to_dev(x, "bf16"), cb=to_dev(cb, "bf16"), codes=codes_to_dev(codes, K),
+               counts=torch.empty((G, K), dtype=torch.int32, device=DEV), sums=torch.empty((G, K, dg), dtype=torch.float32, device=DEV),
+               sqerr=torch.empty(G, dtype=torch.float32, device=DEV),
+               ws=torch.empty(max(B.astra_codebook_stats_workspace_bytes(desc, T), 256), dtype=torch.uint8, device=DEV))
+    counts, sums, sqerr = run_stats(desc, dev, T)
+    for g in range(G):
+        ref = np.zeros((K, dg))
+        np.add.at(ref, codes[:, g], x[:, g * dg:(g + 1) * dg])
+        np.testing.assert_array_equal(counts[g], np.bincount(codes[:, g], minlength=K))
+        np.testing.assert_array_equal(sums[g], ref)
+        assert sqerr[g] == ((x[:, g * dg:(g + 1) * dg] - cb[g, codes[:, g]]) ** 2).sum(dtype=np.float64)   # below 2^24: exact
+
+
 @pytest.mark.parametrize("name", ["tiny_vit_f32", "gpt2_small_bf16"])
 def test_navq(name):
     import torch
