@@ -19,7 +19,8 @@ namespace astra {
 // tiles trade concurrency for fewer operand bytes per flop; with 128 x 128 and one stage the fragments of a whole stage sit in
 // registers while the next one is transferred (1024 x 4096 outputs, K = 4096: 42.7 us, tile kernel on 128 x 128: 53 us).
 //
-// GATHER: problems with codes rebuild their A rows from the codebook; the tile's codes are copied to LDS first.
+// GATHER: problems with codes rebuild their A rows from the codebook; the tile's codes are copied to LDS first.  Rows beyond M are copies of
+// row M - 1 there too: a transposed store writes them into its padding, which attention multiplies by zero.
 // ------------------------------------------------------------------------------------------------
 constexpr int kWaveThreads = 256;
 constexpr int kWaveWaves = kWaveThreads / kWave;
@@ -83,10 +84,13 @@ __global__ __launch_bounds__(kWaveThreads) void gemm_wave_kernel(const GemmBatch
     // transfer j of a stage fills rows 8j + lane / 8 of the stage (A rows, then B rows); a lane's piece depends on j's parity only
     const int r8 = lane >> 3;
     const int piece[2] = {(lane & 7) ^ (r8 >> 1), (lane & 7) ^ (4 + (r8 >> 1))};
-    uint32_t off[DM];
+    const int m_codes = min(m0, M - 1), n_codes = min(BM, M - m_codes);      // rows whose codes the tile holds (one when all of it is padding)
+    uint32_t off[DM];                      // byte offsets; a gathered row: that of its codes, in codes
 #pragma unroll
     for (int j = 0; j < DM; ++j) {
-        if (j < DA) {
+        if (GATHER && gather && j < DA) {
+            off[j] = (uint32_t)min(8 * j + r8, n_codes - 1) * (uint32_t)P.G;
+        } else if (j < DA) {
             off[j] = (uint32_t)min(m0 + 8 * j + r8, M - 1) * (uint32_t)P.lda * 2u + 16u * piece[j & 1];
         } else {
             int rb = n0 + 8 * (j - DA) + r8;
@@ -112,8 +116,8 @@ __global__ __launch_bounds__(kWaveThreads) void gemm_wave_kernel(const GemmBatch
     int k_next = wave * kBK;                               // contraction index of the slice whose transfers are issued next
     if (GATHER && gather) {
         const int row_b = G * P.code_bytes;
-        const int total = min(BM, M - m0) * row_b;
-        const char* __restrict__ src = (const char*)P.codes + (int64_t)m0 * row_b;
+        const int total = n_codes * row_b;
+        const char* __restrict__ src = (const char*)P.codes + (int64_t)m_codes * row_b;
         char* dst = wv_lds + S::kBytes;
         for (int o = tid * 16; o < total; o += kWaveThreads * 16) {
             if (o + 16 <= total) *reinterpret_cast<u32x4*>(dst + o) = *reinterpret_cast<const u32x4*>(src + o);
@@ -137,7 +141,7 @@ __global__ __launch_bounds__(kWaveThreads) void gemm_wave_kernel(const GemmBatch
             }
 #pragma unroll
             for (int j = 0; j < DA; ++j) {
-                const uint32_t x = (uint32_t)(8 * j + r8) * (uint32_t)G + g_[j & 1];
+                const uint32_t x = off[j] + g_[j & 1];
                 const uint32_t code = code16 ? (uint32_t)reinterpret_cast<const uint16_t*>(codes_lds)[x] : (uint32_t)reinterpret_cast<const uint8_t*>(codes_lds)[x];
                 const uint32_t go = (at[j & 1] + min(code, (uint32_t)Kc - 1u) * (uint32_t)dg) * 2u;
                 dma_global_to_lds_16(P.codebook, go, dst + (uint32_t)(j * 1024));

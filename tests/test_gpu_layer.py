@@ -136,6 +136,31 @@ def test_llama_dims_ragged_rows_in_every_projection_tile_shape(seq_len, lo, fuse
     assert n_tie <= max(2, codes.size // 2000)
 
 
+@pytest.mark.parametrize("d,hq,hkv,dh,groups,words,n_local,n_nonlocal", [
+    (768, 12, 12, 64, 16, 256, 100, 20),         # the peers' rows end inside a tile, and the padding after them has a tile of its own
+    (768, 12, 12, 64, 16, 256, 256, 777),
+    (4096, 32, 8, 128, 64, 1024, 40, 100),       # 16-bit codes
+    (4096, 32, 8, 128, 64, 1024, 150, 449),      # tiles of 128 rows
+    (4096, 32, 8, 128, 64, 1024, 1000, 2917),    # the large tiles
+])
+def test_codewords_that_no_code_names_do_not_matter(d, hq, hkv, dh, groups, words, n_local, n_nonlocal):
+    """Three codewords of a group are used, the others are NaN in one call and finite in the other: the same output, bit for bit.
+    (Rows beyond the peers' last token pad the transposed V; their weight is zero, but zero times a NaN is not.)"""
+    import torch
+    from gpu_util import LayerOnGpu
+    cfg = wl.LayerConfig("unused", "bf16", d, hq, hkv, dh, n_local + n_nonlocal, 2, groups, words, seed=51)
+    data = wl.generate(cfg)
+    codes_nl = np.random.default_rng(52).integers(0, 3, (n_nonlocal, groups)).astype(np.int32)
+    y = []
+    for fill in (float("nan"), 0.5):
+        layer = LayerOnGpu(cfg, data, data["x"][:n_local], codes_nl, 0)
+        layer.codebook[:, 3:] = fill
+        layer.run()
+        torch.cuda.synchronize()
+        y.append(layer.y)
+    assert bool(torch.isfinite(y[1]).all()) and torch.equal(y[0], y[1])
+
+
 def test_fused_encode_equals_the_standalone_encode_and_calls_repeat_bit_exactly():
     """The encode inside the projection launch and astra_vq_encode run the same arithmetic in the same order: equal codes,
     bit for bit.  Two calls of the layer, and the call with stage events, give identical bits too."""
