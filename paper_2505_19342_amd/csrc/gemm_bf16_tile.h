@@ -53,18 +53,16 @@ __device__ __forceinline__ int xcd_remap(int wg, int total) {
 __device__ __forceinline__ int swz(int r) { return (r >> 1) & 7; }
 
 // Activations of the position-wise MLP that follows the attention layer inside a block (paper Sec. 3.1), applied in
-// the epilogue.  x * sigmoid(2u) is 0.5 x (1 + tanh u).  FAST uses the hardware exponential and reciprocal (1 ulp; results are rounded
-// to bf16 afterwards); otherwise the library routines.
+// the epilogue.  x * sigmoid(2u) is 0.5 x (1 + tanh u).  FAST uses the hardware exponential (results are rounded to bf16 afterwards);
+// otherwise the library routines.  The quotient is a division, not the hardware reciprocal: that one returns zero where 1 / (1 + e^-v)
+// is below the smallest normal number, while v times it (-5e-37 at v = -88) is well inside bf16's range.
 template <bool FAST>
-__device__ __forceinline__ float silu(float v) {
-    if (FAST) return v * __builtin_amdgcn_rcpf(1.f + __expf(-v));
-    return v / (1.f + expf(-v));
-}
+__device__ __forceinline__ float silu(float v) { return v / (1.f + (FAST ? __expf(-v) : expf(-v))); }
 template <bool FAST>
 __device__ __forceinline__ float apply_act(float v, int act) {
     if (act == kActGeluTanh) {
         const float u = 0.7978845608028654f * (v + 0.044715f * v * v * v);
-        return FAST ? v * __builtin_amdgcn_rcpf(1.f + __expf(-2.f * u)) : 0.5f * v * (1.f + tanhf(u));
+        return FAST ? v / (1.f + __expf(-2.f * u)) : 0.5f * v * (1.f + tanhf(u));
     }
     if (act == kActGeluErf) return 0.5f * v * (1.f + erff(v * 0.7071067811865476f));
     return v;

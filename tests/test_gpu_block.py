@@ -163,6 +163,39 @@ def test_rotary_positions_need_a_causal_layer():
     assert bool((blk.x_out == -7.0).all())
 
 
+@pytest.mark.parametrize("rows", [3, 4100])
+@pytest.mark.parametrize("mlp,gate,up,down", [("swiglu", (-88.0, 0.0), 2.0 ** 100, 2.0 ** 20), ("gelu_tanh", (-10.0, -0.03125), None, 2.0 ** 120)])
+def test_activations_far_out_on_the_negative_side(mlp, gate, up, down, rows):
+    """Where 1 / (1 + e^z) is below the smallest normal number the activation itself is not: silu(-88) = -5.3e-37.  Rows of ones make
+    the pre-activation exactly the sum of `gate`; `up` and `down` bring the product back into sight.  The bar is the hidden value's bf16 rounding
+    and one step more."""
+    import torch
+    from gpu_util import DEV
+    from paper_2505_19342_amd import binding as B
+    D, F = 64, 2048
+    layer = B.LayerDesc(B.vq_desc("bf16", D, 1, 16), B.attn_desc("bf16", 1, 1, 64, 0, rows, 0, False, 0))
+    desc = B.block_desc(layer, "rmsnorm", mlp, F, 0.0, 0.0)
+    zeros = lambda *shape: torch.zeros(shape, dtype=torch.bfloat16, device=DEV)
+    t = dict(codebook=zeros(1, 16, D), cnorm=torch.zeros((1, 16), device=DEV), wq=zeros(64, D), wk=zeros(64, D), wv=zeros(64, D), wo=zeros(D, 64),
+             w1=zeros(2 * F if up else F, D), w2=zeros(D, F), norm1_gain=torch.ones(D, device=DEV), norm2_gain=torch.ones(D, device=DEV))
+    t["w1"][0, 0], t["w1"][0, 1] = gate
+    if up:
+        t["w1"][F, 0] = up
+    t["w2"][5, 0] = down
+    x = torch.ones((rows, D), device=DEV)
+    out = torch.empty_like(x)
+    ws = torch.empty(B.astra_block_workspace_bytes(desc), dtype=torch.uint8, device=DEV)
+    codes = torch.empty((rows, 1), dtype=torch.uint8, device=DEV)
+    B.astra_block_forward(desc, B.block_weights(**t), x, None, None, out, codes, None, ws)
+    torch.cuda.synchronize()
+    v = np.float64(sum(gate))
+    act = v / (1.0 + np.exp(-v)) if up else v / (1.0 + np.exp(-2.0 * 0.7978845608028654 * (v + 0.044715 * v ** 3)))
+    step = act * (up or 1.0) * down
+    assert abs(step) > 0.05
+    got = out.cpu().numpy().astype(np.float64)
+    assert np.all(np.abs(got[:, 5] - 1.0 - step) <= 2.0 ** -8 * abs(step)) and np.all(np.delete(got, 5, axis=1) == 1.0)
+
+
 def test_block_argument_errors_launch_nothing():
     import torch
     from gpu_util import BlockOnGpu
