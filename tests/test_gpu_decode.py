@@ -155,3 +155,42 @@ def test_matrix_core_forms(hq, hkv, dh, groups, K, n_local, n_nonlocal):
     cfg = wl.LayerConfig("step", "bf16", 256, hq, hkv, dh, 1024, 4, groups, K, causal=True, seed=31)
     valid = (np.random.default_rng(n_nonlocal).random(n_nonlocal) > 0.1).astype(np.uint8)
     run_case(cfg, n_local, n_nonlocal, seed=32, valid=valid, n_groups_kv=groups, real_codes=False)
+
+
+@pytest.mark.parametrize("hq,hkv,dh,groups,K,n_local,n_nonlocal", [
+    (32, 8, 128, 32, 1024, 129, 256),     # four query heads per KV head, gathered keys; the last row of the cache is repeated past the end
+    (32, 8, 128, 32, 1024, 1025, 40000),  # score table
+    (64, 8, 128, 32, 256, 200, 300),      # eight query heads per KV head: a third product for the third part
+    (16, 16, 64, 16, 256, 70, 9000),      # one query head per KV head
+    (6, 3, 64, 8, 20, 64, 63),            # groups that straddle heads
+])
+@pytest.mark.parametrize("where", ["local", "last", "codeword"])
+def test_an_infinite_value(hq, hkv, dh, groups, K, n_local, n_nonlocal, where):
+    """One infinite value in one channel of a KV head that is attended to: every query head of it gets that infinity there and finite
+    numbers elsewhere, whatever bits its probability has."""
+    import torch
+    from gpu_util import DEV
+    from paper_2505_19342_amd import binding as B
+    g = torch.Generator(device=DEV)
+    g.manual_seed(n_local)
+    normal = lambda *shape: torch.randn(shape, generator=g, device=DEV).to(torch.bfloat16)
+    q, k, v = normal(hq, dh), normal(n_local, hkv, dh), normal(n_local, hkv, dh)
+    cbk, cbv = normal(groups, K, hkv * dh // groups), normal(groups, K, hkv * dh // groups)
+    code = lambda: torch.randint(0, K - 1, (n_nonlocal, groups), generator=g, device=DEV)
+    ck, cv = code(), code()
+    want = -float("inf") if where == "last" else float("inf")
+    if where == "codeword":
+        cv[7, 0] = K - 1
+        cbv[0, K - 1, 3] = want
+    else:
+        v[-1 if where == "last" else 5, 0, 3] = want
+    ct = torch.uint8 if K <= 256 else torch.int16
+    desc = B.DecodeDesc(B.vq_desc("bf16", hkv * dh, groups, K), hq, hkv, dh, n_local, n_nonlocal, 0.0)
+    out = torch.empty((hq, dh), dtype=torch.bfloat16, device=DEV)
+    ws = torch.empty(B.astra_decode_attention_workspace_bytes(desc), dtype=torch.uint8, device=DEV)
+    B.astra_decode_attention(desc, q, k, v, ck.to(ct), cv.to(ct), None, cbk, cbv, out, None, ws)
+    torch.cuda.synchronize()
+    out = out.float().view(hkv, hq // hkv, dh)
+    assert bool((out[0, :, 3] == want).all()), out[0, :, 3]
+    out[0, :, 3] = 0.0
+    assert bool(torch.isfinite(out).all())
