@@ -520,7 +520,8 @@ DecodeStreamPlan plan_decode_stream(int dtype, int Hq, int Hkv, int dh, int n_lo
     // look-ups are cheaper than the multiplications: it pays from K / 2 tokens per workgroup of a launch of one per unit (8 000 + 24 000
     // rows, K = 1024: 23.4 us against 27.9), but not for short caches, where twice the workgroups on half the wavefronts come first
     // (2 181 + 6 546 rows, K = 256: 16.6 us against 15.0).
-    const int wgs_table = std::max(2, kDsCus / Hkv);
+    const int at_least = t_loc > 0 && t_nl > 0 ? 2 : 1;      // many KV heads: one workgroup per kind of tiles, and no partial results beyond those
+    const int wgs_table = std::max(at_least, kDsCus / Hkv);
     const size_t table = (size_t)(dh / std::max(dg, 1)) * K * rep * sizeof(float);
     const size_t xs = (size_t)rep * (dh + 4) * sizeof(float);
     pl.table = (dg == dh || dg == dh / 2 || dg == dh / 4) && dg >= 32 && (int64_t)K * rep * 4 <= 65536 && table <= 140 * 1024 &&
@@ -529,7 +530,7 @@ DecodeStreamPlan plan_decode_stream(int dtype, int Hq, int Hkv, int dh, int n_lo
         wgs = wgs_table;
         pl.lds = std::max(table, kDsTableWaves * xs);
     } else {
-        wgs = (int)std::min<int64_t>(std::max(2, 2 * kDsCus / Hkv), ceil_div(t_loc, kDsGatherWaves) + ceil_div(t_nl, kDsGatherWaves));
+        wgs = (int)std::min<int64_t>(std::max(at_least, 2 * kDsCus / Hkv), ceil_div(t_loc, kDsGatherWaves) + ceil_div(t_nl, kDsGatherWaves));
         pl.lds = kDsGatherWaves * xs;
     }
     // Dealt to the two kinds of tiles in proportion to the time a unit takes for them: a tile of local rows (16 KB from memory) 1.5 times an

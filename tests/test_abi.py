@@ -128,3 +128,11 @@ def test_block_kv_and_decode_planning_is_host_only():
     assert B.astra_decode_attention_workspace_bytes(three) == 0
     empty = B.DecodeDesc(B.vq_desc("bf16", 1024, 32, 1024), 32, 8, 128, 0, 0, 0.0)
     assert B.astra_decode_attention_workspace_bytes(empty) > 0
+
+
+def test_one_sided_caches_of_many_heads_fit_the_librarys_own_scratch():
+    """8192 query heads over 1024 KV heads and only one kind of cache: one partial result per query head, 4.1 MiB of the 8 MiB that
+    astra_decode_attention_static has."""
+    for n_local, n_nonlocal in ((1154, 0), (0, 1154), (200000, 0)):
+        desc = B.DecodeDesc(B.vq_desc("bf16", 1024 * 128, 1024, 16), 8192, 1024, 128, n_local, n_nonlocal, 0.0)
+        assert 0 < B.astra_decode_attention_workspace_bytes(desc) <= B.astra_decode_attention_static_max_bytes()
