@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <atomic>
+
 #include "../../include/astra.h"
 
 namespace astra {
@@ -104,6 +106,21 @@ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 inline int launch_status() { return hipGetLastError() == hipSuccess ? ASTRA_OK : ASTRA_ERR_HIP; }
+
+// Raises a kernel's cap on dynamic LDS (64 KiB by default) to `bytes` on the current device, once per device; a refusal is reported and the
+// next call asks again.  `done`: the kernel's own, one bit per device.
+inline int allow_dynamic_lds(std::atomic<uint64_t>& done, const void* kernel, int bytes) {
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0) return ASTRA_ERR_HIP;
+    const uint64_t bit = dev < 64 ? (uint64_t)1 << dev : 0;          // a device beyond those is asked every time
+    if (done.load(std::memory_order_acquire) & bit) return ASTRA_OK;
+    if (hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) != hipSuccess) {
+        (void)hipGetLastError();
+        return ASTRA_ERR_HIP;
+    }
+    done.fetch_or(bit, std::memory_order_release);
+    return ASTRA_OK;
+}
 
 int check_vq_desc(const astra_vq_desc* d);
 int check_attn_desc(const astra_attn_desc* d);

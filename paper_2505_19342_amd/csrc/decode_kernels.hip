@@ -637,14 +637,9 @@ static int make_decode_plan(const astra_decode_desc& d, DecodePlan* pl) {
 
 template <typename T, int DH, int REP>
 static int launch_partial(const DecodeParams& p, const DecodePlan& pl, hipStream_t s) {
-    static bool lds_raised = false;
-    if (!lds_raised) {
-        // the default cap on dynamic LDS is 64 KiB
-        if (hipFuncSetAttribute((const void*)decode_partial_kernel<T, DH, REP>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                150 * 1024) != hipSuccess)
-            return ASTRA_ERR_HIP;
-        lds_raised = true;
-    }
+    static std::atomic<uint64_t> allowed{0};
+    const int rc = allow_dynamic_lds(allowed, (const void*)decode_partial_kernel<T, DH, REP>, 150 * 1024);
+    if (rc) return rc;
     const int n = p.n_chunks_loc + p.n_chunks_nl;
     if (n > 0)
         decode_partial_kernel<T, DH, REP><<<dim3(n, p.Hkv), kDecThreads, p.n_chunks_nl > 0 ? pl.lds_nl : pl.lds_loc, s>>>(p);

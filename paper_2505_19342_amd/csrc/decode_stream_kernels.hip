@@ -548,9 +548,9 @@ DecodeStreamPlan plan_decode_stream(int dtype, int Hq, int Hkv, int dh, int n_lo
 template <int DH, int REP, int WAVES, int NGH, bool TABLE>
 static int launch_form(const DecodeParams& p, const DecodeStreamPlan& pl, hipStream_t s) {
     if (TABLE) {
-        static const hipError_t raised = hipFuncSetAttribute((const void*)decode_stream_kernel<DH, REP, WAVES, NGH, TABLE>,
-                                                             hipFuncAttributeMaxDynamicSharedMemorySize, 150 * 1024);
-        if (raised != hipSuccess) return ASTRA_ERR_HIP;      // the default cap on dynamic LDS is 64 KiB
+        static std::atomic<uint64_t> allowed{0};
+        const int rc = allow_dynamic_lds(allowed, (const void*)decode_stream_kernel<DH, REP, WAVES, NGH, TABLE>, 150 * 1024);
+        if (rc) return rc;
     }
     decode_stream_kernel<DH, REP, WAVES, NGH, TABLE><<<dim3(pl.wgs_loc + pl.wgs_nl, p.Hkv), 64 * WAVES, pl.lds, s>>>(p);
     return ASTRA_OK;

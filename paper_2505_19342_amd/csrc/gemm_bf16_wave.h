@@ -311,8 +311,9 @@ template <int MT, int NT, int ST, bool GATHER, bool ENC, int EPI>
 static int launch_wave_form(const GemmBatch& batch, int grid, int code_lds, hipStream_t s) {
     auto* kernel = gemm_wave_kernel<MT, NT, ST, GATHER, ENC, EPI>;
     const int lds = (ENC && kWaveEncBytes > WaveShape<MT, NT, ST>::kBytes ? kWaveEncBytes : WaveShape<MT, NT, ST>::kBytes) + code_lds;
-    static const hipError_t raised = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    if (raised != hipSuccess) return ASTRA_ERR_HIP;          // the default cap on dynamic LDS is 64 KiB
+    static std::atomic<uint64_t> allowed{0};
+    const int rc = allow_dynamic_lds(allowed, (const void*)kernel, 160 * 1024);
+    if (rc) return rc;
     kernel<<<grid, kWaveThreads, lds, s>>>(batch);
     return launch_status();
 }

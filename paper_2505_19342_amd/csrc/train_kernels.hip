@@ -244,9 +244,9 @@ __global__ __launch_bounds__(kSortThreads) void sort_group_kernel(int T, int K, 
 
 static int launch_sort_group(const void* codes, int code16, int T, int G, int K, int32_t* counts, int32_t* offs, int32_t* perm,
                              uint16_t* scode, hipStream_t s) {
-    static const hipError_t raised = hipFuncSetAttribute((const void*)sort_group_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                         kSortWaves * kSortMaxCodes * 4 + kSortMaxTokens * 4);
-    if (raised != hipSuccess) return ASTRA_ERR_HIP;
+    static std::atomic<uint64_t> allowed{0};
+    const int rc = allow_dynamic_lds(allowed, (const void*)sort_group_kernel, kSortWaves * kSortMaxCodes * 4 + kSortMaxTokens * 4);
+    if (rc) return rc;
     const size_t lds = (size_t)kSortWaves * K * sizeof(int) + (size_t)T * 4;
     if (T > 0) code_transpose_kernel<<<dim3((int)ceil_div(T, 64), (int)ceil_div(G, 64)), kTrThreads, 0, s>>>(codes, code16, T, G, K, (uint16_t*)perm);
     sort_group_kernel<<<G, kSortThreads, lds, s>>>(T, K, (int)ceil_div(T, kSortThreads), counts, offs, perm, scode);
