@@ -130,7 +130,7 @@ __global__ __launch_bounds__(kTrThreads) void sort_place_kernel(const void* __re
     }
 }
 
-// ---- the same sort as one launch, for token counts and codebooks whose counters and sorted sequence fit a compute unit's LDS:
+// ---- the same sort as one launch, where a group's counters and sorted sequence fit a compute unit's LDS (and see sort_in_one_launch):
 // one workgroup per group, every one of its 16 wavefronts owning a contiguous run of tokens.  A wavefront ranks its tokens by
 // ballots against counters of its own (no barrier and no atomics: at most one lane per code writes, in program order), one scan over
 // codes and wavefronts turns the counters into first write positions, and the sorted sequence is put together in LDS and
@@ -240,6 +240,19 @@ __global__ __launch_bounds__(kSortThreads) void sort_group_kernel(int T, int K, 
         perm[(int64_t)g * T + i] = l_perm[i];
         scode[(int64_t)g * T + i] = l_code[i];
     }
+}
+
+// One launch or three?  One wherever a group fits a unit's LDS and
+//  * there are many groups and many codes: the three launches' strided reads and scattered words then cost more than the ballots
+//    (whole statistics, one launch against three, 64 groups x 16384 tokens: K = 256 61.6 / 66.1 us, K = 1024 68.4 / 83.1; 64 x 8000, K = 256:
+//    41.7 / 38.4; 48 x 5000, K = 1024: 38.2 / 42.4), or
+//  * the codebook is large and the number of segments is no multiple of eight, in which the scan launch walks them with its loads in flight
+//    (1 group of K = 1024: 7000 tokens in 7 segments 29.8 / 34.8 us, 8000 in 8 30.3 / 29.4, 15000 in 15 35.3 / 38.3, 16384 in 16 36.2 / 31.5).
+// Few groups leave the one launch on as many units, where the segments of the three spread a group over up to 16
+// (1 group x 16384 tokens, K = 256: 34.3 / 24.7 us; 32 groups: 46.0 / 38.4).
+static bool sort_in_one_launch(int T, int G, int K, int n_seg) {
+    if (T > kSortMaxTokens || K > kSortMaxCodes) return false;
+    return (G >= 48 && (int64_t)G * T * K >= 190000000) || (K > 512 && n_seg % 8 >= 2);
 }
 
 static int launch_sort_group(const void* codes, int code16, int T, int G, int K, int32_t* counts, int32_t* offs, int32_t* perm,
@@ -619,10 +632,7 @@ int astra_codebook_stats(const astra_vq_desc* desc, const void* x, const void* c
     int32_t* hist = (int32_t*)(ws + pl.off_hist);
     uint16_t* scode = (uint16_t*)(ws + pl.off_scode);
     float* part = (float*)(ws + pl.off_part);
-    // the single launch wherever a group fits a unit's LDS (16384 tokens of 1024 codewords in 64
-    // groups: 28 us against 39); longer batches and larger codebooks
-    // take the three launches, whose segments of tokens spread a group over many units
-    if (T <= kSortMaxTokens && K <= kSortMaxCodes) {
+    if (sort_in_one_launch(T, G, K, pl.n_seg)) {
         rc = launch_sort_group(codes, code16, T, G, K, counts_out, offs, perm, scode, s);
         if (rc) return rc;
     } else {

@@ -116,12 +116,25 @@ def test_stats_edge_cases():
 @pytest.mark.parametrize("T,K", [(1, 3), (63, 1024), (1023, 256), (1024, 1024), (1025, 255), (16383, 1024), (16384, 3), (16384, 1024),
                                  (16385, 1024), (2000, 1025)])
 def test_stats_sort_edges(T, K):
-    """Both forms of the sort on either side of their limits (16384 tokens, 1024 codewords).  The rows are small whole numbers, so
-    that every sum is exact in fp32 whatever its order: the results are equal to the reference's, not near them."""
+    """A few groups, on either side of the token counts and codebook sizes at which the sort changes its form.  The rows are small whole
+    numbers, so that every sum is exact in fp32 whatever its order: the results are equal to the reference's, not near them."""
+    check_exact_stats(T, 3, K, 16)
+
+
+# tokens, groups, codewords of the one-launch sort: its largest sizes, a last pass and a last wavefront that are not full, wavefronts without
+# a token, codebooks that are no whole number of wavefronts
+ONE_LAUNCH_SORTS = [(16384, 48, 1024), (16383, 48, 1023), (15361, 49, 259), (5000, 3, 513), (1025, 1, 1024), (1100, 2, 1000)]
+
+
+@pytest.mark.parametrize("T,G,K", ONE_LAUNCH_SORTS)
+def test_stats_one_launch_sort(T, G, K):
+    check_exact_stats(T, G, K, 8)
+
+
+def check_exact_stats(T, G, K, dg):
     import torch
     from gpu_util import codes_to_dev, to_dev, DEV
     from paper_2505_19342_amd import binding as B
-    G, dg = 3, 16
     rng = np.random.default_rng(T + K)
     x = rng.integers(-4, 5, (T, G * dg)).astype(np.float32)
     cb = rng.integers(-4, 5, (G, K, dg)).astype(np.float32)

@@ -31,3 +31,20 @@ def test_a_refused_cap_is_an_error_that_does_not_last(tmp_path):
     calls = [dict(c, fail_attributes=f) for c in LARGE_LDS for f in (True, False)]
     for c, r in zip(calls, record(calls, tmp_path)):
         assert (r["rc"] == "ok") == (not c["fail_attributes"]), (c, r["rc"])
+
+
+def kernels(result):
+    assert result["rc"] == "ok", result["rc"]
+    return [name for name, *_ in result["launches"]]
+
+
+def test_the_sort_of_the_statistics(tmp_path):
+    """One launch for many groups, or for a large codebook and a number of segments that is no multiple of eight; three launches otherwise."""
+    from test_gpu_training import ONE_LAUNCH_SORTS
+    cases = [(t, g, k, True) for t, g, k in ONE_LAUNCH_SORTS]
+    cases += [(16384, 64, 1024, True), (16384, 64, 256, True), (8000, 64, 256, False), (16384, 1, 256, False), (16384, 32, 1024, False),
+              (7000, 1, 1024, True), (8000, 1, 1024, False), (718, 32, 1024, False), (16385, 64, 1024, False), (16384, 64, 1025, False), (0, 64, 1024, False)]
+    results = record([dict(entry="stats", tokens=t, groups=g, words=k, dg=8) for t, g, k, _ in cases], tmp_path)
+    for (t, g, k, one), r in zip(cases, results):
+        names = kernels(r)
+        assert ("sort_group_kernel" in names) == one and ("sort_place_kernel" in names) == (not one), (t, g, k, names)
