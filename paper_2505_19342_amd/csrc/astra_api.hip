@@ -394,7 +394,8 @@ static int layer_forward_impl(const astra_layer_desc* desc, const void* x_local,
     po.residual = residual; // inside a block: y_out = residual + layer output
 
     // every launch of the layer is validated before the first one runs: an error leaves all outputs untouched
-    rc = launch_gemm_batch(vq.dtype, pr, n_pr, s, offer_fused ? &ej : nullptr, offer_fused ? &enc_fused : nullptr, true);
+    const double enc_later_us = offer_fused ? attention_encode_us(ap, at.head_dim, ej) : -1.0;
+    rc = launch_gemm_batch(vq.dtype, pr, n_pr, s, offer_fused ? &ej : nullptr, offer_fused ? &enc_fused : nullptr, true, nullptr, 0, true, enc_later_us);
     if (rc == ASTRA_OK && pl.wide_enc && !scores_in_projection_launch) {
         for (int g0 = 0; g0 < vq.n_groups && rc == ASTRA_OK; g0 += kMaxGemmProblems) {
             GemmProblem sp[kMaxGemmProblems];
@@ -415,7 +416,7 @@ static int layer_forward_impl(const astra_layer_desc* desc, const void* x_local,
         rc = launch_vq_decode(vq, codes_nonlocal, pl.Tn_vis, codebook, Xh, s);
         if (rc) return rc;
     }
-    rc = launch_gemm_batch(vq.dtype, pr, n_pr, s, offer_fused ? &ej : nullptr, offer_fused ? &enc_fused : nullptr, false);
+    rc = launch_gemm_batch(vq.dtype, pr, n_pr, s, offer_fused ? &ej : nullptr, offer_fused ? &enc_fused : nullptr, false, nullptr, 0, true, enc_later_us);
     if (rc) return rc;
     if (preprojected && pl.Tn_vis > 0) {
         rc = launch_preproj_gather(vq.dtype, vq.code_type, codes_nonlocal, pre_k, bk, pl.Tn_vis, vq.n_groups, vq.codebook_size, pl.dkv,

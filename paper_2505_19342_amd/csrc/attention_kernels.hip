@@ -602,6 +602,15 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const AttnParams p, int d
     if (p.lse && lane == 0) p.lse[(int64_t)head * p.Tq + row] = M + logf(L);
 }
 
+double attention_encode_us(const AttnParams& p, int head_dim, const EncodeJob& e) {
+    if (head_dim != 128 || !p.v_transposed || e.n_tokens <= 0 || !vq_encode_fast_ok(e.K, e.dg)) return -1.0;
+    const int64_t total = ceil_div(p.Tq, kAttQ) * p.Hq, items = ceil_div(e.n_tokens, kAttThreads / 2) * e.G;
+    const int64_t rounds = ceil_div(total + items, (int64_t)kAttCus) - ceil_div(total, (int64_t)kAttCus);
+    const double item = 256.0 * e.K * e.dg / 1048576.0 + 2.5;               // 16.5 us and its start at K = 1024, dg = 64
+    const double walk = 6.0 + 1.1 * (p.Tn_vis + p.Tq) / kAttKV;             // a workgroup's tiles of 64 keys
+    return rounds > 0 ? rounds * item : std::max(0.0, item - walk);
+}
+
 int launch_attention(int dtype, const AttnParams& p_in, int head_dim, hipStream_t s, bool plan_only, const EncodeJob* enc, int n_enc,
                      bool* enc_fused) {
     AttnParams p = p_in;

@@ -178,10 +178,11 @@ constexpr int kMaxGemmProblems = 6;
 struct EncodeJob;
 // enc / enc_fused (both or neither): offers the VQ encode of the local rows to the launch; *enc_fused tells whether the
 // launch took it (extra workgroups) or the caller still has to run it.  plan_only: decide and validate, launch nothing.
+// enc_later_us: what the encode adds to a later launch that takes it if this one does not; negative: it needs a launch of its own.
 // split_ws: optional scratch of gemm_split_workspace_bytes() for a single fp32-output problem whose contraction is cut into slices.
 int launch_gemm_batch(int dtype, const GemmProblem* problems, int n_problems, hipStream_t s, const EncodeJob* enc = nullptr,
                       bool* enc_fused = nullptr, bool plan_only = false, void* split_ws = nullptr, size_t split_ws_bytes = 0,
-                      bool may_cut = true);
+                      bool may_cut = true, double enc_later_us = -1.0);
 size_t gemm_split_workspace_bytes(int dtype, int64_t M, int64_t N, int64_t K);
 
 // Row-wise LayerNorm (kind 0) / RMSNorm (kind 1) of the fp32 residual stream x [T, D] into the element type of the layer
@@ -214,8 +215,10 @@ struct AttnParams {
 // plan_only: validate the launch (shape limits, kernel availability) and launch nothing
 // enc / n_enc / enc_fused: up to two VQ encodes that nothing in the launch depends on, offered to it; *enc_fused tells whether
 // the launch took them (extra workgroups in its tail) or the caller still has to run them
+// attention_encode_us: about what one encode adds to the launch (us), negative if the launch would not take it
 int launch_attention(int dtype, const AttnParams& p, int head_dim, hipStream_t s, bool plan_only = false, const EncodeJob* enc = nullptr,
                      int n_enc = 0, bool* enc_fused = nullptr);
+double attention_encode_us(const AttnParams& p, int head_dim, const EncodeJob& e);
 int launch_mfma_probe(float* out, int n_blocks, int iters, hipStream_t s);
 
 }  // namespace astra

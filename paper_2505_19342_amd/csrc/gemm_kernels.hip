@@ -8,6 +8,7 @@
 #include "gemm_bf16_wave.h"
 
 #include <algorithm>
+#include <cmath>
 
 namespace astra {
 
@@ -175,7 +176,41 @@ static int64_t count_tiles(const GemmProblem* problems, int n_problems, int bm, 
     return t;
 }
 
-// ---- durations (us) by which a launch's form is chosen, fitted to the kernels one by one (MI355X)
+// ---- durations (us) by which a launch's form is chosen, fitted to 4819 products of 4 - 6000 rows, 64 - 8192 columns and contractions of
+// 64 - 14336, every form timed on each (20 launches back to back).  In 99 of 100 the form chosen is within 3.4 % of the fastest the product
+// has had, with the forms there are or with the two-contraction-group tiles they took the place of; 14 % off at most but for a few of more than
+// 4000 rows over 2000 - 5000 (30 %).  Gathered rows: 1087 layers of 17 - 1500 rows at three widths, every form of their projection launch timed,
+// within 2.8 % in 99 of 100.
+
+constexpr double kLaunchUs = 4.0;             // a dependent launch that does next to nothing
+
+struct FormTimes {
+    double first, first_k;        // the first workgroup of a unit, and its part per 1000 of contraction
+    double next, next_k;          // one more, where that makes the number of workgroups on the unit even ...
+    double pair, pair_k;          // ... and two more (two fit a unit at a time, or this is twice the line above)
+    double store;                 // TB/s at which results leave: a round's stores are all issued at its end
+    double fetch;                 // TB/s at which operands come in at best
+    double codes = 0, codes_k = 0, codes_next = 0, codes_next_k = 0;      // gathered rows, on top of what they add to the tile kernel: the codes are
+                                  // copied to LDS before a workgroup fetches anything, which two on a unit hide from each other; ... per further round
+    double from_memory = 1.0;     // factor where the weights are too large for the second-level caches
+};
+// 2000 x 4096 outputs over K = 64: 16.4 us on 64 x 64 tiles (a workgroup's start, reduction and stores come again in every round), 25.6 on 32 x 32,
+// 10.8 on 128 x 256.  6 x 718 x 1024 over K = 128 in one launch after another: 89.8 on 64 x 64, 79.3 on 128 x 128 of the tile kernel.
+// 64 x 1024 over K = 1024: 3.7 on 32 x 32, 11.5 on 128 x 128.
+constexpr FormTimes kWaveTimes[kWaveConfigs] = {
+    {2.8, 0.91, 0.0, 1.6, 0.75, 2.6, 5.0, 6.0, 2.0, -1.5, 0.4, -0.1},      // 32 x 32
+    {3.1, 1.55, 0.9, 2.6, 1.8, 5.2, 2.65, 6.0, 2.8, -1.2, 0.3, 1.1},       // 64 x 32
+    {3.3, 2.45, 1.1, 3.2, 2.2, 6.4, 3.3, 6.0, 2.5, -0.7, 1.4, 0.4},        // 64 x 64, two stages
+    {3.4, 2.9, 0.0, 2.3, 0.4, 5.9, 3.8, 6.0, 2.2, -1.1, 0.6, -0.2, 1.04},  // 64 x 64, one stage
+    {4.5, 4.6, 1.2, 5.9, 2.4, 11.8, 2.9, 6.0, 3.0, 0.1, 1.9, 1.1},         // 128 x 64
+    {6.5, 6.05, 1.2, 8.2, 2.4, 16.4, 2.9, 6.0, 3.3, 0.9, 3.4, 2.1}};       // 128 x 128
+constexpr FormTimes kTile256 = {8.9, 20.2, 4.6, 23.3, 9.2, 46.6, 8.4, 4.2};       // 256 x 256
+constexpr FormTimes kTile128x256 = {5.7, 13.1, 5.7, 13.1, 11.4, 26.2, 6.7, 4.2};  // a single round
+// 128 x 128 on eight wavefronts.  Its two stages do not cover a round trip to memory: a Llama block of 335 rows took 337 us with its projections on
+// these tiles and 317 with them on the wavefront-private ones, which are level when the same layer is repeated and the weights stay in the caches
+// (2543 products with weights of 15 - 300 MB that change with every launch: 1.6 times the time below, 1.1 - 1.4 for the other forms).
+constexpr FormTimes kTile128 = {3.7, 8.35, 1.0, 2.0, 4.0, 10.0, 4.5, 4.2, 0, 0, 0, 0, 1.25};
+constexpr double kCachedWeights = 16e6;       // bytes; half of the second-level caches
 
 static bool plain_layer(const GemmProblem* problems, int n_problems) {
     for (int i = 0; i < n_problems; ++i)
@@ -183,44 +218,52 @@ static bool plain_layer(const GemmProblem* problems, int n_problems) {
     return true;
 }
 
-// Tile kernel: rounds of 256 x 256 tiles (about 105 us per 4096 of contraction), one round of 128 x 256 tiles (70), else 128 x 128 tiles
-// on eight wavefronts, two workgroups per unit (80 per round).
-static double tile_launch_us(const GemmProblem* problems, int n_problems, bool can_split) {
-    int k_max = 0;
-    for (int i = 0; i < n_problems; ++i) k_max = std::max(k_max, problems[i].K);
-    const double kf = k_max / 4096.0;
-    const int64_t big = count_tiles(problems, n_problems, 256, 256);
-    if (big == 0) return 0.0;
-    const bool plain = plain_layer(problems, n_problems);
-    if (plain && big <= 128) {
-        const int64_t mid = count_tiles(problems, n_problems, 128, 256);
-        if (mid > kCus / 2 && mid <= kCus) return 70.0 * kf + 8.0;
-    }
-    if (big >= 128) return (double)ceil_div(big, (int64_t)kCus) * 105.0 * kf + 8.0;
-    const GemmProblem& p0 = problems[0];
-    const int ns = !plain && can_split && p0.c_mode == kCF32 && p0.ldc % 4 == 0 ? gemm_split_factor(ASTRA_BF16, p0.M, p0.N, p0.K) : 1;
-    if (ns > 1) return 105.0 * kf / ns + 8.0 + 4.5 + (ns + 2.0) * p0.M * p0.N * 4.0 / 5.0e6;      // sliced contraction and its reduction
-    return (double)ceil_div(count_tiles(problems, n_problems, 128, 128), (int64_t)(2 * kCus)) * 80.0 * kf + 8.0;
-}
-
-// Wavefront-private kernel: a tile takes its operand bytes at 98 B/ns and its matrix work at 8.4 Gflop/ms (the two add up on four
-// wavefronts; 128 x 64 tiles fall short of that), workgroups beyond the first per unit queue for the same intake; around them the launch, a latency at either end and the
-// reduction through LDS, which two workgroups of a unit hide for each other; never faster than memory delivers the operands.
-static double wave_launch_us(const GemmProblem* problems, int n_problems, int cfg) {
-    const WaveConfig& c = kWaveTable[cfg];
-    int k_max = 0;
-    double bytes = 0.0;
+static double form_us(const FormTimes& f, const GemmProblem* problems, int n_problems, int64_t tiles) {
+    double k = 0.0, operands = 0.0, weights = 0.0, results = 0.0;
+    bool gather = false;
     for (int i = 0; i < n_problems; ++i) {
         const GemmProblem& p = problems[i];
         if (p.M <= 0 || p.N <= 0) continue;
-        k_max = std::max(k_max, p.K);
-        bytes += ((double)p.N + (p.codes ? 0.0 : (double)p.M)) * p.K * 2.0 + (double)p.M * p.N * 2.0;
+        k = std::max(k, p.K * 1e-3);
+        gather = gather || p.codes;
+        weights += (double)p.N * p.K * 2.0;
+        if (!p.codes) operands += (double)p.M * p.K * 2.0;
+        results += (double)p.M * p.N * (p.c_mode == kCF32 ? 4.0 : p.c_mode == kCSwiGLU ? 1.0 : 2.0);
     }
-    const int64_t tiles = count_tiles(problems, n_problems, c.bm, c.bn);
-    const double tile = (c.bm == 128 && c.bn == 64 ? 1.1 : 1.0) * k_max * ((c.bm + c.bn) * 2.0 / 98.0e3 + (double)c.bm * c.bn * 2.0 / 8.4e6);
-    const double tail = 3.8 * c.bm * c.bn / 16384.0;
-    const double rounds = (double)ceil_div(tiles, (int64_t)kCus);
-    return std::max(2.2 + tail + rounds * tile + (c.per_cu == 1 ? (rounds - 1.0) * tail : 0.0), 4.0 + bytes / 5.1e6);
+    const double more = (double)(std::max<int64_t>(ceil_div(tiles, (int64_t)kCus), 1) - 1), pairs = std::floor(more / 2.0), odd = more - 2.0 * pairs;
+    const double compute = f.first + f.first_k * k + odd * (f.next + f.next_k * k) + pairs * (f.pair + f.pair_k * k);
+    const double codes = gather ? f.codes + f.codes_k * k + more * (f.codes_next + f.codes_next_k * k) : 0.0;
+    const double us = codes + std::max(compute, 3.0 + (operands + weights) / (f.fetch * 1e6)) + results / (f.store * 1e6);
+    return weights > kCachedWeights ? us * f.from_memory : us;
+}
+
+// the tile kernel's form for a set of problems, in the order launch_gemm_batch picks it
+static const FormTimes& tile_form(const GemmProblem* problems, int n_problems, int64_t* tiles) {
+    const int64_t big = count_tiles(problems, n_problems, 256, 256);
+    if (plain_layer(problems, n_problems) && big <= 128) {
+        *tiles = count_tiles(problems, n_problems, 128, 256);
+        if (*tiles > kCus / 2 && *tiles <= kCus) return kTile128x256;
+    }
+    *tiles = big >= 128 ? big : count_tiles(problems, n_problems, 128, 128);
+    return big >= 128 ? kTile256 : kTile128;
+}
+
+static double tile_launch_us(const GemmProblem* problems, int n_problems, bool can_split) {
+    int64_t tiles = 0;
+    const FormTimes& f = tile_form(problems, n_problems, &tiles);
+    const GemmProblem& p0 = problems[0];
+    const int ns = can_split && &f == &kTile128 && n_problems == 1 && !plain_layer(problems, 1) && p0.c_mode == kCF32 && p0.ldc % 4 == 0
+                       ? gemm_split_factor(ASTRA_BF16, p0.M, p0.N, p0.K) : 1;
+    if (ns > 1) {
+        // the sliced contraction and its reduction.  The other forms' times fall short by a fifth over contractions as long as these
+        // (1024 x 4096 outputs, K = 14336: 130 us sliced and 135 on 128 x 128 tiles; 2048 x 2048, K = 8192: 83 and 72)
+        GemmProblem slice = p0;
+        slice.K = p0.K / ns;
+        const double mn = (double)p0.M * p0.N * 4.0;
+        return 0.8 * (form_us(kTile256, &slice, 1, count_tiles(problems, 1, 256, 256) * ns) + (ns - 1.0) * mn / (kTile256.store * 1e6) + 4.5 +
+                      (ns + 2.0) * mn / 5.0e6);
+    }
+    return form_us(f, problems, n_problems, tiles);
 }
 
 // LDS bytes for a tile's codes (the largest of the problems); -1: they do not fit beside the ring
@@ -232,34 +275,69 @@ static int wave_code_bytes(const GemmProblem* problems, int n_problems, int cfg)
     return kWaveTable[cfg].lds + need <= 156 * 1024 ? (int)need : -1;
 }
 
-constexpr double kWaveMargin = 0.97;       // what the fits are good for
+// ---- the encode of the local rows, offered to a projection launch.  An item is 128 tokens of one group on four wavefronts, or 256 on eight.
+static double encode_item_us(const EncodeJob& e) { return 256.0 * e.K * e.dg / 1048576.0; }      // its codewords; 2.5 us before the first of them
+// otherwise: in a later launch, or as one of its own (two items share a unit in 0.9 of their time)
+static double encode_later_us(const EncodeJob& e, double later_us) {
+    if (later_us >= 0.0) return later_us;
+    const double items = (double)ceil_div(e.n_tokens, (int64_t)kWaveThreads / 2) * e.G;
+    return kLaunchUs + 2.5 + encode_item_us(e) * std::max(1.0, 0.45 * items / kCus);
+}
 
-// the fastest wavefront-private form of a set of problems, -1: none applies
-static int best_wave(const GemmProblem* problems, int n_problems, double* us) {
+// Workgroups for it in a launch of `tiles` 256 x 256 or 128 x 256 tiles; 0: it does not ride.  It takes units that the last round leaves idle, and
+// must not outlast the tiles (16.5 us measured for an item at K = 1024, dg = 64).
+static int tile_encode_wgs(const EncodeJob& e, int64_t tiles, bool mid, int k_max) {
+    const int rem = (int)(tiles % kCus), E = rem == 0 ? 0 : (kCus - rem) & ~7;
+    const int64_t items = ceil_div(e.n_tokens, 256) * e.G;
+    const double tile_us = (mid ? 70.0 : 105.0) * k_max / 4096.0;
+    return E >= 8 && E <= kCus / 2 && items <= 0x7fffffff && (double)ceil_div(items, (int64_t)E) * encode_item_us(e) <= 1.05 * tile_us ? E : 0;
+}
+
+// The same in a launch of the wavefront-private kernel that lasts `us` without it; *extra_us: what the encode adds, riding or later.  It rides
+// in what room the last round leaves, from when that round begins, if it outlasts the products by less than it costs later.
+static int wave_encode_wgs(const EncodeJob& e, const WaveConfig& wc, int64_t tiles, double us, double later_us, double* extra_us) {
+    const int64_t items = ceil_div(e.n_tokens, (int64_t)kWaveThreads / 2) * e.G, slots = (int64_t)kCus * wc.per_cu;
+    const int64_t room = (ceil_div(tiles, slots) * slots - tiles) & ~(int64_t)7;
+    const int64_t E = std::min<int64_t>(align_up((size_t)items, 8), room > 0 ? std::min<int64_t>(room, kCus) : kCus);
+    const double ride = (double)ceil_div(items, E) * (encode_item_us(e) + 2.5), later = encode_later_us(e, later_us);
+    const double begins = room > 0 ? us * (1.0 - 1.0 / (double)std::max<int64_t>(ceil_div(tiles, slots), 1)) : us;
+    const double over = std::max(0.0, begins + ride - us);
+    *extra_us = std::min(over, later);
+    return items <= 0x7fffffff && over < later ? (int)E : 0;
+}
+
+struct WaveChoice {
+    int cfg;                 // -1: none applies
+    int enc_wgs;             // workgroups for the encode
+    double us;               // with the encode, riding or later
+};
+
+// the fastest wavefront-private form of a set of problems; enc: the encode it is offered (nullable)
+static WaveChoice best_wave(const GemmProblem* problems, int n_problems, const EncodeJob* enc, double enc_later_us) {
+    WaveChoice best = {-1, 0, 0.0};
     for (int i = 0; i < n_problems; ++i) {
         const GemmProblem& p = problems[i];
-        if (p.M > 0 && (p.N % 8 != 0 || p.ldc % 4 != 0)) return -1;          // four consecutive columns per thread
+        if (p.M > 0 && (p.N % 8 != 0 || p.ldc % 4 != 0)) return best;          // four consecutive columns per thread
     }
-    int best = -1;
     for (int cfg = 0; cfg < kWaveConfigs; ++cfg) {
         if (wave_code_bytes(problems, n_problems, cfg) < 0) continue;
-        const double t = wave_launch_us(problems, n_problems, cfg);
-        if (best < 0 || t < *us) {
-            best = cfg;
-            *us = t;
-        }
+        const int64_t tiles = count_tiles(problems, n_problems, kWaveTable[cfg].bm, kWaveTable[cfg].bn);
+        const double t = form_us(kWaveTimes[cfg], problems, n_problems, tiles);
+        double extra = 0.0;
+        const int E = enc ? wave_encode_wgs(*enc, kWaveTable[cfg], tiles, t, enc_later_us, &extra) : 0;
+        if (best.cfg < 0 || t + extra < best.us) best = {cfg, E, t + extra};
     }
     return best;
 }
 
 static double launch_us(const GemmProblem* problems, int n_problems) {
     const double t = tile_launch_us(problems, n_problems, false);
-    double w = 0.0;
-    return best_wave(problems, n_problems, &w) >= 0 && w < kWaveMargin * t ? w : t;
+    const WaveChoice w = best_wave(problems, n_problems, nullptr, -1.0);
+    return w.cfg >= 0 && w.us < t ? w.us : t;
 }
 
 int launch_gemm_batch(int dtype, const GemmProblem* problems, int n_problems, hipStream_t s, const EncodeJob* enc, bool* enc_fused,
-                      bool plan_only, void* split_ws, size_t split_ws_bytes, bool may_cut) {
+                      bool plan_only, void* split_ws, size_t split_ws_bytes, bool may_cut, double enc_later_us) {
     if (enc_fused) *enc_fused = false;
     if (n_problems > kMaxGemmProblems) return ASTRA_ERR_UNSUPPORTED;
     // A launch whose last round of 256 x 256 tiles is nearly empty lasts a whole tile longer for a few tiles.  When the
@@ -289,10 +367,10 @@ int launch_gemm_batch(int dtype, const GemmProblem* problems, int n_problems, hi
                     rc = launch_gemm_batch(dtype, b, nb, s, nullptr, nullptr, true, nullptr, 0, false);
                     if (rc) return rc;
                 }
-                rc = launch_gemm_batch(dtype, a, na, s, enc, enc ? &fused_a : nullptr, plan_only, nullptr, 0, false);
+                rc = launch_gemm_batch(dtype, a, na, s, enc, enc ? &fused_a : nullptr, plan_only, nullptr, 0, false, enc_later_us);
                 if (rc) return rc;
                 rc = launch_gemm_batch(dtype, b, nb, s, fused_a ? nullptr : enc, enc && !fused_a ? &fused_b : nullptr, plan_only,
-                                       nullptr, 0, false);
+                                       nullptr, 0, false, enc_later_us);
                 if (enc_fused) *enc_fused = fused_a || fused_b;
                 return rc;
             }
@@ -329,33 +407,32 @@ int launch_gemm_batch(int dtype, const GemmProblem* problems, int n_problems, hi
         else if (p0.c_mode == kCF32 && p0.act == kActNone) epi = kEpiResidualF32;
         else return ASTRA_ERR_UNSUPPORTED;
     }
-    double wave_us = 0.0;
-    const int wave_cfg = best_wave(problems, n_problems, &wave_us);
-    if (wave_cfg >= 0 && wave_us < kWaveMargin * tile_launch_us(problems, n_problems, plan_only || split_ws != nullptr)) {
-        const WaveConfig& wc = kWaveTable[wave_cfg];
+    const EncodeJob* offered = enc && enc_fused && epi == kEpiLayer && enc->n_tokens > 0 && vq_encode_fast_ok(enc->K, enc->dg) ? enc : nullptr;
+    const WaveChoice wave = best_wave(problems, n_problems, offered, enc_later_us);
+    double tile_us = tile_launch_us(problems, n_problems, plan_only || split_ws != nullptr);
+    int k_max = 0;
+    for (int i = 0; i < n_problems; ++i) k_max = std::max(k_max, problems[i].K);
+    if (offered) {
+        int64_t tiles = 0;
+        const FormTimes& f = tile_form(problems, n_problems, &tiles);
+        if (&f == &kTile128 || tile_encode_wgs(*enc, tiles, &f == &kTile128x256, k_max) == 0) tile_us += encode_later_us(*enc, enc_later_us);
+    }
+    if (wave.cfg >= 0 && wave.us < tile_us) {
+        const WaveConfig& wc = kWaveTable[wave.cfg];
         int rc = fill_batch(batch, dtype, problems, n_problems, wc.bm, wc.bn, &total);
         if (rc) return rc;
         if (total == 0) return ASTRA_OK;
         bool gather = false;
         for (int i = 0; i < batch.n; ++i) gather = gather || batch.p[i].codes != nullptr;
-        // The encode of the local rows rides along (128 tokens of one group an item: about 1 us per 2^20 codeword elements of 256 tokens,
-        // and 2.5 us before its first tile) when the last round has room for its workgroups and they outlast the products by less than
-        // a launch of their own would cost, or when they are short enough to follow the tiles.
-        if (enc && enc_fused && epi == kEpiLayer && enc->n_tokens > 0 && vq_encode_fast_ok(enc->K, enc->dg)) {
-            const int64_t n_tb = ceil_div(enc->n_tokens, kWaveThreads / 2), items = n_tb * enc->G;
-            const int64_t slots = (int64_t)kCus * wc.per_cu, room = (ceil_div(total, slots) * slots - total) & ~(int64_t)7;
-            const int64_t E = std::min<int64_t>(align_up((size_t)items, 8), room > 0 ? std::min<int64_t>(room, kCus) : kCus);
-            const double enc_us = (double)ceil_div(items, E) * 256.0 * enc->K * enc->dg / 1048576.0 + 2.5;
-            if (items <= 0x7fffffff && enc_us <= (room > 0 ? wave_us + 4.0 : 6.0)) {
-                batch.n_enc_wgs = (int)E;
-                batch.enc = *enc;
-                batch.enc.n_tb = (int)n_tb;
-                batch.enc.n_wgs = (int)E;
-                *enc_fused = true;
-            }
+        if (wave.enc_wgs > 0) {
+            batch.n_enc_wgs = wave.enc_wgs;
+            batch.enc = *enc;
+            batch.enc.n_tb = (int)ceil_div(enc->n_tokens, kWaveThreads / 2);
+            batch.enc.n_wgs = wave.enc_wgs;
+            *enc_fused = true;
         }
         if (plan_only) return ASTRA_OK;
-        return launch_gemm_wave(wave_cfg, epi, gather, batch, total + batch.n_enc_wgs, wave_code_bytes(problems, n_problems, wave_cfg), s);
+        return launch_gemm_wave(wave.cfg, epi, gather, batch, total + batch.n_enc_wgs, wave_code_bytes(problems, n_problems, wave.cfg), s);
     }
     if (mlp) {
         const GemmProblem& p0 = problems[0];
@@ -379,7 +456,8 @@ int launch_gemm_batch(int dtype, const GemmProblem* problems, int n_problems, hi
         return launch_gemm_mlp(epi, false, batch, total, s);
     }
     // Large tiles quarter the operand traffic per flop; use them once they still fill most of the chip.  What is left after the choice above
-    // are launches of many tiles, and cuts into groups whose codes do not fit the wavefront-private kernel's LDS.
+    // are launches of many tiles, short contractions with large outputs, outputs that are no multiple of eight columns wide, and cuts into groups
+    // whose codes do not fit the wavefront-private kernel's LDS.
     int rc = fill_batch(batch, dtype, problems, n_problems, 256, 256, &total);
     if (rc) return rc;
     bool big = total >= 128;
@@ -400,21 +478,12 @@ int launch_gemm_batch(int dtype, const GemmProblem* problems, int n_problems, hi
         }
     }
     // Fuse the encode into the launch when the tiles leave a good part of the last round of compute units idle.
-    if ((big || mid) && enc && enc_fused && vq_encode_fast_ok(enc->K, enc->dg) && enc->n_tokens > 0) {
-        const int rem = total % kCus;
-        const int E = rem == 0 ? 0 : ((kCus - rem) & ~7);
-        const int64_t n_tb = ceil_div(enc->n_tokens, 256);
-        // The encode workgroups must not outlast the tiles: an item (256 tokens of one group against its K codewords)
-        // takes about 1 us per 2^20 codeword elements (16.5 us measured at K = 1024, dg = 64), a 256 x 256 tile about
-        // 105 us per 4096 of contraction, a 128 x 256 tile about 70.
-        int k_max = 0;
-        for (int i = 0; i < batch.n; ++i) k_max = batch.p[i].K > k_max ? batch.p[i].K : k_max;
-        const double tile_us = (mid ? 70.0 : 105.0) * k_max / 4096.0;
-        const double enc_us = E > 0 ? (double)ceil_div(n_tb * enc->G, (int64_t)E) * 256.0 * enc->K * enc->dg / 1048576.0 : 0.0;
-        if (E >= 8 && E <= kCus / 2 && n_tb * enc->G <= 0x7fffffff && enc_us <= 1.05 * tile_us) {
+    if ((big || mid) && offered) {
+        const int E = tile_encode_wgs(*enc, total, mid, k_max);
+        if (E > 0) {
             batch.n_enc_wgs = E;
             batch.enc = *enc;
-            batch.enc.n_tb = (int)n_tb;
+            batch.enc.n_tb = (int)ceil_div(enc->n_tokens, 256);
             batch.enc.n_wgs = E;
             *enc_fused = true;
             if (plan_only) return ASTRA_OK;

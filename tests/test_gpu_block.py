@@ -163,6 +163,36 @@ def test_rotary_positions_need_a_causal_layer():
     assert bool((blk.x_out == -7.0).all())
 
 
+# width, rows, groups, codewords, MLP, hidden width, and forms among the block's products with their epilogues, as tests/test_launches.py checks
+MLP_LAUNCHES = [
+    (256, 1032, 32, 256, "gelu_tanh", 512, ("wave<2, 1, 2> residual", "wave<2, 2, 2> gelu_tanh", "wave<1, 1, 2> residual")),
+    (512, 76, 8, 256, "gelu_erf", 3072, ("wave<2, 1, 2> gelu_erf",)),
+    (512, 94, 8, 16, "gelu_tanh", 3072, ("wave<2, 1, 2> gelu_tanh",)),
+    (512, 93, 16, 16, "swiglu", 2048, ("wave<2, 1, 2> swiglu",)),
+    (1024, 1049, 8, 16, "swiglu", 512, ("wave<2, 2, 1> residual", "wave<2, 2, 1> swiglu")),
+    (256, 522, 32, 1024, "gelu_tanh", 2048, ("wave<2, 2, 1> gelu_tanh",)),
+    (256, 357, 8, 1024, "gelu_erf", 3072, ("wave<2, 2, 1> gelu_erf",)),
+    (512, 1072, 8, 16, "swiglu", 512, ("wave<2, 2, 2> residual",)),
+    (256, 70, 4, 256, "swiglu", 3072, ("wave<2, 2, 2> swiglu",)),
+    (256, 172, 16, 16, "gelu_erf", 3072, ("wave<2, 2, 2> gelu_erf",)),
+    (256, 655, 32, 1024, "gelu_tanh", 3072, ("tile<128, 128> gelu_tanh",)),
+    (256, 667, 4, 16, "gelu_erf", 3072, ("tile<128, 128> gelu_erf",)),
+    (256, 333, 8, 256, "swiglu", 3072, ("tile<128, 128> swiglu",)),
+    (1024, 1048, 8, 16, "gelu_tanh", 3072, ("wave<4, 2, 1> residual",)),
+    (2048, 355, 8, 256, "swiglu", 3072, ("wave<4, 4, 1> swiglu",)),
+    (2048, 283, 8, 1024, "swiglu", 2048, ("wave<4, 2, 1> swiglu",)),
+    (2048, 1047, 8, 1024, "swiglu", 512, ("wave<4, 4, 1> residual", "tile<128, 128> residual")),
+]
+
+
+@pytest.mark.parametrize("d,rows,groups,words,mlp,d_ff,forms", MLP_LAUNCHES)
+def test_products_of_the_block_with_ragged_rows(d, rows, groups, words, mlp, d_ff, forms):
+    from test_gpu_layer import MODEL_OF_WIDTH
+    hq, hkv, dh = MODEL_OF_WIDTH[d]
+    layer = wl.LayerConfig("forms", "bf16", d, hq, hkv, dh, rows, 1, groups, words, causal=True, seed=63)
+    run_case(wl.BlockConfig("forms_block", layer, "layernorm", mlp, d_ff, 1e-5, True), 0)
+
+
 @pytest.mark.parametrize("rows", [3, 4100])
 @pytest.mark.parametrize("mlp,gate,up,down", [("swiglu", (-88.0, 0.0), 2.0 ** 100, 2.0 ** 20), ("gelu_tanh", (-10.0, -0.03125), None, 2.0 ** 120)])
 def test_activations_far_out_on_the_negative_side(mlp, gate, up, down, rows):

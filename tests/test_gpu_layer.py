@@ -114,8 +114,8 @@ def test_llama_dims_ragged_rows_in_every_projection_tile_shape(seq_len, lo, fuse
     so the last tile of every projection and the last token block of the encode are ragged.  The cases take the
     launch shapes of the projections: 256x256 tiles with the encode on the units left over (the configuration
     bench.py times), 192 tiles of 128x256 with the encode on the units left over (no visible peers), 256 tiles of
-    128x256 that fill the chip (the encode then runs as a kernel of its own), and 288 tiles of 256x256, which are dealt
-    into two launches (one of 256x256 tiles that fills its round, one on 128x128 tiles)."""
+    128x256 that fill the chip (the attention launch then takes the encode), and 288 tiles of 256x256, which are dealt
+    into two launches (one of 256x256 tiles that fills its round, one on smaller tiles)."""
     from gpu_util import LayerOnGpu, compare_codes
     from paper_2505_19342_amd import binding as B
     cfg = dataclasses.replace(wl.LLAMA3_8B, name="llama_ragged", seq_len=seq_len, seed=41)
@@ -133,6 +133,50 @@ def test_llama_dims_ragged_rows_in_every_projection_tile_shape(seq_len, lo, fuse
     err = np.abs(y - y_ref).max()
     print(f"llama dims, {seq_len - lo} local / {lo} non-local rows: max abs err {err:.3e}, near-tie codes {n_tie}/{codes.size}")
     assert err <= Y_TOL["bf16"]
+    assert n_tie <= max(2, codes.size // 2000)
+
+
+# width, local rows, visible peer rows, groups, codewords, and the form of the projection launch (GATHER: the peers' rows from their codes; ENC: with
+# the encode), as tests/test_launches.py checks
+MODEL_OF_WIDTH = {256: (4, 2, 64), 512: (4, 2, 128), 768: (12, 12, 64), 1024: (8, 8, 128), 2048: (16, 4, 128), 4096: (32, 8, 128)}
+PROJECTION_LAUNCHES = [
+    (256, 36, 14, 4, 16, "wave<1, 1, 2> GATHER ENC"),
+    (512, 27, 6, 4, 256, "wave<1, 1, 2> GATHER"),
+    (768, 104, 0, 64, 16, "wave<2, 1, 2>"),
+    (768, 108, 0, 32, 256, "wave<2, 1, 2> ENC"),
+    (256, 865, 95, 16, 16, "wave<2, 2, 1> GATHER ENC"),
+    (768, 153, 70, 8, 16, "wave<2, 2, 1> GATHER"),
+    (256, 802, 425, 4, 1024, "wave<2, 2, 2> GATHER ENC"),        # 16-bit codes
+    (2048, 116, 140, 32, 256, "wave<2, 2, 2> GATHER"),
+    (4096, 131, 0, 8, 1024, "wave<4, 2, 1>"),
+    (768, 834, 0, 32, 16, "wave<4, 2, 1> ENC"),
+    (768, 733, 0, 16, 1024, "wave<4, 4, 1> ENC"),
+    (768, 590, 197, 16, 1024, "wave<4, 4, 1> GATHER ENC"),
+    (2048, 1015, 25, 16, 16, "wave<4, 4, 1> GATHER"),
+    (512, 925, 180, 8, 1024, "tile<128, 128> GATHER"),
+]
+
+
+@pytest.mark.parametrize("d,n_local,n_nonlocal,groups,words,form", PROJECTION_LAUNCHES)
+def test_projection_launches_with_ragged_rows(d, n_local, n_nonlocal, groups, words, form):
+    """Every form of the projection launch on rows that end inside a tile, causal, with biases: stores to rows and to the transposed V, gathered
+    rows, the encode alongside."""
+    from gpu_util import LayerOnGpu, compare_codes
+    hq, hkv, dh = MODEL_OF_WIDTH[d]
+    cfg = wl.LayerConfig("forms", "bf16", d, hq, hkv, dh, n_local + n_nonlocal, 1, groups, words, causal=True, seed=61)
+    data = wl.generate(cfg)
+    rng = np.random.default_rng(62)
+    b = [wl.round_to_bf16((0.1 * rng.standard_normal(n)).astype(np.float32)) for n in (hq * dh, hkv * dh, hkv * dh, d)]
+    x_nl, x_local = data["x"][:n_nonlocal], data["x"][n_nonlocal:]
+    codes_nl = oracle.vq_encode(x_nl, data["codebook"])
+    y_ref, codes_ref, gap = oracle.layer_forward(x_local, codes_nl, data["codebook"], data["wq"], data["wk"], data["wv"], data["wo"],
+                                                 n_q_heads=hq, n_kv_heads=hkv, causal=True, n_before=n_nonlocal, return_gap=True,
+                                                 bq=b[0], bk=b[1], bv=b[2], bo=b[3])
+    layer = LayerOnGpu(cfg, data, x_local, codes_nl, n_nonlocal, biases=b)
+    layer.run()
+    y, codes = layer.results()
+    n_tie = compare_codes(codes, codes_ref, gap, NEAR_TIE)
+    assert np.abs(y - y_ref).max() <= Y_TOL["bf16"]
     assert n_tie <= max(2, codes.size // 2000)
 
 

@@ -8,17 +8,30 @@ from paper_2505_19342_amd import workloads as wl
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("m,n,k", [
-    (4, 8, 64),          # one contraction slice: three of the four wavefronts of a workgroup have none
-    (32, 32, 256),       # one tile, one slice per wavefront
-    (33, 40, 320),       # one row and eight columns beyond a tile, five slices over four wavefronts
-    (60, 768, 768),      # ring of two stages, three slices per wavefront
-    (260, 1032, 192),    # several column tiles, the last one of eight columns
-    (256, 4096, 1024),   # larger tiles
-    (516, 4096, 512),    # two workgroups per unit
-    (1024, 4096, 576),   # 128 x 128 tiles, nine slices over four wavefronts
-])
-def test_product_forms(m, n, k):
+# rows, columns, contraction, the form that runs them: wave<row tiles of 32, column tiles, stages> or tile<rows, columns> (tests/test_launches.py
+# checks that they do)
+PRODUCTS = [
+    (4, 8, 64, "wave<1, 1, 2>"),            # one contraction slice: three of the four wavefronts of a workgroup have none
+    (32, 32, 256, "wave<1, 1, 2>"),         # one tile, one slice per wavefront
+    (33, 40, 320, "wave<1, 1, 2>"),         # one row and eight columns beyond a tile, five slices over four wavefronts
+    (60, 768, 768, "wave<1, 1, 2>"),        # ring of two stages, three slices per wavefront
+    (260, 1032, 192, "wave<1, 1, 2>"),      # several column tiles, the last one of eight columns
+    (100, 2056, 576, "wave<2, 1, 2>"),      # nine slices over four wavefronts, four rows beyond a tile
+    (228, 2056, 64, "wave<2, 2, 2>"),
+    (256, 4096, 1024, "wave<2, 2, 2>"),
+    (516, 2056, 64, "wave<2, 2, 1>"),       # two workgroups per unit
+    (228, 4104, 2112, "wave<4, 2, 1>"),
+    (1028, 2056, 2112, "wave<4, 4, 1>"),    # 33 slices, the reduction in four passes
+    (1028, 2056, 64, "tile<128, 128>"),     # a loop that is all prologue and tail
+    (516, 4096, 512, "tile<128, 128>"),
+    (1024, 4096, 576, "tile<128, 128>"),
+    (1028, 4104, 64, "tile<128, 256>"),
+    (2052, 4104, 64, "tile<256, 256>"),
+]
+
+
+@pytest.mark.parametrize("m,n,k,form", PRODUCTS)
+def test_product_forms(m, n, k, form):
     import torch
     from gpu_util import to_dev, to_host, DEV
     from paper_2505_19342_amd import binding as B

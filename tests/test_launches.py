@@ -1,4 +1,6 @@
 """What the host code launches, without a GPU: the library on top of a recorder in the place of the HIP runtime (launch_record.py)."""
+import re
+
 import pytest
 
 from launch_record import record
@@ -48,3 +50,73 @@ def test_the_sort_of_the_statistics(tmp_path):
     for (t, g, k, one), r in zip(cases, results):
         names = kernels(r)
         assert ("sort_group_kernel" in names) == one and ("sort_place_kernel" in names) == (not one), (t, g, k, names)
+
+
+EPILOGUES = {0: "", 1: " residual", 2: " slice", 3: " gelu_tanh", 4: " gelu_erf", 5: " swiglu"}
+
+
+def forms(result):
+    """The products of a call, as wave<row tiles, column tiles, stages> or tile<rows, columns>, with what they carry."""
+    out = []
+    for name in kernels(result):
+        m = re.match(r"gemm_wave_kernel<(\d, \d, \d), (\w+), (\w+), (\d)>", name)
+        if m:
+            gather, enc = m[2] == "true", m[3] == "true"
+            out.append(f"wave<{m[1]}>" + " GATHER" * gather + " ENC" * enc + EPILOGUES[int(m[4])])
+        m = re.match(r"gemm_nt_bf16_kernel<(\d+, \d+), \d, \d, (\w+), (\w+), (\d)>", name)
+        if m:
+            out.append(f"tile<{m[1]}>" + " ENC" * (m[3] == "true") + EPILOGUES[int(m[4])])
+    return out
+
+
+def test_the_forms_the_gpu_tests_name(tmp_path):
+    """The products, layers and blocks of the GPU tests run on the forms named beside them."""
+    from test_gpu_block import MLP_LAUNCHES
+    from test_gpu_layer import MODEL_OF_WIDTH, PROJECTION_LAUNCHES
+    from test_gpu_projection import PRODUCTS
+    model = {d: dict(d=d, hq=hq, hkv=hkv, dh=dh, causal=True, bias=True) for d, (hq, hkv, dh) in MODEL_OF_WIDTH.items()}
+    for (m, n, k, form), r in zip(PRODUCTS, record([dict(entry="project", m=m, n=n, k=k) for m, n, k, _ in PRODUCTS], tmp_path)):
+        assert forms(r) == [form], (m, n, k)
+    calls = [dict(model[d], entry="layer", n_local=tl, n_nonlocal=tn, groups=g, words=w) for d, tl, tn, g, w, _ in PROJECTION_LAUNCHES]
+    for case, r in zip(PROJECTION_LAUNCHES, record(calls, tmp_path)):
+        assert forms(r)[0] == case[-1].replace("> GATHER", ">" if case[-1].startswith("tile") else "> GATHER"), (case, forms(r))
+    calls = [dict(model[d], entry="block", n_local=t, n_nonlocal=0, groups=g, words=w, mlp=mlp, dff=f, norm="layernorm")
+             for d, t, g, w, mlp, f, _ in MLP_LAUNCHES]
+    for case, r in zip(MLP_LAUNCHES, record(calls, tmp_path)):
+        assert set(case[-1]) <= set(forms(r)), (case, forms(r))
+
+
+@pytest.mark.parametrize("m,n,k,slow", [
+    (2000, 4096, 64, "wave"),       # us on the form it has against the wavefront-private one: 10.8 / 16.4
+    (6000, 1024, 512, "wave"),      # 16.6 / 24.7
+    (2000, 4096, 256, "wave"),      # 13.9 / 18.3
+    (718, 4096, 128, "wave"),       # 6.8 / 8.7
+    (64, 1024, 4096, "tile"),       # 6.4 / 32.0
+    (1000, 4096, 4096, "tile"),     # 36.6 / 46.1
+])
+def test_short_and_long_contractions(m, n, k, slow, tmp_path):
+    """A product whose contraction is short next to its outputs is not cut into many small workgroups, each with a start and a reduction of its own."""
+    (form,) = forms(record([dict(entry="project", m=m, n=n, k=k)], tmp_path)[0])
+    assert not form.startswith(slow), form
+
+
+def test_score_products_of_wide_groups(tmp_path):
+    """32 groups of 128 channels: six products at a time over K = 128.  (79 us for 718 tokens on 128 x 128 tiles, 117 on 32 x 32.)"""
+    for tokens in (718, 2000):
+        r = record([dict(entry="encode", d=4096, groups=32, words=1024, tokens=tokens)], tmp_path)[0]
+        assert all(f.startswith("tile") for f in forms(r)[:5]), forms(r)
+
+
+def test_where_the_encode_of_the_local_rows_runs(tmp_path):
+    """In the projection launch where its last round has room for it, also if that takes another tile; in the attention launch of 128-wide heads where
+    units are idle anyway; and not six items behind one another on sixteen workgroups."""
+    def layer(d, **more):
+        hq, hkv, dh = {768: (12, 12, 64), 4096: (32, 8, 128)}[d]
+        return dict(entry="layer", d=d, hq=hq, hkv=hkv, dh=dh, causal=True, **more)
+    calls = [layer(768, n_local=342, n_nonlocal=342, before=114, groups=32, words=256), layer(768, n_local=212, n_nonlocal=636, before=318, groups=32, words=1024),
+             layer(4096, n_local=1100, n_nonlocal=1100, before=366, groups=64, words=1024), layer(4096, n_local=208, n_nonlocal=416, before=208, groups=64, words=1024)]
+    a, b, c, d = record(calls, tmp_path)
+    assert forms(a)[0] == forms(b)[0] == "wave<2, 2, 1> GATHER ENC"
+    assert forms(c)[0] == "tile<256, 256> ENC"
+    assert "ENC" not in forms(d)[0] and any(re.match(r"attn_bf16_kernel<128, .*, true>", k) for k in kernels(d))
+    assert not any("vq_encode" in k for r in (a, b, c, d) for k in kernels(r))
