@@ -19,9 +19,9 @@ namespace astra {
 // fp32 probabilities keep their precision: p is cut into three bf16 parts that add up to it exactly (8 + 8 + 8 mantissa bits).  Every
 // head has 16 / REP columns with the same scores; the first three of them take one part each, and their sums are added at the
 // end (REP = 8: a head's two columns take two parts, the third goes through a second product).  A part that is zero would turn an
-// infinite value into a NaN, so the parts of a positive p are kept at the smallest normal number at least, and so are those of the rows
-// past the end of the local cache, which repeat its last row; to a finite sum that adds 2^-126 of a value.  The sums are not normalised
-// until the end and p may reach 2^kDsLazy: values beyond the largest float / (2^kDsLazy times the tokens of a wavefront) can overflow.
+// infinite value into a NaN, so every part is the smallest normal number at least, those of rows past the end too (they repeat the last one);
+// to a finite sum that adds 2^-126 of a value.  The sums are not normalised until the end and p may reach 2^kDsLazy: values
+// beyond the largest float / (2^kDsLazy times the tokens of a wavefront) can overflow.
 //
 // Index cache: values are gathered from the codebook into the same registers, by codes that wait in LDS.  Key scores either the
 // same way (gather and multiply), or (TABLE) as sums of entries of a table [group][codeword][head] of query-codeword products that
@@ -35,10 +35,10 @@ namespace astra {
 // NGH: groups of a head when they are whole groups of the head (1, 2 or 4 of DH / NGH channels); 0: any other cut into groups of whole
 // 16-byte pieces (the codes are then read one by one).
 // ------------------------------------------------------------------------------------------------
+typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
 #define DS_INLINE __attribute__((always_inline))
 constexpr int kDsTile = 32;
 constexpr float kDsLazy = 8.f;       // base-2 units a score may exceed the running reference by before the sums are rescaled
-constexpr float kDsTiny = 1.17549435e-38f;      // smallest normal number
 constexpr int kDsCus = 256;          // compute units of the device the launch shapes are chosen for
 
 __device__ __forceinline__ f32x4 mfma_16x16x32(bf16x8 a, bf16x8 b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
@@ -105,9 +105,8 @@ __global__ __launch_bounds__(64 * WAVES, 2) void decode_stream_kernel(const Deco
     float m_run = -INFINITY, l_run = 0.f;
 
     // scores of a tile (base-2 units, -inf = not attended) and its value pieces into the running sums.  A head's columns have the same
-    // scores bit for bit: the parts they take belong to one p.  REPEATS: the rows that are not attended are copies of one that is
-    auto absorb = [&](const float (&s)[8], const Values& v, auto repeats) DS_INLINE {
-        constexpr bool REPEATS = decltype(repeats)::value;
+    // scores bit for bit: the parts they take belong to one p
+    auto absorb = [&](const float (&s)[8], const Values& v) DS_INLINE {
         float mx = s[0];
 #pragma unroll
         for (int e = 1; e < 8; ++e) mx = fmaxf(mx, s[e]);
@@ -131,22 +130,23 @@ __global__ __launch_bounds__(64 * WAVES, 2) void decode_stream_kernel(const Deco
             const float pr = __builtin_amdgcn_exp2f(s[e] - m_ref);
             l_run += pr;
             // every difference is exact, and after two parts at most 8 mantissa bits are left
-            auto not_zero = [&](float part_of) DS_INLINE {
-                return __float_as_uint(REPEATS ? fmaxf(part_of, kDsTiny) : __builtin_amdgcn_fmed3f(part_of, kDsTiny, pr));
-            };
             const float r1 = pr - __uint_as_float(__float_as_uint(pr) & off1);
-            pa[e] = not_zero(SPLIT2 ? r1 : r1 - __uint_as_float(__float_as_uint(r1) & off2));
+            pa[e] = __float_as_uint(SPLIT2 ? r1 : r1 - __uint_as_float(__float_as_uint(r1) & off2));
             if (SPLIT2) {
                 const float q1 = pr - __uint_as_float(__float_as_uint(pr) & 0xffff0000u);
-                pb[e] = not_zero(q1 - __uint_as_float(__float_as_uint(q1) & 0xffff0000u));
+                pb[e] = __float_as_uint(q1 - __uint_as_float(__float_as_uint(q1) & 0xffff0000u));
             }
         }
+        auto two = [&](uint32_t hi, uint32_t lo) DS_INLINE {      // their upper halves, 2^-126 at least (bits of numbers that are not negative compare as they do)
+            const u16x2 parts = __builtin_bit_cast(u16x2, __builtin_amdgcn_perm(hi, lo, 0x07060302u)), tiny = {0x0080, 0x0080};
+            return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(parts, tiny));
+        };
         auto operand = [&](const uint32_t (&x)[8]) DS_INLINE {
             u32x4 w;
-            w.x = __builtin_amdgcn_perm(x[1], x[0], 0x07060302u);
-            w.y = __builtin_amdgcn_perm(x[3], x[2], 0x07060302u);
-            w.z = __builtin_amdgcn_perm(x[5], x[4], 0x07060302u);
-            w.w = __builtin_amdgcn_perm(x[7], x[6], 0x07060302u);
+            w.x = two(x[1], x[0]);
+            w.y = two(x[3], x[2]);
+            w.z = two(x[5], x[4]);
+            w.w = two(x[7], x[6]);
             return __builtin_bit_cast(bf16x8, w);
         };
         const bf16x8 pf = operand(pa);
@@ -243,7 +243,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void decode_stream_kernel(const Deco
             if (t * kDsTile + kDsTile > p.n_local)
 #pragma unroll
                 for (int e = 0; e < 8; ++e) s[e] = t * kDsTile + tok(e) < p.n_local ? s[e] : -INFINITY;
-            absorb(s, v, std::true_type{});
+            absorb(s, v);
         };
         int t = gw;
         if (t >= tiles) return;
@@ -364,7 +364,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void decode_stream_kernel(const Deco
             auto compute = [&](const Values& v) DS_INLINE {
                 look_up(slot, s);
                 mask_index(t, s);
-                absorb(s, v, std::false_type{});
+                absorb(s, v);
                 t += n_waves;
                 slot ^= 1;
             };
@@ -405,12 +405,12 @@ __global__ __launch_bounds__(64 * WAVES, 2) void decode_stream_kernel(const Deco
                 score(k, s);
                 mask_index(t, s);
                 gather_k(slot ^ 1, k);
-                absorb(s, v, std::false_type{});
+                absorb(s, v);
                 gather_v(slot ^ 1, v);
             }
             score(k, s);
             mask_index(t, s);
-            absorb(s, v, std::false_type{});
+            absorb(s, v);
         }
     };
 
@@ -453,12 +453,12 @@ __global__ __launch_bounds__(64 * WAVES, 2) void decode_stream_kernel(const Deco
             score(k, s);
             mask_index(t, s);
             gather_k(c, k);
-            absorb(s, v, std::false_type{});
+            absorb(s, v);
             gather_v(c, v);
         }
         score(k, s);
         mask_index(t, s);
-        absorb(s, v, std::false_type{});
+        absorb(s, v);
     };
     if (local) walk_local();
     else if constexpr (NGH > 0) walk_index();
