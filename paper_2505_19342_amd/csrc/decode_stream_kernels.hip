@@ -519,29 +519,41 @@ DecodeStreamPlan plan_decode_stream(int dtype, int Hq, int Hkv, int dh, int n_lo
     // The table costs a workgroup one pass over the head's key codebook (K rows of the head), gathering keys one row per token, and the
     // look-ups are cheaper than the multiplications: it pays from K / 2 tokens per workgroup of a launch of one per unit (8 000 + 24 000
     // rows, K = 1024: 23.4 us against 27.9), but not for short caches, where twice the workgroups on half the wavefronts come first
-    // (2 181 + 6 546 rows, K = 256: 16.6 us against 15.0).
+    // (2 181 + 6 546 rows, K = 256: 16.6 us against 15.0).  Heads of 64 multiply half as much, and look-ups cost the same: a table pays only for one
+    // group per head and a small codebook (12 KV heads, 10 000 + 30 000 rows: one group, K = 256 16.6 / 18.9 us; two groups, K = 1024 21.5 / 20.0).
     const int at_least = t_loc > 0 && t_nl > 0 ? 2 : 1;      // many KV heads: one workgroup per kind of tiles, and no partial results beyond those
     const int wgs_table = std::max(at_least, kDsCus / Hkv);
     const size_t table = (size_t)(dh / std::max(dg, 1)) * K * rep * sizeof(float);
     const size_t xs = (size_t)rep * (dh + 4) * sizeof(float);
     pl.table = (dg == dh || dg == dh / 2 || dg == dh / 4) && dg >= 32 && (int64_t)K * rep * 4 <= 65536 && table <= 140 * 1024 &&
-               n_nonlocal / wgs_table > std::max(K / 2, 512);
+               n_nonlocal / wgs_table > std::max(K / 2, 512) && (dh == 128 || (dg == dh && K <= 256));
+    // Dealt to the two kinds of tiles in proportion to the time a unit takes for them: a tile of local rows (16 KB from memory) 1.5 times an
+    // index tile's (8 KB from the second-level cache).  32 769 + 98 304 rows at ratios of 1 / 1.5 / 2 / 3: 63 / 52 / 55 / 58 us.  Heads of 64 without
+    // a table take the same time for both (8 KB either way): 6 000 + 18 000 rows of 12 KV heads 16.4 us dealt evenly, 16.7 at 1.5.
+    const bool even = dh == 64 && !pl.table;
+    auto local_share = [&](int n) {
+        if (t_loc == 0 || t_nl == 0) return t_loc == 0 ? 0 : n;
+        const int64_t w_loc = (even ? 2 : 3) * t_loc, w_nl = 2 * t_nl;
+        return std::min(std::max((int)((2 * w_loc * n + w_loc + w_nl) / (2 * (w_loc + w_nl))), 1), n - 1);
+    };
     if (pl.table) {
         wgs = wgs_table;
         pl.lds = std::max(table, kDsTableWaves * xs);
     } else {
-        wgs = (int)std::min<int64_t>(std::max(at_least, 2 * kDsCus / Hkv), ceil_div(t_loc, kDsGatherWaves) + ceil_div(t_nl, kDsGatherWaves));
+        // two workgroups per unit, or three on heads of 64 if a wavefront then walks fewer tiles (the same rows: 15.2 us; 4 832 + 4 832 rows, two
+        // tiles either way: 10.2 with two per unit, 11.5 with three)
+        const int most = (int)std::min<int64_t>(ceil_div(t_loc, kDsGatherWaves) + ceil_div(t_nl, kDsGatherWaves), 1 << 20);
+        auto walk = [&](int n) {
+            const int loc = local_share(n);
+            return std::max(loc > 0 ? ceil_div(t_loc, (int64_t)loc * kDsGatherWaves) : 0, n > loc ? ceil_div(t_nl, (int64_t)(n - loc) * kDsGatherWaves) : 0);
+        };
+        wgs = std::min(std::max(at_least, 2 * kDsCus / Hkv), most);
+        const int three = std::min(std::max(at_least, 3 * kDsCus / Hkv), most);
+        if (even && at_least == 2 && walk(three) < walk(wgs)) wgs = three;
         pl.lds = kDsGatherWaves * xs;
     }
-    // Dealt to the two kinds of tiles in proportion to the time a unit takes for them: a tile of local rows (16 KB from memory) 1.5 times an
-    // index tile's (8 KB from the second-level cache).  32 769 + 98 304 rows at ratios of 1 / 1.5 / 2 / 3: 63 / 52 / 55 / 58 us.
-    if (t_loc == 0) pl.wgs_nl = wgs;
-    else if (t_nl == 0) pl.wgs_loc = wgs;
-    else {
-        pl.wgs_loc = (int)((6 * t_loc * wgs + 3 * t_loc + 2 * t_nl) / (6 * t_loc + 4 * t_nl));
-        pl.wgs_loc = std::min(std::max(pl.wgs_loc, 1), wgs - 1);
-        pl.wgs_nl = wgs - pl.wgs_loc;
-    }
+    pl.wgs_loc = local_share(wgs);
+    pl.wgs_nl = wgs - pl.wgs_loc;
     return pl;
 }
 

@@ -120,3 +120,14 @@ def test_where_the_encode_of_the_local_rows_runs(tmp_path):
     assert forms(c)[0] == "tile<256, 256> ENC"
     assert "ENC" not in forms(d)[0] and any(re.match(r"attn_bf16_kernel<128, .*, true>", k) for k in kernels(d))
     assert not any("vq_encode" in k for r in (a, b, c, d) for k in kernels(r))
+
+
+def test_the_decode_step_on_heads_of_64(tmp_path):
+    """A score table only for one group per head and a small codebook (19 000 + 19 000 rows, two groups, K = 1024: 22.3 us on the vector ALU, 25.7 with a
+    table, 23.7 gathering); a third workgroup per unit where it shortens what a wavefront walks."""
+    step = dict(entry="step", hq=12, hkv=12, dh=64)
+    calls = [dict(step, n_local=19000, n_nonlocal=19000, groups=24, words=1024), dict(step, n_local=10000, n_nonlocal=30000, groups=12, words=256),
+             dict(step, n_local=4832, n_nonlocal=4832, groups=24, words=16)]
+    kernel, grid = zip(*[r["launches"][0][:2] for r in record(calls, tmp_path)])
+    assert kernel == ("decode_stream_kernel<64, 1, 4, 2, false>", "decode_stream_kernel<64, 1, 8, 1, true>", "decode_stream_kernel<64, 1, 4, 2, false>")
+    assert [g[0] for g in grid] == [64, 21, 42]
