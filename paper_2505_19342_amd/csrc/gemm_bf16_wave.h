@@ -85,12 +85,10 @@ __global__ __launch_bounds__(kWaveThreads) void gemm_wave_kernel(const GemmBatch
     const int r8 = lane >> 3;
     const int piece[2] = {(lane & 7) ^ (r8 >> 1), (lane & 7) ^ (4 + (r8 >> 1))};
     const int m_codes = min(m0, M - 1), n_codes = min(BM, M - m_codes);      // rows whose codes the tile holds (one when all of it is padding)
-    uint32_t off[DM];                      // byte offsets; a gathered row: that of its codes, in codes
+    uint32_t off[DM];
 #pragma unroll
     for (int j = 0; j < DM; ++j) {
-        if (GATHER && gather && j < DA) {
-            off[j] = (uint32_t)min(8 * j + r8, n_codes - 1) * (uint32_t)P.G;
-        } else if (j < DA) {
+        if (j < DA) {
             off[j] = (uint32_t)min(m0 + 8 * j + r8, M - 1) * (uint32_t)P.lda * 2u + 16u * piece[j & 1];
         } else {
             int rb = n0 + 8 * (j - DA) + r8;
@@ -141,7 +139,7 @@ __global__ __launch_bounds__(kWaveThreads) void gemm_wave_kernel(const GemmBatch
             }
 #pragma unroll
             for (int j = 0; j < DA; ++j) {
-                const uint32_t x = off[j] + g_[j & 1];
+                const uint32_t x = (uint32_t)min(8 * j + r8, n_codes - 1) * (uint32_t)G + g_[j & 1];
                 const uint32_t code = code16 ? (uint32_t)reinterpret_cast<const uint16_t*>(codes_lds)[x] : (uint32_t)reinterpret_cast<const uint8_t*>(codes_lds)[x];
                 const uint32_t go = (at[j & 1] + min(code, (uint32_t)Kc - 1u) * (uint32_t)dg) * 2u;
                 dma_global_to_lds_16(P.codebook, go, dst + (uint32_t)(j * 1024));
