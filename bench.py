@@ -5,9 +5,10 @@ A step is one astra_layer_forward call: grouped VQ encode of the local rows, K-h
 the rows rebuilt from the peers' codes (decode fused into the operand load), Q/K/V projection of the
 local rows, mixed-precision attention (Eq. 1) and the output projection.  Inputs are seeded synthetic
 tensors already resident in HBM; the peers' codes are produced by the library's own encode.  Prints
-ONE JSON line: tokens/s per layer (local rows per second), the MFMA roofline of the dominant kernel
+ONE JSON line on stdout: tokens/s per layer (local rows per second), the MFMA roofline of the dominant kernel
 (the grouped projection launch, which at the benchmark shape also carries the encode as extra
-workgroups) from HIP-event stage timing, and the CPU oracle timed on the host cores.
+workgroups) from HIP-event stage timing, and the CPU oracle timed on the host cores.  Everything else that is
+measured goes to stderr as one JSON line of its own: the line on stdout has to fit where only the end of an output is kept.
 """
 from __future__ import annotations
 
@@ -71,6 +72,24 @@ def traffic_from_profiles(stem, kernel_substr, copy_kib=262144.0):
             return None
         total += v * (copy_kib / cal) * 1024.0
     return total
+
+
+HEADLINE = ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better", "scaling", "vs_baseline", "dtype", "data",
+            "config", "layer_tflops", "layer_mfma_frac", "ms_per_step_blocks_p10_p50_p90", "stage_us", "roofline", "cpu_baseline")
+HEADLINE_CHARS = 1900       # what is kept of an output may be its last 2000 characters
+
+
+def split_result(result):
+    """The line for stdout and the rest."""
+    def short(v):
+        if isinstance(v, float):
+            return float(f"{v:.7g}")
+        if isinstance(v, dict):
+            return {k: short(x) for k, x in v.items()}
+        return [short(x) for x in v] if isinstance(v, list) else v
+    line = json.dumps({k: short(result[k]) for k in HEADLINE if k in result})
+    assert len(line) <= HEADLINE_CHARS, f"the line on stdout has {len(line)} characters"
+    return line, {k: v for k, v in result.items() if k not in HEADLINE}
 
 
 def make_layer_call(cfg, rank, data=None):
@@ -720,7 +739,9 @@ def main():
         result["cpu_baseline"] = {"value": n_calls * tq / (c1 - c0), "unit": "tokens/s", "cores": oracle.num_threads(),
                                   "kind": "oracle", "sample": f"{n_calls} whole layer calls of the same workload ({tq} local rows each), "
                                   f"{c1 - c0:.2f} s, fp64 C/OpenMP oracle"}
-    print(json.dumps(result))
+    line, rest = split_result(result)
+    print(json.dumps(rest), file=sys.stderr, flush=True)
+    print(line)
 
 
 if __name__ == "__main__":
