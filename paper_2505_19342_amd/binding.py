@@ -140,8 +140,6 @@ def load(build_if_missing: bool = True):
     lib.astra_status_string.argtypes = [ctypes.c_int]
     lib.astra_status_string.restype = ctypes.c_char_p
     lib.astra_version.restype = ctypes.c_int
-    for name in EXPORTS[:4] + ("astra_layer_forward", "astra_layer_forward_profiled"):
-        getattr(lib, name).restype = ctypes.c_int
     _lib = lib
     return lib
 

@@ -130,6 +130,13 @@ def test_block_kv_and_decode_planning_is_host_only():
     assert B.astra_decode_attention_workspace_bytes(empty) > 0
 
 
+def test_scratch_sizes_of_2_gib_and_more():
+    """Score products of 32 groups of 1024 codewords for 16384 and 40000 tokens: 2 GiB and 4.9 GiB."""
+    desc = B.vq_desc("bf16", 4096, 32, 1024)
+    for tokens in (16384, 40000):
+        assert B.astra_vq_encode_workspace_bytes(desc, tokens) == tokens * 32 * 1024 * 4
+
+
 def test_one_sided_caches_of_many_heads_fit_the_librarys_own_scratch():
     """8192 query heads over 1024 KV heads and only one kind of cache: one partial result per query head, 4.1 MiB of the 8 MiB that
     astra_decode_attention_static has."""
