@@ -90,6 +90,49 @@ def check_codebook(dtype, got, ref64, loose=False):
     assert diff.mean() <= (2e-2 if loose else 2e-3), f"{diff.mean():.2e} of the codewords' elements differ from the oracle's rounding"
 
 
+@pytest.mark.parametrize("dtype,G,K,dg,skew", [
+    ("bf16", 12, 40, 6, 0),          # a width that is no multiple of four: a channel per thread
+    ("f32", 5, 33, 3, 0),
+    ("bf16", 4, 70, 64, 1),          # codebooks one element off: the same
+    ("f32", 3, 41, 64, 1),
+    ("bf16", 2, 9, 1028, 0),         # more than 1024 channels: the same
+    ("bf16", 2, 9, 1024, 0),         # four channels per thread, one codeword per workgroup
+    ("f32", 3, 50, 12, 0),           # 3 threads per codeword, the last workgroup not full
+    ("bf16", 7, 65, 24, 0),
+])
+@pytest.mark.parametrize("in_place", [False, True])
+def test_update_forms(dtype, G, K, dg, skew, in_place):
+    """Both forms of the update, with averages and without, with the new codebook in a buffer of its own and in the old one's place."""
+    import torch
+    from gpu_util import DEV, to_host
+    from paper_2505_19342_amd import binding as B
+    rng = np.random.default_rng(G * K + dg)
+    rnd = (lambda a: wl.round_to_bf16(a.astype(np.float32))) if dtype == "bf16" else (lambda a: a.astype(np.float32))
+    counts = rng.integers(0, 5, (G, K)).astype(np.int32)
+    cb, sums = rnd(rng.standard_normal((G, K, dg))), (rng.standard_normal((G, K, dg)) * counts[..., None]).astype(np.float32)
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    at = lambda a: torch.cat([torch.zeros(skew, dtype=tdt, device=DEV), torch.from_numpy(a).to(DEV, tdt).flatten()])[skew:].view(G, K, dg)
+    desc = B.vq_desc(dtype, G * dg, G, K)
+    for gamma in (0.0, 0.9):
+        n0 = (rng.random((G, K)) * 3 * (counts > 0)).astype(np.float32)
+        m0 = rng.standard_normal((G, K, dg)).astype(np.float32)
+        n_d, m_d = torch.from_numpy(n0).to(DEV), torch.from_numpy(m0).to(DEV)
+        old = at(cb)
+        new = old if in_place else at(np.full_like(cb, 7.0))
+        assert old.data_ptr() % 4 == (2 * skew if dtype == "bf16" else 0)
+        B.astra_codebook_update(desc, torch.from_numpy(counts).to(DEV), torch.from_numpy(sums).to(DEV), gamma, n_d if gamma else None,
+                                m_d if gamma else None, old, new)
+        torch.cuda.synchronize()
+        n_r, m_r = n0.astype(np.float64), m0.astype(np.float64)
+        ref = oracle.codebook_update(counts, sums, cb, gamma=gamma, ema_n=n_r, ema_m=m_r) if gamma else oracle.codebook_update(counts, sums, cb)
+        if gamma:
+            np.testing.assert_allclose(n_d.cpu().numpy(), n_r, rtol=1e-6)
+            assert np.abs(m_d.cpu().numpy() - m_r).max() <= 1e-5 * max(1.0, np.abs(m_r).max())
+        check_codebook(dtype, to_host(new), ref, loose=True)
+        empty = (counts == 0) & (n0 == 0 if gamma else True)
+        np.testing.assert_array_equal(to_host(new)[empty], cb[empty])
+
+
 def test_stats_edge_cases():
     """No tokens; fewer tokens than one pass; every token in one codeword; ragged token count; three codewords only, so that
     every codeword's run of the sorted sequence spans several 32-position units (more than the four a thread of the

@@ -131,3 +131,12 @@ def test_the_decode_step_on_heads_of_64(tmp_path):
     kernel, grid = zip(*[r["launches"][0][:2] for r in record(calls, tmp_path)])
     assert kernel == ("decode_stream_kernel<64, 1, 4, 2, false>", "decode_stream_kernel<64, 1, 8, 1, true>", "decode_stream_kernel<64, 1, 4, 2, false>")
     assert [g[0] for g in grid] == [64, 21, 42]
+
+
+def test_the_forms_of_the_codebook_update(tmp_path):
+    """Four channels per thread for widths of whole 16-byte pieces at aligned addresses, else a channel per thread."""
+    cases = [(64, 0, "bf16", True), (12, 0, "f32", True), (1024, 0, "bf16", True), (6, 0, "bf16", False), (1028, 0, "bf16", False), (64, 2, "bf16", False),
+             (64, 4, "f32", False)]
+    results = record([dict(entry="update", groups=3, words=40, dg=dg, skew=skew, dtype=dtype) for dg, skew, dtype, _ in cases], tmp_path)
+    for case, r in zip(cases, results):
+        assert any("update4" in k for k in kernels(r)) == case[3], case
