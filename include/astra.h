@@ -251,14 +251,15 @@ int astra_layer_forward_kv(const astra_layer_kv_desc* desc, const void* x_local,
  * astra_layer_forward_kv); Sec. 3.1: after the parallel encoding, autoregressive decoding proceeds on the
  * device that holds the most recent token.  The new token's query attends to every cached token:
  *   out[h] = softmax_t( q[h] . [K_cache | K-hat][t, h / (H_q/H_kv)] * scale ) [V_cache | V-hat],
- *   K-hat, V-hat = the rows the codes select from codebook_k, codebook_v (never materialised: key scores are
- *   sums of entries of a per-query table q . codeword, value rows are picked from the codebook).
+ *   K-hat, V-hat = the rows the codes select from codebook_k, codebook_v (never materialised: rows are picked from
+ *   the codebooks, or key scores are sums of entries of a per-query table q . codeword).
  *   vq            both codebooks, vq.d_model = n_kv_heads * head_dim; vq.dtype = element type of q, caches,
  *                 codebooks and out; (H_kv*dh)/G and head_dim even, head_dim <= 256, H_q/H_kv <= 8
  *   q [H_q, dh]; k_cache, v_cache [n_local, H_kv, dh] (the new token's own row included by the caller);
  *   codes_k, codes_v [n_nonlocal, G]; valid_bits nullable, as for astra_mixed_attention_valid
  *   out [H_q, dh]; lse_out nullable [H_q] fp32.  With nothing to attend to, out = 0 and lse = -inf.
- *   workspace     astra_decode_attention_workspace_bytes(desc) bytes (the table and per-chunk partial results)
+ *   workspace     astra_decode_attention_workspace_bytes(desc) bytes (per-chunk partial results, and for the
+ *                 shapes of the general kernels, fp32 among them, the table)
  * Results are independent of the run (no atomics). */
 typedef struct {
     astra_vq_desc vq;
@@ -276,14 +277,15 @@ int astra_decode_attention(const astra_decode_desc* desc, const void* q, const v
                            void* workspace, size_t workspace_bytes, void* stream);
 
 /* astra_decode_attention for callers that cannot allocate device memory or pass a workspace (work recorded under
- * HIP graph capture, tight serving loops, harnesses that forbid allocation): the table and the per-chunk partial
- * results live in a scratch array that is part of the library's device image, astra_decode_attention_static_max_bytes()
+ * HIP graph capture, tight serving loops, harnesses that forbid allocation): what would be in the
+ * workspace lives in a scratch array that is part of the library's device image, astra_decode_attention_static_max_bytes()
  * = 8 MiB per GPU, held by every GPU the library runs on until the process ends.  Same arguments, kernels and results
  * as astra_decode_attention; the call allocates and frees nothing.  A shape whose
  * astra_decode_attention_workspace_bytes exceeds the array returns ASTRA_ERR_WORKSPACE before anything is launched
- * (the Llama-3-8B shapes of a 128 K-token cache need about 2.6 MiB).  The array's device address is looked up once
- * per device, on the first call with that device current (a caller that records calls into a HIP graph makes one call on
- * the device before it starts capturing, so that the lookup and the kernels' one-time set-up are not part of the capture);
+ * (a 128 K-token cache of the Llama-3-8B shapes needs 0.5 to 1 MiB in bf16 and about 2.3 MiB in fp32).  The array's
+ * device address is looked up once per device, on the first call with that device current (a caller that records calls
+ * into a HIP graph makes one call on the device before it starts capturing, so that the lookup and the kernels' one-time
+ * set-up are not part of the capture);
  * a failed lookup returns ASTRA_ERR_HIP.  Nothing in the array
  * has to start at zero (every call writes what it reads), but all calls on one GPU share it: calls that overlap on one
  * GPU (different streams or threads) race; calls that follow each other on one stream do not. */

@@ -3,7 +3,7 @@
 // parallel encoding, decoding proceeds on the device that holds the most recent token).  The new token's query
 // attends to every cached token.
 //
-// Three launches:
+// Three launches (bf16 heads of 64 or 128 with codewords of whole 16-byte pieces take decode_stream_kernels.hip instead of the first two):
 //   decode_lut_kernel      LUT[h][gi][k] = scale * q[h, slice] . codebook_k[g, k, slice] for the groups g that touch
 //                          head h.  The score of a non-local token is then a sum of a few table entries picked by its
 //                          key codes: no key is ever rebuilt, and the key side of the index cache costs its codes only.
@@ -13,7 +13,6 @@
 //                          streamed from the cache; non-local rows picked from the value codebook, which stays in L2).
 //   decode_reduce_kernel   merges the chunks of every query head (log-sum-exp weights) and normalises.
 // Everything is fp32 except the stored element type; results do not depend on the run (no atomics).
-// bf16 heads of 64 or 128 with codewords of whole 16-byte pieces take decode_stream_kernels.hip instead of the first two.
 #include "decode_common.h"
 
 #include <algorithm>

@@ -14,10 +14,10 @@ namespace astra {
 // consecutive columns of a row, whatever the store.  B is the MFMA's M side, so that a lane holds four consecutive columns.
 //
 // What bounds it: a compute unit's intake through its vector L1 (about 50 of the 64 B/clk are reached) and one memory latency at
-// either end; a launch of a few dozen tiles lasts 3.6 us where the 64 x 64 form of the tile kernel, with a barrier and a
-// transfer round trip per 128 of contraction, took 10 us (256 x 768 outputs, K = 768; 6.6 against 24 us at K = 3072).  The larger
-// tiles trade concurrency for fewer operand bytes per flop; with 128 x 128 and one stage the fragments of a whole stage sit in
-// registers while the next one is transferred (1024 x 4096 outputs, K = 4096: 42.7 us, tile kernel on 128 x 128: 53 us).
+// either end.  256 x 768 fp32 outputs on 192 tiles of 32 x 32: 3.3 us at K = 768 and 5.3 at K = 3072, where the tile kernel, with a
+// barrier and a transfer round trip per 128 of contraction, took 6.1 and 12.8 us.  The larger tiles trade concurrency for fewer operand
+// bytes per flop; with 128 x 128 and one stage the fragments of a whole stage sit in registers while the next one is transferred
+// (1024 x 4096 fp32 outputs, K = 4096: 40.3 us; tile kernel on 128 x 128: 42.7).
 //
 // GATHER: problems with codes rebuild their A rows from the codebook; the tile's codes are copied to LDS first.  Rows beyond M are copies of
 // row M - 1 there too: a transposed store writes them into its padding, which attention multiplies by zero.
@@ -179,7 +179,7 @@ __global__ __launch_bounds__(kWaveThreads) void gemm_wave_kernel(const GemmBatch
 #pragma unroll
                 for (int b = 0; b < NT; ++b) acc[a][b] = mfma_32x32x16(fb[ks][b], fa[ks][a], acc[a][b]);
     };
-    static_assert(ST <= 3, "thresholds of the last stages are written out below");
+    static_assert(ST <= 2, "thresholds of the last stages are written out below");
 #pragma unroll
     for (int u = 0; u < ST; ++u)
         if (u < n) issue(u);
@@ -196,8 +196,7 @@ __global__ __launch_bounds__(kWaveThreads) void gemm_wave_kernel(const GemmBatch
 #pragma unroll
     for (int u = ST - 1; u >= 0; --u)
         if (n > u) {                                 // u younger stages are outstanding
-            if (u == 2) wait_vmem<ST == 3 ? 2 * DM : 0>();
-            else if (u == 1) wait_vmem<DM>();
+            if (u == 1) wait_vmem<DM>();
             else wait_vmem<0>();
             read(slot);
             multiply();

@@ -118,7 +118,10 @@ def test_block_kv_and_decode_planning_is_host_only():
 
     dec = B.DecodeDesc(B.vq_desc("bf16", 1024, 32, 1024), 32, 8, 128, 1025, 3072, 0.0)
     need = B.astra_decode_attention_workspace_bytes(dec)
-    assert need >= 32 * 4 * 1024 * 4            # the table: 32 query heads x 4 groups per head x 1024 entries, fp32
+    assert need >= 32 * 4 * 1024 * 4            # 33 partial results of 32 query heads x (128 + 2) fp32; the table is in LDS
+    f32 = B.DecodeDesc(B.vq_desc("f32", 1024, 32, 1024), 32, 8, 128, 1025, 3072, 0.0)
+    table = 32 * 4 * 1024 * 4                   # 32 query heads x 4 groups per head x 1024 entries, fp32, next to the partial results
+    assert B.astra_decode_attention_workspace_bytes(f32) >= table + 8 * 32 * 130 * 4
     assert lib.astra_decode_attention(ctypes.byref(dec), None, None, None, None, None, None, None, None, None, None, None, 0, None) == -1
     for field, value in (("n_q_heads", 12), ("head_dim", 100), ("n_local", -1)):      # 12 % 8; 8 * 100 != 1024; negative
         d = B.DecodeDesc(B.vq_desc("bf16", 1024, 32, 1024), 32, 8, 128, 1025, 3072, 0.0)
