@@ -299,8 +299,8 @@ def main():
         "stage_us_mean": {s: stage_ms_mean[s] * 1e3 for s in STAGES},
         "stage_tflops": {s: (dom_flops if s == dom else flops[s]) / (stage_ms[s] * 1e-3) / 1e12 for s in STAGES},
         "stage_mfma_frac": {s: (dom_flops if s == dom else flops[s]) / (stage_ms[s] * 1e-3) / 1e12 / peak for s in STAGES},
-        "roofline": {"kernel": ("gemm_nt_bf16_kernel (grouped Q/K/V/K-hat/V-hat projections" +
-                                (" + VQ encode of the local rows as extra workgroups)" if enc_fused else ")")) if dt == "bf16"
+        "roofline": {"kernel": (("gemm_nt_bf16_kernel (" if is_bench_shape else "") + "grouped Q/K/V/K-hat/V-hat projections" +
+                                (" + VQ encode of the local rows as extra workgroups" if enc_fused else "") + (")" if is_bench_shape else "")) if dt == "bf16"
                      else "gemm_nt_f32_kernel (grouped projections)",
                      "bound": "mfma" if dt == "bf16" else "alu", "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
                      "frac": achieved / peak,
