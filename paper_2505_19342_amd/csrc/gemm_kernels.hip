@@ -180,7 +180,7 @@ static int64_t count_tiles(const GemmProblem* problems, int n_problems, int bm, 
 // 64 - 14336, every form timed on each (20 launches back to back).  In 99 of 100 the form chosen is within 3.4 % of the fastest the product
 // has had, with the forms there are or with the two-contraction-group tiles they took the place of; 14 % off at most but for a few of more than
 // 4000 rows over 2000 - 5000 (30 %).  Gathered rows: 1087 layers of 17 - 1500 rows at three widths, every form of their projection launch timed,
-// within 2.8 % in 99 of 100.
+// within 4 % in 99 of 100.
 
 constexpr double kLaunchUs = 4.0;             // a dependent launch that does next to nothing
 
@@ -232,7 +232,11 @@ static double form_us(const FormTimes& f, const GemmProblem* problems, int n_pro
     }
     const double more = (double)(std::max<int64_t>(ceil_div(tiles, (int64_t)kCus), 1) - 1), pairs = std::floor(more / 2.0), odd = more - 2.0 * pairs;
     const double compute = f.first + f.first_k * k + odd * (f.next + f.next_k * k) + pairs * (f.pair + f.pair_k * k);
-    const double codes = gather ? f.codes + f.codes_k * k + more * (f.codes_next + f.codes_next_k * k) : 0.0;
+    // Rows from a codebook in the caches come in sooner than others, which is no gain in a launch of few rounds, or of the smallest tiles, that waits for
+    // its weights.  A layer 4096 wide of 87 + 43 rows: 54.2 us with its projections on 64 x 64 in two stages, 58.5 in one, which the bound below keeps
+    // from being 1.4 us ahead here; over the layers above, the form chosen is 0.18 % slower than the fastest on average, 0.26 without the bound.
+    double codes = gather ? f.codes + f.codes_k * k + more * (f.codes_next + f.codes_next_k * k) : 0.0;
+    if (gather && (more <= 1.0 || &f == &kWaveTimes[0])) codes = std::max(codes, -0.5);
     const double us = codes + std::max(compute, 3.0 + (operands + weights) / (f.fetch * 1e6)) + results / (f.store * 1e6);
     return weights > kCachedWeights ? us * f.from_memory : us;
 }

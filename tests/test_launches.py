@@ -140,3 +140,11 @@ def test_the_forms_of_the_codebook_update(tmp_path):
     results = record([dict(entry="update", groups=3, words=40, dg=dg, skew=skew, dtype=dtype) for dg, skew, dtype, _ in cases], tmp_path)
     for case, r in zip(cases, results):
         assert any("update4" in k for k in kernels(r)) == case[3], case
+
+
+def test_gathered_rows_do_not_hide_that_weights_come_from_memory(tmp_path):
+    """Layers 4096 wide with one round of 64 x 64 tiles: two stages (54 us, one stage 58)."""
+    results = record([dict(entry="layer", d=4096, hq=32, hkv=8, dh=128, n_local=m, n_nonlocal=n, causal=True, before=before, groups=groups, words=256)
+                      for m, n, before, groups in ((83, 83, 41, 32), (87, 87, 43, 16), (73, 125, 62, 16), (100, 100, 50, 64))], tmp_path)
+    for r in results:
+        assert kernels(r)[0].startswith("gemm_wave_kernel<2, 2, 2, true"), kernels(r)
