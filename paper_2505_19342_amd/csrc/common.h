@@ -68,6 +68,15 @@ __device__ __forceinline__ void dma_global_to_lds_16(const void* gbase_uniform, 
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(base), "v"(byte_off), "s"(gbase_uniform)
                  : "memory", "m0");
 }
+// One code per lane: lane L's byte (or 16-bit word), zero-extended to 32 bits, to LDS byte address lds_base + 4*L.  Waits as above.
+template <bool CODE16>
+__device__ __forceinline__ void dma_code_to_lds(const void* gbase_uniform, uint32_t byte_off, uint32_t lds_base) {
+    const uint32_t base = __builtin_amdgcn_readfirstlane(lds_base);
+    if (CODE16)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_ushort %1, %2" ::"s"(base), "v"(byte_off), "s"(gbase_uniform) : "memory", "m0");
+    else
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_ubyte %1, %2" ::"s"(base), "v"(byte_off), "s"(gbase_uniform) : "memory", "m0");
+}
 // The waits are emitted through the compiler's own s_waitcnt builtin (gfx9 encoding: vmcnt in bits 3:0 and
 // 15:14, expcnt 6:4 and lgkmcnt 11:8 left at their maxima = no wait), not as inline assembly: the compiler's
 // wait-count bookkeeping then knows that its own earlier global loads have completed too and does not wait for

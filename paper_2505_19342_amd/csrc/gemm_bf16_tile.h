@@ -29,9 +29,8 @@ __device__ __forceinline__ int find_problem(const GemmBatch& b, int tile) {
 // bf16, matrix cores.  A workgroup of WM x WN wavefronts owns a BM x BN output tile; each wavefront
 // owns a (BM/WM) x (BN/WN) sub-tile made of 32x32x16 MFMA tiles.  The contraction runs in steps of 64
 // through double-buffered LDS.  Operand tiles travel from memory straight into LDS (one wavefront instruction
-// fills 64 consecutive 16-byte slots, nothing passes through registers): while the matrix cores work on tile kt
-// out of one buffer, tile kt+1 has landed in the other, tile kt+2 is sent into the first as soon as the barrier
-// of iteration kt has passed and, for gathered A rows, the codes of tile kt+3 are being fetched.  LDS tiles are
+// fills 64 consecutive 16-byte slots, nothing passes through registers), two tiles ahead of the matrix cores; there are two
+// forms of the loop, by halves of a tile and by whole tiles.  LDS tiles are
 // [rows][8 pieces of 8 bf16]; piece p of row r sits at p ^ ((r >> 1) & 7): rows are 128 bytes, the
 // LDS has 64 four-byte banks, so the 16-byte fragment reads of 16 consecutive rows touch every bank once.
 //
@@ -100,6 +99,15 @@ int gemm_split_factor(int dtype, int64_t M, int64_t N, int64_t K);
 //   kEpiSwiGLU       bf16 store of silu(A.gate^T + b_g) * (A.up^T + b_u)
 enum { kEpiLayer = 0, kEpiResidualF32 = 1, kEpiSplit = 2, kEpiGeluTanh = 3, kEpiGeluErf = 4, kEpiSwiGLU = 5 };
 
+template <int B, int W>
+constexpr bool halves() { return B % (64 * W) == 0; }
+// row of the tile that LDS row r holds, for W wavefronts along a side of B
+template <int B, int W, bool QUAD>
+__device__ __forceinline__ int tile_row(int r) {
+    constexpr int P = B / 2 / W;                               // rows of half a wavefront tile
+    return QUAD ? (r % (B / 2)) / P * 2 * P + r / (B / 2) * P + r % P : r;
+}
+
 template <int BM, int BN, int WM, int WN, bool CODE16, bool ENC = false, int EPI = kEpiLayer>
 __global__ __launch_bounds__(64 * WM * WN) void gemm_nt_bf16_kernel(const GemmBatch batch) {
     constexpr int THREADS = 64 * WM * WN;
@@ -107,8 +115,14 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_nt_bf16_kernel(const GemmBa
     constexpr int RPP = THREADS / 8;                           // rows staged per pass
     constexpr int PA = BM / RPP, PB = BN / RPP;                // staging passes per thread
     static_assert(RPP % 16 == 0, "direct transfers: the row swizzle has to be periodic in the pass stride");
+    // Every wavefront's rows and columns come in two halves of whole 32s: the loop in quadrants (below).  In LDS the first halves of all wavefronts then
+    // precede the second ones.
+    constexpr bool QUAD = halves<BM, WM>() && halves<BN, WN>();
+    constexpr bool GATHER = EPI == kEpiLayer;                  // only the layer's launches have problems with codes
+    constexpr int PAH = QUAD ? PA / 2 : 1;                     // staging passes of half of the A rows
     __shared__ u32x4 lds_a[2][BM * kBK / 8];
     __shared__ u32x4 lds_b[2][BN * kBK / 8];
+    __shared__ uint32_t lds_code[QUAD && GATHER ? 4 * PAH * THREADS : 1];
 
     int vt;
     if (ENC) {
@@ -185,19 +199,19 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_nt_bf16_kernel(const GemmBa
     uint32_t aoff[PA], coff[PA], boff[PB];
 #pragma unroll
     for (int it = 0; it < PA; ++it) {
-        int ra = m0 + r0 + RPP * it;
+        int ra = m0 + tile_row<BM, WM, QUAD>(r0 + RPP * it);
         ra = ra < M ? ra : M - 1;
         aoff[it] = gather ? 0u : ((uint32_t)ra * (uint32_t)P.lda + kc * 8) * 2u;
         coff[it] = (uint32_t)ra * (uint32_t)G * (CODE16 ? 2u : 1u);
     }
 #pragma unroll
     for (int it = 0; it < PB; ++it) {
-        int rb = n0 + r0 + RPP * it;
+        int rb = n0 + tile_row<BN, WN, QUAD>(r0 + RPP * it);
         rb = rb < N ? rb : N - 1;
         if (EPI == kEpiSwiGLU) {
             // tile row r of B -> weight row such that, in every wavefront, MFMA column tiles b < TN/2 hold gate rows and
             // tiles b + TN/2 the up rows of the same BN/WN/2 output columns: both factors of an output meet in one lane
-            const int rr = r0 + RPP * it, Fh = N >> 1;
+            const int rr = tile_row<BN, WN, QUAD>(r0 + RPP * it), Fh = N >> 1;
             const int wn_r = rr / (32 * TN), b_r = (rr % (32 * TN)) / 32, i_r = rr % 32;
             int col = n0 / 2 + wn_r * (16 * TN) + (b_r % (TN / 2)) * 32 + i_r;
             col = col < Fh ? col : Fh - 1;
@@ -269,87 +283,273 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_nt_bf16_kernel(const GemmBa
         }
     }
 
-    // fragment rows
-    int arow[TM], brow[TN];
-#pragma unroll
-    for (int a = 0; a < TM; ++a) arow[a] = wm * (BM / WM) + a * 32 + i32;
-#pragma unroll
-    for (int b = 0; b < TN; ++b) brow[b] = wn * (BN / WN) + b * 32 + i32;
-
-    // ---- main loop.  One tile of 64 along the contraction is four MFMA steps of 16.  Per step a wavefront
-    // issues TM*TN MFMAs on fragments it requested from LDS one step earlier (two fragment slots), and between those
-    // MFMAs, in program order, the "side jobs" of the step: the TM+TN fragment reads of the next step and, in step 3,
-    // the transfers of tile kt+2.  LDS and global latencies are covered by the MFMAs issued meanwhile.  The workgroup
-    // barrier follows step 2, after which step 3 may read the first fragments of tile kt+1 from the other buffer, and
-    // the buffer of tile kt (all of whose fragments were requested before the barrier) is free for the transfers.
     const int n_kt = (EPI == kEpiSplit ? batch.k_split : K) / kBK;
-    bf16x8 fa[2][TM], fb[2][TN];
-    auto read_frag = [&](int buf_, int ks, int slot, int j) {
-        if (j < TM) fa[slot][j] = __builtin_bit_cast(bf16x8, lds_a[buf_][arow[j] * 8 + ((2 * ks + h) ^ swz(arow[j]))]);
-        else fb[slot][j - TM] = __builtin_bit_cast(bf16x8, lds_b[buf_][brow[j - TM] * 8 + ((2 * ks + h) ^ swz(brow[j - TM]))]);
-    };
-    constexpr int NR = TM + TN, NM = TM * TN;
-    {
-        // Tiles go from memory straight into LDS.  Buffer kt & 1 is free once every wavefront has passed the barrier of
-        // iteration kt (all reads of tile kt were requested and awaited before it): tile kt + 2 is sent there during step 3
-        // of iteration kt and has until the wait in front of the barrier of iteration kt + 1 to land.
-        // buf_tag: std::integral_constant<int, kt & 1> makes the buffer static (LDS addresses become immediates; steady
-        // state, where tiles kt + 1, kt + 2 and the codes of kt + 3 all exist), std::integral_constant<int, -1> reads it from kt
-        // (the last few tiles, with the run-time guards)
-        auto tile_steps_dma = [&](int kt, auto buf_tag) {
-            constexpr bool FULL = decltype(buf_tag)::value >= 0;
-            const int buf = FULL ? decltype(buf_tag)::value : (kt & 1);
-            const bool nx = FULL || kt + 1 < n_kt, nx2 = FULL || kt + 2 < n_kt;
+    if constexpr (QUAD) {
+        // ---- main loop in quadrants.  A wavefront's rows are two halves, A0 and A1, its columns likewise, B0 and B1.  A tile of 64 along the
+        // contraction is four products A0 B0, A0 B1, A1 B1, A1 B0, each over the whole 64, so that every fragment is read from LDS once and takes the
+        // registers of one that has just been used for the last time: A1 those of A0, B0 of the next tile those of B1, and so on (64 registers of
+        // fragments next to 128 of accumulators on 256 x 256).  Half a tile's rows in LDS are therefore free long before the tile is done.  Two barriers
+        // per tile, in the middle of A0 B0 and of A1 B1, cut the loop into half steps of 8 NQ MFMAs; in each of them the fragments of one half (A1, B1 of
+        // this tile; A0, B0 of the next) are read, and the same half of the tile after the next is sent to the place of the one read a half step ago.
+        // A transfer has two to three half steps to land, one to one and a half tiles' time, and they are spread evenly over the loop.  The loop below
+        // sends whole tiles in the last quarter of the tile before and gives them three quarters of one to land; that, not the matrix cores or the LDS, was
+        // what held it up.  With it, back to back: 256 x 256 tiles, 4096 x 4096 fp32 outputs, K = 256 / 1024 / 4096: 21.8 / 40.3 / 116 us, now
+        // 21.2 / 38.5 / 110; 192 of them at K = 4096 99.8, now 90.9; gate and up rows of 1024 x 14336, K = 4096: 219, now 190.  128 x 256 tiles,
+        // 1024 x 5120, K = 1024 / 4096: 22.2 / 59.7, now 20.1 / 47.9.  Four wavefronts of 128 x 128 read a third less from LDS and take the same time;
+        // transfers behind a branch each (one copy of the loop instead of a tail of its own) take 3 % longer.  128 x 128 tiles have no such
+        // halves on eight wavefronts, and on four they are 1 - 2 us slower than the loop below over short contractions and level over long ones.
+        // The codes of gathered rows come by transfers too, four half steps ahead of the ones that use them: every wavefront sends those of its own rows
+        // to its own part of LDS.  The compiler sees none of it, so nothing but the waits written here holds up the transfers.
+        constexpr int TMH = TM / 2, TNH = TN / 2, PBH = PB / 2, NQ = TMH * TNH;
+        constexpr int DPH = PAH + PBH + (GATHER ? PAH : 0);              // transfers of a half step
+        constexpr int NM = 8 * NQ;                                       // MFMAs of a half step
+        static_assert(!QUAD || NQ % TNH == 0, "a B fragment is replaced no earlier than after its last use");
+        bf16x8 fa[4][TMH], fb[2][4][TNH];
+        const int at_a = (wm * (BM / 2 / WM) + i32) * 8, at_b = (wn * (BN / 2 / WN) + i32) * 8;
+        auto read_a = [&](int buf, int half, int ks, int a) {
+            fa[ks][a] = __builtin_bit_cast(bf16x8, lds_a[buf][at_a + ((2 * ks + h) ^ swz(i32)) + (half * (BM / 2) + a * 32) * 8]);
+        };
+        auto read_b = [&](int buf, int half, int slot, int ks, int b) {
+            fb[slot][ks][b] = __builtin_bit_cast(bf16x8, lds_b[buf][at_b + ((2 * ks + h) ^ swz(i32)) + (half * (BN / 2) + b * 32) * 8]);
+        };
+        int kt_code = 2;                                  // tile whose codes are sent next
+        uint32_t code_q[PAH];
+        auto send_b = [&](int buf, int half, int it) {
+            dma_global_to_lds_16(b_base, boff[half * PBH + it], lds_byte_addr(&lds_b[buf][(wave_rows + RPP * (half * PBH + it)) * 8]));
+        };
+        auto send_a = [&](int buf, int half, int it, uint32_t c_raw) {
+            const uint32_t dst = lds_byte_addr(&lds_a[buf][(wave_rows + RPP * (half * PAH + it)) * 8]);
+            if (GATHER) {
+                const uint32_t g_ = __umulhi((uint32_t)k_use, magic);
+                const uint32_t j_ = (uint32_t)k_use - g_ * (uint32_t)dg;
+                const uint32_t c_ = min(c_raw, (uint32_t)Kc - 1u);
+                dma_global_to_lds_16(a_base, ((((g_ * (uint32_t)Kc + c_) * (uint32_t)dg + j_) * 2u) & gmask) + aoff[half * PAH + it], dst);
+            } else {
+                dma_global_to_lds_16(a_base, aoff[half * PAH + it], dst);
+            }
+        };
+        // codes of half `half` of tile kt_code (or of the last tile: sent for nothing) into ring slot `slot`
+        auto send_code = [&](int slot, int half, int it) {
+            const uint32_t g_ = __umulhi((uint32_t)(kc * 8 + kBK * min(kt_code, n_kt - 1)), magic) * (CODE16 ? 2u : 1u);
+            dma_code_to_lds<CODE16>(c_base, coff[half * PAH + it] + g_, lds_byte_addr(&lds_code[(slot * PAH + it) * THREADS]) + wave_rows * 32u);
+        };
+        // Half step TAG of four (tile kt even: 0, 1, odd: 2, 3).  nx: tile kt + 1 exists; FULL or fetch: tile kt + 2 exists
+        auto half_step = [&](auto tag, auto full_tag, bool nx_, bool fetch_) {
+            constexpr int TAG = decltype(tag)::value, BUF = TAG >> 1, HALF = TAG & 1;
+            constexpr bool FULL = decltype(full_tag)::value;
+            const bool nx = FULL || nx_, fetch = FULL || fetch_;
+            constexpr int S0 = BUF, S1 = BUF ^ 1;                        // where B0 and B1 of tile kt are
+            if (GATHER && fetch) {
 #pragma unroll
-            for (int ks = 0; ks < 4; ++ks) {
-                const int cur = ks & 1, nxt = cur ^ 1;
-                const int nd = ks == 3 ? PA + PB : 0;
-                const int nj = NR + nd;
-                const bool rd = ks < 3 || nx;
+                for (int it = 0; it < PAH; ++it) code_q[it] = lds_code[(TAG * PAH + it) * THREADS + tid];
+            }
 #pragma unroll
-                for (int m = 0; m < NM; ++m) {
-                    const int a = m / TN, b = m % TN;
-                    acc[a][b] = mfma_32x32x16(fa[cur][a], fb[cur][b], acc[a][b]);
+            for (int m = 0; m < NM; ++m) {
+                const int st = m / NQ, a = m % NQ / TNH, b = m % TNH;    // step of 16: two of the first product, four, two of the third
+                const int ks = st < 2 ? st + 2 : st < 6 ? st - 2 : st - 6;
+                const int qa = st < 6 ? HALF : HALF ^ 1, qb = st < 2 ? HALF : st < 6 ? HALF ^ 1 : HALF ^ 1;
+                // B slot of the product: B0, B1, B1; in the second half step B1, B0, and B0 of the next tile (read into the place of B1)
+                const int slot = HALF == 0 ? (st < 2 ? S0 : S1) : (st < 2 ? S1 : st < 6 ? S0 : S1);
+                if (HALF == 0 || st < 6 || nx) acc[qa * TMH + a][qb * TNH + b] = mfma_32x32x16(fa[ks][a], fb[slot][ks][b], acc[qa * TMH + a][qb * TNH + b]);
+                // fragments into the registers of those used for the last time: B steps 0 and 1 during step 0, 2 and 3 after it
+                if (st < 2) {
 #pragma unroll
-                    for (int j = m * nj / NM; j < (m + 1) * nj / NM; ++j) {
-                        if (j < NR) {
-                            if (rd) read_frag(ks < 3 ? buf : buf ^ 1, (ks + 1) & 3, nxt, j);
-                        } else if (nx2) {
-                            dma_piece(buf, j - NR);
-                        }
+                    for (int j = m * 2 * TNH / NQ; j < (m + 1) * 2 * TNH / NQ; ++j) {
+                        if (HALF == 0) read_b(BUF, 1, S1, j / TNH, j % TNH);
+                        else if (nx) read_b(BUF ^ 1, 0, S1, j / TNH, j % TNH);
                     }
-                    __builtin_amdgcn_sched_barrier(0);
+                } else if (st < 6 && b == TNH - 1) {
+                    if (HALF == 0) read_a(BUF, 1, ks, a);
+                    else if (nx) read_a(BUF ^ 1, 0, ks, a);
                 }
-                if (ks == 2) {
-                    wait_vmem_all();          // this wavefront's transfers of tile kt + 1 have landed
-                    __syncthreads();
+                if (fetch) {
+#pragma unroll
+                    for (int j = m * DPH / NM; j < (m + 1) * DPH / NM; ++j) {
+                        if (j < PBH) send_b(BUF, HALF, j);
+                        else if (j < PBH + PAH) send_a(BUF, HALF, j - PBH, GATHER ? code_q[j - PBH] : 0u);
+                        else send_code(TAG, HALF, j - PBH - PAH);
+                    }
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
-            if (nx2) dma_advance();
-            if (FULL || kt + 3 < n_kt) load_codes();
+            if (HALF == 1 && fetch) {
+                dma_advance();
+                ++kt_code;
+            }
+            if (HALF == 0 || nx) {
+                // the half that is read from here on has landed: at most the transfers of the last two half steps are outstanding
+                if (FULL || fetch) wait_vmem<2 * DPH>();
+                else wait_vmem_all();
+                __syncthreads();
+            }
+            __builtin_amdgcn_sched_barrier(0);
         };
-        load_codes();                 // codes of tile 0
+        // prologue: tiles 0 and 1, and the codes of tiles 2 and 3
+        const bool two = n_kt > 1;
 #pragma unroll
-        for (int j = 0; j < PA + PB; ++j) dma_piece(0, j);
-        dma_advance();
-        if (n_kt > 1) {
-            load_codes();             // codes of tile 1
+        for (int j = 0; j < 2; ++j)
 #pragma unroll
-            for (int j = 0; j < PA + PB; ++j) dma_piece(1, j);
-            dma_advance();
+            for (int it = 0; it < PBH; ++it) send_b(0, j, it);
+        uint32_t code_0[PA], code_1[PA];
+        if (GATHER) {
+            const uint32_t g0_ = __umulhi((uint32_t)(kc * 8), magic), g1_ = __umulhi((uint32_t)(kc * 8 + (two ? kBK : 0)), magic);
+#pragma unroll
+            for (int it = 0; it < PA; ++it) {
+                if (CODE16) {
+                    code_0[it] = *reinterpret_cast<const uint16_t*>(c_base + (coff[it] + g0_ * 2u));
+                    code_1[it] = *reinterpret_cast<const uint16_t*>(c_base + (coff[it] + g1_ * 2u));
+                } else {
+                    code_0[it] = *reinterpret_cast<const uint8_t*>(c_base + (coff[it] + g0_));
+                    code_1[it] = *reinterpret_cast<const uint8_t*>(c_base + (coff[it] + g1_));
+                }
+            }
         }
-        if (n_kt > 2) load_codes();   // codes of tile 2
-        wait_vmem_all();
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+#pragma unroll
+            for (int it = 0; it < PAH; ++it) send_a(0, j, it, GATHER ? code_0[j * PAH + it] : 0u);
+            if (GATHER && two)
+#pragma unroll
+                for (int it = 0; it < PAH; ++it) send_code(j, j, it);
+        }
+        dma_advance();
+        ++kt_code;
+        if (two) {
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+#pragma unroll
+                for (int it = 0; it < PBH; ++it) send_b(1, j, it);
+#pragma unroll
+                for (int it = 0; it < PAH; ++it) send_a(1, j, it, GATHER ? code_1[j * PAH + it] : 0u);
+                if (GATHER)
+#pragma unroll
+                    for (int it = 0; it < PAH; ++it) send_code(2 + j, j, it);
+            }
+            dma_advance();
+            ++kt_code;
+            wait_vmem<2 * DPH + (GATHER ? 3 : 1) * PAH>();          // A0 and all of B of tile 0
+        } else {
+            wait_vmem_all();
+        }
         __syncthreads();
 #pragma unroll
-        for (int j = 0; j < NR; ++j) read_frag(0, 0, 0, j);
-        int kt = 0;
-        for (; kt + 4 < n_kt; kt += 2) {
-            tile_steps_dma(kt, std::integral_constant<int, 0>{});
-            tile_steps_dma(kt + 1, std::integral_constant<int, 1>{});
+        for (int ks = 0; ks < 4; ++ks) {
+#pragma unroll
+            for (int b = 0; b < TNH; ++b) read_b(0, 0, 0, ks, b);
+#pragma unroll
+            for (int a = 0; a < TMH; ++a) read_a(0, 0, ks, a);
         }
-        for (; kt < n_kt; ++kt) tile_steps_dma(kt, std::integral_constant<int, -1>{});
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+            for (int a = 0; a < TMH; ++a)
+#pragma unroll
+                for (int b = 0; b < TNH; ++b) acc[a][b] = mfma_32x32x16(fa[ks][a], fb[0][ks][b], acc[a][b]);
+        if (two) wait_vmem<2 * DPH>();
+        else wait_vmem_all();
+        __syncthreads();
+        __builtin_amdgcn_sched_barrier(0);
+        using T = std::true_type;
+        using F = std::false_type;
+        int kt = 0;
+        for (; kt + 3 < n_kt; kt += 2) {
+            half_step(std::integral_constant<int, 0>{}, T{}, true, true);
+            half_step(std::integral_constant<int, 1>{}, T{}, true, true);
+            half_step(std::integral_constant<int, 2>{}, T{}, true, true);
+            half_step(std::integral_constant<int, 3>{}, T{}, true, true);
+        }
+        // the last one to three tiles; only the first of three fetches
+        auto tail = [&](auto even, auto odd) {
+            half_step(even, F{}, kt + 1 < n_kt, kt + 2 < n_kt);
+            half_step(odd, F{}, kt + 1 < n_kt, kt + 2 < n_kt);
+            ++kt;
+        };
+        tail(std::integral_constant<int, 0>{}, std::integral_constant<int, 1>{});
+        if (kt < n_kt) tail(std::integral_constant<int, 2>{}, std::integral_constant<int, 3>{});
+        if (kt < n_kt) tail(std::integral_constant<int, 0>{}, std::integral_constant<int, 1>{});
+    } else {
+        // ---- main loop by whole tiles.
+        // fragment rows
+        int arow[TM], brow[TN];
+    #pragma unroll
+        for (int a = 0; a < TM; ++a) arow[a] = wm * (BM / WM) + a * 32 + i32;
+    #pragma unroll
+        for (int b = 0; b < TN; ++b) brow[b] = wn * (BN / WN) + b * 32 + i32;
+
+        // One tile of 64 along the contraction is four MFMA steps of 16.  Per step a wavefront
+        // issues TM*TN MFMAs on fragments it requested from LDS one step earlier (two fragment slots), and between those
+        // MFMAs, in program order, the "side jobs" of the step: the TM+TN fragment reads of the next step and, in step 3,
+        // the transfers of tile kt+2.  LDS and global latencies are covered by the MFMAs issued meanwhile.  The workgroup
+        // barrier follows step 2, after which step 3 may read the first fragments of tile kt+1 from the other buffer, and
+        // the buffer of tile kt (all of whose fragments were requested before the barrier) is free for the transfers.
+        bf16x8 fa[2][TM], fb[2][TN];
+        auto read_frag = [&](int buf_, int ks, int slot, int j) {
+            if (j < TM) fa[slot][j] = __builtin_bit_cast(bf16x8, lds_a[buf_][arow[j] * 8 + ((2 * ks + h) ^ swz(arow[j]))]);
+            else fb[slot][j - TM] = __builtin_bit_cast(bf16x8, lds_b[buf_][brow[j - TM] * 8 + ((2 * ks + h) ^ swz(brow[j - TM]))]);
+        };
+        constexpr int NR = TM + TN, NM = TM * TN;
+        {
+            // Tiles go from memory straight into LDS.  Buffer kt & 1 is free once every wavefront has passed the barrier of
+            // iteration kt (all reads of tile kt were requested and awaited before it): tile kt + 2 is sent there during step 3
+            // of iteration kt and has until the wait in front of the barrier of iteration kt + 1 to land.
+            // buf_tag: std::integral_constant<int, kt & 1> makes the buffer static (LDS addresses become immediates; steady
+            // state, where tiles kt + 1, kt + 2 and the codes of kt + 3 all exist), std::integral_constant<int, -1> reads it from kt
+            // (the last few tiles, with the run-time guards)
+            auto tile_steps_dma = [&](int kt, auto buf_tag) {
+                constexpr bool FULL = decltype(buf_tag)::value >= 0;
+                const int buf = FULL ? decltype(buf_tag)::value : (kt & 1);
+                const bool nx = FULL || kt + 1 < n_kt, nx2 = FULL || kt + 2 < n_kt;
+    #pragma unroll
+                for (int ks = 0; ks < 4; ++ks) {
+                    const int cur = ks & 1, nxt = cur ^ 1;
+                    const int nd = ks == 3 ? PA + PB : 0;
+                    const int nj = NR + nd;
+                    const bool rd = ks < 3 || nx;
+    #pragma unroll
+                    for (int m = 0; m < NM; ++m) {
+                        const int a = m / TN, b = m % TN;
+                        acc[a][b] = mfma_32x32x16(fa[cur][a], fb[cur][b], acc[a][b]);
+    #pragma unroll
+                        for (int j = m * nj / NM; j < (m + 1) * nj / NM; ++j) {
+                            if (j < NR) {
+                                if (rd) read_frag(ks < 3 ? buf : buf ^ 1, (ks + 1) & 3, nxt, j);
+                            } else if (nx2) {
+                                dma_piece(buf, j - NR);
+                            }
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    if (ks == 2) {
+                        wait_vmem_all();          // this wavefront's transfers of tile kt + 1 have landed
+                        __syncthreads();
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                if (nx2) dma_advance();
+                if (FULL || kt + 3 < n_kt) load_codes();
+            };
+            load_codes();                 // codes of tile 0
+    #pragma unroll
+            for (int j = 0; j < PA + PB; ++j) dma_piece(0, j);
+            dma_advance();
+            if (n_kt > 1) {
+                load_codes();             // codes of tile 1
+    #pragma unroll
+                for (int j = 0; j < PA + PB; ++j) dma_piece(1, j);
+                dma_advance();
+            }
+            if (n_kt > 2) load_codes();   // codes of tile 2
+            wait_vmem_all();
+            __syncthreads();
+    #pragma unroll
+            for (int j = 0; j < NR; ++j) read_frag(0, 0, 0, j);
+            int kt = 0;
+            for (; kt + 4 < n_kt; kt += 2) {
+                tile_steps_dma(kt, std::integral_constant<int, 0>{});
+                tile_steps_dma(kt + 1, std::integral_constant<int, 1>{});
+            }
+            for (; kt < n_kt; ++kt) tile_steps_dma(kt, std::integral_constant<int, -1>{});
+        }
     }
 
     // epilogue.  acc[a][b][v] is C[m, n] with m = wave row base + 32a + acc_row(v, h), n = wave column base + 32b + lane % 32.

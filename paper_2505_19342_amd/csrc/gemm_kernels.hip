@@ -204,8 +204,8 @@ constexpr FormTimes kWaveTimes[kWaveConfigs] = {
     {3.4, 2.9, 0.0, 2.3, 0.4, 5.9, 3.8, 6.0, 2.2, -1.1, 0.6, -0.2, 1.04},  // 64 x 64, one stage
     {4.5, 4.6, 1.2, 5.9, 2.4, 11.8, 2.9, 6.0, 3.0, 0.1, 1.9, 1.1},         // 128 x 64
     {6.5, 6.05, 1.2, 8.2, 2.4, 16.4, 2.9, 6.0, 3.3, 0.9, 3.4, 2.1}};       // 128 x 128
-constexpr FormTimes kTile256 = {8.9, 20.2, 4.6, 23.3, 9.2, 46.6, 8.4, 4.2};       // 256 x 256
-constexpr FormTimes kTile128x256 = {5.7, 13.1, 5.7, 13.1, 11.4, 26.2, 6.7, 4.2};  // a single round
+constexpr FormTimes kTile256 = {8.6, 18.9, 4.4, 22.0, 8.8, 44.0, 8.4, 4.2};       // 256 x 256
+constexpr FormTimes kTile128x256 = {5.5, 10.3, 5.5, 10.3, 11.0, 20.6, 6.7, 4.2};  // a single round
 // 128 x 128 on eight wavefronts.  Its two stages do not cover a round trip to memory: a Llama block of 335 rows took 337 us with its projections on
 // these tiles and 317 with them on the wavefront-private ones, which are level when the same layer is repeated and the weights stay in the caches
 // (2543 products with weights of 15 - 300 MB that change with every launch: 1.6 times the time below, 1.1 - 1.4 for the other forms).
@@ -289,11 +289,11 @@ static double encode_later_us(const EncodeJob& e, double later_us) {
 }
 
 // Workgroups for it in a launch of `tiles` 256 x 256 or 128 x 256 tiles; 0: it does not ride.  It takes units that the last round leaves idle, and
-// must not outlast the tiles (16.5 us measured for an item at K = 1024, dg = 64).
+// must not outlast the tiles by more than it costs later (16.5 us measured for an item at K = 1024, dg = 64).
 static int tile_encode_wgs(const EncodeJob& e, int64_t tiles, bool mid, int k_max) {
     const int rem = (int)(tiles % kCus), E = rem == 0 ? 0 : (kCus - rem) & ~7;
     const int64_t items = ceil_div(e.n_tokens, 256) * e.G;
-    const double tile_us = (mid ? 70.0 : 105.0) * k_max / 4096.0;
+    const double tile_us = (mid ? 70.0 : 105.0) * k_max / 4096.0;      // 52 and 92 measured, and what a launch of its own would add
     return E >= 8 && E <= kCus / 2 && items <= 0x7fffffff && (double)ceil_div(items, (int64_t)E) * encode_item_us(e) <= 1.05 * tile_us ? E : 0;
 }
 

@@ -250,3 +250,40 @@ def test_workspace_too_small_is_an_error():
     layer.workspace = torch.empty(256, dtype=torch.uint8, device=DEV)
     with pytest.raises(B.AstraError):
         layer.run()
+
+
+# contraction, groups, codewords: one to six tiles of 64, groups that end inside a tile, 8- and 16-bit codes
+GATHERED_TILES = [(64, 8, 256), (128, 2, 1024), (192, 8, 256), (256, 4, 1024), (320, 40, 1024), (384, 6, 256)]
+
+
+@pytest.mark.parametrize("n_local,n_nonlocal,form", [(700, 700, "tile<128, 256>"), (1100, 600, "tile<256, 256>")])
+@pytest.mark.parametrize("d,groups,words", GATHERED_TILES)
+def test_gathered_rows_over_few_contraction_tiles(d, groups, words, n_local, n_nonlocal, form):
+    """The large tiles' loop fetches a tile's codes four half steps before its rows: contractions of as few tiles as the prologue and the first steps
+    span.  Logits of standard deviation 5, so that a wrong row of K-hat or V-hat is the whole output of some query.  Bar: bf16 rounding of queries and keys
+    moves such a logit by up to 0.05, probabilities by 5 %; 0.1 of the largest output is twice what that gives."""
+    import torch
+    from gpu_util import DEV, empty_codes
+    from paper_2505_19342_amd import binding as B
+    hq, hkv, dh = 32, 8, 128
+    g = torch.Generator(device=DEV)
+    g.manual_seed(d + n_local)
+    rnd = lambda *s, std=1.0: (torch.randn(s, generator=g, device=DEV) * std).to(torch.bfloat16)
+    x, cb = rnd(n_local, d), rnd(groups, words, d // groups)
+    wq, wk = rnd(hq * dh, d, std=(5 / d) ** 0.5), rnd(hkv * dh, d, std=(5 / d) ** 0.5)
+    wv, wo = rnd(hkv * dh, d, std=d ** -0.5), rnd(d, hq * dh, std=1 / 64)
+    codes = torch.randint(0, words, (n_nonlocal, groups), generator=g, device=DEV)
+    desc = B.LayerDesc(B.vq_desc("bf16", d, groups, words), B.attn_desc("bf16", hq, hkv, dh, 0, n_local, n_nonlocal, True, n_nonlocal))
+    cnorm = torch.empty((groups, words), dtype=torch.float32, device=DEV)
+    B.astra_vq_prepare(desc.vq, cb, cnorm)
+    y = torch.empty((n_local, d), dtype=torch.float32, device=DEV)
+    B.astra_layer_forward(desc, x, codes.to(torch.uint8 if words <= 256 else torch.int16), cb, cnorm, wq, wk, wv, wo, None, None, None, None, y,
+                          empty_codes(n_local, groups, words), torch.empty(B.astra_layer_workspace_bytes(desc), dtype=torch.uint8, device=DEV))
+    rows = torch.cat([cb[torch.arange(groups, device=DEV), codes].reshape(n_nonlocal, d).float(), x.float()])
+    q = (x.float() @ wq.float().T).view(n_local, hkv, hq // hkv, dh).permute(1, 2, 0, 3)
+    k, v = [(rows @ w.float().T).view(-1, hkv, 1, dh).permute(1, 2, 0, 3) for w in (wk, wv)]
+    hidden = torch.ones((n_local, n_nonlocal + n_local), dtype=torch.bool, device=DEV).triu(n_nonlocal + 1)
+    p = ((q @ k.transpose(-1, -2).contiguous()) * dh ** -0.5).masked_fill(hidden, float("-inf")).softmax(-1)
+    ref = (p @ v).permute(2, 0, 1, 3).reshape(n_local, hq * dh) @ wo.float().T
+    assert float((y - ref).abs().max()) <= 0.1 * float(ref.abs().max())
+    assert float((y - ref).norm() / ref.norm()) <= 2e-2

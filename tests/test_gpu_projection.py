@@ -27,6 +27,9 @@ PRODUCTS = [
     (1024, 4096, 576, "tile<128, 128>"),
     (1028, 4104, 64, "tile<128, 256>"),
     (2052, 4104, 64, "tile<256, 256>"),
+    # the loop in halves: two tiles of 64 (no more than the prologue fetches), three to seven (its steady part comes from four on, two at a time)
+    *[(1028, 4104, k, "tile<128, 256>") for k in (128, 192, 256, 320, 448)],
+    *[(2052, 4104, k, "tile<256, 256>") for k in (128, 192, 256, 320, 448)],
 ]
 
 

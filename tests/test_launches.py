@@ -72,7 +72,7 @@ def forms(result):
 def test_the_forms_the_gpu_tests_name(tmp_path):
     """The products, layers and blocks of the GPU tests run on the forms named beside them."""
     from test_gpu_block import MLP_LAUNCHES
-    from test_gpu_layer import MODEL_OF_WIDTH, PROJECTION_LAUNCHES
+    from test_gpu_layer import GATHERED_TILES, MODEL_OF_WIDTH, PROJECTION_LAUNCHES
     from test_gpu_projection import PRODUCTS
     model = {d: dict(d=d, hq=hq, hkv=hkv, dh=dh, causal=True, bias=True) for d, (hq, hkv, dh) in MODEL_OF_WIDTH.items()}
     for (m, n, k, form), r in zip(PRODUCTS, record([dict(entry="project", m=m, n=n, k=k) for m, n, k, _ in PRODUCTS], tmp_path)):
@@ -80,6 +80,11 @@ def test_the_forms_the_gpu_tests_name(tmp_path):
     calls = [dict(model[d], entry="layer", n_local=tl, n_nonlocal=tn, groups=g, words=w) for d, tl, tn, g, w, _ in PROJECTION_LAUNCHES]
     for case, r in zip(PROJECTION_LAUNCHES, record(calls, tmp_path)):
         assert forms(r)[0] == case[-1].replace("> GATHER", ">" if case[-1].startswith("tile") else "> GATHER"), (case, forms(r))
+    tiles = [(d, groups, words, rows, form) for d, groups, words in GATHERED_TILES for rows, form in (((700, 700), "tile<128, 256>"), ((1100, 600), "tile<256, 256>"))]
+    calls = [dict(entry="layer", d=d, hq=32, hkv=8, dh=128, causal=True, n_local=tl, n_nonlocal=tn, groups=groups, words=words)
+             for d, groups, words, (tl, tn), _ in tiles]
+    for case, r in zip(tiles, record(calls, tmp_path)):
+        assert forms(r)[0].replace(" ENC", "") == case[-1], (case, forms(r))
     calls = [dict(model[d], entry="block", n_local=t, n_nonlocal=0, groups=g, words=w, mlp=mlp, dff=f, norm="layernorm")
              for d, t, g, w, mlp, f, _ in MLP_LAUNCHES]
     for case, r in zip(MLP_LAUNCHES, record(calls, tmp_path)):
