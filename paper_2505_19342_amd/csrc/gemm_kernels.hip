@@ -2,8 +2,8 @@
 // named under Eq. 1 of the paper): Q, K, V of the local rows, K-hat, V-hat of the rows rebuilt from
 // codes, and the output projection.  Several problems run in one grouped launch; a problem may take
 // its A rows straight from the codebook through the token codes (decode fused into the operand load).
-// This file holds the layer's instantiations of the bf16 tile kernel, the fp32 kernel and the launcher;
-// the instantiations for the MLP of the surrounding block are compiled in gemm_mlp_kernels.hip.
+// This file holds the layer's instantiations of the bf16 tile kernel and the launcher; the instantiations for the MLP of the
+// surrounding block are compiled in gemm_mlp_kernels.hip, the fp32 kernel in gemm_f32_kernels.hip.
 #include "gemm_bf16_tile.h"
 #include "gemm_bf16_wave.h"
 
@@ -11,121 +11,6 @@
 #include <cmath>
 
 namespace astra {
-
-// ------------------------------------------------------------------------------------------------
-// fp32, vector ALU: 64x64 output tile, 256 threads x (4x4) outputs, contraction in steps of 16 through
-// LDS.  Used for the small fp32 configuration; sums in ascending k with fused multiply-add.
-// ------------------------------------------------------------------------------------------------
-constexpr int kFK = 64;
-
-// TILE x TILE outputs per workgroup (64, or 32 for launches that would leave most of the chip without a workgroup),
-// TILE / 16 x TILE / 16 per thread
-template <int TILE>
-__global__ __launch_bounds__(256) void gemm_nt_f32_kernel(const GemmBatch batch) {
-    constexpr int kFM = TILE, kFN = TILE, RT = TILE / 16;
-    constexpr int kFL = TILE / 4;     // consecutive k one thread stages per row: TILE rows x 64 k over 256 threads
-    __shared__ float sa[kFK][kFM + 4];
-    __shared__ float sb[kFK][kFN + 4];
-
-    const int pi = find_problem(batch, blockIdx.x);
-    const GemmProblem& P = batch.p[pi];
-    const int tile = blockIdx.x - batch.tile_begin[pi];
-    const int tm = tile % batch.tiles_m[pi], tn = tile / batch.tiles_m[pi];
-    const int m0 = tm * kFM, n0 = tn * kFN;
-    const int M = P.M, N = P.N, K = P.K;
-    const float* __restrict__ A = (const float*)P.a;
-    const float* __restrict__ B = (const float*)P.b;
-    const bool gather = P.codes != nullptr;
-    const float* __restrict__ CB = (const float*)P.codebook;
-
-    const int tid = threadIdx.x;
-    const int tx = tid & 15, ty = tid >> 4;
-    // staging: thread loads kFL consecutive k of one row
-    const int lr = tid / (kFK / kFL), lk = (tid % (kFK / kFL)) * kFL;
-    const int am = m0 + lr < M ? m0 + lr : M - 1;
-    const int bn = n0 + lr < N ? n0 + lr : N - 1;
-
-    // the values of the next step are fetched into registers while the current step is multiplied.  No load is guarded (a
-    // guarded load compiles to a branch with a wait of its own, 32 of them in a row per step): addresses are clamped into
-    // the row and values beyond the contraction replaced by zeros afterwards; four consecutive k are one 16-byte load
-    // when every row start and the group length allow it.
-    float av[kFL], bv[kFL];
-    const int64_t ldb = P.ldb ? P.ldb : K;
-    const bool vec = K % 4 == 0 && P.lda % 4 == 0 && ldb % 4 == 0 && (!gather || P.dg % 4 == 0) &&
-                     (reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(B) | reinterpret_cast<uintptr_t>(CB)) % 16 == 0;
-    auto a_ptr = [&](int k) -> const float* {           // address of element (am, k), k < K
-        if (!gather) return A + (int64_t)am * P.lda + k;
-        const int g = k / P.dg, jj = k - g * P.dg;
-        int code;
-        if (P.code_bytes == 1) code = ((const uint8_t*)P.codes)[(int64_t)am * P.G + g];
-        else code = ((const uint16_t*)P.codes)[(int64_t)am * P.G + g];
-        code = code < P.Kc ? code : P.Kc - 1;
-        return CB + ((int64_t)g * P.Kc + code) * P.dg + jj;
-    };
-    auto fetch = [&](int k0) {
-        if (vec) {
-#pragma unroll
-            for (int j = 0; j < kFL; j += 4) {
-                const int k = k0 + lk + j;
-                const int kc = k < K ? k : K - 4;
-                const float4 a4 = *reinterpret_cast<const float4*>(a_ptr(kc));
-                const float4 b4 = *reinterpret_cast<const float4*>(B + (int64_t)bn * ldb + kc);
-                const bool in = k < K;
-                av[j] = in ? a4.x : 0.f; av[j + 1] = in ? a4.y : 0.f; av[j + 2] = in ? a4.z : 0.f; av[j + 3] = in ? a4.w : 0.f;
-                bv[j] = in ? b4.x : 0.f; bv[j + 1] = in ? b4.y : 0.f; bv[j + 2] = in ? b4.z : 0.f; bv[j + 3] = in ? b4.w : 0.f;
-            }
-        } else {
-#pragma unroll
-            for (int j = 0; j < kFL; ++j) {
-                const int k = k0 + lk + j;
-                const int kc = k < K ? k : K - 1;
-                const float a1 = *a_ptr(kc), b1 = B[(int64_t)bn * ldb + kc];
-                av[j] = k < K ? a1 : 0.f;
-                bv[j] = k < K ? b1 : 0.f;
-            }
-        }
-    };
-
-    float acc[RT][RT] = {};
-    fetch(0);
-    for (int k0 = 0; k0 < K; k0 += kFK) {
-#pragma unroll
-        for (int j = 0; j < kFL; ++j) {
-            sa[lk + j][lr] = av[j];
-            sb[lk + j][lr] = bv[j];
-        }
-        __syncthreads();
-        if (k0 + kFK < K) fetch(k0 + kFK);
-#pragma unroll
-        for (int k = 0; k < kFK; ++k) {
-            float a[RT], b[RT];
-#pragma unroll
-            for (int i = 0; i < RT; ++i) { a[i] = sa[k][ty * RT + i]; b[i] = sb[k][tx * RT + i]; }
-#pragma unroll
-            for (int i = 0; i < RT; ++i)
-#pragma unroll
-                for (int j = 0; j < RT; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-        }
-        __syncthreads();
-    }
-    float* C = (float*)P.c;                               // may be the residual itself: no restrict
-    const float* __restrict__ bias = (const float*)P.bias;
-#pragma unroll
-    for (int i = 0; i < RT; ++i) {
-        const int m = m0 + ty * RT + i;
-        if (m >= M) continue;
-#pragma unroll
-        for (int j = 0; j < RT; ++j) {
-            const int n = n0 + tx * RT + j;
-            if (n < N) {
-                const int64_t at = (int64_t)m * P.ldc + n;
-                const float r = apply_act<false>(acc[i][j] + (bias ? bias[n] : 0.f), P.act);
-                C[at] = P.residual ? r + P.residual[at] : r;
-            }
-        }
-    }
-}
-
 
 // row tiles of a problem; a transposed store covers the padded rows too
 static int64_t tile_rows(const GemmProblem& p, int bm) {
@@ -383,17 +268,15 @@ int launch_gemm_batch(int dtype, const GemmProblem* problems, int n_problems, hi
     GemmBatch batch{};
     int total = 0;
     if (dtype != ASTRA_BF16) {
-        int rc = fill_batch(batch, dtype, problems, n_problems, 64, 64, &total);
-        if (rc) return rc;
-        if (total == 0 || plan_only) return ASTRA_OK;
-        if (total >= 128) {
-            gemm_nt_f32_kernel<64><<<total, 256, 0, s>>>(batch);
-        } else {
-            rc = fill_batch(batch, dtype, problems, n_problems, 32, 32, &total);
+        // the largest tile that still gives three quarters of the units one: 257 x 576 outputs, K = 192: 10.0 / 5.8 / 5.4 us on tiles of 64 / 32 / 16;
+        // 500 x 768, K = 768: 21.2 / 15.8 / 18.5; 1000 x 1000, K = 1000: 27.4 on 64, 37.2 on 32
+        int tile = 128;
+        do {
+            tile /= 2;
+            const int rc = fill_batch(batch, dtype, problems, n_problems, tile, tile, &total);
             if (rc) return rc;
-            gemm_nt_f32_kernel<32><<<total, 256, 0, s>>>(batch);
-        }
-        return launch_status();
+        } while (tile > 16 && total > 0 && total < 3 * kCus / 4);
+        return plan_only ? ASTRA_OK : launch_gemm_f32(tile, batch, s);
     }
     bool code16 = false, mlp = false;
     for (int i = 0; i < n_problems; ++i) {

@@ -47,3 +47,20 @@ def test_product_forms(m, n, k, form):
     ref = a.astype(np.float64) @ b.astype(np.float64).T
     scale = (np.abs(a).astype(np.float64) @ np.abs(b).astype(np.float64).T).max()
     assert np.abs(to_host(out)[0] - ref).max() <= 1e-5 * scale
+
+
+@pytest.mark.parametrize("m,n,k", [(1, 8, 1), (17, 24, 7), (33, 40, 16), (64, 192, 192), (50, 72, 1028), (250, 584, 100), (500, 520, 66), (900, 840, 130)])
+def test_f32_product(m, n, k):
+    """Tiles of 16, 32 and 64, contractions of part of a slice, of no whole 16-byte pieces, and of several rounds of slices.  Bar: 2 sqrt(k) roundings of 2^-24
+    of the sum of magnitudes (each of the k products and sums may round; their errors add as a random walk)."""
+    import torch
+    from gpu_util import to_dev, to_host, DEV
+    from paper_2505_19342_amd import binding as B
+    rng = np.random.default_rng(m + n + k)
+    a, b = rng.standard_normal((m, k), dtype=np.float32), rng.standard_normal((n, k), dtype=np.float32)
+    out = torch.full((1, m, n), float("nan"), dtype=torch.float32, device=DEV)
+    B.astra_vq_project_codebook(B.vq_desc("f32", k, 1, m), to_dev(a[None], "f32"), to_dev(b, "f32"), n, out)
+    torch.cuda.synchronize()
+    ref = a.astype(np.float64) @ b.astype(np.float64).T
+    scale = np.abs(a).astype(np.float64) @ np.abs(b).astype(np.float64).T
+    assert np.all(np.abs(to_host(out)[0] - ref) <= 2 * np.sqrt(k) * 2.0 ** -24 * scale)
