@@ -457,8 +457,9 @@ static int layer_forward_impl(const astra_layer_desc* desc, const void* x_local,
     }
 
     // 3. mixed-precision attention (Eq. 1)
-    rc = launch_attention(vq.dtype, ap, at.head_dim, s, false, enc_pending && offer ? &ej : nullptr, enc_pending && offer ? 1 : 0,
-                          enc_pending && offer ? &enc_in_attention : nullptr);
+    const bool to_attention = enc_pending && (offer || vq.dtype == ASTRA_F32);
+    rc = launch_attention(vq.dtype, ap, at.head_dim, s, false, to_attention ? &ej : nullptr, to_attention ? 1 : 0,
+                          to_attention ? &enc_in_attention : nullptr);
     if (rc) return rc;
     if (enc_pending && !enc_in_attention) {
         rc = launch_vq_encode(vq, ej.x, pl.D, at.n_local, codebook, cnorm, codes_local_out, s);
@@ -603,7 +604,7 @@ int astra_layer_forward_kv(const astra_layer_kv_desc* desc, const void* x_local,
         ej[j].n_tokens = at.n_local; ej[j].G = vq.n_groups; ej[j].K = vq.codebook_size; ej[j].dg = pl.dkv / vq.n_groups;
         ej[j].code_bytes = code_bytes(vq.code_type);
     }
-    const bool offer = dtype == ASTRA_BF16 && at.n_local > 0;
+    const bool offer = at.n_local > 0;
     bool enc_fused = false;
 
     // 3. the peers' keys and values, looked up from their codes; values go straight into the attention's layout

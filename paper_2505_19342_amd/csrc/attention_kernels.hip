@@ -4,6 +4,7 @@
 // non-local rows first and the local rows after them (softmax does not depend on key order).
 #include "common.h"
 #include "vq_encode_body.h"
+#include "vq_encode_f32_body.h"
 
 #include <algorithm>
 #include <type_traits>
@@ -474,104 +475,162 @@ __global__ __launch_bounds__(kAttThreads) void attn_bf16_kernel(const AttnParams
 }
 
 // ------------------------------------------------------------------------------------------------
-// fp32, vector ALU: one workgroup of four wavefronts per (query row, head).  The keys ([K-hat | K], 64 at a time: one
-// key per lane for the logits, head-dim values spread over lanes for the output) are dealt to the wavefronts chunk by
-// chunk, each wavefront runs an online softmax over its chunks, and the four partial results are merged through LDS
-// in wavefront order.  U = ceil(dh / 64) output values per lane.
+// fp32, vector ALU: one workgroup of four wavefronts per (query row, head).  The keys ([K-hat | K], 64 at a time) are dealt to the wavefronts chunk by
+// chunk, each wavefront runs an online softmax over its chunks, and the four partial results are merged through LDS in wavefront order.
+//
+// In a chunk 16 lanes hold a row, four values (16 bytes) each and 64 further ones per U = ceil(dh / 64), and a load covers four rows; a lane's sixteen
+// partial dots (rows 4j + lane / 16) are added over the 16 lanes so that lane (r, c) of the wavefront ends with the logit of row 4c + r.  Bound by the
+// latency of the chain keys -> logits -> values: all of a chunk's keys and its first 64 values' columns are requested before anything is computed.
+// 64 rows x 3 heads of 64 over 256 keys, back to back: 7.7 us with a key per lane (a cache line per lane and load) and 16 value rows at a time after
+// the softmax; 4.2 now.  Error against fp64 3.1e-7 of the norm, now 1.5e-7.
+// VEC = false: head dimensions or addresses that 16-byte pieces do not fit.
+//
+// ENC: the workgroups behind the attention's encode the local rows (fp32 codes; nothing here depends on them or the other way round).
 // ------------------------------------------------------------------------------------------------
-template <int U>
-__global__ __launch_bounds__(256) void attn_f32_kernel(const AttnParams p, int dh) {
+template <int U, bool VEC>
+__global__ __launch_bounds__(256) void attn_f32_kernel(const AttnParams p, int dh, const AttnEncode e) {
     constexpr int kWaves = 4;
-    constexpr int kRows = U <= 2 ? 16 : 8;           // value rows in flight
-    __shared__ float part[kWaves][U * kWave + 2];
-    const int lane = lane_id(), wave = threadIdx.x / kWave;
+    __shared__ __align__(16) float part[kWaves][U * kWave + 4];
+    if (e.n_enc_wgs > 0 && (int)blockIdx.x >= e.n_attn_wgs) {
+        __shared__ EncF32Lds enc_lds;
+        int item = (int)blockIdx.x - e.n_attn_wgs;
+        const int j = item >= e.job[0].G * e.job[0].n_tb ? 1 : 0;
+        if (j) item -= e.job[0].G * e.job[0].n_tb;
+        vq_encode_f32_body(e.job[j], item, enc_lds);
+        return;
+    }
+    const int lane = lane_id();
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int head = blockIdx.x / p.Tq, row = blockIdx.x % p.Tq;
     const int hk = head / (p.Hq / p.Hkv);
     const int64_t q_ld = (int64_t)p.Hq * dh, kv_ld = (int64_t)p.Hkv * dh;
     const float* __restrict__ q = (const float*)p.q + (int64_t)row * q_ld + (int64_t)head * dh;
+    const int sub = lane & 15, rg = lane >> 4;
 
     const int n_hat = p.Tn_vis;
     const int n_loc = p.causal ? row + 1 : p.Tq;
     const int chunks_hat = (n_hat + kWave - 1) / kWave, chunks = chunks_hat + (n_loc + kWave - 1) / kWave;
     float m_run = -INFINITY, l_run = 0.f;
-    float o[U];                                      // head-dim values lane, lane + 64, ... (those beyond dh are never stored)
+    f32x4 o[U];                     // VEC: values 64u + 4 sub .. + 3 of the rows 4j + rg; else o[u].x is value 64u + lane of all rows
+    f32x4 qv[U];
+    int col[U];                     // first value of this lane's pieces, clamped into the row; those beyond it count as zeros
 #pragma unroll
-    for (int u = 0; u < U; ++u) o[u] = 0.f;
-    const bool vec4 = dh % 4 == 0 && ((uintptr_t)p.q | (uintptr_t)p.k_loc | (uintptr_t)p.k_hat) % 16 == 0;
+    for (int u = 0; u < U; ++u) {
+        o[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+        col[u] = min(64 * u + 4 * sub, dh - 4);
+        if (VEC) qv[u] = *reinterpret_cast<const f32x4*>(q + col[u]);
+    }
 
     for (int c = wave; c < chunks; c += kWaves) {
         const int src = c < chunks_hat ? 0 : 1;
-        const int count = src == 0 ? n_hat : n_loc;
         const int base = (src == 0 ? c : c - chunks_hat) * kWave;
-        const float* __restrict__ Kp = (const float*)(src == 0 ? p.k_hat : p.k_loc) + (int64_t)hk * dh;
-        const float* __restrict__ Vp = (const float*)(src == 0 ? p.v_hat : p.v_loc) + (int64_t)hk * dh;
-        const int j = base + lane;
-        float s = -INFINITY;
-        const bool arrived = src != 0 || p.valid_bits == nullptr || j >= count || ((p.valid_bits[j >> 6] >> (j & 63)) & 1ull);
-        if (j < count && arrived) {
-            const float* kr = Kp + (int64_t)j * kv_ld;
-            float dot = 0.f;
-            int d = 0;
-            if (vec4) {                   // ascending order of additions, four elements per load
-                // 32 elements at a time: the eight key loads are issued together, then consumed in ascending order
-                for (; d + 32 <= dh; d += 32) {
-                    f32x4 kv[8];
+        const int cnt = min(kWave, (src == 0 ? n_hat : n_loc) - base);          // rows of the chunk
+        const float* __restrict__ Kp = (const float*)(src == 0 ? p.k_hat : p.k_loc) + (int64_t)base * kv_ld + (int64_t)hk * dh;
+        const float* __restrict__ Vp = (const float*)(src == 0 ? p.v_hat : p.v_loc) + (int64_t)base * kv_ld + (int64_t)hk * dh;
+        const int key = 4 * sub + rg;                                           // this lane's row in the chunk
+        const unsigned long long bits = src != 0 || p.valid_bits == nullptr ? ~0ull : p.valid_bits[base >> 6];
+        const bool arrived = key < cnt && ((bits >> key) & 1ull);
+        f32x4 vv[16];
+        float s;
+        if (VEC) {
+            // rows beyond the chunk repeat its last one; their logits are dropped and their values get weight zero
+            float dot[16];
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) kv[u] = *reinterpret_cast<const f32x4*>(kr + d + 4 * u);
+            for (int u = 0; u < U; ++u) {
+                f32x4 kk[16];
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) {
-                        const f32x4 qv = *reinterpret_cast<const f32x4*>(q + d + 4 * u);
-                        dot = fmaf(qv.x, kv[u].x, dot);
-                        dot = fmaf(qv.y, kv[u].y, dot);
-                        dot = fmaf(qv.z, kv[u].z, dot);
-                        dot = fmaf(qv.w, kv[u].w, dot);
-                    }
-                }
-                for (; d + 4 <= dh; d += 4) {
-                    const f32x4 kv = *reinterpret_cast<const f32x4*>(kr + d);
-                    const f32x4 qv = *reinterpret_cast<const f32x4*>(q + d);
-                    dot = fmaf(qv.x, kv.x, dot);
-                    dot = fmaf(qv.y, kv.y, dot);
-                    dot = fmaf(qv.z, kv.z, dot);
-                    dot = fmaf(qv.w, kv.w, dot);
+                for (int j = 0; j < 16; ++j) kk[j] = *reinterpret_cast<const f32x4*>(Kp + (int64_t)min(4 * j + rg, cnt - 1) * kv_ld + col[u]);
+                if (u == 0)
+#pragma unroll
+                    for (int j = 0; j < 16; ++j) vv[j] = *reinterpret_cast<const f32x4*>(Vp + (int64_t)min(4 * j + rg, cnt - 1) * kv_ld + col[0]);
+                __builtin_amdgcn_sched_barrier(0);         // all of them are on their way before the first is waited for
+                const bool in = 64 * u + 4 * sub < dh;
+#pragma unroll
+                for (int j = 0; j < 16; ++j) {
+                    float d = u == 0 ? 0.f : dot[j];
+                    d = fmaf(qv[u].x, kk[j].x, d);
+                    d = fmaf(qv[u].y, kk[j].y, d);
+                    d = fmaf(qv[u].z, kk[j].z, d);
+                    d = fmaf(qv[u].w, kk[j].w, d);
+                    dot[j] = in ? d : (u == 0 ? 0.f : dot[j]);
                 }
             }
-            for (; d < dh; ++d) dot = fmaf(q[d], kr[d], dot);
-            s = dot * p.scale;
+            // sixteen sums over sixteen lanes: every step halves the sums a lane still carries
+            auto halve = [&](auto n) __attribute__((always_inline)) {
+                constexpr int W = decltype(n)::value;
+                const bool up = (sub & W) != 0;
+#pragma unroll
+                for (int j = 0; j < W; ++j) {
+                    const float keep = up ? dot[j + W] : dot[j], give = up ? dot[j] : dot[j + W];
+                    dot[j] = keep + __shfl_xor(give, W);
+                }
+            };
+            halve(std::integral_constant<int, 8>{});
+            halve(std::integral_constant<int, 4>{});
+            halve(std::integral_constant<int, 2>{});
+            halve(std::integral_constant<int, 1>{});
+            s = dot[0] * p.scale;
+        } else {
+            const float* kr = Kp + (int64_t)min(key, cnt - 1) * kv_ld;
+            float d = 0.f;
+            for (int i = 0; i < dh; ++i) d = fmaf(q[i], kr[i], d);
+            s = d * p.scale;
         }
+        if (!arrived) s = -INFINITY;
         float mx = s;
+#pragma unroll
         for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
         const float m_new = fmaxf(m_run, mx);          // -inf only while every key so far was lost
         const float m_safe = m_new == -INFINITY ? 0.f : m_new;
         const float alpha = expf(m_run - m_safe);
-        const float e = (j < count && arrived) ? expf(s - m_safe) : 0.f;
-        float sum = e;
+        const float w = arrived ? expf(s - m_safe) : 0.f;
+        float sum = w;
+#pragma unroll
         for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
         l_run = l_run * alpha + sum;
         m_run = m_new;
+        if (VEC) {
+            float wj[16];
 #pragma unroll
-        for (int u = 0; u < U; ++u) o[u] *= alpha;
-        const int cnt = min(kWave, count - base);
-        // kRows value rows in flight; rows beyond the chunk repeat its last row with weight zero
-        for (int jj = 0; jj < cnt; jj += kRows) {
-            float pj[kRows], vv[kRows][U];
+            for (int j = 0; j < 16; ++j) wj[j] = __shfl(w, (lane & 48) | j);      // weight of row 4j + rg
 #pragma unroll
-            for (int b = 0; b < kRows; ++b) {
-                const int jb = min(jj + b, cnt - 1);
-                pj[b] = jj + b < cnt ? __shfl(e, jb) : 0.f;
-                const float* vr = Vp + (int64_t)(base + jb) * kv_ld;
+            for (int u = 0; u < U; ++u) {
+                if (u > 0)
 #pragma unroll
-                for (int u = 0; u < U; ++u) vv[b][u] = vr[min(lane + 64 * u, dh - 1)];
+                    for (int j = 0; j < 16; ++j) vv[j] = *reinterpret_cast<const f32x4*>(Vp + (int64_t)min(4 * j + rg, cnt - 1) * kv_ld + col[u]);
+                o[u] *= alpha;
+#pragma unroll
+                for (int j = 0; j < 16; ++j) {
+                    o[u].x = fmaf(wj[j], vv[j].x, o[u].x);
+                    o[u].y = fmaf(wj[j], vv[j].y, o[u].y);
+                    o[u].z = fmaf(wj[j], vv[j].z, o[u].z);
+                    o[u].w = fmaf(wj[j], vv[j].w, o[u].w);
+                }
             }
+        } else {
 #pragma unroll
-            for (int b = 0; b < kRows; ++b)
+            for (int u = 0; u < U; ++u) o[u].x *= alpha;
+            for (int r = 0; r < cnt; ++r) {
+                const float wr = __shfl(w, (r >> 2) | ((r & 3) << 4));
 #pragma unroll
-                for (int u = 0; u < U; ++u) o[u] = fmaf(pj[b], vv[b][u], o[u]);
+                for (int u = 0; u < U; ++u) o[u].x = fmaf(wr, Vp[(int64_t)r * kv_ld + min(lane + 64 * u, dh - 1)], o[u].x);
+            }
         }
     }
     // merge: wavefront w leaves (o, m, l); the first wavefront adds the four in order
+    if (VEC) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) part[wave][u * kWave + lane] = o[u];
+        for (int u = 0; u < U; ++u) {
+#pragma unroll
+            for (int off = 16; off < 64; off <<= 1)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) o[u][i] += __shfl_xor(o[u][i], off);
+            if (rg == 0) *reinterpret_cast<f32x4*>(&part[wave][64 * u + 4 * sub]) = o[u];
+        }
+    } else {
+#pragma unroll
+        for (int u = 0; u < U; ++u) part[wave][u * kWave + lane] = o[u].x;
+    }
     if (lane == 0) {
         part[wave][U * kWave] = m_run;
         part[wave][U * kWave + 1] = l_run;
@@ -583,23 +642,31 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const AttnParams p, int d
     for (int w = 0; w < kWaves; ++w) M = fmaxf(M, part[w][U * kWave]);
     const float m_safe = M == -INFINITY ? 0.f : M;
     float L = 0.f;
+    float r[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) o[u] = 0.f;
+    for (int u = 0; u < U; ++u) r[u] = 0.f;
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) {
         const float wgt = expf(part[w][U * kWave] - m_safe);       // exp(-inf) = 0 for a wavefront without keys
         L = fmaf(wgt, part[w][U * kWave + 1], L);
 #pragma unroll
-        for (int u = 0; u < U; ++u) o[u] = fmaf(wgt, part[w][u * kWave + lane], o[u]);
+        for (int u = 0; u < U; ++u) r[u] = fmaf(wgt, part[w][u * kWave + lane], r[u]);
     }
     const float inv = L > 0.f ? 1.f / L : 0.f;
     float* __restrict__ out = (float*)p.out + (int64_t)row * q_ld + (int64_t)head * dh;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         const int d = lane + 64 * u;
-        if (d < dh) out[d] = o[u] * inv;
+        if (d < dh) out[d] = r[u] * inv;
     }
     if (p.lse && lane == 0) p.lse[(int64_t)head * p.Tq + row] = M + logf(L);
+}
+
+template <int U>
+static void launch_attn_f32(int blocks, const AttnParams& p, int head_dim, const AttnEncode& e, hipStream_t s) {
+    const bool vec = head_dim % 4 == 0 && ((uintptr_t)p.q | (uintptr_t)p.k_loc | (uintptr_t)p.k_hat | (uintptr_t)p.v_loc | (uintptr_t)p.v_hat) % 16 == 0;
+    if (vec) attn_f32_kernel<U, true><<<blocks, 256, 0, s>>>(p, head_dim, e);
+    else attn_f32_kernel<U, false><<<blocks, 256, 0, s>>>(p, head_dim, e);
 }
 
 double attention_encode_us(const AttnParams& p, int head_dim, const EncodeJob& e) {
@@ -679,12 +746,25 @@ int launch_attention(int dtype, const AttnParams& p_in, int head_dim, hipStream_
         if (head_dim > 256 || p.v_transposed) return ASTRA_ERR_UNSUPPORTED;
         const int64_t blocks = (int64_t)p.Hq * p.Tq;
         if (blocks > 0x7fffffff) return ASTRA_ERR_SHAPE;
+        int64_t items = 0;
+        for (int j = 0; j < (enc && enc_fused && n_enc <= 2 ? n_enc : 0); ++j) {
+            ae.job[j] = enc[j];
+            ae.job[j].n_tb = (int)ceil_div(enc[j].n_tokens, kEncF32Tokens);
+            items += (int64_t)ae.job[j].n_tb * enc[j].G;
+        }
+        if (items > 0 && blocks + items <= 0x7fffffff) {
+            ae.n_jobs = n_enc;
+            ae.n_attn_wgs = (int)blocks;
+            ae.n_enc_wgs = (int)items;
+            *enc_fused = true;
+        }
         if (plan_only) return ASTRA_OK;
+        const int grid = (int)blocks + ae.n_enc_wgs;
         switch ((head_dim + 63) / 64) {
-            case 1: attn_f32_kernel<1><<<(int)blocks, 256, 0, s>>>(p, head_dim); break;
-            case 2: attn_f32_kernel<2><<<(int)blocks, 256, 0, s>>>(p, head_dim); break;
-            case 3: attn_f32_kernel<3><<<(int)blocks, 256, 0, s>>>(p, head_dim); break;
-            default: attn_f32_kernel<4><<<(int)blocks, 256, 0, s>>>(p, head_dim); break;
+            case 1: launch_attn_f32<1>(grid, p, head_dim, ae, s); break;
+            case 2: launch_attn_f32<2>(grid, p, head_dim, ae, s); break;
+            case 3: launch_attn_f32<3>(grid, p, head_dim, ae, s); break;
+            default: launch_attn_f32<4>(grid, p, head_dim, ae, s); break;
         }
     }
     return launch_status();

@@ -4,6 +4,7 @@
 
 #include "common.h"
 #include "vq_encode_body.h"
+#include "vq_encode_f32_body.h"
 
 namespace astra {
 
@@ -444,67 +445,10 @@ int launch_preproj_gather(int dtype, int code_type, const void* codes, const flo
     return launch_status();
 }
 
-// ------------------------------------------------------------------------------------------------
-// Encode, fp32: one wavefront per (token, group).  Lanes stride over the codewords and evaluate the
-// definition sum_j (x_j - c_j)^2 directly; the wavefront then reduces (distance, index)
-// lexicographically so that the lowest index wins a tie.
-// ------------------------------------------------------------------------------------------------
-template <typename CodeT>
-__global__ __launch_bounds__(256) void vq_encode_f32_kernel(const float* __restrict__ x, int64_t ldx, int64_t n_tokens,
-                                                            const float* __restrict__ codebook, CodeT* __restrict__ codes,
-                                                            int G, int K, int dg) {
-    const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
-    if (wave >= n_tokens * G) return;
-    const int64_t t = wave / G;
-    const int g = (int)(wave - t * G);
-    const int lane = lane_id();
-    const float* z = x + t * ldx + (int64_t)g * dg;
-    float best = INFINITY;
-    int arg = 0x7fffffff;
-    // four elements per load where the slices allow it; the additions keep their order
-    const bool vec4 = dg % 4 == 0 && ldx % 4 == 0 && ((uintptr_t)x | (uintptr_t)codebook) % 16 == 0;
-    for (int k = lane; k < K; k += kWave) {
-        const float* e = codebook + ((int64_t)g * K + k) * dg;
-        float dist = 0.f;
-        int j = 0;
-        if (vec4)
-            // 32 values at a time: the eight codeword loads are issued together, then consumed in ascending order
-            for (; j + 32 <= dg; j += 32) {
-                f32x4 ev[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) ev[u] = *reinterpret_cast<const f32x4*>(e + j + 4 * u);
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const f32x4 zv = *reinterpret_cast<const f32x4*>(z + j + 4 * u);
-                    const f32x4 df = ev[u] - zv;
-                    dist = fmaf(df.x, df.x, dist);
-                    dist = fmaf(df.y, df.y, dist);
-                    dist = fmaf(df.z, df.z, dist);
-                    dist = fmaf(df.w, df.w, dist);
-                }
-            }
-        if (vec4)
-            for (; j + 4 <= dg; j += 4) {
-                const f32x4 ev = *reinterpret_cast<const f32x4*>(e + j);
-                const f32x4 zv = *reinterpret_cast<const f32x4*>(z + j);
-                const f32x4 df = ev - zv;
-                dist = fmaf(df.x, df.x, dist);
-                dist = fmaf(df.y, df.y, dist);
-                dist = fmaf(df.z, df.z, dist);
-                dist = fmaf(df.w, df.w, dist);
-            }
-        for (; j < dg; ++j) {
-            const float diff = e[j] - z[j];
-            dist = fmaf(diff, diff, dist);
-        }
-        if (dist < best) { best = dist; arg = k; }
-    }
-    for (int off = 32; off > 0; off >>= 1) {
-        const float ob = __shfl_xor(best, off);
-        const int oa = __shfl_xor(arg, off);
-        if (ob < best || (ob == best && oa < arg)) { best = ob; arg = oa; }
-    }
-    if (lane == 0) codes[t * G + g] = (CodeT)arg;
+// Encode, fp32, as a kernel of its own: one item per workgroup.
+__global__ __launch_bounds__(kEncF32Threads) void vq_encode_f32_kernel(const EncodeJob job) {
+    __shared__ EncF32Lds lds;
+    vq_encode_f32_body(job, blockIdx.x, lds);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -750,15 +694,14 @@ int launch_vq_encode(const astra_vq_desc& d, const void* x, int64_t ldx, int64_t
             else vq_encode_bf16_kernel<uint16_t, false><<<grid, 256, 0, s>>>(xb, ldx, (int)n_tokens, cb, cnorm, (uint16_t*)codes, G, K, dg);
         }
     } else {
-        const int64_t waves = n_tokens * G;
-        const int64_t blocks = ceil_div(waves, 4);
+        const int64_t blocks = ceil_div(n_tokens, kEncF32Tokens) * G;
         if (blocks > 0x7fffffff) return ASTRA_ERR_SHAPE;
-        if (d.code_type == ASTRA_CODE_U8)
-            vq_encode_f32_kernel<uint8_t><<<(int)blocks, 256, 0, s>>>((const float*)x, ldx, n_tokens, (const float*)codebook,
-                                                                      (uint8_t*)codes, G, K, dg);
-        else
-            vq_encode_f32_kernel<uint16_t><<<(int)blocks, 256, 0, s>>>((const float*)x, ldx, n_tokens, (const float*)codebook,
-                                                                       (uint16_t*)codes, G, K, dg);
+        EncodeJob job{};
+        job.x = x; job.codebook = codebook; job.codes = codes; job.ldx = ldx;
+        job.n_tokens = (int)n_tokens; job.G = G; job.K = K; job.dg = dg;
+        job.code_bytes = code_bytes(d.code_type);
+        job.n_tb = (int)ceil_div(n_tokens, kEncF32Tokens);
+        vq_encode_f32_kernel<<<(int)blocks, kEncF32Threads, 0, s>>>(job);
     }
     return launch_status();
 }

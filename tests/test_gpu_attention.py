@@ -26,6 +26,9 @@ CASES = [
     (64, 192, 3, 3, 64, "f32", 0, False, 0),          # tiny ViT
     (50, 70, 4, 2, 32, "f32", 1, False, 0),           # fp32, GQA, class row, ragged
     (40, 90, 2, 2, 128, "f32", 0, True, 37),          # fp32 causal, middle rank
+    (37, 130, 3, 1, 30, "f32", 0, True, 100),         # fp32, rows of no whole 16-byte pieces
+    (21, 300, 2, 2, 100, "f32", 1, False, 0),         # fp32, pieces beyond the head; more chunks than wavefronts
+    (9, 70, 2, 1, 256, "f32", 0, True, 70),           # fp32, the widest head
     (257, 768, 12, 12, 64, "bf16", 1, False, 0),      # ViT-Base with class row (ragged 257)
     (256, 768, 12, 12, 64, "bf16", 0, True, 768),     # GPT-2 small, last rank
     (256, 768, 12, 12, 64, "bf16", 0, True, 256),     # GPT-2 small, rank 1

@@ -26,6 +26,9 @@ ENCODE_CASES = [
     (64, 4, 256, 48, "f32", "normal"),            # tiny ViT layer
     (300, 4, 256, 48, "f32", "normal"),
     (33, 3, 1000, 20, "f32", "normal"),           # uint16 codes, K not a multiple of the wave
+    (5, 2, 300, 132, "f32", "normal"),            # two chunks of 64 values and a piece, five tokens over blocks of four
+    (6, 2, 70, 520, "f32", "normal"),             # slices too long to wait in LDS
+    (3, 4, 300, 7, "f32", "normal"),              # slices of no whole 16-byte pieces
     (256, 16, 256, 48, "bf16", "normal_shift"),   # ViT-Base
     (256, 32, 256, 24, "bf16", "student_t5"),     # GPT-2 small (dg padded to 32)
     (1024, 64, 1024, 64, "bf16", "rms_normal"),   # Llama-3-8B shape, full size
