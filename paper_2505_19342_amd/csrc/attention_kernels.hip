@@ -96,21 +96,19 @@ __global__ __launch_bounds__(kAttThreads) void attn_bf16_kernel(const AttnParams
             for (int j = 0; j < e.n_jobs; ++j) n_total += e.job[j].G * e.job[j].n_tb;
             const int chunk = (n_total + e.n_enc_wgs - 1) / e.n_enc_wgs;
             const int hi = min((idx + 1) * chunk, n_total);
-            bool zeroed = false;
-            for (int it = idx * chunk; it < hi; ++it) {
-                int j = 0, item = it;
-                while (item >= e.job[j].G * e.job[j].n_tb) {
-                    item -= e.job[j].G * e.job[j].n_tb;
-                    ++j;
-                }
+            if (vq_encode_fast_needs_zero(e.job[0].dg)) {          // every job of a launch has the same group length
+                vq_encode_fast_zero_lds<kAttThreads>(cb);
+                __syncthreads();                           // zero fill done before any transfer lands
+            }
+            int first = 0;                                 // of job j in the sequence
+            for (int j = 0; j < e.n_jobs; ++j) {
                 const EncodeJob& job = e.job[j];
-                if (vq_encode_fast_needs_zero(job.dg) && !zeroed) {       // every job of a launch has the same group length
-                    vq_encode_fast_zero_lds<kAttThreads>(cb);
-                    __syncthreads();                       // zero fill done before any transfer lands
-                    zeroed = true;
+                const int n = job.G * job.n_tb, from = max(idx * chunk - first, 0), to = min(hi - first, n);
+                if (from < to) {
+                    vq_encode_fast_run<kAttThreads, true>(job, from, to, cb, cn);
+                    __syncthreads();                       // all reads of this run's tiles done before the next run's transfers
                 }
-                vq_encode_fast_body<kAttThreads>(job, item / job.n_tb, item % job.n_tb, cb, cn);
-                __syncthreads();                           // all reads of this item's tiles done before the next item's transfers
+                first += n;
             }
             return;
         }
@@ -709,14 +707,17 @@ int launch_attention(int dtype, const AttnParams& p_in, int head_dim, hipStream_
                 items += n_tb * enc[j].G;
             }
             if (ok && items > 0) {
-                ae.n_jobs = n_enc;
+                const int tb = vq_encode_blocks(enc[0], kAttCus / n_enc);
+                items = 0;
                 for (int j = 0; j < n_enc; ++j) {
                     ae.job[j] = enc[j];
-                    ae.job[j].n_tb = (int)ceil_div(enc[j].n_tokens, kAttThreads / 2);
+                    ae.job[j].tb = tb;
+                    ae.job[j].n_tb = (int)ceil_div(enc[j].n_tokens, kAttThreads / 2 * tb);
+                    items += (int64_t)ae.job[j].n_tb * enc[j].G;
                 }
+                ae.n_jobs = n_enc;
                 ae.n_attn_wgs = (int)total;
                 ae.n_enc_wgs = (int)std::min<int64_t>(items, kAttCus);
-                for (int j = 0; j < n_enc; ++j) ae.job[j].n_wgs = ae.n_enc_wgs;
                 *enc_fused = true;
             }
         }

@@ -146,10 +146,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_nt_bf16_kernel(const GemmBa
             const int n_items = job.G * job.n_tb;
             const int chunk = (n_items + batch.n_enc_wgs - 1) / batch.n_enc_wgs;     // consecutive items share the group
             const int hi = min((id.idx + 1) * chunk, n_items);
-            for (int item = id.idx * chunk; item < hi; ++item) {
-                vq_encode_fast_body<THREADS>(job, item / job.n_tb, item % job.n_tb, cb, cn);
-                __syncthreads();                           // all reads of this item's tiles done before the next item's transfers
-            }
+            vq_encode_fast_run<THREADS, true>(job, id.idx * chunk, hi, cb, cn);
             return;
         }
         vt = id.idx;

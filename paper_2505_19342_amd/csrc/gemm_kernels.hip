@@ -314,8 +314,8 @@ int launch_gemm_batch(int dtype, const GemmProblem* problems, int n_problems, hi
         if (wave.enc_wgs > 0) {
             batch.n_enc_wgs = wave.enc_wgs;
             batch.enc = *enc;
+            batch.enc.tb = 1;
             batch.enc.n_tb = (int)ceil_div(enc->n_tokens, kWaveThreads / 2);
-            batch.enc.n_wgs = wave.enc_wgs;
             *enc_fused = true;
         }
         if (plan_only) return ASTRA_OK;
@@ -370,8 +370,8 @@ int launch_gemm_batch(int dtype, const GemmProblem* problems, int n_problems, hi
         if (E > 0) {
             batch.n_enc_wgs = E;
             batch.enc = *enc;
-            batch.enc.n_tb = (int)ceil_div(enc->n_tokens, 256);
-            batch.enc.n_wgs = E;
+            batch.enc.tb = vq_encode_blocks(*enc, E);
+            batch.enc.n_tb = (int)ceil_div(enc->n_tokens, 256 * batch.enc.tb);
             *enc_fused = true;
             if (plan_only) return ASTRA_OK;
             if (mid) {

@@ -25,27 +25,30 @@ struct EncodeJob {
     int64_t ldx;
     int32_t n_tokens, G, K, dg;
     int32_t code_bytes;       // 1 or 2
-    int32_t n_tb;             // token blocks per group (of THREADS/2 tokens)
-    int32_t n_wgs;            // workgroups that share the items (fused launch only)
+    int32_t tb;               // 32-token blocks per wavefront, 1 or 2
+    int32_t n_tb;             // token blocks per group (of THREADS/2 * tb tokens)
 };
 
 // ------------------------------------------------------------------------------------------------
-// Groups of at most 64 values (dg a multiple of 8).  A workgroup of THREADS threads owns THREADS/2 tokens
-// of one group (32 per wavefront, on the N side of the 32x32x16 MFMA) and walks the group's codebook in
-// tiles of 128 codewords (M side).
-//   - The score is kept as a distance, ||c||^2 - 2 x.c: the token fragments are loaded once, negated and
-//     doubled (exact in bf16), and the accumulator is preloaded with ||c||^2 straight from LDS, so no
-//     vector-ALU work is spent on forming the score; the argmin costs a compare and two selects per value.
-//   - Codebook tiles and their norms go from global memory straight into a ring of four LDS buffers,
-//     three tiles ahead of the one being multiplied.  Pieces beyond dg are never transferred; the one such
-//     slot a contraction step can read (dg an odd multiple of 8) is zeroed once by the caller
-//     (vq_encode_fast_zero_lds, when vq_encode_fast_needs_zero) and meets zero token values.
-//   - NKS, the number of contraction steps of 16 (ceil(dg / 16)), is a compile-time value: the tile's work is then
-//     one basic block, and every LDS read of a tile (16 of norms, 4 NKS of codeword fragments) is requested before
-//     its first MFMA, so a wavefront waits for the LDS once per tile, not once per pair of MFMAs.
-// cb_lds: kEncBufs * kEncCbSlots slots, cn_lds: kEncBufs * kEncCnSlots slots.  Ends with every wavefront
-// past its last LDS read only after the caller's next barrier: callers that run several items in a row
-// put a barrier between them.
+// Groups of at most 64 values (dg a multiple of 8).  An item is a group and a block of tokens; a workgroup of THREADS threads takes a run of items,
+// 32 TB tokens per wavefront (on the N side of the 32x32x16 MFMA), and walks the group's codebook in tiles of 128 codewords (M side) for each.
+//   - The score is kept as a distance, ||c||^2 - 2 x.c: the token fragments are loaded negated and doubled (exact in bf16), and the accumulation
+//     starts from ||c||^2, so no vector-ALU work is spent on forming the score.
+//   - Codebook tiles and their norms go from global memory straight into a ring of four LDS buffers, two to three tiles ahead, without a break
+//     between items.  Pieces beyond dg are never transferred; the one such slot a contraction step can read (dg an odd multiple of 8) is
+//     zeroed once by the caller (vq_encode_fast_zero_lds, when vq_encode_fast_needs_zero) and meets zero token values.
+//   - A tile is UNITS units of two accumulators (two token blocks against 32 codewords, or one against 64).  While a unit's MFMAs are issued, the
+//     fragments of the next one are read and the scores of the one before are taken into the running argmin, so that the matrix core, the LDS and
+//     the vector ALU work at the same time whatever the other wavefront of the SIMD does.
+//   - The argmin goes by quads, four consecutive codewords in one lane: the minimum of the best so far and them (two instructions), and where that
+//     is a new one, the quad's number and its first three scores are kept (a compare and four selects): seven instructions for four scores.  Which of the four it
+//     was is worked out once per item.  Strict '<' and the first equal score keep the lowest index.
+//   - With TB = 2 a codeword fragment and the norms are read from LDS once for 64 tokens.
+// 16384 tokens x 64 groups of 64, K = 1024: 192 us as a kernel of one item of 128 tokens per workgroup with an argmin of a compare and two selects per
+// score behind each tile's MFMAs, 150 now (185 with TB = 1); 4096 tokens 52 -> 40, 16384 x 16 groups of 48, K = 256 21 -> 15.  Of the
+// 150, the MFMAs alone are about 70.
+// cb_lds: kEncBufs * kEncCbSlots slots, cn_lds: kEncBufs * kEncCnSlots slots.  Ends with every wavefront past its last LDS read only after the
+// caller's next barrier: callers that make several runs put a barrier between them.
 // ------------------------------------------------------------------------------------------------
 template <int THREADS>
 __device__ __forceinline__ void vq_encode_fast_zero_lds(u32x4* cb_lds) {
@@ -53,153 +56,242 @@ __device__ __forceinline__ void vq_encode_fast_zero_lds(u32x4* cb_lds) {
 }
 __device__ __forceinline__ bool vq_encode_fast_needs_zero(int dg) { return (dg & 8) != 0; }
 
-template <int THREADS, int NKS>
-__device__ __forceinline__ void vq_encode_fast_body_nks(const EncodeJob& job, int g, int tb, u32x4* cb_lds, f32x4* cn_lds) {
+// NKS = ceil(dg / 16) contraction steps
+template <int THREADS, int TB, int NKS>
+__device__ __forceinline__ void vq_encode_fast_run_nks(const EncodeJob& job, int lo, int hi, u32x4* cb_lds, f32x4* cn_lds) {
     constexpr int WAVES = THREADS / 64;
-    constexpr int TOKENS = WAVES * 32;                  // tokens per workgroup
+    constexpr int TOKENS = WAVES * 32 * TB;             // tokens per item
     constexpr int ITS = kEncCbSlots / THREADS;          // codebook transfers per thread per tile
     constexpr int NORM_LANES = kEncCnSlots / WAVES;     // lanes per wavefront that fetch 4 norms each
-    const int K = job.K, dg = job.dg, n_tokens = job.n_tokens;
+    constexpr int DMA = ITS + 1;                        // transfers of a wavefront per tile: "tile s has landed" is a fixed vmcnt threshold
+    constexpr int UNITS = TB == 2 ? 4 : 2, NA = TB == 2 ? 1 : 2;      // units of a tile, codeword blocks of 32 in one
+    if (lo >= hi) return;
+    const int K = job.K, dg = job.dg, n_tokens = job.n_tokens, n_tb = job.n_tb;
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int i32 = lane & 31, h = lane >> 5;
     const int n_pieces = dg >> 3;                       // valid 16-byte pieces per codeword
-
-    const char* __restrict__ cb_g = (const char*)((const uint16_t*)job.codebook + (int64_t)g * K * dg);
-    const char* __restrict__ cn_g = (const char*)(job.cnorm + (int64_t)g * K);
     const uint32_t row_b = (uint32_t)dg * 2u;
-    const int n_tiles = (K + kEncCw - 1) / kEncCw;
-    // Transfer geometry: slot c = tid + THREADS*it is (codeword c/8, physical piece c%8) and receives logical
-    // piece (c%8) ^ swz(c/8); swz has period 16 codewords and THREADS/8 codewords separate two `it`.  Every
-    // wavefront issues exactly kEncDma transfers per tile (ITS codebook passes + its share of the norms),
-    // so "tile t has landed" is a fixed vmcnt threshold.
-    constexpr int kEncDma = ITS + 1;
+    const int n_tiles = (K + kEncCw - 1) / kEncCw, n_steps = (hi - lo) * n_tiles;
+
+    // ---- transfers.  Slot c = tid + THREADS*it is (codeword c/8, physical piece c%8) and receives logical piece (c%8) ^ swz(c/8); swz has period 16
+    // codewords and THREADS/8 codewords separate two `it`.  Byte offsets past the group's last codeword are clamped to its row K-1.
     const int cw_l = tid >> 3;
     const int piece = (tid & 7) ^ enc_swz(cw_l);
     const bool piece_ok = piece < n_pieces;
-    // byte offsets of this thread's pieces in tile 0; a tile further on is a wave-uniform step, and offsets past the
-    // group's last codeword are clamped to its row K-1 (the last tile of a K that is no multiple of 128)
     uint32_t cb_off[ITS];
 #pragma unroll
     for (int it = 0; it < ITS; ++it) cb_off[it] = (uint32_t)(cw_l + (THREADS / 8) * it) * row_b + (uint32_t)piece * 16u;
     const uint32_t cb_off_max = (uint32_t)(K - 1) * row_b + (uint32_t)piece * 16u;
     const uint32_t cn_off = (uint32_t)(4 * NORM_LANES * wave + 4 * lane) * 4u, cn_off_max = (uint32_t)(K - 4) * 4u;
-    auto issue_tile = [&](int t) {
-        const int buf = t % kEncBufs;
+    const char* s_cb = (const char*)job.codebook + (int64_t)(lo / n_tb) * K * row_b;      // the tile that is sent next
+    const char* s_cn = (const char*)(job.cnorm + (int64_t)(lo / n_tb) * K);
+    int s_block = lo % n_tb, s_tile = 0, s_step = 0;
+    auto send_tile = [&]() __attribute__((always_inline)) {
+        if (s_step >= n_steps) return;
+        const int buf = s_step % kEncBufs;
         const uint32_t base = lds_byte_addr(cb_lds + buf * kEncCbSlots);
-        const uint32_t tile_b = (uint32_t)t * (uint32_t)kEncCw * row_b;
+        const uint32_t tile_b = (uint32_t)s_tile * (uint32_t)kEncCw * row_b;
         if (piece_ok) {
 #pragma unroll
             for (int it = 0; it < ITS; ++it)
-                dma_global_to_lds_16(cb_g, min(cb_off[it] + tile_b, cb_off_max), base + (uint32_t)(64 * (wave + WAVES * it)) * 16u);
+                dma_global_to_lds_16(s_cb, min(cb_off[it] + tile_b, cb_off_max), base + (uint32_t)(64 * (wave + WAVES * it)) * 16u);
         }
         if (lane < NORM_LANES)                          // 128 norms = WAVES x NORM_LANES lanes x 16 bytes
-            dma_global_to_lds_16(cn_g, min(cn_off + (uint32_t)t * (uint32_t)(kEncCw * 4), cn_off_max),
+            dma_global_to_lds_16(s_cn, min(cn_off + (uint32_t)s_tile * (uint32_t)(kEncCw * 4), cn_off_max),
                                  lds_byte_addr(cn_lds + buf * kEncCnSlots) + (uint32_t)wave * (16u * NORM_LANES));
+        ++s_step;
+        if (++s_tile == n_tiles) {
+            s_tile = 0;
+            if (++s_block == n_tb) {
+                s_block = 0;
+                s_cb += (int64_t)K * row_b;
+                s_cn += (int64_t)K * 4;
+            }
+        }
     };
+
+    // ---- tokens: raw values of an item, and as -2x
+    u32x4 raw[TB][NKS];
+    auto load_tokens = [&](int item) __attribute__((always_inline)) {
+        const int g = item / n_tb, t0 = (item - g * n_tb) * TOKENS + wave * (32 * TB) + i32;
+#pragma unroll
+        for (int b = 0; b < TB; ++b) {
+            const uint16_t* xrow = (const uint16_t*)job.x + (int64_t)min(t0 + 32 * b, n_tokens - 1) * job.ldx + (int64_t)g * dg;
+#pragma unroll
+            for (int ks = 0; ks < NKS; ++ks) {
+                const int k = 16 * ks + 8 * h;
+                raw[b][ks] = *reinterpret_cast<const u32x4*>(xrow + (k < dg ? k : 0));
+            }
+        }
+    };
+    bf16x8 xf[TB][NKS];
+    auto take_tokens = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int b = 0; b < TB; ++b)
+#pragma unroll
+            for (int ks = 0; ks < NKS; ++ks) {
+                const bf16x8 xv = __builtin_bit_cast(bf16x8, raw[b][ks]);
+                const bool in = 16 * ks + 8 * h < dg;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) xf[b][ks][e] = (__bf16)(in ? -2.f * (float)xv[e] : 0.f);
+            }
+    };
+
+    // ---- fragments of unit u of the tile in LDS buffer buf: rows 32 mb + lane % 32 (A), norms of rows 32 mb + 8q + 4h .. + 3
+    bf16x8 fa[NKS][NA];
+    f32x16 cn[NA];
+    auto block_of = [&](int u, int n) { return TB == 2 ? u : 2 * u + n; };
+    auto read_a = [&](int buf, int u, int ks) __attribute__((always_inline)) {
+#pragma unroll
+        for (int n = 0; n < NA; ++n)
+            fa[ks][n] = __builtin_bit_cast(bf16x8, cb_lds[buf * kEncCbSlots + (block_of(u, n) * 32 + i32) * 8 + ((2 * ks + h) ^ enc_swz(i32))]);
+    };
+    auto read_cn = [&](int buf, int u) __attribute__((always_inline)) {
+#pragma unroll
+        for (int n = 0; n < NA; ++n)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const f32x4 v = cn_lds[buf * kEncCnSlots + block_of(u, n) * 8 + 2 * q + h];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) cn[n][4 * q + e] = v[e];
+            }
+    };
+
+    // ---- running argmin of this lane's tokens: quad grp (0..31) of tile til, and the quad's first three scores
+    float best[TB], best_in[TB], k0[TB], k1[TB], k2[TB];
+    int grp[TB], til[TB];
+    f32x16 acc[2][2];
+    auto take_quad = [&](int set, int u, int i) __attribute__((always_inline)) {         // i-th of a unit's eight
+        const int j = i >> 2, q = i & 3, b = TB == 2 ? j : 0;
+        const float s0 = acc[set][j][4 * q], s1 = acc[set][j][4 * q + 1], s2 = acc[set][j][4 * q + 2], s3 = acc[set][j][4 * q + 3];
+        const float m = fminf(fminf(fminf(fminf(best[b], s0), s1), s2), s3);
+        const bool better = m < best[b];
+        best[b] = m;
+        grp[b] = better ? block_of(u, j) * 4 + q : grp[b];
+        k0[b] = better ? s0 : k0[b];
+        k1[b] = better ? s1 : k1[b];
+        k2[b] = better ? s2 : k2[b];
+    };
+    auto close_tile = [&](int t) __attribute__((always_inline)) {
+#pragma unroll
+        for (int b = 0; b < TB; ++b) {
+            til[b] = best[b] < best_in[b] ? t : til[b];
+            best_in[b] = best[b];
+        }
+    };
+
     // the first tiles are on their way before the token values are asked for: the two latencies overlap
 #pragma unroll
-    for (int t = 0; t < kEncBufs - 1; ++t)
-        if (t < n_tiles) issue_tile(t);
+    for (int t = 0; t < kEncBufs - 1; ++t) send_tile();
+    load_tokens(lo);
+    take_tokens();
+    wait_vmem_all();
+    __syncthreads();
+    read_cn(0, 0);
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks) read_a(0, 0, ks);
 
-    // this lane's token (N side), as -2x so that the MFMA accumulates ||c||^2 - 2 x.c
-    const int tok = tb * TOKENS + wave * 32 + i32;
-    const int tok_ld = tok < n_tokens ? tok : n_tokens - 1;
-    const uint16_t* xrow = (const uint16_t*)job.x + (int64_t)tok_ld * job.ldx + (int64_t)g * dg;
-    bf16x8 xfrag[NKS];
+    int step = 0;
+    for (int item = lo; item < hi; ++item) {
+        const int t_load = n_tiles > 3 ? n_tiles - 3 : 0;       // the next item's tokens are asked for two tiles before the end
 #pragma unroll
-    for (int ks = 0; ks < NKS; ++ks) {
-        const int k = 16 * ks + 8 * h;
-        u32x4 raw = u32x4{0u, 0u, 0u, 0u};
-        if (k < dg) raw = *reinterpret_cast<const u32x4*>(xrow + k);
-        const bf16x8 xv = __builtin_bit_cast(bf16x8, raw);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) xfrag[ks][e] = (__bf16)(-2.f * (float)xv[e]);
-    }
-
-    // Running argmin of this lane.  The winner is remembered as (tile, slot) with slot = mb*16 + v, a
-    // small compile-time constant per accumulator value, so the loop spends exactly a compare and two
-    // selects per score; slots ascend with the codeword index inside a lane and strict '<' keeps the
-    // lowest index.
-    float best = INFINITY;
-    int arg_slot = 0, arg_tile = 0;
-    auto process_tile = [&](int t, auto ragged_tag) {
-        constexpr bool kRagged = decltype(ragged_tag)::value;
-        const int buf = t % kEncBufs;
-        const int cw0 = t * kEncCw;
-        const u32x4* __restrict__ cb = cb_lds + buf * kEncCbSlots;
-        const f32x4* __restrict__ cnb = cn_lds + buf * kEncCnSlots;
-        // all LDS reads of the tile, in the order the MFMAs use them
-        f32x16 acc[4];
-        bf16x8 a[NKS][4];
-#pragma unroll
-        for (int mb = 0; mb < 4; ++mb) {
-#pragma unroll
-            for (int vq = 0; vq < 4; ++vq) {
-                const f32x4 cn = cnb[mb * 8 + 2 * vq + h];             // rows 32*mb + 8*vq + 4*h .. +3
-#pragma unroll
-                for (int e = 0; e < 4; ++e) acc[mb][4 * vq + e] = cn[e];
-            }
-            const int row = mb * 32 + i32;
-            a[0][mb] = __builtin_bit_cast(bf16x8, cb[row * 8 + (h ^ enc_swz(row))]);
+        for (int b = 0; b < TB; ++b) {
+            best[b] = best_in[b] = k0[b] = k1[b] = k2[b] = INFINITY;
+            grp[b] = til[b] = 0;
         }
 #pragma unroll
-        for (int ks = 1; ks < NKS; ++ks)
+        for (int j = 0; j < 2; ++j)
 #pragma unroll
-            for (int mb = 0; mb < 4; ++mb) {
-                const int row = mb * 32 + i32;
-                a[ks][mb] = __builtin_bit_cast(bf16x8, cb[row * 8 + ((2 * ks + h) ^ enc_swz(row))]);
+            for (int v = 0; v < 16; ++v) acc[1][j][v] = INFINITY;         // in the place of the unit before the first
+        for (int t = 0; t < n_tiles; ++t, ++step) {
+            const int buf = step % kEncBufs, next_buf = (step + 1) % kEncBufs;
+            const int lim = K - t * kEncCw;                     // codewords of this tile and beyond
+#pragma unroll
+            for (int u = 0; u < UNITS; ++u) {
+                if (u == UNITS - 1) {
+                    // the next tile has landed (the one after it may be outstanding, and the tokens asked for a tile ago); every wavefront is done with
+                    // the tile before this one, whose place takes the one three ahead
+                    if (step + 2 < n_steps) {
+                        if (t == t_load + 1 && item + 1 < hi) wait_vmem<DMA + TB * NKS>();
+                        else wait_vmem<DMA>();
+                    } else {
+                        wait_vmem_all();
+                    }
+                    __syncthreads();
+                    if (t == t_load && item + 1 < hi) load_tokens(item + 1);
+                    send_tile();
+                }
+                if (lim < kEncCw) {                             // codewords past K (the last tile of a K that is no multiple of 128) are infinitely far
+#pragma unroll
+                    for (int n = 0; n < NA; ++n) {
+                        const int left = lim - 32 * block_of(u, n) - 4 * h;
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) cn[n][v] = acc_row(v, 0) >= left ? INFINITY : cn[n][v];
+                    }
+                }
+                const int set = u & 1, rb = u == UNITS - 1 ? next_buf : buf, ru = (u + 1) % UNITS, pu = (u + UNITS - 1) % UNITS;
+#pragma unroll
+                for (int i = 0; i < 2 * NKS; ++i) {
+                    const int ks = i >> 1, j = i & 1;
+                    acc[set][j] = mfma_32x32x16(fa[ks][TB == 2 ? 0 : j], xf[TB == 2 ? j : 0][ks], ks == 0 ? cn[TB == 2 ? 0 : j] : acc[set][j]);
+                    if (i == 1) read_cn(rb, ru);
+                    if (j == 1) read_a(rb, ru, ks);
+#pragma unroll
+                    for (int x = i * 8 / (2 * NKS); x < (i + 1) * 8 / (2 * NKS); ++x) take_quad(set ^ 1, pu, x);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                if (u == 0) close_tile(t - 1);                  // the quads were those of the tile before
+                // the argmin is worked out here: moved behind the branches that follow, it would keep the scores of several units alive
+#pragma unroll
+                for (int b = 0; b < TB; ++b) asm volatile("" : "+v"(best[b]), "+v"(grp[b]), "+v"(k0[b]), "+v"(k1[b]), "+v"(k2[b]), "+v"(til[b]));
             }
+        }
 #pragma unroll
-        for (int ks = 0; ks < NKS; ++ks)
+        for (int x = 0; x < 8; ++x) take_quad(1, UNITS - 1, x);
+        close_tile(n_tiles - 1);
+        const int g = item / n_tb, t0 = (item - g * n_tb) * TOKENS + wave * (32 * TB) + i32;
 #pragma unroll
-            for (int mb = 0; mb < 4; ++mb) acc[mb] = mfma_32x32x16(a[ks][mb], xfrag[ks], acc[mb]);
-        const float best_in = best;
-#pragma unroll
-        for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                float sc = acc[mb][v];
-                if (kRagged && cw0 + mb * 32 + acc_row(v, h) >= K) sc = INFINITY;   // codewords past K: last tile only
-                const bool better = sc < best;
-                best = better ? sc : best;
-                arg_slot = better ? (mb * 16 + v) : arg_slot;
+        for (int b = 0; b < TB; ++b) {
+            const int e = k0[b] == best[b] ? 0 : k1[b] == best[b] ? 1 : k2[b] == best[b] ? 2 : 3;
+            int arg = til[b] * kEncCw + (grp[b] >> 2) * 32 + (grp[b] & 3) * 8 + 4 * h + e;
+            // merge the two half-waves that hold the same token
+            const float ob = __shfl_xor(best[b], 32);
+            const int oa = __shfl_xor(arg, 32);
+            if (ob < best[b] || (ob == best[b] && oa < arg)) arg = oa;
+            if (h == 0 && t0 + 32 * b < n_tokens) {
+                const int64_t at = (int64_t)(t0 + 32 * b) * job.G + g;
+                if (job.code_bytes == 2) ((uint16_t*)job.codes)[at] = (uint16_t)arg;
+                else ((uint8_t*)job.codes)[at] = (uint8_t)arg;
             }
-        arg_tile = best < best_in ? t : arg_tile;
-    };
-
-    const int n_full = K / kEncCw;                      // tiles without codewords past K
-    for (int t = 0; t < n_tiles; ++t) {
-        // tile t has landed once at most the transfers of the (up to two) younger tiles are outstanding
-        if (t + 2 < n_tiles) wait_vmem<2 * kEncDma>();
-        else if (t + 1 < n_tiles) wait_vmem<kEncDma>();
-        else wait_vmem<0>();
-        __syncthreads();        // everyone's share of tile t is visible; everyone is done with tile t-1
-        if (t + kEncBufs - 1 < n_tiles) issue_tile(t + kEncBufs - 1);     // into the buffer tile t-1 used
-        if (t < n_full) process_tile(t, std::false_type{});
-        else process_tile(t, std::true_type{});
-    }
-    // (tile, slot) -> codeword index
-    int arg = arg_tile * kEncCw + (arg_slot >> 4) * 32 + acc_row(arg_slot & 15, h);
-    // merge the two half-waves that hold the same token
-    const float ob = __shfl_xor(best, 32);
-    const int oa = __shfl_xor(arg, 32);
-    if (ob < best || (ob == best && oa < arg)) { best = ob; arg = oa; }
-    if (h == 0 && tok < n_tokens) {
-        if (job.code_bytes == 2) ((uint16_t*)job.codes)[(int64_t)tok * job.G + g] = (uint16_t)arg;
-        else ((uint8_t*)job.codes)[(int64_t)tok * job.G + g] = (uint8_t)arg;
+        }
+        if (item + 1 < hi) take_tokens();
     }
 }
 
-template <int THREADS>
-__device__ __forceinline__ void vq_encode_fast_body(const EncodeJob& job, int g, int tb, u32x4* cb_lds, f32x4* cn_lds) {
+template <int THREADS, int TB>
+__device__ __forceinline__ void vq_encode_fast_run_tb(const EncodeJob& job, int lo, int hi, u32x4* cb_lds, f32x4* cn_lds) {
     switch ((job.dg + 15) >> 4) {
-        case 1: vq_encode_fast_body_nks<THREADS, 1>(job, g, tb, cb_lds, cn_lds); break;
-        case 2: vq_encode_fast_body_nks<THREADS, 2>(job, g, tb, cb_lds, cn_lds); break;
-        case 3: vq_encode_fast_body_nks<THREADS, 3>(job, g, tb, cb_lds, cn_lds); break;
-        default: vq_encode_fast_body_nks<THREADS, 4>(job, g, tb, cb_lds, cn_lds); break;
+        case 1: vq_encode_fast_run_nks<THREADS, TB, 1>(job, lo, hi, cb_lds, cn_lds); break;
+        case 2: vq_encode_fast_run_nks<THREADS, TB, 2>(job, lo, hi, cb_lds, cn_lds); break;
+        case 3: vq_encode_fast_run_nks<THREADS, TB, 3>(job, lo, hi, cb_lds, cn_lds); break;
+        default: vq_encode_fast_run_nks<THREADS, TB, 4>(job, lo, hi, cb_lds, cn_lds); break;
     }
+}
+
+// items lo .. hi - 1 of the job; both: the job may have one or two blocks per wavefront, else it has one
+template <int THREADS, bool BOTH>
+__device__ __forceinline__ void vq_encode_fast_run(const EncodeJob& job, int lo, int hi, u32x4* cb_lds, f32x4* cn_lds) {
+    if (BOTH && job.tb == 2) vq_encode_fast_run_tb<THREADS, 2>(job, lo, hi, cb_lds, cn_lds);
+    else vq_encode_fast_run_tb<THREADS, 1>(job, lo, hi, cb_lds, cn_lds);
+}
+
+// Token blocks per wavefront for an encode that `wgs` workgroups of 512 threads share.  Two take 1.6 times as long as one (16384 tokens x 64 groups, K = 1024:
+// 150 us, 185 with one), so they pay where one block each makes more than 1.6 times the rounds.
+inline int vq_encode_blocks(const EncodeJob& e, int64_t wgs) {
+    const int64_t one = ceil_div(e.n_tokens, (int64_t)256) * e.G, two = ceil_div(e.n_tokens, (int64_t)512) * e.G;
+    return 1.6 * (double)ceil_div(two, wgs) < (double)ceil_div(one, wgs) ? 2 : 1;
 }
 
 // true when the fast body handles this configuration

@@ -464,6 +464,7 @@ __global__ __launch_bounds__(kEncF32Threads) void vq_encode_f32_kernel(const Enc
 // pieces); a token's slice stays in registers when dg <= 64, otherwise it is re-read per tile.
 // ------------------------------------------------------------------------------------------------
 constexpr int kEncTokens = 128;   // tokens per workgroup
+constexpr int kEncSlots = 512;    // workgroups of the fast path that run at a time: two on each of 256 compute units
 
 // 8 consecutive bf16 of a row slice of length dg starting at element k; zero beyond dg.  Loads are never guarded
 // (a guarded load compiles to a branch with a wait of its own): addresses are clamped into the slice and the
@@ -641,11 +642,11 @@ __global__ __launch_bounds__(256) void vq_encode_bf16_kernel(const uint16_t* __r
 }
 
 // ------------------------------------------------------------------------------------------------
-// Encode, bf16, fast path (vq_encode_body.h) as a kernel of its own: one workgroup of 256 threads per
-// (group, block of 128 tokens).  Workgroup ids are remapped so that all token blocks of a group run on the
-// same XCD and find the group's codebook in that XCD's L2.
+// Encode, bf16, fast path (vq_encode_body.h) as a kernel of its own: workgroups of 256 threads, two of which fit a unit, share the items in runs
+// of equal length.  Workgroup ids are remapped so that the items of a group run on the same XCD and find the group's codebook in that XCD's L2.
 // ------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void vq_encode_bf16_fast_kernel(const EncodeJob job) {
+template <int TB>
+__global__ __launch_bounds__(256, 2) void vq_encode_bf16_fast_kernel(const EncodeJob job) {
     __shared__ u32x4 cb_lds[kEncBufs * kEncCbSlots];    // 4 x 16 KiB: [128 codewords][8 pieces of 8 bf16], swizzled
     __shared__ f32x4 cn_lds[kEncBufs * kEncCnSlots];    // 4 x 512 B
     // contiguous runs of workgroups per XCD; consecutive virtual ids share the group
@@ -656,7 +657,8 @@ __global__ __launch_bounds__(256) void vq_encode_bf16_fast_kernel(const EncodeJo
         vq_encode_fast_zero_lds<256>(cb_lds);
         __syncthreads();                               // zero fill done before any transfer lands
     }
-    vq_encode_fast_body<256>(job, vid / job.n_tb, vid % job.n_tb, cb_lds, cn_lds);
+    const int items = job.G * job.n_tb, chunk = (items + total - 1) / total;
+    vq_encode_fast_run_tb<256, TB>(job, min(vid * chunk, items), min((vid + 1) * chunk, items), cb_lds, cn_lds);
 }
 
 int launch_vq_encode(const astra_vq_desc& d, const void* x, int64_t ldx, int64_t n_tokens, const void* codebook,
@@ -669,13 +671,19 @@ int launch_vq_encode(const astra_vq_desc& d, const void* x, int64_t ldx, int64_t
         const int64_t n_tb = ceil_div(n_tokens, kEncTokens);
         // fast path: whole 16-byte pieces, one contraction tile, norms readable as aligned groups of 4
         if (vq_encode_fast_ok(K, dg) && n_tb * G <= 0x7fffffff) {
-            const int total = (int)(n_tb * G);
             EncodeJob job{};
             job.x = x; job.codebook = codebook; job.cnorm = cnorm; job.codes = codes; job.ldx = ldx;
             job.n_tokens = (int)n_tokens; job.G = G; job.K = K; job.dg = dg;
             job.code_bytes = d.code_type == ASTRA_CODE_U8 ? 1 : 2;
-            job.n_tb = (int)n_tb; job.n_wgs = total;
-            vq_encode_bf16_fast_kernel<<<total, 256, 0, s>>>(job);
+            // 64 tokens per wavefront once that gives every unit an item: 1024 / 1531 / 2048 tokens x 64 groups, K = 1024: 13.5 / 18.9 / 20.3 us, with
+            // 32 tokens per wavefront 13.9 / 24.1 / 25.3; 700 x 32 groups, K = 256 (96 items): 6.6 and 5.6
+            const int64_t wide = ceil_div(n_tokens, 2 * kEncTokens) * G;
+            const bool two = wide >= kEncSlots / 2;
+            job.n_tb = (int)(two ? ceil_div(n_tokens, 2 * kEncTokens) : n_tb);
+            const int64_t items = (int64_t)job.n_tb * G, chunk = ceil_div(items, (int64_t)kEncSlots);
+            const int grid = (int)ceil_div(items, chunk);
+            if (two) vq_encode_bf16_fast_kernel<2><<<grid, 256, 0, s>>>(job);
+            else vq_encode_bf16_fast_kernel<1><<<grid, 256, 0, s>>>(job);
             return launch_status();
         }
         if (G > 65535) return ASTRA_ERR_SHAPE;

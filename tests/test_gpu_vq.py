@@ -43,6 +43,12 @@ ENCODE_CASES = [
     (150, 3, 260, 56, "bf16", "normal"),          # four steps, the last piece zero-filled; K = 2 tiles + 4 codewords
     (100, 5, 132, 16, "bf16", "normal"),          # one step; second tile holds 4 codewords
     (70, 2, 1024, 8, "bf16", "normal"),           # one step, upper half of it zero-filled
+    # two token blocks per wavefront (256 items of 256 tokens or more): every contraction-step count, one to eight tiles, runs of several items
+    (300, 128, 132, 8, "bf16", "normal"),
+    (513, 128, 260, 24, "bf16", "student_t5"),
+    (257, 200, 100, 40, "bf16", "normal"),
+    (1100, 128, 1000, 64, "bf16", "rms_normal"),  # 640 items: runs of two, a group's last item next to the first of the next group
+    (4500, 40, 600, 56, "bf16", "normal"),        # 720 items of five tiles, the last one of 88 codewords
     # wide groups (dg a multiple of 64 above 64): the kernel that streams both operands over dg
     (300, 1, 1024, 4096, "bf16", "rms_normal"),   # Llama width with the paper's G = 1; ragged token tail
     (1024, 2, 1024, 2048, "bf16", "rms_normal"),  # G = 2, full row count
@@ -88,6 +94,24 @@ def test_encode_codewords_and_exact_ties(dtype):
     assert np.array_equal(got, expect)
     assert np.array_equal(got, oracle.vq_encode(x, cb))
     assert np.array_equal(gpu_vq_decode(got, cb, dtype), x)          # decode(encode(c)) == c
+
+
+@pytest.mark.parametrize("T,G", [(40, 3), (300, 130)])          # one token block per wavefront, two
+def test_encode_ties_wherever_they_lie(T, G):
+    """Equal codewords in one quad, in the two halves of a wavefront, in other blocks and tiles: the lowest index wins; and a codebook of equal codewords."""
+    from gpu_util import gpu_vq_encode
+    rng = np.random.default_rng(11)
+    K, dg = 300, 16
+    cb = wl.round_to_bf16(rng.standard_normal((G, K, dg), dtype=np.float32))
+    sets = [(5, 6, 7), (1, 12), (9, 13, 41), (100, 101, 131, 299), (250, 251)]
+    for s in sets:
+        cb[:, list(s)] = cb[:, s[:1]]
+    pick = rng.choice([i for s in sets for i in s], size=(T, G))
+    x = cb[np.arange(G)[None], pick].reshape(T, G * dg)
+    first = {i: s[0] for s in sets for i in s}
+    assert np.array_equal(gpu_vq_encode(x, cb, "bf16"), np.vectorize(first.get)(pick))
+    cb[:] = cb[:, :1]
+    assert not gpu_vq_encode(x, cb, "bf16").any()
 
 
 @pytest.mark.parametrize("T,G,K,dg", [(300, 1, 1024, 4096), (257, 2, 1000, 384), (100, 7, 1024, 128), (64, 4, 16, 192), (33, 16, 256, 48)])
