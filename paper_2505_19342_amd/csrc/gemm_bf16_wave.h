@@ -109,22 +109,14 @@ __global__ __launch_bounds__(kWaveThreads) void gemm_wave_kernel(const GemmBatch
     const bool code16 = gather && P.code_bytes == 2;
     const char* const codes_lds = wv_lds + S::kBytes;
     int k_next = wave * kBK;                               // contraction index of the slice whose transfers are issued next
-    if (GATHER && gather) {
-        const int row_b = G * P.code_bytes;
-        const int total = n_codes * row_b;
-        const char* __restrict__ src = (const char*)P.codes + (int64_t)m_codes * row_b;
-        char* dst = wv_lds + S::kBytes;
-        for (int o = tid * 16; o < total; o += kWaveThreads * 16) {
-            if (o + 16 <= total) *reinterpret_cast<u32x4*>(dst + o) = *reinterpret_cast<const u32x4*>(src + o);
-            else for (int b = o; b < total; ++b) dst[b] = src[b];
-        }
-        __syncthreads();
-    }
-
-    auto issue = [&](int slot) __attribute__((always_inline)) {
+    auto issue_b = [&](int slot) __attribute__((always_inline)) {
         const uint32_t dst = ring_a + (uint32_t)(slot * S::kStage);
 #pragma unroll
         for (int j = DA; j < DM; ++j) dma_global_to_lds_16(b_base, off[j], dst + (uint32_t)(j * 1024));
+        b_base += 128 * kWaveWaves;
+    };
+    auto issue_a = [&](int slot) __attribute__((always_inline)) {
+        const uint32_t dst = ring_a + (uint32_t)(slot * S::kStage);
         if (GATHER && gather) {
             uint32_t g_[2], at[2];
 #pragma unroll
@@ -146,9 +138,24 @@ __global__ __launch_bounds__(kWaveThreads) void gemm_wave_kernel(const GemmBatch
             for (int j = 0; j < DA; ++j) dma_global_to_lds_16(a_base, off[j], dst + (uint32_t)(j * 1024));
             a_base += 128 * kWaveWaves;
         }
-        b_base += 128 * kWaveWaves;
         k_next += kBK * kWaveWaves;
     };
+    // the first stages: all of their B rows before the codes are copied, which only A rows need
+#pragma unroll
+    for (int u = 0; u < ST; ++u)
+        if (u < n) issue_b(u);
+    if (GATHER && gather) {
+        const int row_b = G * P.code_bytes;
+        const int total = n_codes * row_b;
+        const char* __restrict__ src = (const char*)P.codes + (int64_t)m_codes * row_b;
+        char* dst = wv_lds + S::kBytes;
+        for (int o = tid * 16; o < total; o += kWaveThreads * 16) {
+            if (o + 16 <= total) *reinterpret_cast<u32x4*>(dst + o) = *reinterpret_cast<const u32x4*>(src + o);
+            else for (int b = o; b < total; ++b) dst[b] = src[b];
+        }
+        __syncthreads();
+    }
+
 
     f32x16 acc[MT][NT];
 #pragma unroll
@@ -179,14 +186,16 @@ __global__ __launch_bounds__(kWaveThreads) void gemm_wave_kernel(const GemmBatch
     static_assert(ST <= 2, "thresholds of the last stages are written out below");
 #pragma unroll
     for (int u = 0; u < ST; ++u)
-        if (u < n) issue(u);
+        if (u < n) issue_a(u);
+    if (ST == 2 && n > 1) wait_vmem<DA>();           // the first stage has landed: younger than its A rows are those of the second only
     int i = 0, slot = 0;
     for (; i + ST < n; ++i) {
         wait_vmem<(ST - 1) * DM>();                  // the oldest stage has landed
         read(slot);
         __builtin_amdgcn_s_waitcnt(0xC07F);          // its fragments are in registers (lgkmcnt 0): the slot is free
         asm volatile("" ::: "memory");
-        issue(slot);
+        issue_b(slot);
+        issue_a(slot);
         multiply();
         slot = slot + 1 == ST ? 0 : slot + 1;
     }
