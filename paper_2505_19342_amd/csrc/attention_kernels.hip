@@ -722,6 +722,9 @@ int launch_attention(int dtype, const AttnParams& p_in, int head_dim, hipStream_
             }
         }
         if (plan_only) return ASTRA_OK;
+        // 64-wide heads: a workgroup per 32 query rows where those make a single round of the units.  12 heads, 256 + 768 / 256 + 8000 rows: whole layer
+        // 27.4 / 79.0 us on the kernel above, 23.7 / 64.7 this way; 700 + 700 rows (264 workgroups) 38.0 and 37.4, 700 + 3000 50.3 and 56.6.
+        if (head_dim == 64 && vt && ceil_div(p.Tq, 32) * p.Hq <= kAttCus) return launch_attention_short(p, s);
         if (ae.n_enc_wgs > 0) {
             if (lost) attn_bf16_kernel<128, true, true, 2, true><<<(int)total + ae.n_enc_wgs, kAttThreads, 0, s>>>(p, ae);
             else attn_bf16_kernel<128, true, false, 2, true><<<(int)total + ae.n_enc_wgs, kAttThreads, 0, s>>>(p, ae);

@@ -287,3 +287,45 @@ def test_gathered_rows_over_few_contraction_tiles(d, groups, words, n_local, n_n
     ref = (p @ v).permute(2, 0, 1, 3).reshape(n_local, hq * dh) @ wo.float().T
     assert float((y - ref).abs().max()) <= 0.1 * float(ref.abs().max())
     assert float((y - ref).norm() / ref.norm()) <= 2e-2
+
+
+@pytest.mark.parametrize("n_local,n_nonlocal,hq,hkv,n_cls,causal,lost", [
+    (1, 0, 2, 1, 0, True, None),             # one row, one key: seven of the eight wavefronts have no tile
+    (32, 0, 4, 4, 1, False, None),           # a second block of one row
+    (31, 480, 12, 12, 0, True, None),        # eight tiles and one key's worth of a ninth for the first wavefront
+    (33, 513, 12, 4, 0, True, None),         # grouped heads; nine tiles of peers, the last of one row
+    (100, 700, 12, 12, 1, False, "some"),
+    (100, 700, 12, 12, 0, True, "tiles"),    # the first and third tile lost whole: two wavefronts without a key before the local rows
+    (40, 200, 4, 4, 0, True, "all"),
+    (150, 1100, 16, 8, 0, True, None),       # three tiles for a wavefront
+    (672, 96, 12, 12, 0, True, None),        # 252 blocks of 32 rows: the last round number of heads that is a single round
+    (673, 96, 12, 12, 0, True, None),        # 264: the other kernel
+])
+def test_short_sequences_of_64_wide_heads(n_local, n_nonlocal, hq, hkv, n_cls, causal, lost):
+    """Attention on blocks of 32 query rows whose wavefronts walk the tiles for themselves: fewer tiles than wavefronts, ragged ends, masks."""
+    from gpu_util import LayerOnGpu, compare_codes
+    d = hq * 64
+    cfg = wl.LayerConfig("short", "bf16", d, hq, hkv, 64, n_local + n_nonlocal, 1, 16, 256, n_cls=n_cls, causal=causal, seed=71)
+    data = wl.generate(cfg)
+    rows = data["x"]
+    cls_rows = rows[-n_cls:] if n_cls else rows[:0]
+    x_nl = rows[:n_nonlocal]
+    x_local = np.concatenate([cls_rows, rows[n_nonlocal:n_nonlocal + n_local]])
+    codes_nl = oracle.vq_encode(x_nl, data["codebook"])
+    valid = None
+    if lost:
+        valid = np.ones(n_nonlocal, dtype=bool)
+        if lost == "some":
+            valid = np.random.default_rng(5).random(n_nonlocal) >= 0.3
+        elif lost == "tiles":
+            valid[:64] = valid[128:192] = False
+        else:
+            valid[:] = False
+    n_before = n_nonlocal if causal else 0
+    y_ref, codes_ref, gap = oracle.layer_forward(x_local, codes_nl, data["codebook"], data["wq"], data["wk"], data["wv"], data["wo"], n_q_heads=hq,
+                                                 n_kv_heads=hkv, n_cls=n_cls, causal=causal, n_before=n_before, return_gap=True, valid_nonlocal=valid)
+    layer = LayerOnGpu(cfg, data, x_local, codes_nl, n_before)
+    layer.run(valid_nonlocal=valid)
+    y, codes = layer.results()
+    compare_codes(codes, codes_ref, gap, NEAR_TIE)
+    assert np.abs(y - y_ref).max() <= Y_TOL["bf16"]
