@@ -2,8 +2,7 @@
 // full-precision local keys/values and to keys/values projected from the tokens rebuilt from codes.
 // The two key/value sources are never concatenated in memory: the kernels walk the visible
 // non-local rows first and the local rows after them (softmax does not depend on key order).
-#include "common.h"
-#include "vq_encode_body.h"
+#include "attention_encode.h"
 #include "vq_encode_f32_body.h"
 
 #include <algorithm>
@@ -61,14 +60,7 @@ __device__ __forceinline__ int swz_vt(int r) { return (r >> 1) & 7; }
 
 // LOST: the caller passed a validity bit per non-local token (an instantiation of its own, so that the code for it does
 // not disturb the register allocation and schedule of the kernel that runs without)
-// ENC: the grid is the attention workgroups followed by e.n_enc_wgs workgroups that run VQ encodes nothing in this launch
-// depends on (the layer that quantises K and V after projection sends their codes to its peers): they are dispatched as
-// attention workgroups finish, i.e. into the tail that causal masking leaves on the units of the light query blocks.
-struct AttnEncode {
-    EncodeJob job[2];
-    int32_t n_jobs, n_attn_wgs, n_enc_wgs;
-};
-
+// ENC: VQ encodes ride in the launch (AttnEncode)
 template <int DH, bool VT, bool LOST = false, int NPAR = 2, bool ENC = false>
 __global__ __launch_bounds__(kAttThreads) void attn_bf16_kernel(const AttnParams p, const AttnEncode e) {
     static_assert(NPAR == 2 || NPAR == 4, "two or four tile parities");
@@ -90,26 +82,7 @@ __global__ __launch_bounds__(kAttThreads) void attn_bf16_kernel(const AttnParams
         if ((int)blockIdx.x >= e.n_attn_wgs) {
             u32x4* cb = &lds_k[0][0][0];
             f32x4* cn = reinterpret_cast<f32x4*>(&lds_v[0][0][0]);
-            // the items of all jobs in one sequence, dealt in consecutive runs (consecutive items share the group)
-            const int idx = (int)blockIdx.x - e.n_attn_wgs;
-            int n_total = 0;
-            for (int j = 0; j < e.n_jobs; ++j) n_total += e.job[j].G * e.job[j].n_tb;
-            const int chunk = (n_total + e.n_enc_wgs - 1) / e.n_enc_wgs;
-            const int hi = min((idx + 1) * chunk, n_total);
-            if (vq_encode_fast_needs_zero(e.job[0].dg)) {          // every job of a launch has the same group length
-                vq_encode_fast_zero_lds<kAttThreads>(cb);
-                __syncthreads();                           // zero fill done before any transfer lands
-            }
-            int first = 0;                                 // of job j in the sequence
-            for (int j = 0; j < e.n_jobs; ++j) {
-                const EncodeJob& job = e.job[j];
-                const int n = job.G * job.n_tb, from = max(idx * chunk - first, 0), to = min(hi - first, n);
-                if (from < to) {
-                    vq_encode_fast_run<kAttThreads, true>(job, from, to, cb, cn);
-                    __syncthreads();                       // all reads of this run's tiles done before the next run's transfers
-                }
-                first += n;
-            }
+            attn_encode_wgs<kAttThreads>(e, (int)blockIdx.x - e.n_attn_wgs, cb, cn);
             return;
         }
     }
@@ -667,13 +640,34 @@ static void launch_attn_f32(int blocks, const AttnParams& p, int head_dim, const
     else attn_f32_kernel<U, false><<<blocks, 256, 0, s>>>(p, head_dim, e);
 }
 
+static double encode_item_us(const EncodeJob& e) { return 256.0 * e.K * e.dg / 1048576.0 + 2.5; }      // 16.5 us and its start at K = 1024, dg = 64
+
+// About how long an attention launch lasts with `items` workgroups of encodes behind its own, by either kernel (us).
+static double attention_us(const AttnParams& p, bool few, int64_t items, double item) {
+    const int64_t total = ceil_div(p.Tq, few ? 32 : kAttQ) * p.Hq, rounds = ceil_div(total, (int64_t)kAttCus);
+    const int64_t more = ceil_div(total + items, (int64_t)kAttCus) - rounds;
+    const double tiles = (double)(p.Tn_vis + p.Tq) / kAttKV;                // a workgroup walks them all
+    const double walk = few ? 5.0 + 0.8 * tiles : 6.0 + 1.1 * tiles;
+    return walk * rounds + (items == 0 ? 0.0 : more > 0 ? more * item : std::max(0.0, item - walk));
+}
+
+// A workgroup per 32 query rows (attention_short_kernels.hip) where those make a single round of the units, and where encodes in the launch do not
+// lose the units that fewer workgroups would leave them.  Whole layers, there / on the kernel above:
+// 12 heads of 64, 256 + 768 / 256 + 8000 rows 23.7 / 27.4, 64.7 / 79.0 us; 700 + 700 rows (264 workgroups) 37.4 / 38.0, 700 + 3000 56.6 / 50.3.
+// 32 heads of 128 over 8 KV heads, 17 + 51 rows 29.8 / 32.8, 128 + 384 47.2 / 53.0, 256 + 768 71 / 78, 256 + 4096 130 / 149; 384 + 1152 rows (two rounds)
+// 94.4 / 93.7, 512 + 4096 174 / 168.  With the encodes of K and V, 1024 codewords each, in the launch: 100 + 300 rows 40.6 / 44.3, but 256 + 768, whose
+// workgroups take every unit, 66.5 / 64.2.
+static bool attention_short(const AttnParams& p, int head_dim, int64_t items, double item) {
+    if ((head_dim != 64 && head_dim != 128) || !p.v_transposed || ceil_div(p.Tq, 32) * p.Hq > kAttCus) return false;
+    return items == 0 || attention_us(p, true, items, item) < attention_us(p, false, items, item);
+}
+
 double attention_encode_us(const AttnParams& p, int head_dim, const EncodeJob& e) {
     if (head_dim != 128 || !p.v_transposed || e.n_tokens <= 0 || !vq_encode_fast_ok(e.K, e.dg)) return -1.0;
-    const int64_t total = ceil_div(p.Tq, kAttQ) * p.Hq, items = ceil_div(e.n_tokens, kAttThreads / 2) * e.G;
-    const int64_t rounds = ceil_div(total + items, (int64_t)kAttCus) - ceil_div(total, (int64_t)kAttCus);
-    const double item = 256.0 * e.K * e.dg / 1048576.0 + 2.5;               // 16.5 us and its start at K = 1024, dg = 64
-    const double walk = 6.0 + 1.1 * (p.Tn_vis + p.Tq) / kAttKV;             // a workgroup's tiles of 64 keys
-    return rounds > 0 ? rounds * item : std::max(0.0, item - walk);
+    const int64_t items = ceil_div(e.n_tokens, kAttThreads / 2) * e.G;
+    const double item = encode_item_us(e);
+    const double with = attention_us(p, attention_short(p, head_dim, items, item), items, item);
+    return std::max(0.0, with - attention_us(p, attention_short(p, head_dim, 0, 0.0), 0, 0.0));
 }
 
 int launch_attention(int dtype, const AttnParams& p_in, int head_dim, hipStream_t s, bool plan_only, const EncodeJob* enc, int n_enc,
@@ -685,10 +679,6 @@ int launch_attention(int dtype, const AttnParams& p_in, int head_dim, hipStream_
     if (dtype == ASTRA_BF16) {
         int64_t total = (int64_t)ceil_div(p.Tq, kAttQ) * p.Hq;
         if (total > 0x7fffffff) return ASTRA_ERR_SHAPE;
-        // short sequences with 64-wide heads: when 128-row query blocks would leave half of the compute units without a
-        // workgroup, 64-row blocks whose tiles are dealt to four wavefronts per query group (half the iterations each)
-        const bool four = head_dim == 64 && total <= kAttCus / 2;
-        if (four) total = (int64_t)ceil_div(p.Tq, kAttQ / 2) * p.Hq;
         const bool vt = p.v_transposed != 0;
         const bool lost = p.valid_bits != nullptr;
         if (head_dim != 64 && head_dim != 128) return ASTRA_ERR_UNSUPPORTED;
@@ -697,34 +687,38 @@ int launch_attention(int dtype, const AttnParams& p_in, int head_dim, hipStream_
         if (vt && (int64_t)max(p.ldv_loc, p.ldv_hat) * 2 * head_dim >= (1ll << 32)) return ASTRA_ERR_UNSUPPORTED;
         if ((int64_t)p.Hkv * head_dim * 2 * kAttKV >= (1ll << 32)) return ASTRA_ERR_UNSUPPORTED;
         // encodes offered by the caller ride in the launch's tail (128-wide heads on transposed V: the instantiations built)
+        int64_t items = 0;
         if (enc && enc_fused && n_enc >= 1 && n_enc <= 2 && head_dim == 128 && vt && total + kAttCus <= 0x7fffffff) {
             bool ok = true;
-            int64_t items = 0;
             for (int j = 0; j < n_enc; ++j) {
                 ok = ok && enc[j].n_tokens > 0 && vq_encode_fast_ok(enc[j].K, enc[j].dg);
                 const int64_t n_tb = ceil_div(enc[j].n_tokens, kAttThreads / 2);
                 ok = ok && n_tb * enc[j].G <= 0x3fffffff && enc[j].dg == enc[0].dg;
                 items += n_tb * enc[j].G;
             }
-            if (ok && items > 0) {
-                const int tb = vq_encode_blocks(enc[0], kAttCus / n_enc);
-                items = 0;
-                for (int j = 0; j < n_enc; ++j) {
-                    ae.job[j] = enc[j];
-                    ae.job[j].tb = tb;
-                    ae.job[j].n_tb = (int)ceil_div(enc[j].n_tokens, kAttThreads / 2 * tb);
-                    items += (int64_t)ae.job[j].n_tb * enc[j].G;
-                }
-                ae.n_jobs = n_enc;
-                ae.n_attn_wgs = (int)total;
-                ae.n_enc_wgs = (int)std::min<int64_t>(items, kAttCus);
-                *enc_fused = true;
+            if (!ok) items = 0;
+        }
+        // 64-wide heads otherwise: when 128-row query blocks would leave half of the compute units without a
+        // workgroup, 64-row blocks whose tiles are dealt to four wavefronts per query group (half the iterations each)
+        const bool few = attention_short(p, head_dim, items, items > 0 ? encode_item_us(enc[0]) : 0.0);
+        const bool four = !few && head_dim == 64 && total <= kAttCus / 2;
+        if (few || four) total = (int64_t)ceil_div(p.Tq, few ? 32 : kAttQ / 2) * p.Hq;
+        if (items > 0) {
+            const int tb = vq_encode_blocks(enc[0], kAttCus / n_enc);
+            items = 0;
+            for (int j = 0; j < n_enc; ++j) {
+                ae.job[j] = enc[j];
+                ae.job[j].tb = tb;
+                ae.job[j].n_tb = (int)ceil_div(enc[j].n_tokens, kAttThreads / 2 * tb);
+                items += (int64_t)ae.job[j].n_tb * enc[j].G;
             }
+            ae.n_jobs = n_enc;
+            ae.n_attn_wgs = (int)total;
+            ae.n_enc_wgs = (int)std::min<int64_t>(items, kAttCus);
+            *enc_fused = true;
         }
         if (plan_only) return ASTRA_OK;
-        // 64-wide heads: a workgroup per 32 query rows where those make a single round of the units.  12 heads, 256 + 768 / 256 + 8000 rows: whole layer
-        // 27.4 / 79.0 us on the kernel above, 23.7 / 64.7 this way; 700 + 700 rows (264 workgroups) 38.0 and 37.4, 700 + 3000 50.3 and 56.6.
-        if (head_dim == 64 && vt && ceil_div(p.Tq, 32) * p.Hq <= kAttCus) return launch_attention_short(p, s);
+        if (few) return launch_attention_short(p, head_dim, ae, s);
         if (ae.n_enc_wgs > 0) {
             if (lost) attn_bf16_kernel<128, true, true, 2, true><<<(int)total + ae.n_enc_wgs, kAttThreads, 0, s>>>(p, ae);
             else attn_bf16_kernel<128, true, false, 2, true><<<(int)total + ae.n_enc_wgs, kAttThreads, 0, s>>>(p, ae);

@@ -1,5 +1,5 @@
 // Mixed-precision attention of one device (paper Sec. 3.2, Eq. 1) for launches that a few large workgroups cannot fill: short sequences, few heads.
-#include "common.h"
+#include "attention_encode.h"
 
 #include <type_traits>
 
@@ -10,36 +10,49 @@ namespace astra {
 // S^T = K . Q^T with the keys on the M side of the 32x32x16 MFMA, a lane's scores all of one query, probabilities already in the layout of the B operand
 // of O^T += V^T . P^T, a reference maximum that is raised lazily.
 //
-// A workgroup of eight wavefronts owns 32 query rows of one head; wavefront w walks the tiles w, w + 8, ... of 64 keys (visible non-local ones first)
-// for itself: direct transfers bring its keys and values into LDS of its own (rows of 128 bytes, XOR-swizzled pieces), so that the loop has no barrier and
-// no other wavefront to wait for.  A tile's fragments are read into registers whole, and its place takes the wavefront's next tile at once.  The
+// A workgroup of eight wavefronts owns 32 query rows of one head; wavefront w walks the tiles w, w + 8, ... of 4096 / DH keys (64 or 32; visible
+// non-local ones first) for itself: direct transfers bring its keys and values into LDS of its own (8 KiB each, XOR-swizzled pieces), so that the loop has
+// no barrier and no other wavefront to wait for.  A tile's fragments are read into registers whole, and its place takes the wavefront's next tile at once.  The
 // eight (max, sum, O) triples meet in LDS, and every thread adds four of the workgroup's outputs in wavefront order.
 //
-// What bounds it: a launch, a memory latency at either end, and a unit's intake (256 bytes a key for every 32 queries at 64 B/clk; with the fragments loaded
-// straight into registers, 32 rows a load, it took several times that).
+// What bounds it: a launch, a memory latency at either end, and what the second-level caches give all units together (4 DH bytes a key for every 32
+// queries: 32 heads of 128, 256 + 4096 rows are 570 MB in about 50 us; with the fragments loaded straight into registers, 32 rows a load, a short launch
+// took several times as long).
 // 12 heads, causal, whole layer on attn_bf16_kernel (64 query rows per workgroup, tiles shared by two wavefronts) and here: 17 rows 16.3 -> 13.8 us,
-// 256 + 768 rows 26.0 -> 23.1, 512 + 1024 35.2 -> 31.4.
+// 256 + 768 rows 26.0 -> 23.1, 512 + 1024 35.2 -> 31.4.  32 heads of 128 (128 query rows per workgroup before): 17 rows 27.4 -> 24.2, 128 + 384
+// 53.0 -> 47.2, 256 + 4096 149 -> 130.
+//
+// ENC: VQ encodes ride in the launch (AttnEncode).
 // Longer walks and more rows are better off sharing tiles through LDS (launch_attention).
 // ------------------------------------------------------------------------------------------------
 constexpr int kShortThreads = 512;
 constexpr int kShortWaves = kShortThreads / kWave;
 constexpr float kLazyShort = 8.f;     // base-2 units
 
-template <bool LOST>
-__global__ __launch_bounds__(kShortThreads) void attn_short_kernel(const AttnParams p) {
-    constexpr int DH = 64, TK = 64, NMB = TK / 32, NKS = DH / 16, NDB = DH / 32, NPV = TK / 16, LDP = DH + 4;
-    constexpr int NT = 8;                      // transfers of a tile of keys or of values: eight rows each
-    __shared__ __align__(16) u32x4 ring[kShortWaves][2][64 * 8];          // keys [64 keys][64 values], values [64 values][64 keys]
+template <int DH, bool LOST, bool ENC>
+__global__ __launch_bounds__(kShortThreads) void attn_short_kernel(const AttnParams p, const AttnEncode e) {
+    constexpr int TK = 4096 / DH, NMB = TK / 32, NKS = DH / 16, NDB = DH / 32, NPV = TK / 16, LDP = DH + 4;
+    constexpr int KP = DH / 8, VP = TK / 8;    // 16-byte pieces of a row of keys, of values
+    constexpr int NT = 8, KR = 64 / KP, VR = 64 / VP;      // transfers of a tile of keys or of values, and their rows
+    constexpr int kTile = TK * KP;             // pieces of a tile: keys [TK keys][DH values], values [DH values][TK keys]
+    constexpr int kPart = kShortWaves * 32 * LDP / 4;      // the partial outputs, once every wavefront is done with its tiles
+    __shared__ __align__(16) u32x4 ring[kPart > kShortWaves * 2 * kTile ? kPart : kShortWaves * 2 * kTile];
     __shared__ float part_m[kShortWaves][32], part_l[kShortWaves][32];
-    auto part = reinterpret_cast<float(*)[32][LDP]>(&ring[0][0][0]);      // the partial outputs, once every wavefront is done with its tiles
-    static_assert(sizeof(ring) >= sizeof(float) * kShortWaves * 32 * LDP, "the partial outputs fit the tiles");
+    auto part = reinterpret_cast<float(*)[32][LDP]>(&ring[0]);
+    if constexpr (ENC) {
+        static_assert(sizeof(ring) >= sizeof(u32x4) * kEncBufs * (kEncCbSlots + kEncCnSlots), "the encode's codebook tiles and norms fit");
+        if ((int)blockIdx.x >= e.n_attn_wgs) {
+            attn_encode_wgs<kShortThreads>(e, (int)blockIdx.x - e.n_attn_wgs, ring, reinterpret_cast<f32x4*>(ring + kEncBufs * kEncCbSlots));
+            return;
+        }
+    }
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int i32 = lane & 31, h = lane >> 5;
     const int Tq = p.Tq, n_qb = (Tq + 31) / 32;
     // contiguous runs of heads per XCD, so that a KV head's keys and values stay in one L2; later (longer) query blocks first
-    const int total = gridDim.x, xq = total / 8, xr = total % 8, xcd = blockIdx.x % 8, slot = blockIdx.x / 8;
+    const int total = ENC ? e.n_attn_wgs : (int)gridDim.x, xq = total / 8, xr = total % 8, xcd = blockIdx.x % 8, slot = blockIdx.x / 8;
     const int vid = xcd < xr ? xcd * (xq + 1) + slot : xr * (xq + 1) + (xcd - xr) * xq + slot;
     const int head = vid / n_qb, q0 = (n_qb - 1 - vid % n_qb) * 32;
     const int hk = head / (p.Hq / p.Hkv);
@@ -68,27 +81,38 @@ __global__ __launch_bounds__(kShortThreads) void attn_short_kernel(const AttnPar
         tl.count = tl.is_loc ? Tq : p.Tn_vis;
         return tl;
     };
-    // transfer j of a tile fills rows 8j + lane / 8; slot lane % 8 of row r holds piece (lane % 8) ^ (r / 2) % 8, which depends on j's parity only.
-    // Rows beyond the source's last one are copies of it; their scores are dropped.
-    const int r8 = lane >> 3;
-    const uint32_t piece[2] = {16u * ((lane & 7) ^ (r8 >> 1)), 16u * ((lane & 7) ^ (4 + (r8 >> 1)))};
-    const uint32_t lds_k = lds_byte_addr(&ring[wave][0][0]), lds_v = lds_byte_addr(&ring[wave][1][0]);
+    // Slot c of row r of a tile holds piece c ^ swizzle(r), by which the rows a fragment read takes at a time lie in different banks.
+    // Transfer j of a tile fills rows KR j + lane / KP of keys, VR j + lane / VP of values.  Rows beyond the source's last one are copies of it;
+    // their scores are dropped.
+    auto swz_keys = [](int r) __attribute__((always_inline)) { return DH == 128 ? r & 15 : (r >> 1) & 7; };
+    auto swz_vals = [](int r) __attribute__((always_inline)) { return DH == 128 ? (r >> 2) & 3 : (r >> 1) & 7; };
+    const int rk = lane / KP, rv = lane / VP;
+    u32x4* const tiles = &ring[wave * 2 * kTile];
+    const uint32_t lds_k = lds_byte_addr(tiles), lds_v = lds_byte_addr(tiles + kTile);
     auto send_k = [&](const Tile& tl) __attribute__((always_inline)) {
         const char* __restrict__ base = (const char*)(tl.is_loc ? p.k_loc : p.k_hat) + ((int64_t)tl.row0 * kv_ld_b + (int64_t)hk * (DH * 2));
         const uint32_t lim = (uint32_t)min(tl.count - 1 - tl.row0, TK - 1) * kv_ld_b;
 #pragma unroll
-        for (int j = 0; j < NT; ++j)
-            dma_global_to_lds_16(base, min((uint32_t)r8 * kv_ld_b + (uint32_t)(8 * j) * kv_ld_b, lim) + piece[j & 1], lds_k + 1024u * j);
+        for (int j = 0; j < NT; ++j) {
+            const uint32_t piece = 16u * ((lane % KP) ^ swz_keys(KR * j + rk));
+            dma_global_to_lds_16(base, min((uint32_t)rk * kv_ld_b + (uint32_t)(KR * j) * kv_ld_b, lim) + piece, lds_k + 1024u * j);
+        }
     };
     auto send_v = [&](const Tile& tl) __attribute__((always_inline)) {
         const uint32_t v_ld_b = (uint32_t)(tl.is_loc ? p.ldv_loc : p.ldv_hat) * 2u;
         const char* __restrict__ base = (const char*)(tl.is_loc ? p.v_loc : p.v_hat) + ((int64_t)hk * DH * v_ld_b + (int64_t)tl.row0 * 2);
 #pragma unroll
-        for (int j = 0; j < NT; ++j) dma_global_to_lds_16(base, (uint32_t)r8 * v_ld_b + (uint32_t)(8 * j) * v_ld_b + piece[j & 1], lds_v + 1024u * j);
+        for (int j = 0; j < NT; ++j) {
+            const uint32_t piece = 16u * ((lane % VP) ^ swz_vals(VR * j + rv));
+            dma_global_to_lds_16(base, (uint32_t)rv * v_ld_b + (uint32_t)(VR * j) * v_ld_b + piece, lds_v + 1024u * j);
+        }
     };
     // fragment (row block, step) of a tile in LDS: lane holds row 32 block + lane % 32, piece 2 step + lane / 32
-    auto frag = [&](int kv, int block, int step) __attribute__((always_inline)) {
-        return __builtin_bit_cast(bf16x8, ring[wave][kv][(32 * block + i32) * 8 + ((2 * step + h) ^ ((i32 >> 1) & 7))]);
+    auto frag_k = [&](int block, int step) __attribute__((always_inline)) {
+        return __builtin_bit_cast(bf16x8, tiles[(32 * block + i32) * KP + ((2 * step + h) ^ swz_keys(i32))]);
+    };
+    auto frag_v = [&](int block, int step) __attribute__((always_inline)) {
+        return __builtin_bit_cast(bf16x8, tiles[kTile + (32 * block + i32) * VP + ((2 * step + h) ^ swz_vals(i32))]);
     };
     auto reads_done = [&]() __attribute__((always_inline)) {
         __builtin_amdgcn_s_waitcnt(0xC07F);      // the fragments are in registers (lgkmcnt 0): their place is free
@@ -115,7 +139,7 @@ __global__ __launch_bounds__(kShortThreads) void attn_short_kernel(const AttnPar
 #pragma unroll
         for (int ks = 0; ks < NKS; ++ks)
 #pragma unroll
-            for (int mb = 0; mb < NMB; ++mb) kf[mb][ks] = frag(0, mb, ks);
+            for (int mb = 0; mb < NMB; ++mb) kf[mb][ks] = frag_k(mb, ks);
         reads_done();
         if (more) send_k(next);
         __builtin_amdgcn_sched_barrier(0);
@@ -131,8 +155,8 @@ __global__ __launch_bounds__(kShortThreads) void attn_short_kernel(const AttnPar
 
         const bool diag = tl.is_loc && p.causal && (tl.row0 + TK - 1 > q0);          // some pair of this tile is hidden
         unsigned long long lost = 0ull;                                              // non-local keys whose codes never arrived
-        if (LOST && !tl.is_loc) {
-            lost = ~load_uniform_u64(p.valid_bits + (tl.row0 >> 6));
+        if (LOST && !tl.is_loc) {                                                    // bit = key of the tile
+            lost = ~load_uniform_u64(p.valid_bits + (tl.row0 >> 6)) >> (tl.row0 & 63);
         }
         if (diag || tl.row0 + TK > tl.count || lost != 0ull) {
             const uint32_t lost_w[2] = {(uint32_t)(lost >> (4 * h)), (uint32_t)(lost >> (32 + 4 * h))};
@@ -180,7 +204,7 @@ __global__ __launch_bounds__(kShortThreads) void attn_short_kernel(const AttnPar
 #pragma unroll
         for (int u = 0; u < NPV; ++u)
 #pragma unroll
-            for (int db = 0; db < NDB; ++db) vf[db][u] = frag(1, db, u);
+            for (int db = 0; db < NDB; ++db) vf[db][u] = frag_v(db, u);
         reads_done();
         if (more) send_v(next);
         __builtin_amdgcn_sched_barrier(0);
@@ -206,8 +230,8 @@ __global__ __launch_bounds__(kShortThreads) void attn_short_kernel(const AttnPar
     __syncthreads();
     constexpr int PER_ROW = DH / 4;
 #pragma unroll
-    for (int e = tid; e < 32 * PER_ROW; e += kShortThreads) {
-        const int r = e / PER_ROW, d = e % PER_ROW * 4;
+    for (int i = tid; i < 32 * PER_ROW; i += kShortThreads) {
+        const int r = i / PER_ROW, d = i % PER_ROW * 4;
         float m = -INFINITY;
 #pragma unroll
         for (int w = 0; w < kShortWaves; ++w) m = fmaxf(m, part_m[w][r]);
@@ -231,10 +255,19 @@ __global__ __launch_bounds__(kShortThreads) void attn_short_kernel(const AttnPar
     }
 }
 
-int launch_attention_short(const AttnParams& p, hipStream_t s) {
-    const int grid = (int)(ceil_div(p.Tq, 32) * p.Hq);
-    if (p.valid_bits) attn_short_kernel<true><<<grid, kShortThreads, 0, s>>>(p);
-    else attn_short_kernel<false><<<grid, kShortThreads, 0, s>>>(p);
+int launch_attention_short(const AttnParams& p, int head_dim, const AttnEncode& e, hipStream_t s) {
+    const int grid = (int)(ceil_div(p.Tq, 32) * p.Hq) + e.n_enc_wgs;
+    const bool lost = p.valid_bits != nullptr;
+    if (head_dim == 64) {
+        if (lost) attn_short_kernel<64, true, false><<<grid, kShortThreads, 0, s>>>(p, e);
+        else attn_short_kernel<64, false, false><<<grid, kShortThreads, 0, s>>>(p, e);
+    } else if (e.n_enc_wgs > 0) {
+        if (lost) attn_short_kernel<128, true, true><<<grid, kShortThreads, 0, s>>>(p, e);
+        else attn_short_kernel<128, false, true><<<grid, kShortThreads, 0, s>>>(p, e);
+    } else {
+        if (lost) attn_short_kernel<128, true, false><<<grid, kShortThreads, 0, s>>>(p, e);
+        else attn_short_kernel<128, false, false><<<grid, kShortThreads, 0, s>>>(p, e);
+    }
     return launch_status();
 }
 

@@ -227,7 +227,6 @@ struct AttnParams {
 // attention_encode_us: about what one encode adds to the launch (us), negative if the launch would not take it
 int launch_attention(int dtype, const AttnParams& p, int head_dim, hipStream_t s, bool plan_only = false, const EncodeJob* enc = nullptr,
                      int n_enc = 0, bool* enc_fused = nullptr);
-int launch_attention_short(const AttnParams& p, hipStream_t s);      // 64-wide heads, bf16, V transposed
 double attention_encode_us(const AttnParams& p, int head_dim, const EncodeJob& e);
 int launch_mfma_probe(float* out, int n_blocks, int iters, hipStream_t s);
 

@@ -303,9 +303,28 @@ def test_gathered_rows_over_few_contraction_tiles(d, groups, words, n_local, n_n
 ])
 def test_short_sequences_of_64_wide_heads(n_local, n_nonlocal, hq, hkv, n_cls, causal, lost):
     """Attention on blocks of 32 query rows whose wavefronts walk the tiles for themselves: fewer tiles than wavefronts, ragged ends, masks."""
+    _short_sequence(64, n_local, n_nonlocal, hq, hkv, n_cls, causal, lost)
+
+
+@pytest.mark.parametrize("n_local,n_nonlocal,hq,hkv,n_cls,causal,lost", [
+    (1, 0, 2, 1, 0, True, None),
+    (31, 225, 4, 2, 1, False, None),         # eight tiles of 32 keys of peers, the last of one; a class row makes whole blocks
+    (33, 257, 4, 4, 0, True, None),          # nine, and a second block of one row
+    (100, 700, 4, 4, 0, True, "some"),
+    (100, 700, 4, 4, 1, False, "tiles"),     # both halves of a word of arrivals, and a half alone
+    (40, 200, 4, 1, 0, True, "all"),
+    (256, 200, 32, 8, 0, True, None),        # 256 blocks: a single round
+    (257, 200, 32, 8, 0, True, None),        # the other kernel
+])
+def test_short_sequences_of_128_wide_heads(n_local, n_nonlocal, hq, hkv, n_cls, causal, lost):
+    """The same on tiles of 32 keys."""
+    _short_sequence(128, n_local, n_nonlocal, hq, hkv, n_cls, causal, lost)
+
+
+def _short_sequence(dh, n_local, n_nonlocal, hq, hkv, n_cls, causal, lost):
     from gpu_util import LayerOnGpu, compare_codes
-    d = hq * 64
-    cfg = wl.LayerConfig("short", "bf16", d, hq, hkv, 64, n_local + n_nonlocal, 1, 16, 256, n_cls=n_cls, causal=causal, seed=71)
+    d = 64 * hq
+    cfg = wl.LayerConfig("short", "bf16", d, hq, hkv, dh, n_local + n_nonlocal, 1, 16, 256, n_cls=n_cls, causal=causal, seed=71)
     data = wl.generate(cfg)
     rows = data["x"]
     cls_rows = rows[-n_cls:] if n_cls else rows[:0]
@@ -319,6 +338,8 @@ def test_short_sequences_of_64_wide_heads(n_local, n_nonlocal, hq, hkv, n_cls, c
             valid = np.random.default_rng(5).random(n_nonlocal) >= 0.3
         elif lost == "tiles":
             valid[:64] = valid[128:192] = False
+            if dh == 128:
+                valid[288:320] = valid[384:416] = False
         else:
             valid[:] = False
     n_before = n_nonlocal if causal else 0
