@@ -42,6 +42,7 @@ __global__ __launch_bounds__(kWaveThreads) void gemm_wave_kernel(const GemmBatch
     using S = WaveShape<MT, NT, ST>;
     constexpr int BM = S::BM, BN = S::BN, R = S::R, LDN = S::LDN, MP = S::MP;
     constexpr int DA = BM / 8, DB = BN / 8, DM = DA + DB;                     // transfers per stage: A rows, B rows
+    constexpr bool HALVES = MT == 4 && NT == 4 && ST == 1;
     extern __shared__ __align__(16) char wv_lds[];
 
     int vt;
@@ -113,26 +114,30 @@ __global__ __launch_bounds__(kWaveThreads) void gemm_wave_kernel(const GemmBatch
         const uint32_t dst = ring_a + (uint32_t)(slot * S::kStage);
 #pragma unroll
         for (int j = DA; j < DM; ++j) dma_global_to_lds_16(b_base, off[j], dst + (uint32_t)(j * 1024));
-        b_base += 128 * kWaveWaves;
+        if (!HALVES) b_base += 128 * kWaveWaves;
+    };
+    // gathered rows: transfers from .. to - 1 of the slice at contraction index k0
+    auto gather_a = [&](int k0, int from, int to, uint32_t dst) __attribute__((always_inline)) {
+        uint32_t g_[2], at[2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const uint32_t k = (uint32_t)(k0 + 8 * piece[q]);
+            g_[q] = __umulhi(k, magic);
+            at[q] = g_[q] * (uint32_t)Kc;
+            at[q] = at[q] * (uint32_t)dg + (k - g_[q] * (uint32_t)dg);
+        }
+#pragma unroll
+        for (int j = from; j < to; ++j) {
+            const uint32_t x = (uint32_t)min(8 * j + r8, n_codes - 1) * (uint32_t)G + g_[j & 1];
+            const uint32_t code = code16 ? (uint32_t)reinterpret_cast<const uint16_t*>(codes_lds)[x] : (uint32_t)reinterpret_cast<const uint8_t*>(codes_lds)[x];
+            const uint32_t go = (at[j & 1] + min(code, (uint32_t)Kc - 1u) * (uint32_t)dg) * 2u;
+            dma_global_to_lds_16(P.codebook, go, dst + (uint32_t)(j * 1024));
+        }
     };
     auto issue_a = [&](int slot) __attribute__((always_inline)) {
         const uint32_t dst = ring_a + (uint32_t)(slot * S::kStage);
         if (GATHER && gather) {
-            uint32_t g_[2], at[2];
-#pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                const uint32_t k = (uint32_t)(k_next + 8 * piece[q]);
-                g_[q] = __umulhi(k, magic);
-                at[q] = g_[q] * (uint32_t)Kc;
-                at[q] = at[q] * (uint32_t)dg + (k - g_[q] * (uint32_t)dg);
-            }
-#pragma unroll
-            for (int j = 0; j < DA; ++j) {
-                const uint32_t x = (uint32_t)min(8 * j + r8, n_codes - 1) * (uint32_t)G + g_[j & 1];
-                const uint32_t code = code16 ? (uint32_t)reinterpret_cast<const uint16_t*>(codes_lds)[x] : (uint32_t)reinterpret_cast<const uint8_t*>(codes_lds)[x];
-                const uint32_t go = (at[j & 1] + min(code, (uint32_t)Kc - 1u) * (uint32_t)dg) * 2u;
-                dma_global_to_lds_16(P.codebook, go, dst + (uint32_t)(j * 1024));
-            }
+            gather_a(k_next, 0, DA, dst);
         } else {
 #pragma unroll
             for (int j = 0; j < DA; ++j) dma_global_to_lds_16(a_base, off[j], dst + (uint32_t)(j * 1024));
@@ -164,6 +169,97 @@ __global__ __launch_bounds__(kWaveThreads) void gemm_wave_kernel(const GemmBatch
         for (int b = 0; b < NT; ++b)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.f;
+    if constexpr (HALVES) {
+        // ---- the slice in halves: rows A0, A1 and columns B0, B1 of 64 each, multiplied as A0 B0, A0 B1, A1 B1, A1 B0.  While one product runs, the half that
+        // the next one needs is read into the registers of the half whose last product is over (B1 and the next slice's B0 take each other's), and
+        // the same half of the next slice is sent to its place as soon as it is read: three of four halves are always on their way, where a
+        // slice read whole left none of them while it was waited for and read.
+        bf16x8 ha[2][4][MT / 2], hb[2][4][NT / 2];
+        const u32x4* rows = reinterpret_cast<const u32x4*>(ring);
+        auto read_a = [&](int half, int ks, int a) __attribute__((always_inline)) {
+            ha[half][ks][a] = __builtin_bit_cast(bf16x8, rows[(16 * MT * half + 32 * a + i32) * 8 + ((2 * ks + h) ^ swz(i32))]);
+        };
+        auto read_b = [&](int half, int slot, int ks, int b) __attribute__((always_inline)) {
+            hb[slot][ks][b] = __builtin_bit_cast(bf16x8, rows[(BM + 16 * NT * half + 32 * b + i32) * 8 + ((2 * ks + h) ^ swz(i32))]);
+        };
+        constexpr int DH = 2 * MT;                           // transfers of a half
+        auto send_a = [&](int half, int j, int slice) __attribute__((always_inline)) {
+            if (GATHER && gather) gather_a((slice * kWaveWaves + wave) * kBK, half * DH + j, half * DH + j + 1, ring_a);
+            else dma_global_to_lds_16(a_base + (int64_t)slice * (128 * kWaveWaves), off[half * DH + j], ring_a + (uint32_t)((half * DH + j) * 1024));
+        };
+        auto send_b = [&](int half, int j, int slice) __attribute__((always_inline)) {
+            dma_global_to_lds_16(b_base + (int64_t)slice * (128 * kWaveWaves), off[DA + half * DH + j], ring_a + (uint32_t)((DA + half * DH + j) * 1024));
+        };
+        auto reads_done = [&]() __attribute__((always_inline)) {
+            __builtin_amdgcn_s_waitcnt(0xC07F);              // lgkmcnt 0: the half is in registers, its place is free
+            asm volatile("" ::: "memory");
+        };
+        // product Q of slice i, whose B0 is in register slot S0; FULL: slice i + 2 exists
+        auto product = [&](auto q_tag, auto s_tag, auto full_tag, int i) __attribute__((always_inline)) {
+            constexpr int Q = decltype(q_tag)::value, S0 = decltype(s_tag)::value, S1 = S0 ^ 1;
+            constexpr bool FULL = decltype(full_tag)::value;
+            constexpr int HA = Q >= 2, HB = Q == 1 || Q == 2, SB = HB ? S1 : S0;
+            const bool reads = FULL || Q < 2 || i + 1 < n, sends = FULL || i + (Q < 2 ? 1 : 2) < n;
+            if (FULL) wait_vmem<3 * DH>();                   // the half read here has landed: the three sent after it may be outstanding
+            else if (reads) wait_vmem_all();
+            constexpr int NM = 4 * (MT / 2) * (NT / 2);
+#pragma unroll
+            for (int m = 0; m < NM; ++m) {
+                const int ks = m / (NM / 4), a = m / (NT / 2) % (MT / 2), b = m % (NT / 2);
+                acc[HA * (MT / 2) + a][HB * (NT / 2) + b] = mfma_32x32x16(hb[SB][ks][b], ha[HA][ks][a], acc[HA * (MT / 2) + a][HB * (NT / 2) + b]);
+                if (reads && m < 8) {
+                    if (Q == 0) read_b(1, S1, m / 2, m % 2);
+                    else if (Q == 1) read_a(1, m / 2, m % 2);
+                    else if (Q == 2) read_a(0, m / 2, m % 2);
+                    else read_b(0, S1, m / 2, m % 2);
+                }
+                if (sends && m == 9) reads_done();
+                if (sends && m >= 10)
+#pragma unroll
+                    for (int j = (m - 10) * DH / (NM - 10); j < (m - 9) * DH / (NM - 10); ++j) {
+                        if (Q == 0) send_b(1, j, i + 1);
+                        else if (Q == 1) send_a(1, j, i + 1);
+                        else if (Q == 2) send_a(0, j, i + 2);
+                        else send_b(0, j, i + 2);
+                    }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        auto slice = [&](auto s_tag, auto full_tag, int i) __attribute__((always_inline)) {
+            product(std::integral_constant<int, 0>{}, s_tag, full_tag, i);
+            product(std::integral_constant<int, 1>{}, s_tag, full_tag, i);
+            product(std::integral_constant<int, 2>{}, s_tag, full_tag, i);
+            product(std::integral_constant<int, 3>{}, s_tag, full_tag, i);
+        };
+        if (n > 0) {
+#pragma unroll
+            for (int j = 0; j < 2 * DH; ++j) send_a(j / DH, j % DH, 0);       // behind the slice's B rows
+            wait_vmem<DH>();
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    read_a(0, ks, t);
+                    read_b(0, 0, ks, t);
+                }
+            reads_done();
+            if (n > 1) {
+#pragma unroll
+                for (int j = 0; j < DH; ++j) send_a(0, j, 1);
+#pragma unroll
+                for (int j = 0; j < DH; ++j) send_b(0, j, 1);
+            }
+            int i = 0;
+            for (; i + 3 < n; i += 2) {
+                slice(std::integral_constant<int, 0>{}, std::true_type{}, i);
+                slice(std::integral_constant<int, 1>{}, std::true_type{}, i + 1);
+            }
+            for (; i < n; i += 2) {
+                slice(std::integral_constant<int, 0>{}, std::false_type{}, i);
+                if (i + 1 < n) slice(std::integral_constant<int, 1>{}, std::false_type{}, i + 1);
+            }
+        }
+    } else {
     bf16x8 fa[4][MT], fb[4][NT];
     auto read = [&](int slot) __attribute__((always_inline)) {
         const u32x4* s = reinterpret_cast<const u32x4*>(ring + slot * S::kStage);
@@ -208,6 +304,8 @@ __global__ __launch_bounds__(kWaveThreads) void gemm_wave_kernel(const GemmBatch
             multiply();
             slot = slot + 1 == ST ? 0 : slot + 1;
         }
+
+    }
 
     // ---- the four partial tiles, 32 MP rows at a time, and the store
     const uint16_t* __restrict__ bias = (const uint16_t*)P.bias;
