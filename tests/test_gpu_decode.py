@@ -194,3 +194,17 @@ def test_an_infinite_value(hq, hkv, dh, groups, K, n_local, n_nonlocal, where):
     assert bool((out[0, :, 3] == want).all()), out[0, :, 3]
     out[0, :, 3] = 0.0
     assert bool(torch.isfinite(out).all())
+
+
+@pytest.mark.parametrize("dh,groups,n_local,n_nonlocal", [
+    (6, 2, 300, 200),          # three pairs of channels: one workgroup per head, pairs that fill no power of two
+    (40, 4, 1000, 700),        # five pairs for each of four workgroups
+    (250, 10, 900, 130),       # 125 pairs in one
+    (64, 4, 8064, 0),          # 63, 64 and 65 partial results of 128 tokens: up to a lane each, and one more than that
+    (64, 4, 8065, 0),
+    (64, 4, 4096, 4097),
+])
+def test_merge_of_the_partial_results(dh, groups, n_local, n_nonlocal):
+    """The partial results of a head: numbers of them, and head widths that four workgroups do not share evenly."""
+    cfg = wl.LayerConfig("merge", "f32", 64, 4, 2, dh, 1024, 4, groups, 16, causal=True, seed=37)
+    run_case(cfg, n_local, n_nonlocal, seed=38, n_groups_kv=groups, real_codes=False)
