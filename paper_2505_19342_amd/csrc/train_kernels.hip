@@ -9,6 +9,7 @@
 namespace astra {
 
 constexpr int kTrThreads = 256;
+constexpr int kTrCus = 256;         // compute units the launch shapes are chosen for
 
 template <typename T>
 __device__ __forceinline__ float tr_ld(const T* p);
@@ -135,9 +136,12 @@ __global__ __launch_bounds__(kTrThreads) void sort_place_kernel(const void* __re
 // ballots against counters of its own (no barrier and no atomics: at most one lane per code writes, in program order), one scan over
 // codes and wavefronts turns the counters into first write positions, and the sorted sequence is put together in LDS and
 // leaves as whole lines.  The codes are transposed first: read with their stride they cost one line per token through one
-// compute unit (36.7 us instead of 8.6 + 19.0).  Bound by the vector ALU of that unit (the ballots).  In the three launches
+// compute unit (36.7 us instead of 4.9 + 19.4).  Bound by the vector ALU of that unit (the ballots).  In the three launches
 // above the strided read is repeated, a pass of 256 tokens is four serial turns of its wavefronts, and perm and scode leave as single
-// scattered words.  16384 x 64 codes, K = 1024: 5.4 + 10.6 + 23.0 us there, 8.6 + 19.0 us here.
+// scattered words.  16384 x 64 codes, K = 1024: 5.4 + 10.6 + 23.0 us there, 4.9 + 13.4 us here.
+// PARTS: few groups leave units idle, so a group's codes are dealt in ranges to gridDim.y workgroups.  Every one reads all of the group's codes, its
+// wavefronts keep their tokens whose codes are in the range (in order, by ballots again: one instead of eleven), and ranks, counters and the part of
+// the sorted sequence are those of the range only.  The same 64 groups: 19.4 us on 64 units, 13.4 on 256.
 constexpr int kSortThreads = 1024, kSortWaves = kSortThreads / kWave, kSortSteps = 16;
 constexpr int kSortMaxTokens = kSortThreads * kSortSteps;         // sorted tokens and codes: 4 bytes each, 64 KB
 constexpr int kSortMaxCodes = kSortThreads;                       // a code per thread in the scan; counters 64 KB
@@ -147,42 +151,79 @@ __device__ __forceinline__ void sort_lds_order() {                // LDS accesse
     __builtin_amdgcn_wave_barrier();
 }
 
-// out[2 T g + t] = code of (t, g): the codes of a group as one run, in the first half of the group's place in perm.
-// 64 tokens x 64 groups per workgroup.
+// out[stride g + t] = code of (t, g): the codes of a group as one run.
+// 64 tokens x 64 groups per workgroup.  Bound by memory latency: 16384 x 64 codes 8.8 us with a guard, and so a wait, around every load; 4.9 now.
 __global__ __launch_bounds__(kTrThreads) void code_transpose_kernel(const void* __restrict__ codes, int code16, int T, int G, int K,
-                                                                    uint16_t* __restrict__ out) {
+                                                                    int stride, uint16_t* __restrict__ out) {
     __shared__ uint16_t tile[64][66];
     const int t0 = blockIdx.x * 64, g0 = blockIdx.y * 64, col = threadIdx.x & 63, row = threadIdx.x >> 6;
+    constexpr int N = 64 * 64 / kTrThreads;
+    uint16_t v[N];               // requested all at once; beyond the last token or group its code again, which nobody stores
 #pragma unroll
-    for (int i = row; i < 64; i += kTrThreads / 64)
-        if (t0 + i < T && g0 + col < G) tile[col][i] = (uint16_t)tr_code(codes, code16, (int64_t)(t0 + i) * G + g0 + col, K);
+    for (int i = 0; i < N; ++i) v[i] = (uint16_t)tr_code(codes, code16, (int64_t)min(t0 + row + i * (kTrThreads / 64), T - 1) * G + min(g0 + col, G - 1), K);
+#pragma unroll
+    for (int i = 0; i < N; ++i) tile[col][row + i * (kTrThreads / 64)] = v[i];
     __syncthreads();
 #pragma unroll
     for (int i = row; i < 64; i += kTrThreads / 64)
-        if (t0 + col < T && g0 + i < G) out[(int64_t)(g0 + i) * 2 * T + t0 + col] = tile[i][col];
+        if (t0 + col < T && g0 + i < G) out[(int64_t)(g0 + i) * stride + t0 + col] = tile[i][col];
 }
 
-__global__ __launch_bounds__(kSortThreads) void sort_group_kernel(int T, int K, int steps, int32_t* __restrict__ counts, int32_t* __restrict__ offs,
-                                                                  int32_t* perm, uint16_t* __restrict__ scode) {
+// tcodes: the transposed codes, stride apart per group; with one workgroup per group they may lie in its place in perm (read whole before it is written)
+template <bool PARTS>
+__global__ __launch_bounds__(kSortThreads) void sort_group_kernel(const uint16_t* tcodes, int stride, int T, int K, int steps,
+                                                                  int32_t* __restrict__ counts, int32_t* __restrict__ offs, int32_t* perm,
+                                                                  uint16_t* __restrict__ scode) {
     extern __shared__ int lds_i[];
-    __shared__ int wave_sum[kSortWaves];
-    const int g = blockIdx.x, tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
-    int* mine = lds_i + wave * K;                                                  // [kSortWaves][K] counters
-    uint16_t* l_perm = reinterpret_cast<uint16_t*>(lds_i + kSortWaves * K);        // [T] token of a sorted position
+    __shared__ int wave_sum[kSortWaves], wave_below[kSortWaves];
+    const int g = blockIdx.x, tid = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int k_lo = PARTS ? (int)((int64_t)K * blockIdx.y / gridDim.y) : 0, k_hi = PARTS ? (int)((int64_t)K * (blockIdx.y + 1) / gridDim.y) : K;
+    const int Kp = k_hi - k_lo;                                                    // codes of this workgroup
+    int* mine = lds_i + wave * Kp;                                                 // [kSortWaves][Kp] counters
+    uint16_t* l_perm = reinterpret_cast<uint16_t*>(lds_i + kSortWaves * Kp);       // [T] token of a sorted position
     uint16_t* l_code = l_perm + T;                                                 // [T] its code
-    const uint16_t* mine_codes = reinterpret_cast<const uint16_t*>(perm + (int64_t)g * T);   // read whole before perm is written
+    const uint16_t* mine_codes = tcodes + (int64_t)g * stride;
     const int t0 = wave * steps * kWave + lane;
-    int c[kSortSteps], pos[kSortSteps];
+    int c[kSortSteps], pos[kSortSteps], tok[PARTS ? kSortSteps : 1];
 #pragma unroll
     for (int i = 0; i < kSortSteps; ++i) {
         const int t = t0 + i * kWave;
         c[i] = i < steps && t < T ? (int)mine_codes[t] : -1;
     }
-    for (int k = lane; k < K; k += kWave) mine[k] = 0;
+    for (int k = lane; k < Kp; k += kWave) mine[k] = 0;
     sort_lds_order();
+    int my_steps = steps;
+    if constexpr (PARTS) {
+        // this wavefront's tokens of the range, in order, through its own stretch of the sequence's place
+        int n = 0, below = 0;
+        const int at = wave * steps * kWave;
+#pragma unroll
+        for (int i = 0; i < kSortSteps; ++i)
+            if (i < steps) {
+                const bool in = c[i] >= k_lo && c[i] < k_hi;                       // no token: -1
+                const unsigned long long b = __builtin_amdgcn_ballot_w64(in);
+                below += __popcll(__builtin_amdgcn_ballot_w64(c[i] >= 0 && c[i] < k_lo));
+                if (in) {
+                    const int w = at + n + __popcll(b & ((1ull << lane) - 1ull));
+                    l_perm[w] = (uint16_t)(t0 + i * kWave);
+                    l_code[w] = (uint16_t)c[i];
+                }
+                n += __popcll(b);
+            }
+        if (lane == 0) wave_below[wave] = below;
+        sort_lds_order();
+        my_steps = (n + kWave - 1) / kWave;
+#pragma unroll
+        for (int i = 0; i < kSortSteps; ++i) {
+            const bool on = i * kWave + lane < n;
+            const int w = at + i * kWave + lane;
+            c[i] = on ? (int)l_code[w] : -1;
+            tok[i] = on ? (int)l_perm[w] : 0;
+        }
+    }
 #pragma unroll
     for (int i = 0; i < kSortSteps; ++i) {
-        if (i < steps) {
+        if (i < my_steps) {
             uint32_t p_lo = ~0u, p_hi = ~0u;
 #pragma unroll
             for (int b = 0; b < 11; ++b) {                                         // codes below 1024; all ones: no token
@@ -193,18 +234,18 @@ __global__ __launch_bounds__(kSortThreads) void sort_group_kernel(int T, int K, 
             }
             const unsigned long long peers = (unsigned long long)p_hi << 32 | p_lo;
             const int rank = __popcll(peers & ((1ull << lane) - 1ull));
-            const int before = c[i] >= 0 ? mine[c[i]] : 0;
+            const int before = c[i] >= 0 ? mine[c[i] - k_lo] : 0;
             pos[i] = before + rank;
             sort_lds_order();
-            if (c[i] >= 0 && rank == 0) mine[c[i]] = before + __popcll(peers);
+            if (c[i] >= 0 && rank == 0) mine[c[i] - k_lo] = before + __popcll(peers);
             sort_lds_order();
         }
     }
     __syncthreads();
     int total = 0;
-    if (tid < K)
+    if (tid < Kp)
 #pragma unroll
-        for (int w = 0; w < kSortWaves; ++w) total += lds_i[w * K + tid];
+        for (int w = 0; w < kSortWaves; ++w) total += lds_i[w * Kp + tid];
     int incl = total;
 #pragma unroll
     for (int o = 1; o < kWave; o <<= 1) {
@@ -213,36 +254,43 @@ __global__ __launch_bounds__(kSortThreads) void sort_group_kernel(int T, int K, 
     }
     if (lane == kWave - 1) wave_sum[wave] = incl;
     __syncthreads();
-    int base = incl - total;
+    int base = incl - total, first = 0, n_all = T;                                 // first: position of the range in the group's sequence
     for (int w = 0; w < wave; ++w) base += wave_sum[w];
-    if (tid < K) {
-        counts[(int64_t)g * K + tid] = total;
-        offs[(int64_t)g * (K + 1) + tid] = base;
-        if (tid == K - 1) offs[(int64_t)g * (K + 1) + K] = base + total;
+    if (PARTS) {
+        n_all = 0;
+        for (int w = 0; w < kSortWaves; ++w) {
+            first += wave_below[w];
+            n_all += wave_sum[w];
+        }
+    }
+    if (tid < Kp) {
+        counts[(int64_t)g * K + k_lo + tid] = total;
+        offs[(int64_t)g * (K + 1) + k_lo + tid] = first + base;
+        if (k_lo + tid == K - 1) offs[(int64_t)g * (K + 1) + K] = first + base + total;
         int run = base;
 #pragma unroll
         for (int w = 0; w < kSortWaves; ++w) {
-            const int n = lds_i[w * K + tid];
-            lds_i[w * K + tid] = run;                                              // first write position of (wavefront, code)
+            const int n = lds_i[w * Kp + tid];
+            lds_i[w * Kp + tid] = run;                                             // first write position of (wavefront, code)
             run += n;
         }
     }
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < kSortSteps; ++i)
-        if (i < steps && c[i] >= 0) {
-            const int p = mine[c[i]] + pos[i];
-            l_perm[p] = (uint16_t)(t0 + i * kWave);
+        if (i < my_steps && c[i] >= 0) {
+            const int p = mine[c[i] - k_lo] + pos[i];
+            l_perm[p] = (uint16_t)(PARTS ? tok[PARTS ? i : 0] : t0 + i * kWave);
             l_code[p] = (uint16_t)c[i];
         }
     __syncthreads();
-    for (int i = tid; i < T; i += kSortThreads) {
-        perm[(int64_t)g * T + i] = l_perm[i];
-        scode[(int64_t)g * T + i] = l_code[i];
+    for (int i = tid; i < n_all; i += kSortThreads) {
+        perm[(int64_t)g * T + first + i] = l_perm[i];
+        scode[(int64_t)g * T + first + i] = l_code[i];
     }
 }
 
-// One launch or three?  One wherever a group fits a unit's LDS and
+// One launch or three?  (Timed with one workgroup per group, which is the slower form of the one launch.)  One wherever a group fits a unit's LDS and
 //  * there are many groups and many codes: the three launches' strided reads and scattered words then cost more than the ballots
 //    (whole statistics, one launch against three, 64 groups x 16384 tokens: K = 256 61.6 / 66.1 us, K = 1024 68.4 / 83.1; 64 x 8000, K = 256:
 //    41.7 / 38.4; 48 x 5000, K = 1024: 38.2 / 42.4), or
@@ -255,14 +303,23 @@ static bool sort_in_one_launch(int T, int G, int K, int n_seg) {
     return (G >= 48 && (int64_t)G * T * K >= 190000000) || (K > 512 && n_seg % 8 >= 2);
 }
 
+// spare: scratch that the sort does not use otherwise, 2 G T bytes, or null: a group is then one workgroup's
 static int launch_sort_group(const void* codes, int code16, int T, int G, int K, int32_t* counts, int32_t* offs, int32_t* perm,
-                             uint16_t* scode, hipStream_t s) {
-    static std::atomic<uint64_t> allowed{0};
-    const int rc = allow_dynamic_lds(allowed, (const void*)sort_group_kernel, kSortWaves * kSortMaxCodes * 4 + kSortMaxTokens * 4);
+                             uint16_t* scode, uint16_t* spare, hipStream_t s) {
+    const int most = kSortWaves * kSortMaxCodes * 4 + kSortMaxTokens * 4;
+    static std::atomic<uint64_t> allowed{0}, allowed_parts{0};
+    int parts = 1;
+    while (spare && parts < 4 && 2 * parts * G <= kTrCus && 2 * parts <= K) parts *= 2;
+    const int rc = parts > 1 ? allow_dynamic_lds(allowed_parts, (const void*)sort_group_kernel<true>, most)
+                             : allow_dynamic_lds(allowed, (const void*)sort_group_kernel<false>, most);
     if (rc) return rc;
-    const size_t lds = (size_t)kSortWaves * K * sizeof(int) + (size_t)T * 4;
-    if (T > 0) code_transpose_kernel<<<dim3((int)ceil_div(T, 64), (int)ceil_div(G, 64)), kTrThreads, 0, s>>>(codes, code16, T, G, K, (uint16_t*)perm);
-    sort_group_kernel<<<G, kSortThreads, lds, s>>>(T, K, (int)ceil_div(T, kSortThreads), counts, offs, perm, scode);
+    uint16_t* tcodes = parts > 1 ? spare : (uint16_t*)perm;
+    const int stride = parts > 1 ? T : 2 * T;
+    const size_t lds = (size_t)kSortWaves * ceil_div(K, parts) * sizeof(int) + (size_t)T * 4;
+    const int steps = (int)ceil_div(T, kSortThreads);
+    if (T > 0) code_transpose_kernel<<<dim3((int)ceil_div(T, 64), (int)ceil_div(G, 64)), kTrThreads, 0, s>>>(codes, code16, T, G, K, stride, tcodes);
+    if (parts > 1) sort_group_kernel<true><<<dim3(G, parts), kSortThreads, lds, s>>>(tcodes, stride, T, K, steps, counts, offs, perm, scode);
+    else sort_group_kernel<false><<<G, kSortThreads, lds, s>>>(tcodes, stride, T, K, steps, counts, offs, perm, scode);
     return ASTRA_OK;
 }
 
@@ -633,7 +690,7 @@ int astra_codebook_stats(const astra_vq_desc* desc, const void* x, const void* c
     uint16_t* scode = (uint16_t*)(ws + pl.off_scode);
     float* part = (float*)(ws + pl.off_part);
     if (sort_in_one_launch(T, G, K, pl.n_seg)) {
-        rc = launch_sort_group(codes, code16, T, G, K, counts_out, offs, perm, scode, s);
+        rc = launch_sort_group(codes, code16, T, G, K, counts_out, offs, perm, scode, pl.units ? (uint16_t*)part : nullptr, s);
         if (rc) return rc;
     } else {
         const dim3 sgrid(pl.n_seg, G);

@@ -174,7 +174,18 @@ def test_stats_one_launch_sort(T, G, K):
     check_exact_stats(T, G, K, 8)
 
 
-def check_exact_stats(T, G, K, dg):
+@pytest.mark.parametrize("T,G,K,used", [
+    (16384, 48, 1024, (1023, 1023)),         # four workgroups per group: every token in the last one's range of codes
+    (16383, 64, 1024, (255, 256)),           # ... in the first two, at their border
+    (8191, 65, 1023, (0, 1023)),             # two
+    (2047, 129, 1024, (0, 1024)),            # one
+])
+def test_stats_sort_ranges_of_codes(T, G, K, used):
+    """A group's codes dealt in ranges to several workgroups, with ranges that no token or every token falls into."""
+    check_exact_stats(T, G, K, 8, used)
+
+
+def check_exact_stats(T, G, K, dg, used=None):
     import torch
     from gpu_util import codes_to_dev, to_dev, DEV
     from paper_2505_19342_amd import binding as B
@@ -182,6 +193,8 @@ def check_exact_stats(T, G, K, dg):
     x = rng.integers(-4, 5, (T, G * dg)).astype(np.float32)
     cb = rng.integers(-4, 5, (G, K, dg)).astype(np.float32)
     codes = (K * rng.random((T, G)) ** 1.5).astype(np.int64)
+    if used is not None:
+        codes = np.minimum(used[0] + codes % max(used[1] - used[0] + 1, 1), K - 1)
     desc = B.vq_desc("bf16", G * dg, G, K)
     dev = dict(x=to_dev(x, "bf16"), cb=to_dev(cb, "bf16"), codes=codes_to_dev(codes, K),
                counts=torch.empty((G, K), dtype=torch.int32, device=DEV), sums=torch.empty((G, K, dg), dtype=torch.float32, device=DEV),
