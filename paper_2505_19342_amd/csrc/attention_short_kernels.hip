@@ -13,6 +13,9 @@ namespace astra {
 // A workgroup of eight wavefronts owns 32 query rows of one head; wavefront w walks the tiles w, w + 8, ... of 4096 / DH keys (64 or 32; visible
 // non-local ones first) for itself: direct transfers bring its keys and values into LDS of its own (8 KiB each, XOR-swizzled pieces), so that the loop has
 // no barrier and no other wavefront to wait for.  A tile's fragments are read into registers whole, and its place takes the wavefront's next tile at once.  The
+// reference maxima start from the ones attn_bf16_kernel would have (its wavefronts' first tiles: a quarter of the 64-key tiles each on 64-wide heads, half on
+// 128-wide ones), exchanged once through LDS: probabilities are then rounded to bf16 on the same scale and a row's output does not depend on which kernel
+// took it but for the order of fp32 sums (layers' outputs then differ by 2e-5 of the norm instead of 2e-3, for 0.5 us of a ViT layer's 23.9).  The
 // eight (max, sum, O) triples meet in LDS, and every thread adds four of the workgroup's outputs in wavefront order.
 //
 // What bounds it: a launch, a memory latency at either end, and what the second-level caches give all units together (4 DH bytes a key for every 32
@@ -130,6 +133,9 @@ __global__ __launch_bounds__(kShortThreads) void attn_short_kernel(const AttnPar
     if (wave < n_tiles) {
         send_k(tile_of(wave));
         send_v(tile_of(wave));
+    } else {
+        if (h == 0) part_m[wave][i32] = -INFINITY;
+        __syncthreads();                         // the others' meeting over their first tiles
     }
     for (int t = wave; t < n_tiles; t += kShortWaves) {
         const Tile tl = tile_of(t), next = tile_of(min(t + kShortWaves, n_tiles - 1));
@@ -175,6 +181,11 @@ __global__ __launch_bounds__(kShortThreads) void attn_short_kernel(const AttnPar
 #pragma unroll
             for (int v = 0; v < 16; ++v) mx = fmaxf(mx, acc_s[mb][v]);
         mx = fmaxf(mx, __shfl_xor(mx, 32)) * sl2;
+        if (t == wave) {
+            if (h == 0) part_m[wave][i32] = mx;
+            __syncthreads();
+            m_run = DH == 64 ? part_m[wave & 3][i32] : fmaxf(part_m[wave & 2][i32], part_m[(wave & 2) | 1][i32]);
+        }
         float alpha = 1.f;
         const bool rescale = mx > m_run + kLazyShort;          // also true for the first visible key (m_run = -inf)
         if (rescale) {
