@@ -290,25 +290,16 @@ __global__ __launch_bounds__(kSortThreads) void sort_group_kernel(const uint16_t
     }
 }
 
-// workgroups per group of the one launch; spare: there is room for the transposed codes outside perm
-static int sort_parts(int G, int K, bool spare) {
-    int parts = 1;
-    while (spare && parts < 4 && 2 * parts * G <= kTrCus && 2 * parts <= K) parts *= 2;
-    return parts;
-}
-
-// One launch or three?  Whole statistics, us, three launches / one with a group's codes dealt in ranges: 64 groups of 64, K = 1024, 16384 tokens 81.8 / 59.7,
-// 2000 36.7 / 31.7, 500 28.0 / 28.0; 4 groups 33.4 / 30.2, 29.0 / 24.6, 23.9 / 24.0.  K = 256: 64 groups 65.1 / 53.4, 29.5 / 28.2, 23.8 / 25.5 (1000 tokens
-// 26.0 / 26.5); 16 groups 44.6 / 46.0, 25.6 / 24.7, 22.2 / 23.6 (4000: 27.4 / 26.4, 8000: 31.4 / 32.0): few codes rank quickly in the three launches'
-// segments, which are up to 16 per group where the ranges are four.
-// With one workgroup per group (more than 128 groups, rows without whole 16-byte pieces) the one launch is the faster wherever
+// One launch or three?  (Timed with one workgroup per group, which is the slower form of the one launch.)  One wherever a group fits a unit's LDS and
 //  * there are many groups and many codes: the three launches' strided reads and scattered words then cost more than the ballots
-//    (64 groups x 16384 tokens: K = 256 61.6 / 66.1 us for one / three, K = 1024 68.4 / 83.1; 64 x 8000, K = 256: 41.7 / 38.4; 48 x 5000, K = 1024: 38.2 / 42.4), or
+//    (whole statistics, one launch against three, 64 groups x 16384 tokens: K = 256 61.6 / 66.1 us, K = 1024 68.4 / 83.1; 64 x 8000, K = 256:
+//    41.7 / 38.4; 48 x 5000, K = 1024: 38.2 / 42.4), or
 //  * the codebook is large and the number of segments is no multiple of eight, in which the scan launch walks them with its loads in flight
 //    (1 group of K = 1024: 7000 tokens in 7 segments 29.8 / 34.8 us, 8000 in 8 30.3 / 29.4, 15000 in 15 35.3 / 38.3, 16384 in 16 36.2 / 31.5).
-static bool sort_in_one_launch(int T, int G, int K, int n_seg, bool spare) {
+// Few groups leave the one launch on as many units, where the segments of the three spread a group over up to 16
+// (1 group x 16384 tokens, K = 256: 34.3 / 24.7 us; 32 groups: 46.0 / 38.4).
+static bool sort_in_one_launch(int T, int G, int K, int n_seg) {
     if (T > kSortMaxTokens || K > kSortMaxCodes) return false;
-    if (sort_parts(G, K, spare) > 1) return K > 512 ? T >= 500 : T >= 1500 && (G > 16 || T <= 6000);
     return (G >= 48 && (int64_t)G * T * K >= 190000000) || (K > 512 && n_seg % 8 >= 2);
 }
 
@@ -317,7 +308,8 @@ static int launch_sort_group(const void* codes, int code16, int T, int G, int K,
                              uint16_t* scode, uint16_t* spare, hipStream_t s) {
     const int most = kSortWaves * kSortMaxCodes * 4 + kSortMaxTokens * 4;
     static std::atomic<uint64_t> allowed{0}, allowed_parts{0};
-    const int parts = sort_parts(G, K, spare != nullptr);
+    int parts = 1;
+    while (spare && parts < 4 && 2 * parts * G <= kTrCus && 2 * parts <= K) parts *= 2;
     const int rc = parts > 1 ? allow_dynamic_lds(allowed_parts, (const void*)sort_group_kernel<true>, most)
                              : allow_dynamic_lds(allowed, (const void*)sort_group_kernel<false>, most);
     if (rc) return rc;
@@ -697,7 +689,7 @@ int astra_codebook_stats(const astra_vq_desc* desc, const void* x, const void* c
     int32_t* hist = (int32_t*)(ws + pl.off_hist);
     uint16_t* scode = (uint16_t*)(ws + pl.off_scode);
     float* part = (float*)(ws + pl.off_part);
-    if (sort_in_one_launch(T, G, K, pl.n_seg, pl.units)) {
+    if (sort_in_one_launch(T, G, K, pl.n_seg)) {
         rc = launch_sort_group(codes, code16, T, G, K, counts_out, offs, perm, scode, pl.units ? (uint16_t*)part : nullptr, s);
         if (rc) return rc;
     } else {
