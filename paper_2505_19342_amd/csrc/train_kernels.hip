@@ -171,9 +171,8 @@ __global__ __launch_bounds__(kTrThreads) void code_transpose_kernel(const void* 
 
 // tcodes: the transposed codes, stride apart per group; with one workgroup per group they may lie in its place in perm (read whole before it is written)
 template <bool PARTS>
-__global__ __launch_bounds__(kSortThreads) void sort_group_kernel(const uint16_t* tcodes, int stride, int T, int K, int steps,
-                                                                  int32_t* __restrict__ counts, int32_t* __restrict__ offs, int32_t* perm,
-                                                                  uint16_t* __restrict__ scode) {
+__device__ __forceinline__ void sort_group_body(const uint16_t* tcodes, int stride, int T, int K, int steps, int32_t* __restrict__ counts,
+                                                int32_t* __restrict__ offs, int32_t* perm, uint16_t* __restrict__ scode) {
     extern __shared__ int lds_i[];
     __shared__ int wave_sum[kSortWaves], wave_below[kSortWaves];
     const int g = blockIdx.x, tid = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
@@ -290,6 +289,19 @@ __global__ __launch_bounds__(kSortThreads) void sort_group_kernel(const uint16_t
     }
 }
 
+// a group's ranges of codes dealt to gridDim.y workgroups
+__global__ __launch_bounds__(kSortThreads) void sort_group_kernel(const uint16_t* tcodes, int stride, int T, int K, int steps,
+                                                                  int32_t* __restrict__ counts, int32_t* __restrict__ offs, int32_t* perm,
+                                                                  uint16_t* __restrict__ scode) {
+    sort_group_body<true>(tcodes, stride, T, K, steps, counts, offs, perm, scode);
+}
+// one workgroup per group: many groups, or no room for the transposed codes outside perm
+__global__ __launch_bounds__(kSortThreads) void sort_whole_group_kernel(const uint16_t* tcodes, int stride, int T, int K, int steps,
+                                                                        int32_t* __restrict__ counts, int32_t* __restrict__ offs, int32_t* perm,
+                                                                        uint16_t* __restrict__ scode) {
+    sort_group_body<false>(tcodes, stride, T, K, steps, counts, offs, perm, scode);
+}
+
 // One launch or three?  (Timed with one workgroup per group, which is the slower form of the one launch.)  One wherever a group fits a unit's LDS and
 //  * there are many groups and many codes: the three launches' strided reads and scattered words then cost more than the ballots
 //    (whole statistics, one launch against three, 64 groups x 16384 tokens: K = 256 61.6 / 66.1 us, K = 1024 68.4 / 83.1; 64 x 8000, K = 256:
@@ -310,16 +322,16 @@ static int launch_sort_group(const void* codes, int code16, int T, int G, int K,
     static std::atomic<uint64_t> allowed{0}, allowed_parts{0};
     int parts = 1;
     while (spare && parts < 4 && 2 * parts * G <= kTrCus && 2 * parts <= K) parts *= 2;
-    const int rc = parts > 1 ? allow_dynamic_lds(allowed_parts, (const void*)sort_group_kernel<true>, most)
-                             : allow_dynamic_lds(allowed, (const void*)sort_group_kernel<false>, most);
+    const int rc = parts > 1 ? allow_dynamic_lds(allowed_parts, (const void*)sort_group_kernel, most)
+                             : allow_dynamic_lds(allowed, (const void*)sort_whole_group_kernel, most);
     if (rc) return rc;
     uint16_t* tcodes = parts > 1 ? spare : (uint16_t*)perm;
     const int stride = parts > 1 ? T : 2 * T;
     const size_t lds = (size_t)kSortWaves * ceil_div(K, parts) * sizeof(int) + (size_t)T * 4;
     const int steps = (int)ceil_div(T, kSortThreads);
     if (T > 0) code_transpose_kernel<<<dim3((int)ceil_div(T, 64), (int)ceil_div(G, 64)), kTrThreads, 0, s>>>(codes, code16, T, G, K, stride, tcodes);
-    if (parts > 1) sort_group_kernel<true><<<dim3(G, parts), kSortThreads, lds, s>>>(tcodes, stride, T, K, steps, counts, offs, perm, scode);
-    else sort_group_kernel<false><<<G, kSortThreads, lds, s>>>(tcodes, stride, T, K, steps, counts, offs, perm, scode);
+    if (parts > 1) sort_group_kernel<<<dim3(G, parts), kSortThreads, lds, s>>>(tcodes, stride, T, K, steps, counts, offs, perm, scode);
+    else sort_whole_group_kernel<<<G, kSortThreads, lds, s>>>(tcodes, stride, T, K, steps, counts, offs, perm, scode);
     return ASTRA_OK;
 }
 
