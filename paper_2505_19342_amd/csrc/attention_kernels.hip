@@ -504,7 +504,7 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const AttnParams p, int d
         f32x4 vv[16];
         float s;
         if (VEC) {
-            // rows beyond the chunk repeat its last one; their logits are dropped and their values get weight zero
+            // rows beyond the chunk repeat its last one; their logits are dropped and their values are zeros (an infinity times a weight of zero is none)
             float dot[16];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
@@ -569,6 +569,9 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const AttnParams p, int d
                 if (u > 0)
 #pragma unroll
                     for (int j = 0; j < 16; ++j) vv[j] = *reinterpret_cast<const f32x4*>(Vp + (int64_t)min(4 * j + rg, cnt - 1) * kv_ld + col[u]);
+                if (cnt < kWave)
+#pragma unroll
+                    for (int j = 0; j < 16; ++j) vv[j] = 4 * j + rg < cnt ? vv[j] : f32x4{0.f, 0.f, 0.f, 0.f};
                 o[u] *= alpha;
 #pragma unroll
                 for (int j = 0; j < 16; ++j) {

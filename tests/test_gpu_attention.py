@@ -89,6 +89,27 @@ def test_scale_and_large_logits():
     assert np.abs(got2 - ref2).max() <= TOL["bf16"]
 
 
+@pytest.mark.parametrize("dh,Tn,at", [(64, 48, 47), (64, 70, 69), (100, 16, 15), (200, 37, 36), (30, 48, 47)])
+def test_an_infinite_value_gives_an_infinity(dh, Tn, at):
+    """fp32: the last non-local value row, or the last local one a causal row sees, holds an infinity in one channel; rows that see it get the infinity in that
+    channel and nothing else changes.  (Rows beyond a chunk of 64 repeat its last row with weight zero.)"""
+    from gpu_util import gpu_mixed_attention
+    Tq = 35
+    q, k, v, kh, vh = rand_case(dh + Tn, Tq, Tn, 2, 1, dh, "f32")
+    clean, _ = gpu_mixed_attention(q, k, v, kh, vh, "f32", causal=True, n_before=Tn, want_lse=True)
+    vh[at, 0, 7] = np.inf
+    got, _ = gpu_mixed_attention(q, k, v, kh, vh, "f32", causal=True, n_before=Tn, want_lse=True)
+    assert np.all(got[:, :, 7] == np.inf)
+    others = np.arange(dh) != 7
+    np.testing.assert_array_equal(got[:, :, others], clean[:, :, others])
+    vh[at, 0, 7] = 0.0
+    for row in (15, 31, 33):
+        w = v.copy()
+        w[row, 0, 7] = -np.inf
+        got, _ = gpu_mixed_attention(q, k, w, kh, vh, "f32", causal=True, n_before=Tn, want_lse=True)
+        assert np.all(got[row:, :, 7] == -np.inf) and np.all(np.isfinite(got[:row])), row
+
+
 def test_argument_errors():
     import torch
     from gpu_util import DEV
