@@ -451,24 +451,31 @@ __global__ __launch_bounds__(kAttThreads) void attn_bf16_kernel(const AttnParams
 //
 // In a chunk 16 lanes hold a row, four values (16 bytes) each and 64 further ones per U = ceil(dh / 64), and a load covers four rows; a lane's sixteen
 // partial dots (rows 4j + lane / 16) are added over the 16 lanes so that lane (r, c) of the wavefront ends with the logit of row 4c + r.  Bound by the
-// latency of the chain keys -> logits -> values: all of a chunk's keys and its first 64 values' columns are requested before anything is computed.
-// 64 rows x 3 heads of 64 over 256 keys, back to back: 7.7 us with a key per lane (a cache line per lane and load) and 16 value rows at a time after
-// the softmax; 4.2 now.  Error against fp64 3.1e-7 of the norm, now 1.5e-7.
-// VEC = false: head dimensions or addresses that 16-byte pieces do not fit.
+// latency of the chain keys -> logits -> values, so by the loads in flight on a unit: a wavefront's (JB U at a time, batches beyond a ragged chunk
+// left out) times its wavefronts.  Eight loads per batch leave room for three to four wavefronts per SIMD.  All of a chunk's keys and values at once (176 registers and more,
+// one or two wavefronts) are no faster for one round of workgroups and slower beyond it.  A key per lane and a cache line per lane and load / everything at once /
+// this: 64 rows x 3 heads of 64 over 256 keys 7.8 / 4.4 / 4.3 us; 12 heads, 257 rows over 1025 keys: heads of 64 145 / 79 / 65, of 128
+// 257 / 211 / 115, of 256 489 / 365 / 226; 100 causal rows, heads of 128 12.5 / 20.6 / 8.1, of 256 19.1 / 31.6 / 12.5.  Error against fp64 3.1e-7
+// of the norm, now 1.5e-7.
+// VEC = false: head dimensions or addresses that 16-byte pieces do not fit; a key per lane, 16 of its values at a time (one by one: 3 heads of 50, 64 rows over 256 keys
+// 13.0 us, now 10.3; 12 heads of 130, 257 rows over 1025 keys 1766, now 850).
 //
 // ENC: the workgroups behind the attention's encode the local rows (fp32 codes; nothing here depends on them or the other way round).
 // ------------------------------------------------------------------------------------------------
-template <int U, bool VEC>
+template <int U, bool VEC, bool ENC>
 __global__ __launch_bounds__(256) void attn_f32_kernel(const AttnParams p, int dh, const AttnEncode e) {
     constexpr int kWaves = 4;
+    constexpr int JB = U == 1 ? 8 : U == 2 ? 4 : 2;        // loads of a batch, 4 rows each, per 64 values of a row
     __shared__ __align__(16) float part[kWaves][U * kWave + 4];
-    if (e.n_enc_wgs > 0 && (int)blockIdx.x >= e.n_attn_wgs) {
+    if constexpr (ENC) {
         __shared__ EncF32Lds enc_lds;
-        int item = (int)blockIdx.x - e.n_attn_wgs;
-        const int j = item >= e.job[0].G * e.job[0].n_tb ? 1 : 0;
-        if (j) item -= e.job[0].G * e.job[0].n_tb;
-        vq_encode_f32_body(e.job[j], item, enc_lds);
-        return;
+        if ((int)blockIdx.x >= e.n_attn_wgs) {
+            int item = (int)blockIdx.x - e.n_attn_wgs;
+            const int j = item >= e.job[0].G * e.job[0].n_tb ? 1 : 0;
+            if (j) item -= e.job[0].G * e.job[0].n_tb;
+            vq_encode_f32_body(e.job[j], item, enc_lds);
+            return;
+        }
     }
     const int lane = lane_id();
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -477,6 +484,7 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const AttnParams p, int d
     const int64_t q_ld = (int64_t)p.Hq * dh, kv_ld = (int64_t)p.Hkv * dh;
     const float* __restrict__ q = (const float*)p.q + (int64_t)row * q_ld + (int64_t)head * dh;
     const int sub = lane & 15, rg = lane >> 4;
+    const uint32_t ld_b = (uint32_t)kv_ld * 4u;
 
     const int n_hat = p.Tn_vis;
     const int n_loc = p.causal ? row + 1 : p.Tq;
@@ -498,33 +506,53 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const AttnParams p, int d
         const int cnt = min(kWave, (src == 0 ? n_hat : n_loc) - base);          // rows of the chunk
         const float* __restrict__ Kp = (const float*)(src == 0 ? p.k_hat : p.k_loc) + (int64_t)base * kv_ld + (int64_t)hk * dh;
         const float* __restrict__ Vp = (const float*)(src == 0 ? p.v_hat : p.v_loc) + (int64_t)base * kv_ld + (int64_t)hk * dh;
-        const int key = 4 * sub + rg;                                           // this lane's row in the chunk
+        const int key = VEC ? 4 * sub + rg : lane;                              // this lane's row in the chunk
         const unsigned long long bits = src != 0 || p.valid_bits == nullptr ? ~0ull : p.valid_bits[base >> 6];
         const bool arrived = key < cnt && ((bits >> key) & 1ull);
-        f32x4 vv[16];
+        // rows beyond the chunk repeat its last one; their logits are dropped and their values are zeros (an infinity times a weight of zero is none)
+        auto piece = [&](const float* base_, int j, int u) __attribute__((always_inline)) {
+            return *reinterpret_cast<const f32x4*>((const char*)base_ + ((uint32_t)min(4 * j + rg, cnt - 1) * ld_b + (uint32_t)col[u] * 4u));
+        };
+        constexpr int kRows = VEC ? 1 : U <= 2 ? 16 : 8;        // not VEC: value rows in flight, the first of them on narrow heads sent before the keys
+        constexpr bool EARLY = U <= 2;
+        float x[kRows][U];
+        auto load_rows = [&](int r0) __attribute__((always_inline)) {
+#pragma unroll
+            for (int b = 0; b < kRows; ++b)
+#pragma unroll
+                for (int u = 0; u < U; ++u) x[b][u] = Vp[(int64_t)min(r0 + b, cnt - 1) * kv_ld + min(lane + 64 * u, dh - 1)];
+        };
         float s;
         if (VEC) {
-            // rows beyond the chunk repeat its last one; their logits are dropped and their values are zeros (an infinity times a weight of zero is none)
             float dot[16];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                f32x4 kk[16];
+            for (int j = 0; j < 16; ++j) dot[j] = 0.f;
 #pragma unroll
-                for (int j = 0; j < 16; ++j) kk[j] = *reinterpret_cast<const f32x4*>(Kp + (int64_t)min(4 * j + rg, cnt - 1) * kv_ld + col[u]);
-                if (u == 0)
+            for (int b = 0; b < 16; b += JB) {
+                if (b > 0 && 4 * b >= cnt) break;
+                f32x4 kk[JB][U];
 #pragma unroll
-                    for (int j = 0; j < 16; ++j) vv[j] = *reinterpret_cast<const f32x4*>(Vp + (int64_t)min(4 * j + rg, cnt - 1) * kv_ld + col[0]);
+                for (int u = 0; u < U; ++u)
+#pragma unroll
+                    for (int j = 0; j < JB; ++j) kk[j][u] = piece(Kp, b + j, u);
                 __builtin_amdgcn_sched_barrier(0);         // all of them are on their way before the first is waited for
-                const bool in = 64 * u + 4 * sub < dh;
 #pragma unroll
-                for (int j = 0; j < 16; ++j) {
-                    float d = u == 0 ? 0.f : dot[j];
-                    d = fmaf(qv[u].x, kk[j].x, d);
-                    d = fmaf(qv[u].y, kk[j].y, d);
-                    d = fmaf(qv[u].z, kk[j].z, d);
-                    d = fmaf(qv[u].w, kk[j].w, d);
-                    dot[j] = in ? d : (u == 0 ? 0.f : dot[j]);
+                for (int u = 0; u < U; ++u) {
+                    const bool in = 64 * u + 4 * sub < dh;
+#pragma unroll
+                    for (int j = 0; j < JB; ++j) {
+                        float d = dot[b + j];
+                        d = fmaf(qv[u].x, kk[j][u].x, d);
+                        d = fmaf(qv[u].y, kk[j][u].y, d);
+                        d = fmaf(qv[u].z, kk[j][u].z, d);
+                        d = fmaf(qv[u].w, kk[j][u].w, d);
+                        dot[b + j] = in ? d : dot[b + j];
+                    }
                 }
+                // worked out here: moved behind the branches that follow, the sums would keep the keys of all batches alive
+#pragma unroll
+                for (int j = 0; j < JB; ++j) asm volatile("" : "+v"(dot[b + j]));
+                __builtin_amdgcn_sched_barrier(0);
             }
             // sixteen sums over sixteen lanes: every step halves the sums a lane still carries
             auto halve = [&](auto n) __attribute__((always_inline)) {
@@ -542,9 +570,26 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const AttnParams p, int d
             halve(std::integral_constant<int, 1>{});
             s = dot[0] * p.scale;
         } else {
-            const float* kr = Kp + (int64_t)min(key, cnt - 1) * kv_ld;
+            if (EARLY) load_rows(0);
+            const float* kr = Kp + (int64_t)key * kv_ld;
             float d = 0.f;
-            for (int i = 0; i < dh; ++i) d = fmaf(q[i], kr[i], d);
+            // a row per lane (none for the keys that are not there), 16 values at a time and the rest at once
+            auto take = [&](int i, auto n) __attribute__((always_inline)) {
+                constexpr int N = decltype(n)::value;
+                float kk[N];
+#pragma unroll
+                for (int t = 0; t < N; ++t) kk[t] = kr[min(i + t, dh - 1)];
+#pragma unroll
+                for (int t = 0; t < N; ++t) d = i + t < dh ? fmaf(q[min(i + t, dh - 1)], kk[t], d) : d;
+            };
+            if (arrived) {
+                int i = 0;
+                for (; i + 16 <= dh; i += 16) take(i, std::integral_constant<int, 16>{});
+                if (dh - i > 12) take(i, std::integral_constant<int, 16>{});
+                else if (dh - i > 8) take(i, std::integral_constant<int, 12>{});
+                else if (dh - i > 4) take(i, std::integral_constant<int, 8>{});
+                else if (dh - i > 0) take(i, std::integral_constant<int, 4>{});
+            }
             s = d * p.scale;
         }
         if (!arrived) s = -INFINITY;
@@ -561,33 +606,48 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const AttnParams p, int d
         l_run = l_run * alpha + sum;
         m_run = m_new;
         if (VEC) {
-            float wj[16];
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int j = 0; j < 16; ++j) wj[j] = __shfl(w, (lane & 48) | j);      // weight of row 4j + rg
+            for (int u = 0; u < U; ++u) o[u] *= alpha;
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                if (u > 0)
+            for (int b = 0; b < 16; b += JB) {
+                if (b > 0 && 4 * b >= cnt) break;
+                f32x4 x[JB][U];
 #pragma unroll
-                    for (int j = 0; j < 16; ++j) vv[j] = *reinterpret_cast<const f32x4*>(Vp + (int64_t)min(4 * j + rg, cnt - 1) * kv_ld + col[u]);
-                if (cnt < kWave)
+                for (int j = 0; j < JB; ++j)
 #pragma unroll
-                    for (int j = 0; j < 16; ++j) vv[j] = 4 * j + rg < cnt ? vv[j] : f32x4{0.f, 0.f, 0.f, 0.f};
-                o[u] *= alpha;
+                    for (int u = 0; u < U; ++u) x[j][u] = piece(Vp, b + j, u);
+                if (4 * (b + JB) > cnt)
 #pragma unroll
-                for (int j = 0; j < 16; ++j) {
-                    o[u].x = fmaf(wj[j], vv[j].x, o[u].x);
-                    o[u].y = fmaf(wj[j], vv[j].y, o[u].y);
-                    o[u].z = fmaf(wj[j], vv[j].z, o[u].z);
-                    o[u].w = fmaf(wj[j], vv[j].w, o[u].w);
+                    for (int j = 0; j < JB; ++j)
+#pragma unroll
+                        for (int u = 0; u < U; ++u) x[j][u] = 4 * (b + j) + rg < cnt ? x[j][u] : f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int j = 0; j < JB; ++j) {
+                    const float wj = __shfl(w, (lane & 48) | (b + j));           // weight of row 4 (b + j) + rg
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        o[u].x = fmaf(wj, x[j][u].x, o[u].x);
+                        o[u].y = fmaf(wj, x[j][u].y, o[u].y);
+                        o[u].z = fmaf(wj, x[j][u].z, o[u].z);
+                        o[u].w = fmaf(wj, x[j][u].w, o[u].w);
+                    }
                 }
+#pragma unroll
+                for (int u = 0; u < U; ++u) asm volatile("" : "+v"(o[u]));
+                __builtin_amdgcn_sched_barrier(0);
             }
         } else {
 #pragma unroll
             for (int u = 0; u < U; ++u) o[u].x *= alpha;
-            for (int r = 0; r < cnt; ++r) {
-                const float wr = __shfl(w, (r >> 2) | ((r & 3) << 4));
+            for (int r0 = 0; r0 < cnt; r0 += kRows) {
+                if (!EARLY || r0 > 0) load_rows(r0);
 #pragma unroll
-                for (int u = 0; u < U; ++u) o[u].x = fmaf(wr, Vp[(int64_t)r * kv_ld + min(lane + 64 * u, dh - 1)], o[u].x);
+                for (int b = 0; b < kRows; ++b) {
+                    const float wr = __shfl(w, r0 + b);
+#pragma unroll
+                    for (int u = 0; u < U; ++u) o[u].x = r0 + b < cnt ? fmaf(wr, x[b][u], o[u].x) : o[u].x;
+                }
             }
         }
     }
@@ -638,9 +698,15 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const AttnParams p, int d
 
 template <int U>
 static void launch_attn_f32(int blocks, const AttnParams& p, int head_dim, const AttnEncode& e, hipStream_t s) {
-    const bool vec = head_dim % 4 == 0 && ((uintptr_t)p.q | (uintptr_t)p.k_loc | (uintptr_t)p.k_hat | (uintptr_t)p.v_loc | (uintptr_t)p.v_hat) % 16 == 0;
-    if (vec) attn_f32_kernel<U, true><<<blocks, 256, 0, s>>>(p, head_dim, e);
-    else attn_f32_kernel<U, false><<<blocks, 256, 0, s>>>(p, head_dim, e);
+    const bool vec = head_dim % 4 == 0 && (int64_t)p.Hkv * head_dim * 4 * kWave < (1ll << 32) &&       // offsets in a chunk are 32 bits wide
+                     ((uintptr_t)p.q | (uintptr_t)p.k_loc | (uintptr_t)p.k_hat | (uintptr_t)p.v_loc | (uintptr_t)p.v_hat) % 16 == 0;
+    if (e.n_enc_wgs > 0) {
+        if (vec) attn_f32_kernel<U, true, true><<<blocks, 256, 0, s>>>(p, head_dim, e);
+        else attn_f32_kernel<U, false, true><<<blocks, 256, 0, s>>>(p, head_dim, e);
+    } else {
+        if (vec) attn_f32_kernel<U, true, false><<<blocks, 256, 0, s>>>(p, head_dim, e);
+        else attn_f32_kernel<U, false, false><<<blocks, 256, 0, s>>>(p, head_dim, e);
+    }
 }
 
 static double encode_item_us(const EncodeJob& e) { return 256.0 * e.K * e.dg / 1048576.0 + 2.5; }      // 16.5 us and its start at K = 1024, dg = 64

@@ -89,6 +89,18 @@ def test_scale_and_large_logits():
     assert np.abs(got2 - ref2).max() <= TOL["bf16"]
 
 
+@pytest.mark.parametrize("dh", [5, 12, 50, 64, 77, 128, 130, 192, 253, 256])
+def test_f32_rows_around_a_batch(dh):
+    """fp32: causal rows end their chunk at every number of keys from 1 to 66, among them those around a batch of 8, 16 and 32 rows; heads on either side of each
+    64 values, with and without whole 16-byte pieces."""
+    from gpu_util import gpu_mixed_attention
+    q, k, v, kh, vh = rand_case(dh, 66, 9, 2, 1, dh, "f32")
+    ref, ref_lse = oracle.mixed_attention(q, k, v, kh, vh, causal=True, n_before=9, return_lse=True)
+    got, lse = gpu_mixed_attention(q, k, v, kh, vh, "f32", causal=True, n_before=9, want_lse=True)
+    assert np.abs(got - ref).max() <= TOL["f32"]
+    np.testing.assert_allclose(lse, ref_lse, atol=1e-4)
+
+
 @pytest.mark.parametrize("dh,Tn,at", [(64, 48, 47), (64, 70, 69), (100, 16, 15), (200, 37, 36), (30, 48, 47)])
 def test_an_infinite_value_gives_an_infinity(dh, Tn, at):
     """fp32: the last non-local value row, or the last local one a causal row sees, holds an infinity in one channel; rows that see it get the infinity in that
