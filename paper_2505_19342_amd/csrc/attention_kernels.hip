@@ -452,7 +452,7 @@ __global__ __launch_bounds__(kAttThreads) void attn_bf16_kernel(const AttnParams
 // In a chunk 16 lanes hold a row, four values (16 bytes) each and 64 further ones per U = ceil(dh / 64), and a load covers four rows; a lane's sixteen
 // partial dots (rows 4j + lane / 16) are added over the 16 lanes so that lane (r, c) of the wavefront ends with the logit of row 4c + r.  Bound by the
 // latency of the chain keys -> logits -> values, so by the loads in flight on a unit: a wavefront's (JB U at a time, batches beyond a ragged chunk
-// left out) times its wavefronts.  Eight loads per batch leave room for three to four wavefronts per SIMD.  All of a chunk's keys and values at once (176 registers and more,
+// left out; the first batch of values lands behind the softmax) times its wavefronts.  Eight loads per batch leave room for three to four wavefronts per SIMD.  All of a chunk's keys and values at once (176 registers and more,
 // one or two wavefronts) are no faster for one round of workgroups and slower beyond it.  A key per lane and a cache line per lane and load / everything at once /
 // this: 64 rows x 3 heads of 64 over 256 keys 7.8 / 4.4 / 4.3 us; 12 heads, 257 rows over 1025 keys: heads of 64 145 / 79 / 65, of 128
 // 257 / 211 / 115, of 256 489 / 365 / 226; 100 causal rows, heads of 128 12.5 / 20.6 / 8.1, of 256 19.1 / 31.6 / 12.5.  Error against fp64 3.1e-7
@@ -522,6 +522,13 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const AttnParams p, int d
 #pragma unroll
                 for (int u = 0; u < U; ++u) x[b][u] = Vp[(int64_t)min(r0 + b, cnt - 1) * kv_ld + min(lane + 64 * u, dh - 1)];
         };
+        f32x4 vv[JB][U];                                   // VEC: a batch of values
+        auto load_values = [&](int b) __attribute__((always_inline)) {
+#pragma unroll
+            for (int j = 0; j < JB; ++j)
+#pragma unroll
+                for (int u = 0; u < U; ++u) vv[j][u] = piece(Vp, b + j, u);
+        };
         float s;
         if (VEC) {
             float dot[16];
@@ -554,6 +561,8 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const AttnParams p, int d
                 for (int j = 0; j < JB; ++j) asm volatile("" : "+v"(dot[b + j]));
                 __builtin_amdgcn_sched_barrier(0);
             }
+            load_values(0);                                // lands behind the softmax
+            __builtin_amdgcn_sched_barrier(0);
             // sixteen sums over sixteen lanes: every step halves the sums a lane still carries
             auto halve = [&](auto n) __attribute__((always_inline)) {
                 constexpr int W = decltype(n)::value;
@@ -606,33 +615,30 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const AttnParams p, int d
         l_run = l_run * alpha + sum;
         m_run = m_new;
         if (VEC) {
-            __builtin_amdgcn_sched_barrier(0);
+            float wj[16];
+#pragma unroll
+            for (int j = 0; j < 16; ++j) wj[j] = __shfl(w, (lane & 48) | j);      // weight of row 4j + rg
 #pragma unroll
             for (int u = 0; u < U; ++u) o[u] *= alpha;
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int b = 0; b < 16; b += JB) {
                 if (b > 0 && 4 * b >= cnt) break;
-                f32x4 x[JB][U];
-#pragma unroll
-                for (int j = 0; j < JB; ++j)
-#pragma unroll
-                    for (int u = 0; u < U; ++u) x[j][u] = piece(Vp, b + j, u);
+                if (b > 0) load_values(b);
                 if (4 * (b + JB) > cnt)
 #pragma unroll
                     for (int j = 0; j < JB; ++j)
 #pragma unroll
-                        for (int u = 0; u < U; ++u) x[j][u] = 4 * (b + j) + rg < cnt ? x[j][u] : f32x4{0.f, 0.f, 0.f, 0.f};
+                        for (int u = 0; u < U; ++u) vv[j][u] = 4 * (b + j) + rg < cnt ? vv[j][u] : f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int j = 0; j < JB; ++j) {
-                    const float wj = __shfl(w, (lane & 48) | (b + j));           // weight of row 4 (b + j) + rg
+                for (int j = 0; j < JB; ++j)
 #pragma unroll
                     for (int u = 0; u < U; ++u) {
-                        o[u].x = fmaf(wj, x[j][u].x, o[u].x);
-                        o[u].y = fmaf(wj, x[j][u].y, o[u].y);
-                        o[u].z = fmaf(wj, x[j][u].z, o[u].z);
-                        o[u].w = fmaf(wj, x[j][u].w, o[u].w);
+                        o[u].x = fmaf(wj[b + j], vv[j][u].x, o[u].x);
+                        o[u].y = fmaf(wj[b + j], vv[j][u].y, o[u].y);
+                        o[u].z = fmaf(wj[b + j], vv[j][u].z, o[u].z);
+                        o[u].w = fmaf(wj[b + j], vv[j][u].w, o[u].w);
                     }
-                }
 #pragma unroll
                 for (int u = 0; u < U; ++u) asm volatile("" : "+v"(o[u]));
                 __builtin_amdgcn_sched_barrier(0);
