@@ -446,9 +446,15 @@ int launch_preproj_gather(int dtype, int code_type, const void* codes, const flo
 }
 
 // Encode, fp32, as a kernel of its own: one item per workgroup.
+template <int FORM, bool VEC>
 __global__ __launch_bounds__(kEncF32Threads) void vq_encode_f32_kernel(const EncodeJob job) {
     __shared__ EncF32Lds lds;
-    vq_encode_f32_body(job, blockIdx.x, lds);
+    vq_encode_f32_form_body<FORM, VEC>(job, blockIdx.x, lds);
+}
+template <int FORM>
+static void launch_encode_f32(const EncodeJob& job, int blocks, hipStream_t s) {
+    if (vq_encode_f32_vec(job, FORM)) vq_encode_f32_kernel<FORM, true><<<blocks, kEncF32Threads, 0, s>>>(job);
+    else vq_encode_f32_kernel<FORM, false><<<blocks, kEncF32Threads, 0, s>>>(job);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -709,7 +715,12 @@ int launch_vq_encode(const astra_vq_desc& d, const void* x, int64_t ldx, int64_t
         job.n_tokens = (int)n_tokens; job.G = G; job.K = K; job.dg = dg;
         job.code_bytes = code_bytes(d.code_type);
         job.n_tb = (int)ceil_div(n_tokens, kEncF32Tokens);
-        vq_encode_f32_kernel<<<(int)blocks, kEncF32Threads, 0, s>>>(job);
+        switch (vq_encode_f32_form(job)) {
+            case kEncF32Shared: launch_encode_f32<kEncF32Shared>(job, (int)blocks, s); break;
+            case kEncF32Long: launch_encode_f32<kEncF32Long>(job, (int)blocks, s); break;
+            case kEncF32Few: launch_encode_f32<kEncF32Few>(job, (int)blocks, s); break;
+            default: launch_encode_f32<kEncF32Solo>(job, (int)blocks, s); break;
+        }
     }
     return launch_status();
 }

@@ -109,7 +109,7 @@ def _update(B, c, t):
 
 
 def _encode(B, c, t):
-    desc = B.vq_desc("bf16", c["d"], c["groups"], c["words"])
+    desc = B.vq_desc(c.get("dtype", "bf16"), c["d"], c["groups"], c["words"])
     n = B.astra_vq_encode_workspace_bytes(desc, c["tokens"])
     B.astra_vq_encode_ws(desc, t(), c["tokens"], t(), t(), t(), _Tensor(n))
     return n

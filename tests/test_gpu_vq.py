@@ -27,8 +27,23 @@ ENCODE_CASES = [
     (300, 4, 256, 48, "f32", "normal"),
     (33, 3, 1000, 20, "f32", "normal"),           # uint16 codes, K not a multiple of the wave
     (5, 2, 300, 132, "f32", "normal"),            # two chunks of 64 values and a piece, five tokens over blocks of four
-    (6, 2, 70, 520, "f32", "normal"),             # slices too long to wait in LDS
+    (6, 2, 70, 520, "f32", "normal"),
     (3, 4, 300, 7, "f32", "normal"),              # slices of no whole 16-byte pieces
+    # fp32 forms: slices that wait in LDS whole and in stages, a token per wavefront out of LDS and without it; codebooks around a wavefront's and a workgroup's lanes
+    (9, 2, 300, 1024, "f32", "normal"),           # one full stage
+    (9, 1, 257, 1028, "f32", "normal"),           # a stage and a piece; two rounds of codewords
+    (5, 1, 256, 1027, "f32", "normal"),           # the same value by value
+    (6, 1, 129, 2048, "f32", "normal"),           # two full stages
+    (7, 3, 64, 1040, "f32", "normal"),            # a token per wavefront, staged twice
+    (7, 2, 16, 2050, "f32", "normal"),            # the same value by value, K of a quarter wavefront
+    (600, 4, 32, 40, "f32", "normal"),            # 600 workgroups: shared
+    (13, 4, 32, 40, "f32", "normal"),             # 16 workgroups: a token per wavefront
+    (9, 3, 128, 12, "f32", "normal"),             # without LDS, two codewords per lane
+    (9, 3, 129, 12, "f32", "normal"),             # one codeword too many for that
+    (9, 5, 64, 32, "f32", "normal"),              # two chunks of 16 values
+    (9, 5, 64, 29, "f32", "normal"),              # value by value
+    (9, 5, 65, 36, "f32", "normal"),
+    (2, 5, 33, 1, "f32", "normal"),               # a single value
     (256, 16, 256, 48, "bf16", "normal_shift"),   # ViT-Base
     (256, 32, 256, 24, "bf16", "student_t5"),     # GPT-2 small (dg padded to 32)
     (1024, 64, 1024, 64, "bf16", "rms_normal"),   # Llama-3-8B shape, full size
@@ -189,6 +204,30 @@ def test_wide_group_encode_exact_ties_across_wavefronts_and_passes():
         expect[later] = first
     assert np.array_equal(got, expect)
     assert np.array_equal(got, oracle.vq_encode(x, cb))
+
+
+def test_f32_encode_of_long_slices_keeps_pace():
+    """500 tokens of 768 values against 1024 codewords take about as long as one group as they do as two: 91 us and 49.  (Longer slices were once read
+    value by value from memory, 438 us and 51.)"""
+    import torch
+    from gpu_util import DEV
+    from paper_2505_19342_amd import binding as B
+    took = []
+    for groups in (1, 2):
+        x, cb = torch.randn(500, 768, device=DEV), torch.randn(groups, 1024, 768 // groups, device=DEV)
+        desc = B.vq_desc("f32", 768, groups, 1024)
+        codes, cnorm = torch.empty(500, groups, dtype=torch.int16, device=DEV), torch.empty(groups, 1024, device=DEV)
+        times = []
+        for _ in range(6):
+            begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            begin.record()
+            for _ in range(10):
+                B.astra_vq_encode(desc, x, 500, cb, cnorm, codes)
+            end.record()
+            torch.cuda.synchronize()
+            times.append(begin.elapsed_time(end))
+        took.append(min(times))
+    assert took[0] < 4 * took[1], took
 
 
 DECODE_CASES = [(192, 4, 256, 48, "f32"), (768, 16, 256, 48, "bf16"), (777, 32, 256, 24, "bf16"),

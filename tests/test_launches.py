@@ -153,3 +153,14 @@ def test_gathered_rows_do_not_hide_that_weights_come_from_memory(tmp_path):
                       for m, n, before, groups in ((83, 83, 41, 32), (87, 87, 43, 16), (73, 125, 62, 16), (100, 100, 50, 64))], tmp_path)
     for r in results:
         assert kernels(r)[0].startswith("gemm_wave_kernel<2, 2, 2, true"), kernels(r)
+
+
+def test_the_forms_of_the_fp32_encode(tmp_path):
+    """(tokens, groups, codewords, group length): shared 0, in stages 1, a token per wavefront 2, and without LDS 3; in 16-byte pieces or not."""
+    cases = [(64, 4, 256, 48, 0, True), (500, 1, 1024, 768, 0, True), (500, 1, 1024, 1028, 1, True), (500, 1, 1024, 1027, 1, False), (3, 4, 300, 7, 0, False),
+             (1024, 2, 16, 384, 2, True), (1028, 2, 16, 384, 0, True), (256, 4, 64, 48, 2, True), (257, 4, 64, 48, 0, True), (64, 1, 64, 512, 0, True),
+             (64, 1, 64, 768, 2, True), (64, 1, 64, 1100, 2, True), (4000, 4, 64, 32, 3, True), (64, 4, 65, 32, 0, True), (4000, 4, 128, 12, 3, True), (64, 4, 128, 16, 0, True),
+             (64, 4, 128, 3, 3, False)]
+    results = record([dict(entry="encode", dtype="f32", tokens=t, groups=g, words=k, d=g * dg) for t, g, k, dg, _, _ in cases], tmp_path)
+    for case, r in zip(cases, results):
+        assert kernels(r) == [f"vq_encode_f32_kernel<{case[4]}, {str(case[5]).lower()}>"], (case, kernels(r))
