@@ -715,7 +715,9 @@ static void launch_attn_f32(int blocks, const AttnParams& p, int head_dim, const
     }
 }
 
-static double encode_item_us(const EncodeJob& e) { return 256.0 * e.K * e.dg / 1048576.0 + 2.5; }      // 16.5 us and its start at K = 1024, dg = 64
+// 16.5 us and its start at K = 1024, dg = 64, beside other work.  (By quads an item of one block per wavefront takes what it took before: 1000 tokens x 64 groups, K = 1024
+// as a kernel of its own 13.9 us, 13.7; K = 256 6.6, 6.2.)
+static double encode_item_us(const EncodeJob& e) { return 256.0 * e.K * e.dg / 1048576.0 + 2.5; }
 
 // About how long an attention launch lasts with `items` workgroups of encodes behind its own, by either kernel (us).
 static double attention_us(const AttnParams& p, bool few, int64_t items, double item) {

@@ -85,9 +85,10 @@ __device__ __forceinline__ void vq_encode_fast_run_nks(const EncodeJob& job, int
     for (int it = 0; it < ITS; ++it) cb_off[it] = (uint32_t)(cw_l + (THREADS / 8) * it) * row_b + (uint32_t)piece * 16u;
     const uint32_t cb_off_max = (uint32_t)(K - 1) * row_b + (uint32_t)piece * 16u;
     const uint32_t cn_off = (uint32_t)(4 * NORM_LANES * wave + 4 * lane) * 4u, cn_off_max = (uint32_t)(K - 4) * 4u;
-    const char* s_cb = (const char*)job.codebook + (int64_t)(lo / n_tb) * K * row_b;      // the tile that is sent next
-    const char* s_cn = (const char*)(job.cnorm + (int64_t)(lo / n_tb) * K);
-    int s_block = lo % n_tb, s_tile = 0, s_step = 0;
+    int g = lo / n_tb, block = lo - g * n_tb;      // of the item that is worked on
+    const char* s_cb = (const char*)job.codebook + (int64_t)g * K * row_b;                // the tile that is sent next
+    const char* s_cn = (const char*)(job.cnorm + (int64_t)g * K);
+    int s_block = block, s_tile = 0, s_step = 0;
     auto send_tile = [&]() __attribute__((always_inline)) {
         if (s_step >= n_steps) return;
         const int buf = s_step % kEncBufs;
@@ -114,11 +115,11 @@ __device__ __forceinline__ void vq_encode_fast_run_nks(const EncodeJob& job, int
 
     // ---- tokens: raw values of an item, and as -2x
     u32x4 raw[TB][NKS];
-    auto load_tokens = [&](int item) __attribute__((always_inline)) {
-        const int g = item / n_tb, t0 = (item - g * n_tb) * TOKENS + wave * (32 * TB) + i32;
+    auto load_tokens = [&](int of_g, int of_block) __attribute__((always_inline)) {
+        const int t0 = of_block * TOKENS + wave * (32 * TB) + i32;
 #pragma unroll
         for (int b = 0; b < TB; ++b) {
-            const uint16_t* xrow = (const uint16_t*)job.x + (int64_t)min(t0 + 32 * b, n_tokens - 1) * job.ldx + (int64_t)g * dg;
+            const uint16_t* xrow = (const uint16_t*)job.x + (int64_t)min(t0 + 32 * b, n_tokens - 1) * job.ldx + (int64_t)of_g * dg;
 #pragma unroll
             for (int ks = 0; ks < NKS; ++ks) {
                 const int k = 16 * ks + 8 * h;
@@ -159,7 +160,7 @@ __device__ __forceinline__ void vq_encode_fast_run_nks(const EncodeJob& job, int
             }
     };
 
-    // ---- running argmin of this lane's tokens: quad grp (0..31) of tile til, and the quad's first three scores
+    // ---- running argmin of this lane's tokens: quad grp (0..15) of tile til, and the quad's first three scores
     float best[TB], best_in[TB], k0[TB], k1[TB], k2[TB];
     int grp[TB], til[TB];
     f32x16 acc[2][2];
@@ -185,7 +186,7 @@ __device__ __forceinline__ void vq_encode_fast_run_nks(const EncodeJob& job, int
     // the first tiles are on their way before the token values are asked for: the two latencies overlap
 #pragma unroll
     for (int t = 0; t < kEncBufs - 1; ++t) send_tile();
-    load_tokens(lo);
+    load_tokens(g, block);
     take_tokens();
     wait_vmem_all();
     __syncthreads();
@@ -195,6 +196,8 @@ __device__ __forceinline__ void vq_encode_fast_run_nks(const EncodeJob& job, int
 
     int step = 0;
     for (int item = lo; item < hi; ++item) {
+        const bool wraps = block + 1 == n_tb;                   // the next item is the next group's first
+        const int next_g = wraps ? g + 1 : g, next_block = wraps ? 0 : block + 1;
         const int t_load = n_tiles > 3 ? n_tiles - 3 : 0;       // the next item's tokens are asked for two tiles before the end
 #pragma unroll
         for (int b = 0; b < TB; ++b) {
@@ -210,7 +213,7 @@ __device__ __forceinline__ void vq_encode_fast_run_nks(const EncodeJob& job, int
             const int lim = K - t * kEncCw;                     // codewords of this tile and beyond
 #pragma unroll
             for (int u = 0; u < UNITS; ++u) {
-                if (u == UNITS - 1) {
+                if (u == UNITS - 1 && step + 1 < n_steps) {
                     // the next tile has landed (the one after it may be outstanding, and the tokens asked for a tile ago); every wavefront is done with
                     // the tile before this one, whose place takes the one three ahead
                     if (step + 2 < n_steps) {
@@ -220,7 +223,7 @@ __device__ __forceinline__ void vq_encode_fast_run_nks(const EncodeJob& job, int
                         wait_vmem_all();
                     }
                     __syncthreads();
-                    if (t == t_load && item + 1 < hi) load_tokens(item + 1);
+                    if (t == t_load && item + 1 < hi) load_tokens(next_g, next_block);
                     send_tile();
                 }
                 if (lim < kEncCw) {                             // codewords past K (the last tile of a K that is no multiple of 128) are infinitely far
@@ -251,7 +254,7 @@ __device__ __forceinline__ void vq_encode_fast_run_nks(const EncodeJob& job, int
 #pragma unroll
         for (int x = 0; x < 8; ++x) take_quad(1, UNITS - 1, x);
         close_tile(n_tiles - 1);
-        const int g = item / n_tb, t0 = (item - g * n_tb) * TOKENS + wave * (32 * TB) + i32;
+        const int t0 = block * TOKENS + wave * (32 * TB) + i32;
 #pragma unroll
         for (int b = 0; b < TB; ++b) {
             const int e = k0[b] == best[b] ? 0 : k1[b] == best[b] ? 1 : k2[b] == best[b] ? 2 : 3;
@@ -267,6 +270,8 @@ __device__ __forceinline__ void vq_encode_fast_run_nks(const EncodeJob& job, int
             }
         }
         if (item + 1 < hi) take_tokens();
+        g = next_g;
+        block = next_block;
     }
 }
 

@@ -652,7 +652,7 @@ __global__ __launch_bounds__(256) void vq_encode_bf16_kernel(const uint16_t* __r
 // of equal length.  Workgroup ids are remapped so that the items of a group run on the same XCD and find the group's codebook in that XCD's L2.
 // ------------------------------------------------------------------------------------------------
 template <int TB>
-__global__ __launch_bounds__(256, 2) void vq_encode_bf16_fast_kernel(const EncodeJob job) {
+__global__ __launch_bounds__(256, 2) void vq_encode_bf16_fast_kernel(const EncodeJob job, int chunk) {
     __shared__ u32x4 cb_lds[kEncBufs * kEncCbSlots];    // 4 x 16 KiB: [128 codewords][8 pieces of 8 bf16], swizzled
     __shared__ f32x4 cn_lds[kEncBufs * kEncCnSlots];    // 4 x 512 B
     // contiguous runs of workgroups per XCD; consecutive virtual ids share the group
@@ -663,7 +663,7 @@ __global__ __launch_bounds__(256, 2) void vq_encode_bf16_fast_kernel(const Encod
         vq_encode_fast_zero_lds<256>(cb_lds);
         __syncthreads();                               // zero fill done before any transfer lands
     }
-    const int items = job.G * job.n_tb, chunk = (items + total - 1) / total;
+    const int items = job.G * job.n_tb;
     vq_encode_fast_run_tb<256, TB>(job, min(vid * chunk, items), min((vid + 1) * chunk, items), cb_lds, cn_lds);
 }
 
@@ -681,15 +681,16 @@ int launch_vq_encode(const astra_vq_desc& d, const void* x, int64_t ldx, int64_t
             job.x = x; job.codebook = codebook; job.cnorm = cnorm; job.codes = codes; job.ldx = ldx;
             job.n_tokens = (int)n_tokens; job.G = G; job.K = K; job.dg = dg;
             job.code_bytes = d.code_type == ASTRA_CODE_U8 ? 1 : 2;
-            // 64 tokens per wavefront once that gives every unit an item: 1024 / 1531 / 2048 tokens x 64 groups, K = 1024: 13.5 / 18.9 / 20.3 us, with
-            // 32 tokens per wavefront 13.9 / 24.1 / 25.3; 700 x 32 groups, K = 256 (96 items): 6.6 and 5.6
+            // 64 tokens per wavefront where 32 would make more than one round of the slots, and for large codebooks once that gives every unit an item.  With 32 / 64,
+            // 64 groups of 64: 1000 tokens (256 items of 64 per wavefront), K = 16 5.6 / 5.9 us, K = 512 8.8 / 8.8, K = 1024 13.9 / 13.2; 2000 x 32 groups of 32, K = 16
+            // 4.8 / 5.1, K = 256 5.5 / 5.6; 2000 x 64 (more than a round), K = 256 10.5 / 8.7.
             const int64_t wide = ceil_div(n_tokens, 2 * kEncTokens) * G;
-            const bool two = wide >= kEncSlots / 2;
+            const bool two = n_tb * G > kEncSlots || (K > 256 && wide >= kEncSlots / 2);
             job.n_tb = (int)(two ? ceil_div(n_tokens, 2 * kEncTokens) : n_tb);
             const int64_t items = (int64_t)job.n_tb * G, chunk = ceil_div(items, (int64_t)kEncSlots);
             const int grid = (int)ceil_div(items, chunk);
-            if (two) vq_encode_bf16_fast_kernel<2><<<grid, 256, 0, s>>>(job);
-            else vq_encode_bf16_fast_kernel<1><<<grid, 256, 0, s>>>(job);
+            if (two) vq_encode_bf16_fast_kernel<2><<<grid, 256, 0, s>>>(job, (int)chunk);
+            else vq_encode_bf16_fast_kernel<1><<<grid, 256, 0, s>>>(job, (int)chunk);
             return launch_status();
         }
         if (G > 65535) return ASTRA_ERR_SHAPE;

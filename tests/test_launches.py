@@ -164,3 +164,12 @@ def test_the_forms_of_the_fp32_encode(tmp_path):
     results = record([dict(entry="encode", dtype="f32", tokens=t, groups=g, words=k, d=g * dg) for t, g, k, dg, _, _ in cases], tmp_path)
     for case, r in zip(cases, results):
         assert kernels(r) == [f"vq_encode_f32_kernel<{case[4]}, {str(case[5]).lower()}>"], (case, kernels(r))
+
+
+def test_tokens_per_wavefront_of_the_bf16_encode(tmp_path):
+    """64 where 32 would make more than one round of 512 workgroups, and for more than 256 codewords from 256 items on."""
+    cases = [(1000, 64, 256, 1, 512), (1025, 64, 256, 2, 320), (1000, 64, 512, 2, 256), (768, 64, 1024, 1, 384), (769, 64, 1024, 2, 256), (2048, 32, 16, 1, 512),
+             (2049, 32, 16, 2, 288)]
+    results = record([dict(entry="encode", tokens=t, groups=g, words=k, d=64 * g) for t, g, k, _, _ in cases], tmp_path)
+    for (t, g, k, blocks, grid), r in zip(cases, results):
+        assert [(n, s[0]) for n, s, *_ in r["launches"]] == [(f"vq_encode_bf16_fast_kernel<{blocks}>", grid)], (t, g, k, r["launches"])
