@@ -329,7 +329,8 @@ static int layer_forward_impl(const astra_layer_desc* desc, const void* x_local,
     // 1. indices this device transmits: the encode of the content rows (the class row is not encoded) depends on
     //    nothing else in the layer and nothing in the layer depends on it.  It is offered to the projection launch,
     //    which runs it as extra workgroups on compute units its tiles leave idle; if that launch does not take it
-    //    (other element type, tile count, group size), it runs as a kernel of its own on the same stream.
+    //    (other element type, tile count, group size), it is offered to the attention launch, which takes every fp32 encode, and else it
+    //    runs as a kernel of its own on the same stream.
     EncodeJob ej{};
     ej.x = (const char*)x_local + (size_t)at.n_cls * pl.D * eb;
     ej.codebook = codebook; ej.cnorm = cnorm; ej.codes = codes_local_out; ej.ldx = pl.D;

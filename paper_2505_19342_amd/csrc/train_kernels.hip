@@ -411,6 +411,7 @@ __global__ __launch_bounds__(kTrThreads) void stats_sum_kernel(const T* __restri
 // (part[g, unit, 0] when the run comes in from the previous unit, part[g, unit, 1] when it starts inside the unit and
 // goes on), which stats_fix_kernel adds in ascending unit order: a fixed tree, whatever the codes' distribution.
 constexpr int kUnitRows = 32;
+static_assert(2 * 8 * sizeof(float) >= kUnitRows * sizeof(uint16_t), "the partial sums of the narrowest groups (8 values) hold the transposed codes meanwhile");
 
 __global__ __launch_bounds__(kTrThreads) void stats_units_kernel(const uint16_t* __restrict__ x, int64_t ldx, const uint16_t* __restrict__ codebook,
                                                                  const int32_t* __restrict__ perm, const uint16_t* __restrict__ scode, int T, int G,

@@ -102,6 +102,20 @@ def test_llama_width_ragged_rows_and_lost_codes():
     np.testing.assert_array_equal(a["codes_v"], b["codes_v"])
 
 
+# d_model, query heads, KV heads, tokens over four devices, groups, codewords: 32 query rows per workgroup of attention, the encodes of K and V behind them (as
+# tests/test_launches.py checks)
+SHORT = [(4096, 32, 8, 400, 32, 1024), (4096, 32, 8, 240, 16, 256), (1536, 12, 3, 362, 16, 260), (1024, 8, 8, 140, 128, 16)]
+
+
+@pytest.mark.parametrize("lost", [False, True])
+@pytest.mark.parametrize("d,hq,hkv,seq_len,groups,words", SHORT)
+def test_short_sequences_of_128_wide_heads(d, hq, hkv, seq_len, groups, words, lost):
+    """Ragged token blocks, one and two blocks per wavefront, groups of an odd multiple of 8 values (24 and 8, filled up with zeros)."""
+    cfg = wl.LayerConfig("kv_short", "bf16", d, hq, hkv, 128, seq_len, 4, groups, words, causal=True, seed=73)
+    rng = np.random.default_rng(9)
+    run_case(cfg, 3, valid=(rng.random(cfg.n_nonlocal) > 0.2).astype(np.uint8) if lost else None)
+
+
 def test_results_do_not_depend_on_where_k_and_v_are_kept():
     from gpu_util import KvLayerOnGpu
     cfg = wl.GPT2_SMALL

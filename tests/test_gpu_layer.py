@@ -65,11 +65,17 @@ def test_biases_f32_and_bf16():
 
 
 def test_f32_launches_of_large_and_small_tiles():
-    """The fp32 product runs on 64 x 64 tiles once a launch has 128 of them and on 32 x 32 tiles below (the tiny shape): a
+    """The fp32 product runs on the largest of 64 x 64, 32 x 32 and 16 x 16 tiles of which a launch has 192 (the tiny shape: the smallest): a
     longer sequence with ragged rows takes the large ones for the projections and, with two heads of 96, output values
     beyond the first 64 lanes in the attention."""
     cfg = dataclasses.replace(wl.TINY_VIT, name="f32_long", seq_len=1500, n_q_heads=2, n_kv_heads=2, head_dim=96, seed=17)
     run_case(cfg, 1, biases=True)
+
+
+@pytest.mark.parametrize("groups,words,seq_len", [(32, 300, 256), (64, 256, 300), (96, 16, 1100)])
+def test_f32_rows_gathered_value_by_value(groups, words, seq_len):
+    """fp32 products whose gathered slices (6, 3 and 2 values) are no whole 16-byte pieces, on tiles of 16 to 64."""
+    run_case(dataclasses.replace(wl.TINY_VIT, name="f32_gather", n_groups=groups, codebook_size=words, seq_len=seq_len, seed=18), 1, biases=True)
 
 
 @pytest.mark.parametrize("i_dev", [0, 1, 2])
@@ -138,7 +144,7 @@ def test_llama_dims_ragged_rows_in_every_projection_tile_shape(seq_len, lo, fuse
 
 # width, local rows, visible peer rows, groups, codewords, and the form of the projection launch (GATHER: the peers' rows from their codes; ENC: with
 # the encode), as tests/test_launches.py checks
-MODEL_OF_WIDTH = {256: (4, 2, 64), 512: (4, 2, 128), 768: (12, 12, 64), 1024: (8, 8, 128), 2048: (16, 4, 128), 4096: (32, 8, 128)}
+MODEL_OF_WIDTH = {256: (4, 2, 64), 320: (5, 5, 64), 512: (4, 2, 128), 640: (10, 10, 64), 768: (12, 12, 64), 1024: (8, 8, 128), 2048: (16, 4, 128), 4096: (32, 8, 128)}
 PROJECTION_LAUNCHES = [
     (256, 36, 14, 4, 16, "wave<1, 1, 2> GATHER ENC"),
     (512, 27, 6, 4, 256, "wave<1, 1, 2> GATHER"),
@@ -153,6 +159,10 @@ PROJECTION_LAUNCHES = [
     (768, 733, 0, 16, 1024, "wave<4, 4, 1> ENC"),
     (768, 590, 197, 16, 1024, "wave<4, 4, 1> GATHER ENC"),
     (2048, 1015, 25, 16, 16, "wave<4, 4, 1> GATHER"),
+    (256, 3401, 0, 8, 256, "wave<4, 4, 1> ENC"),                 # one slice of 64 per wavefront
+    (320, 1673, 500, 8, 256, "wave<4, 4, 1> GATHER ENC"),        # two for the first
+    (512, 1675, 200, 8, 256, "wave<4, 4, 1> GATHER ENC"),        # two
+    (640, 627, 500, 16, 1024, "wave<4, 4, 1> GATHER ENC"),       # three and two
     (512, 925, 180, 8, 1024, "tile<128, 128> GATHER"),
 ]
 

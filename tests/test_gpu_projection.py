@@ -27,6 +27,8 @@ PRODUCTS = [
     (1024, 4096, 576, "tile<128, 128>"),
     (1028, 4104, 64, "tile<128, 256>"),
     (2052, 4104, 64, "tile<256, 256>"),
+    # slices in halves: four to seven per wavefront (prologue, pairs in steady state, one to three in the tail), and one more for some of them
+    *[(252, 8312, k, "wave<4, 4, 1>") for k in (1024, 1280, 1536, 1600, 1664, 1728, 1792)],
     # the loop in halves: two tiles of 64 (no more than the prologue fetches), three to seven (its steady part comes from four on, two at a time)
     *[(1028, 4104, k, "tile<128, 256>") for k in (128, 192, 256, 320, 448)],
     *[(2052, 4104, k, "tile<256, 256>") for k in (128, 192, 256, 320, 448)],

@@ -15,6 +15,7 @@ LARGE_LDS = [
     dict(entry="step", hq=64, hkv=8, dh=128, n_local=8001, n_nonlocal=40000, groups=32, words=1024),
     dict(entry="step", hq=32, hkv=8, dh=128, n_local=100, n_nonlocal=300, groups=32, words=1024, dtype="f32"),
     dict(entry="stats", groups=64, dg=64, words=1024, tokens=16384),
+    dict(entry="stats", groups=129, dg=8, words=1024, tokens=16384),
 ]
 
 
@@ -173,3 +174,27 @@ def test_tokens_per_wavefront_of_the_bf16_encode(tmp_path):
     results = record([dict(entry="encode", tokens=t, groups=g, words=k, d=64 * g) for t, g, k, _, _ in cases], tmp_path)
     for (t, g, k, blocks, grid), r in zip(cases, results):
         assert [(n, s[0]) for n, s, *_ in r["launches"]] == [(f"vq_encode_bf16_fast_kernel<{blocks}>", grid)], (t, g, k, r["launches"])
+
+
+def test_workgroups_per_group_of_the_sort(tmp_path):
+    """A group's codes in ranges on up to four workgroups while all of them fit 256 units and the partial sums' place holds the transposed codes; else one."""
+    cases = [(16384, 48, 1024, 8, 4), (16384, 64, 1024, 64, 4), (16384, 65, 1024, 8, 2), (16384, 128, 1024, 8, 2), (16384, 129, 1024, 8, 1), (16384, 64, 1024, 6, 1)]
+    results = record([dict(entry="stats", tokens=t, groups=g, words=k, dg=dg) for t, g, k, dg, _ in cases], tmp_path)
+    for (t, g, k, dg, parts), r in zip(cases, results):
+        (name, grid), = [(n, s) for n, s, *_ in r["launches"] if n in ("sort_group_kernel", "sort_whole_group_kernel")]
+        assert (name == "sort_group_kernel") == (parts > 1) and grid[:2] == [g, parts], (t, g, k, dg, name, grid)
+
+
+def test_attention_of_short_sequences(tmp_path):
+    """32 query rows per workgroup where those make a single round of 256, unless encodes behind them would lose units; the shapes the GPU tests name."""
+    from test_gpu_kv_variant import SHORT
+    layer = lambda dh, h, n, m=96: dict(entry="layer", d=64 * h, hq=h, hkv=h, dh=dh, causal=True, n_local=n, n_nonlocal=m, groups=16, words=256)
+    calls = [layer(64, 12, 672), layer(64, 12, 673), layer(128, 32, 256, 200), layer(128, 32, 257, 200)]
+    for r, name in zip(record(calls, tmp_path), ("attn_short_kernel<64, false, false>", "attn_bf16_kernel<64", "attn_short_kernel<128", "attn_bf16_kernel<128")):
+        assert any(k.startswith(name) for k in kernels(r)), (name, kernels(r))
+    calls = [dict(entry="kv", d=d, hq=hq, hkv=hkv, dh=128, causal=True, n_local=t // 4, n_nonlocal=t - t // 4, groups=g, words=w) for d, hq, hkv, t, g, w in SHORT]
+    calls.append(dict(calls[0], n_local=256, n_nonlocal=768))
+    results = record(calls, tmp_path)
+    for c, r in zip(calls[:-1], results):
+        assert "attn_short_kernel<128, false, true>" in kernels(r), (c, kernels(r))
+    assert "attn_bf16_kernel<128, true, false, 2, true>" in kernels(results[-1])
