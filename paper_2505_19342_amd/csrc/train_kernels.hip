@@ -302,7 +302,9 @@ __global__ __launch_bounds__(kSortThreads) void sort_whole_group_kernel(const ui
     sort_group_body<false>(tcodes, stride, T, K, steps, counts, offs, perm, scode);
 }
 
-// One launch or three?  (Timed with one workgroup per group, which is the slower form of the one launch.)  One wherever a group fits a unit's LDS and
+// One launch or three?  The lines are those of one workgroup per group; with ranges, the form up to 128 groups, the one launch is the faster one for
+// more sizes than they give it (whole statistics, three / one in ranges, K = 1024: 32 groups x 16384 tokens 62.0 / 53.5 us, x 8000 43.1 / 37.8, 16 groups 57.3 / 51.8;
+// 64 groups x 8000, K = 256 38.1 / 35.6).  One wherever a group fits a unit's LDS and
 //  * there are many groups and many codes: the three launches' strided reads and scattered words then cost more than the ballots
 //    (whole statistics, one launch against three, 64 groups x 16384 tokens: K = 256 61.6 / 66.1 us, K = 1024 68.4 / 83.1; 64 x 8000, K = 256:
 //    41.7 / 38.4; 48 x 5000, K = 1024: 38.2 / 42.4), or
