@@ -452,11 +452,12 @@ __global__ __launch_bounds__(kAttThreads) void attn_bf16_kernel(const AttnParams
 // In a chunk 16 lanes hold a row, four values (16 bytes) each and 64 further ones per U = ceil(dh / 64), and a load covers four rows; a lane's sixteen
 // partial dots (rows 4j + lane / 16) are added over the 16 lanes so that lane (r, c) of the wavefront ends with the logit of row 4c + r.  Bound by the
 // latency of the chain keys -> logits -> values, so by the loads in flight on a unit: a wavefront's (JB U at a time, batches beyond a ragged chunk
-// left out; the first batch of values lands behind the softmax) times its wavefronts.  Eight loads per batch leave room for three to four wavefronts per SIMD.  All of a chunk's keys and values at once (176 registers and more,
-// one or two wavefronts) are no faster for one round of workgroups and slower beyond it.  A key per lane and a cache line per lane and load / everything at once /
-// this: 64 rows x 3 heads of 64 over 256 keys 7.8 / 4.4 / 4.3 us; 12 heads, 257 rows over 1025 keys: heads of 64 145 / 79 / 65, of 128
-// 257 / 211 / 115, of 256 489 / 365 / 226; 100 causal rows, heads of 128 12.5 / 20.6 / 8.1, of 256 19.1 / 31.6 / 12.5.  Error against fp64 3.1e-7
-// of the norm, now 1.5e-7.
+// left out; the first batch of values lands behind the softmax) times its wavefronts.  Heads of up to 64 take a chunk in one batch, wider ones in batches of eight
+// loads, which leaves room for three to four wavefronts per SIMD.  A key per lane and a cache line per lane and load / keys and values of a chunk at once (176 registers
+// and more, one or two wavefronts) / this: 64 rows x 3 heads of 64 over 256 keys 7.8 / 4.3 / 4.1 us; 12 heads, 257 rows over 1025 keys: heads of 64
+// 146 / 78 / 62, of 128 257 / 131 / 113, of 256 489 / 361 / 225; 100 causal rows, heads of 64 9.1 / 9.1 / 6.5, of 128 12.4 / 11.9 / 8.0, of 256
+// 19.2 / 25.6 / 12.5.  (Heads of 64 in two batches of eight: 4.9 for the last of 64, but 0.4 to 0.8 us more for layers whose keys are not in the second-level cache:
+// 82 rows over 328 keys 15.6, now 15.0.)  Error against fp64 3.1e-7 of the norm, now 1.5e-7.
 // VEC = false: head dimensions or addresses that 16-byte pieces do not fit; a key per lane, 16 of its values at a time (one by one: 3 heads of 50, 64 rows over 256 keys
 // 13.0 us, now 10.3; 12 heads of 130, 257 rows over 1025 keys 1766, now 850).
 //
@@ -465,7 +466,7 @@ __global__ __launch_bounds__(kAttThreads) void attn_bf16_kernel(const AttnParams
 template <int U, bool VEC, bool ENC>
 __global__ __launch_bounds__(256) void attn_f32_kernel(const AttnParams p, int dh, const AttnEncode e) {
     constexpr int kWaves = 4;
-    constexpr int JB = U == 1 ? 8 : U == 2 ? 4 : 2;        // loads of a batch, 4 rows each, per 64 values of a row
+    constexpr int JB = U == 1 ? 16 : U == 2 ? 4 : 2;       // loads of a batch, 4 rows each, per 64 values of a row
     __shared__ __align__(16) float part[kWaves][U * kWave + 4];
     if constexpr (ENC) {
         __shared__ EncF32Lds enc_lds;
@@ -509,9 +510,16 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const AttnParams p, int d
         const int key = VEC ? 4 * sub + rg : lane;                              // this lane's row in the chunk
         const unsigned long long bits = src != 0 || p.valid_bits == nullptr ? ~0ull : p.valid_bits[base >> 6];
         const bool arrived = key < cnt && ((bits >> key) & 1ull);
-        // rows beyond the chunk repeat its last one; their logits are dropped and their values are zeros (an infinity times a weight of zero is none)
-        auto piece = [&](const float* base_, int j, int u) __attribute__((always_inline)) {
-            return *reinterpret_cast<const f32x4*>((const char*)base_ + ((uint32_t)min(4 * j + rg, cnt - 1) * ld_b + (uint32_t)col[u] * 4u));
+        // VEC: values of rows beyond the chunk are zeros (an infinity times a weight of zero is none), their logits are dropped.  Up to 64 values a row the rows are
+        // out of a buffer's range, which costs nothing (a layer of 28 rows over 81 keys 11.5 -> 11.3 us); on wider heads, where the buffers' addresses
+        // take a wavefront's room (heads of 256 12.6 -> 16.2), they repeat the last row and its values are replaced.
+        constexpr bool BUFFERS = U == 1;
+        const int range = (int)((uint32_t)(cnt - 1) * ld_b + 4u * (uint32_t)dh);
+        const auto k_buf = __builtin_amdgcn_make_buffer_rsrc((void*)Kp, 0, range, 0x00020000), v_buf = __builtin_amdgcn_make_buffer_rsrc((void*)Vp, 0, range, 0x00020000);
+        auto piece = [&](const float* base_, __amdgpu_buffer_rsrc_t buf, int j, int u) __attribute__((always_inline)) {
+            const uint32_t at = (uint32_t)(BUFFERS ? 4 * j + rg : min(4 * j + rg, cnt - 1)) * ld_b + (uint32_t)col[u] * 4u;
+            if (BUFFERS) return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(buf, (int)at, 0, 0));
+            return *reinterpret_cast<const f32x4*>((const char*)base_ + at);
         };
         constexpr int kRows = VEC ? 1 : U <= 2 ? 16 : 8;        // not VEC: value rows in flight, the first of them on narrow heads sent before the keys
         constexpr bool EARLY = U <= 2;
@@ -527,7 +535,7 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const AttnParams p, int d
 #pragma unroll
             for (int j = 0; j < JB; ++j)
 #pragma unroll
-                for (int u = 0; u < U; ++u) vv[j][u] = piece(Vp, b + j, u);
+                for (int u = 0; u < U; ++u) vv[j][u] = piece(Vp, v_buf, b + j, u);
         };
         float s;
         if (VEC) {
@@ -541,7 +549,7 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const AttnParams p, int d
 #pragma unroll
                 for (int u = 0; u < U; ++u)
 #pragma unroll
-                    for (int j = 0; j < JB; ++j) kk[j][u] = piece(Kp, b + j, u);
+                    for (int j = 0; j < JB; ++j) kk[j][u] = piece(Kp, k_buf, b + j, u);
                 __builtin_amdgcn_sched_barrier(0);         // all of them are on their way before the first is waited for
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
@@ -625,7 +633,7 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const AttnParams p, int d
             for (int b = 0; b < 16; b += JB) {
                 if (b > 0 && 4 * b >= cnt) break;
                 if (b > 0) load_values(b);
-                if (4 * (b + JB) > cnt)
+                if (!BUFFERS && 4 * (b + JB) > cnt)
 #pragma unroll
                     for (int j = 0; j < JB; ++j)
 #pragma unroll
