@@ -53,6 +53,7 @@ struct LayerPlan {
     bool vt;                 // V, V-hat kept transposed for the attention kernel (bf16)
     int ldv_loc, ldv_hat;    // padded token counts of the transposed V buffers
     size_t off_q, off_k, off_v, off_kh, off_vh, off_o, off_xhat, off_scores, total;
+    size_t part;             // partial results of the attention, behind `total`: a workspace without them is taken, and the attention walks every block whole
 };
 
 static int make_plan(const astra_layer_desc* desc, LayerPlan* pl) {
@@ -94,6 +95,11 @@ static int make_plan(const astra_layer_desc* desc, LayerPlan* pl) {
                    (size_t)a.n_local * desc->vq.n_groups * desc->vq.codebook_size * 4 <= ((size_t)256 << 20);
     pl->off_scores = take(pl->wide_enc ? (size_t)a.n_local * desc->vq.n_groups * desc->vq.codebook_size * 4 : 0);
     pl->total = off > 0 ? off : 256;
+    AttnParams ap = attn_params(a, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
+    ap.v_transposed = pl->vt ? 1 : 0;
+    EncodeJob ej{};
+    ej.n_tokens = a.n_local; ej.G = desc->vq.n_groups; ej.K = desc->vq.codebook_size; ej.dg = dg;
+    pl->part = attention_part_bytes(desc->vq.dtype, ap, a.head_dim, &ej, a.n_local > 0 && vq_encode_fast_ok(ej.K, dg) ? 1 : 0);
     return ASTRA_OK;
 }
 
@@ -102,6 +108,7 @@ struct KvPlan {
     bool vt;
     int ldv_loc, ldv_hat;
     size_t off_q, off_k, off_v, off_vt, off_kh, off_vh, off_o, total;
+    size_t part;             // as in LayerPlan
 };
 
 static int make_kv_plan(const astra_layer_kv_desc* desc, KvPlan* pl) {
@@ -134,6 +141,11 @@ static int make_kv_plan(const astra_layer_kv_desc* desc, KvPlan* pl) {
     pl->off_vh = take((size_t)(pl->vt ? pl->ldv_hat : pl->Tn_vis) * pl->dkv * eb);
     pl->off_o = take((size_t)pl->Tq * pl->dq * eb);
     pl->total = off > 0 ? off : 256;
+    AttnParams ap = attn_params(a, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
+    ap.v_transposed = pl->vt ? 1 : 0;
+    EncodeJob ej[2] = {};
+    for (EncodeJob& j : ej) { j.n_tokens = a.n_local; j.G = desc->vq.n_groups; j.K = desc->vq.codebook_size; j.dg = pl->dkv / desc->vq.n_groups; }
+    pl->part = attention_part_bytes(dtype, ap, a.head_dim, ej, a.n_local > 0 && vq_encode_fast_ok(ej[0].K, ej[0].dg) ? 2 : 0);
     return ASTRA_OK;
 }
 
@@ -286,7 +298,7 @@ int astra_mixed_attention_valid(const astra_attn_desc* desc, const void* q, cons
 size_t astra_layer_workspace_bytes(const astra_layer_desc* desc) {
     LayerPlan pl;
     if (make_plan(desc, &pl) != ASTRA_OK) return 0;
-    return pl.total;
+    return pl.total + pl.part;
 }
 
 static int layer_forward_impl(const astra_layer_desc* desc, const void* x_local, const void* codes_nonlocal,
@@ -296,7 +308,7 @@ static int layer_forward_impl(const astra_layer_desc* desc, const void* x_local,
                               void* y_out, void* codes_local_out, void* workspace, size_t workspace_bytes, void* stream,
                               void* const* ev, int* plan_encode_fused = nullptr, const uint64_t* valid_bits = nullptr,
                               const float* residual = nullptr, const float* pre_k = nullptr, const float* pre_v = nullptr,
-                              float rope_base = 0.f) {
+                              float rope_base = 0.f, void* part = nullptr, size_t part_bytes = 0) {
     // plan_encode_fused: validate the shapes and report whether the projection launch would carry the encode;
     // nothing is launched and no pointer is dereferenced
     const bool plan_only = plan_encode_fused != nullptr;
@@ -389,6 +401,8 @@ static int layer_forward_impl(const astra_layer_desc* desc, const void* x_local,
     ap.valid_bits = (const unsigned long long*)valid_bits;
     ap.ldv_loc = pl.ldv_loc;
     ap.ldv_hat = pl.ldv_hat;
+    ap.part = (float*)(part ? part : ws + pl.total);
+    ap.part_bytes = part ? part_bytes : plan_only ? pl.part : workspace_bytes - pl.total;
     GemmProblem po = {};
     po.a = O; po.b = wo; po.bias = bo; po.c = y_out; po.M = pl.Tq; po.N = pl.D; po.K = pl.dq; po.lda = pl.dq; po.ldc = pl.D;
     po.c_mode = kCF32;      // y leaves the layer as the fp32 accumulator, for both element types
@@ -548,7 +562,7 @@ int astra_layer_forward_valid(const astra_layer_desc* desc, const void* x_local,
 size_t astra_layer_kv_workspace_bytes(const astra_layer_kv_desc* desc) {
     KvPlan pl;
     if (make_kv_plan(desc, &pl) != ASTRA_OK) return 0;
-    return pl.total;
+    return pl.total + pl.part;
 }
 
 int astra_layer_forward_kv(const astra_layer_kv_desc* desc, const void* x_local, const void* codes_k_nonlocal,
@@ -627,6 +641,8 @@ int astra_layer_forward_kv(const astra_layer_kv_desc* desc, const void* x_local,
     ap.valid_bits = (const unsigned long long*)valid_nonlocal_bits;
     ap.ldv_loc = pl.ldv_loc;
     ap.ldv_hat = pl.ldv_hat;
+    ap.part = (float*)(ws + pl.total);
+    ap.part_bytes = workspace_bytes - pl.total;
     rc = launch_attention(dtype, ap, at.head_dim, s, false, offer ? ej : nullptr, offer ? 2 : 0, offer ? &enc_fused : nullptr);
     if (rc) return rc;
     if (!enc_fused && at.n_local > 0) {
@@ -641,7 +657,7 @@ int astra_layer_forward_kv(const astra_layer_kv_desc* desc, const void* x_local,
 size_t astra_block_workspace_bytes(const astra_block_desc* desc) {
     BlockPlan bp;
     if (make_block_plan(desc, &bp) != ASTRA_OK) return 0;
-    return bp.total;
+    return bp.total + bp.layer.part;
 }
 
 // validate_only: every check of the call, no launch
@@ -700,7 +716,7 @@ static int block_forward_impl(const astra_block_desc* desc, const astra_block_we
     // r = x + layer(h), written to x_out by the output projection's epilogue
     rc = layer_forward_impl(&desc->layer, h, codes_nonlocal, w->codebook, w->cnorm, w->wq, w->wk, w->wv, w->wo, w->bq, w->bk, w->bv,
                             w->bo, x_out, codes_local_out, workspace, pl.total, stream, nullptr, nullptr, valid_nonlocal_bits, x,
-                            nullptr, nullptr, desc->rope_base);
+                            nullptr, nullptr, desc->rope_base, ws + bp.total, workspace_bytes - bp.total);
     if (rc) return rc;
     rc = launch_norm(dtype, desc->norm_kind, x_out, pl.Tq, pl.D, desc->eps, w->norm2_gain, w->norm2_bias, h2, s);
     if (rc) return rc;

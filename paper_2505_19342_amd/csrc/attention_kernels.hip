@@ -6,6 +6,7 @@
 #include "vq_encode_f32_body.h"
 
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 namespace astra {
@@ -43,6 +44,8 @@ constexpr int kAttThreads = 512;
 constexpr int kXcdsA = 8;
 constexpr int kAttCus = 256;     // compute units of the device the launch shapes are chosen for
 constexpr float kLazy = 8.f;     // base-2 units
+constexpr int kPartFloats = kAttQ * 128 + 2 * kAttQ;     // partial result of a part of a walk: O of 128 rows, their maxima, their sums
+constexpr int kMaxParts = 8;
 
 __device__ __forceinline__ int xcd_remap_attn(int wg, int total) {
     const int q = total / kXcdsA, r = total % kXcdsA;
@@ -61,8 +64,12 @@ __device__ __forceinline__ int swz_vt(int r) { return (r >> 1) & 7; }
 // LOST: the caller passed a validity bit per non-local token (an instantiation of its own, so that the code for it does
 // not disturb the register allocation and schedule of the kernel that runs without)
 // ENC: VQ encodes ride in the launch (AttnEncode)
-template <int DH, bool VT, bool LOST = false, int NPAR = 2, bool ENC = false>
-__global__ __launch_bounds__(kAttThreads) void attn_bf16_kernel(const AttnParams p, const AttnEncode e) {
+// CUT: walks may be cut between workgroups (AttnParams::n_whole, n_cut); a part leaves its unnormalised result in AttnParams::part.  Few query blocks leave
+// units idle, and a few more than a round of them leave most units idle for a second whole walk.  A part costs 6 us before its first tile and after its
+// last, and its 64 KiB.  Layers 4096 wide, every walk whole / cut (us): 20 + 4096 rows 132.1 / 123.5, 300 + 2565 157.8 / 151.1, 512 + 3584 185.6 / 175.9,
+// 1030 + 2565 261.1 / 251.0, 1400 + 4096 383.6 / 366.2; with K and V quantised after projection 300 + 2100 104.3 / 100.9, 1280 + 3840 276.1 / 261.9.
+template <int DH, bool VT, bool LOST, int NPAR, bool ENC, bool CUT>
+__device__ __forceinline__ void attn_bf16_body(const AttnParams& p, const AttnEncode& e) {
     static_assert(NPAR == 2 || NPAR == 4, "two or four tile parities");
     constexpr int NQG = 8 / NPAR;              // query groups of 32 rows (wavefronts per parity)
     constexpr int kQRows = 32 * NQG;           // query rows per workgroup
@@ -97,9 +104,27 @@ __global__ __launch_bounds__(kAttThreads) void attn_bf16_kernel(const AttnParams
     const int ptid = tid & (kParThreads - 1);
 
     const int n_qb = (p.Tq + kQRows - 1) / kQRows;
-    const int vt_id = xcd_remap_attn(blockIdx.x, ENC ? e.n_attn_wgs : (int)gridDim.x);
-    const int head = vt_id / n_qb;
-    const int qb = n_qb - 1 - (vt_id % n_qb);
+    int head, qb, part = 0;
+    bool cut = false;
+    if (CUT) {
+        // one block of every head of the XCD after the other, the whole walks first: the long pieces start first and the short ones fill the end
+        int piece;
+        if (p.Hq % kXcdsA == 0) {
+            const int per_xcd = p.Hq / kXcdsA, slot = blockIdx.x / kXcdsA;
+            head = (int)blockIdx.x % kXcdsA * per_xcd + slot % per_xcd;
+            piece = slot / per_xcd;
+        } else {
+            head = (int)blockIdx.x % p.Hq;
+            piece = (int)blockIdx.x / p.Hq;
+        }
+        cut = piece >= p.n_whole;
+        qb = cut ? n_qb - 1 - (piece - p.n_whole) / p.n_cut : p.n_whole - 1 - piece;
+        part = cut ? (piece - p.n_whole) % p.n_cut : 0;
+    } else {
+        const int vt_id = xcd_remap_attn(blockIdx.x, ENC ? e.n_attn_wgs : (int)gridDim.x);
+        head = vt_id / n_qb;
+        qb = n_qb - 1 - (vt_id % n_qb);
+    }
     const int hk = head / (p.Hq / p.Hkv);
     const int q0 = qb * kQRows;
     const int Tq = p.Tq;
@@ -125,11 +150,18 @@ __global__ __launch_bounds__(kAttThreads) void attn_bf16_kernel(const AttnParams
 
     const int n_hat_tiles = (p.Tn_vis + kAttKV - 1) / kAttKV;
     const int loc_rows = p.causal ? min(q0 + kQRows, Tq) : Tq;    // local keys any row of this block may see
-    const int n_tiles = n_hat_tiles + (loc_rows + kAttKV - 1) / kAttKV;
-    const int n_pairs = (n_tiles + NPAR - 1) / NPAR;
+    int n_tiles = n_hat_tiles + (loc_rows + kAttKV - 1) / kAttKV;     // the walk ends before this tile ...
+    int n_pairs = (n_tiles + NPAR - 1) / NPAR;
+    int t_first = 0;                                                  // ... and begins at this one
+    if (CUT && cut) {                                                 // every part has a pair: the launcher sees to it
+        const int from = n_pairs * part / p.n_cut, to = n_pairs * (part + 1) / p.n_cut;
+        t_first = NPAR * from;
+        n_tiles = min(NPAR * to, n_tiles);
+        n_pairs = to - from;
+    }
     const int wave_q_lo = q0 + 32 * qg;
 
-    // ---- tiles of this wavefront's parity: own iteration i works on tile NPAR * i + par of the walk (visible
+    // ---- tiles of this wavefront's parity: own iteration i works on tile t_first + NPAR * i + par of the walk (visible
     // non-local tiles first, local tiles after them).  An index past the end (odd tile count) is the last
     // tile again with every key masked, so all wavefronts run the same number of iterations.
     struct Tile {
@@ -137,7 +169,7 @@ __global__ __launch_bounds__(kAttThreads) void attn_bf16_kernel(const AttnParams
         int row0, count;
     };
     auto tile_of = [&](int i) {
-        const int t_in = NPAR * i + par;
+        const int t_in = t_first + NPAR * i + par;
         const int t = t_in < n_tiles ? t_in : n_tiles - 1;
         Tile tl;
         tl.is_loc = t >= n_hat_tiles;
@@ -415,6 +447,32 @@ __global__ __launch_bounds__(kAttThreads) void attn_bf16_kernel(const AttnParams
             ao[q] = __builtin_amdgcn_exp2f(mo[q] - m_safe);
             l += lo[q] * ao[q];
         }
+        if (CUT && cut) {
+            if (wave_q_lo >= Tq) return;                  // a group without rows
+            // a part of a walk: unnormalised, in the register order of the lanes (1 KiB per store), with its maximum and sum per row
+            const int slot = (head * (n_qb - p.n_whole) + n_qb - 1 - qb) * p.n_cut + part;
+            float* __restrict__ P = p.part + (int64_t)slot * kPartFloats;
+#pragma unroll
+            for (int db = 0; db < NDB; ++db)
+#pragma unroll
+                for (int vq = 0; vq < 4; ++vq) {
+                    f32x4 o;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const int v = 4 * vq + e;
+                        o[e] = acc_o[db][v] * a0;
+#pragma unroll
+                        for (int q = 0; q < NPAR - 1; ++q)
+                            o[e] += xch[(((qg * (NPAR - 1) + q) * NDB + db) * 16 + v) * 64 + lane] * ao[q];
+                    }
+                    *reinterpret_cast<f32x4*>(P + (((qg * NDB + db) * 4 + vq) * 64 + lane) * 4) = o;
+                }
+            if (h == 0) {
+                P[kAttQ * DH + 32 * qg + i32] = m;
+                P[kAttQ * DH + kAttQ + 32 * qg + i32] = l;
+            }
+            return;
+        }
         const float inv = l > 0.f ? 1.f / l : 0.f;
         const float c0 = a0 * inv;
         float co[NPAR - 1];
@@ -443,6 +501,82 @@ __global__ __launch_bounds__(kAttThreads) void attn_bf16_kernel(const AttnParams
             if (p.lse && h == 0) p.lse[(int64_t)head * Tq + qrow] = (m + log2f(l)) * 0.6931471805599453f;
         }
     }
+}
+
+template <int DH, bool VT, bool LOST = false, int NPAR = 2, bool ENC = false>
+__global__ __launch_bounds__(kAttThreads) void attn_bf16_kernel(const AttnParams p, const AttnEncode e) {
+    attn_bf16_body<DH, VT, LOST, NPAR, ENC, false>(p, e);
+}
+
+template <bool LOST, bool ENC>
+__global__ __launch_bounds__(kAttThreads) void attn_cut_kernel(const AttnParams p, const AttnEncode e) {
+    attn_bf16_body<128, true, LOST, 2, ENC, true>(p, e);
+}
+
+// ------------------------------------------------------------------------------------------------
+// The parts of the walks that were cut: O = sum_i 2^(m_i - m) O_i / sum_i 2^(m_i - m) l_i, parts in ascending order.  A wavefront owns 32 rows x 32
+// channels of a block, in the lanes' order of the accumulators that wrote them; all parts are requested before the first is needed.  Bound by memory: 16.8 MB, 256 parts, in 5.5 us.
+// ------------------------------------------------------------------------------------------------
+template <int PARTS>
+__global__ __launch_bounds__(256) void attn_merge_kernel(const AttnParams p) {
+    constexpr int DH = 128;
+    const int n_qb = (p.Tq + kAttQ - 1) / kAttQ;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, i32 = lane & 31, h = lane >> 5;
+    const int blk = blockIdx.x >> 2, qg = blockIdx.x & 3, db = wave;      // the cut blocks of a head one after the other, the last first
+    const int head = blk / (n_qb - p.n_whole), qb = n_qb - 1 - blk % (n_qb - p.n_whole);
+    if (qb * kAttQ + 32 * qg >= p.Tq) return;
+    const float* __restrict__ P = p.part + (int64_t)blk * PARTS * kPartFloats;
+    f32x4 o[PARTS][4];
+    float m_i[PARTS], l_i[PARTS];
+#pragma unroll
+    for (int i = 0; i < PARTS; ++i) {
+        m_i[i] = P[(int64_t)i * kPartFloats + kAttQ * DH + 32 * qg + i32];
+        l_i[i] = P[(int64_t)i * kPartFloats + kAttQ * DH + kAttQ + 32 * qg + i32];
+    }
+#pragma unroll
+    for (int i = 0; i < PARTS; ++i)
+#pragma unroll
+        for (int vq = 0; vq < 4; ++vq)
+            o[i][vq] = *reinterpret_cast<const f32x4*>(P + (int64_t)i * kPartFloats + (((qg * 4 + db) * 4 + vq) * 64 + lane) * 4);
+    float m = m_i[0];
+#pragma unroll
+    for (int i = 1; i < PARTS; ++i) m = fmaxf(m, m_i[i]);
+    const float m_safe = m == -INFINITY ? 0.f : m;
+    float l = 0.f;
+#pragma unroll
+    for (int i = 0; i < PARTS; ++i) {
+        m_i[i] = __builtin_amdgcn_exp2f(m_i[i] - m_safe);
+        l += l_i[i] * m_i[i];
+    }
+    const float inv = l > 0.f ? 1.f / l : 0.f;
+    const int row = qb * kAttQ + 32 * qg + i32;
+    if (row >= p.Tq) return;
+    uint16_t* __restrict__ O = (uint16_t*)p.out + (int64_t)row * p.Hq * DH + (int64_t)head * DH + 32 * db + 4 * h;
+#pragma unroll
+    for (int vq = 0; vq < 4; ++vq) {
+        f32x4 r = o[0][vq] * (m_i[0] * inv);
+#pragma unroll
+        for (int i = 1; i < PARTS; ++i) r += o[i][vq] * (m_i[i] * inv);
+        u32x2 w;
+        w.x = pack_bf16x2(r.x, r.y);
+        w.y = pack_bf16x2(r.z, r.w);
+        *reinterpret_cast<u32x2*>(O + 8 * vq) = w;
+    }
+}
+
+static int launch_attn_merge(const AttnParams& p, hipStream_t s) {
+    const int blocks = (int)(ceil_div(p.Tq, kAttQ) - p.n_whole) * p.Hq * 4;
+    switch (p.n_cut) {
+        case 2: attn_merge_kernel<2><<<blocks, 256, 0, s>>>(p); break;
+        case 3: attn_merge_kernel<3><<<blocks, 256, 0, s>>>(p); break;
+        case 4: attn_merge_kernel<4><<<blocks, 256, 0, s>>>(p); break;
+        case 5: attn_merge_kernel<5><<<blocks, 256, 0, s>>>(p); break;
+        case 6: attn_merge_kernel<6><<<blocks, 256, 0, s>>>(p); break;
+        case 7: attn_merge_kernel<7><<<blocks, 256, 0, s>>>(p); break;
+        case 8: attn_merge_kernel<8><<<blocks, 256, 0, s>>>(p); break;
+        default: return ASTRA_ERR_UNSUPPORTED;
+    }
+    return launch_status();
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -727,13 +861,60 @@ static void launch_attn_f32(int blocks, const AttnParams& p, int head_dim, const
 // as a kernel of its own 13.9 us, 13.7; K = 256 6.6, 6.2.)
 static double encode_item_us(const EncodeJob& e) { return 256.0 * e.K * e.dg / 1048576.0 + 2.5; }
 
-// About how long an attention launch lasts with `items` workgroups of encodes behind its own, by either kernel (us).
+// About how long an attention launch lasts with `items` workgroups of encodes behind its own, by either kernel, every block walked whole (us).
 static double attention_us(const AttnParams& p, bool few, int64_t items, double item) {
     const int64_t total = ceil_div(p.Tq, few ? 32 : kAttQ) * p.Hq, rounds = ceil_div(total, (int64_t)kAttCus);
     const int64_t more = ceil_div(total + items, (int64_t)kAttCus) - rounds;
     const double tiles = (double)(p.Tn_vis + p.Tq) / kAttKV;                // a workgroup walks them all
     const double walk = few ? 5.0 + 0.8 * tiles : 6.0 + 1.1 * tiles;
     return walk * rounds + (items == 0 ? 0.0 : more > 0 ? more * item : std::max(0.0, item - walk));
+}
+
+struct AttnCut {
+    int n_whole, n_cut;      // n_cut 0: every block is walked whole
+    double us;
+};
+
+// About how long the launch lasts with the first `w` blocks of a head walked whole and the others in `c` parts (us): the units' mean load, or what the
+// number of pieces leaves of it, and the partial results on their way out and back in.  A tile takes the longer the more units are at it (0.73 us on 32 of
+// them, 0.81 on 96, 1.01 on 256: the clock and the second-level caches are everyone's); 6 us go before the first and after the last.
+static double cut_us(const AttnParams& p, int w, int c, int64_t items, double item) {
+    const int n_qb = (int)ceil_div(p.Tq, kAttQ), hat = (int)ceil_div(p.Tn_vis, kAttKV), per_head = w + (n_qb - w) * c;
+    const double tile = 0.69 + 0.00125 * std::min<int64_t>((int64_t)per_head * p.Hq + items, kAttCus);
+    auto piece_us = [&](int k) {
+        const int qb = k < w ? w - 1 - k : n_qb - 1 - (k - w) / c;
+        const int tiles = hat + (int)ceil_div(p.causal ? std::min(kAttQ * (qb + 1), p.Tq) : p.Tq, kAttKV);
+        return 6.0 + tile * tiles / (k < w ? 1 : c);
+    };
+    double load = 0.0, us = 0.0;
+    for (int k = 0; k < per_head; ++k) load += piece_us(k);
+    for (int64_t j = 0; j * kAttCus < (int64_t)per_head * p.Hq; ++j) us = std::max(us, (j + 1) * piece_us((int)(j * kAttCus / p.Hq)));
+    us = std::max(us, (load * p.Hq + items * item) / kAttCus);
+    const int64_t pieces = (int64_t)per_head * p.Hq;
+    if (pieces <= kAttCus && pieces + items > kAttCus) us = std::max(us, item + (pieces < kAttCus ? std::min(item, piece_us(per_head - 1)) : piece_us(per_head - 1)));
+    if (items > 0) us += 0.25 * item;
+    // 16.8 MB of partial results behind a single round: 12 us; behind whole walks they leave while others still run
+    return us + (w == n_qb ? 0.0 : w > 0 ? 3.0 : 4.0) + (w == n_qb ? 0.0 : (w > 0 ? 1.0 : 2.0) * (p.Tq - w * kAttQ) * c * p.Hq * 520.0 / 4.0e6);
+}
+
+static size_t cut_bytes(const AttnParams& p, int w, int c) { return (size_t)(ceil_div(p.Tq, kAttQ) - w) * c * p.Hq * kPartFloats * sizeof(float); }
+
+static AttnCut attention_cut(const AttnParams& p, int head_dim, int64_t items, double item, size_t part_bytes) {
+    AttnCut best = {0, 0, 0.0};
+    const int n_qb = (int)ceil_div(p.Tq, kAttQ);
+    if (head_dim != 128 || !p.v_transposed || p.lse || (int64_t)n_qb * p.Hq > 4 * kAttCus) return best;
+    best.us = cut_us(p, n_qb, 1, items, item);
+    const int hat = (int)ceil_div(p.Tn_vis, kAttKV);
+    for (int j = 0; j * kAttCus / p.Hq < n_qb; ++j) {
+        const int w = j * kAttCus / p.Hq;
+        const int pairs = (int)ceil_div(hat + ceil_div(p.causal ? std::min(kAttQ * (w + 1), p.Tq) : p.Tq, kAttKV), 2);     // of the shortest one cut
+        for (int c = 2; c <= kMaxParts && c <= pairs; ++c) {
+            if (cut_bytes(p, w, c) > part_bytes) break;
+            const double us = cut_us(p, w, c, items, item);
+            if (us < best.us) best = {w, c, us};
+        }
+    }
+    return best;
 }
 
 // A workgroup per 32 query rows (attention_short_kernels.hip) where those make a single round of the units, and where encodes in the launch do not
@@ -747,12 +928,37 @@ static bool attention_short(const AttnParams& p, int head_dim, int64_t items, do
     return items == 0 || attention_us(p, true, items, item) < attention_us(p, false, items, item);
 }
 
+// The kernel of a launch and where its walks are cut.  The short form gives way where its walk takes longer than parts of one on the kernel above do.
+static AttnCut attention_form(const AttnParams& p, int head_dim, int64_t items, double item, size_t part_bytes, bool* few) {
+    *few = attention_short(p, head_dim, items, item);
+    const AttnCut cut = attention_cut(p, head_dim, items, item, part_bytes);
+    if (!*few || cut.n_cut == 0) return cut;
+    const int64_t units = ceil_div(p.Tq, 32) * p.Hq;
+    const double walk = 5.0 + std::max(0.37, 0.56 * units / kAttCus) * (p.Tn_vis + p.Tq) / kAttKV;
+    const double behind = (double)std::max<int64_t>(kAttCus - units, 0) * std::floor(walk / std::max(item, 1.0)) >= (double)items ? 0.0 : item;
+    *few = walk + behind < cut.us + 1.0;
+    return *few ? AttnCut{0, 0, 0.0} : cut;
+}
+
 double attention_encode_us(const AttnParams& p, int head_dim, const EncodeJob& e) {
     if (head_dim != 128 || !p.v_transposed || e.n_tokens <= 0 || !vq_encode_fast_ok(e.K, e.dg)) return -1.0;
     const int64_t items = ceil_div(e.n_tokens, kAttThreads / 2) * e.G;
     const double item = encode_item_us(e);
     const double with = attention_us(p, attention_short(p, head_dim, items, item), items, item);
     return std::max(0.0, with - attention_us(p, attention_short(p, head_dim, 0, 0.0), 0, 0.0));
+}
+
+size_t attention_part_bytes(int dtype, const AttnParams& p, int head_dim, const EncodeJob* enc, int n_enc) {
+    if (dtype != ASTRA_BF16 || p.Tq == 0) return 0;
+    size_t bytes = 0;
+    for (int with = 0; with < 2; ++with) {               // the encodes may find another place
+        int64_t items = 0;
+        for (int j = 0; j < (with ? n_enc : 0); ++j) items += ceil_div(enc[j].n_tokens, kAttThreads / 2) * enc[j].G;
+        bool few = false;
+        const AttnCut cut = attention_form(p, head_dim, items, items > 0 ? encode_item_us(enc[0]) : 0.0, SIZE_MAX, &few);
+        if (cut.n_cut > 1) bytes = std::max(bytes, cut_bytes(p, cut.n_whole, cut.n_cut));
+    }
+    return bytes;
 }
 
 int launch_attention(int dtype, const AttnParams& p_in, int head_dim, hipStream_t s, bool plan_only, const EncodeJob* enc, int n_enc,
@@ -785,9 +991,13 @@ int launch_attention(int dtype, const AttnParams& p_in, int head_dim, hipStream_
         }
         // 64-wide heads otherwise: when 128-row query blocks would leave half of the compute units without a
         // workgroup, 64-row blocks whose tiles are dealt to four wavefronts per query group (half the iterations each)
-        const bool few = attention_short(p, head_dim, items, items > 0 ? encode_item_us(enc[0]) : 0.0);
+        bool few = false;
+        const AttnCut cut = attention_form(p, head_dim, items, items > 0 ? encode_item_us(enc[0]) : 0.0, p.part ? p.part_bytes : 0, &few);
+        p.n_whole = cut.n_whole;
+        p.n_cut = cut.n_cut;
         const bool four = !few && head_dim == 64 && total <= kAttCus / 2;
         if (few || four) total = (int64_t)ceil_div(p.Tq, few ? 32 : kAttQ / 2) * p.Hq;
+        if (p.n_cut > 1) total = (p.n_whole + (ceil_div(p.Tq, kAttQ) - p.n_whole) * p.n_cut) * p.Hq;
         if (items > 0) {
             const int tb = vq_encode_blocks(enc[0], kAttCus / n_enc);
             items = 0;
@@ -804,6 +1014,15 @@ int launch_attention(int dtype, const AttnParams& p_in, int head_dim, hipStream_
         }
         if (plan_only) return ASTRA_OK;
         if (few) return launch_attention_short(p, head_dim, ae, s);
+        if (p.n_cut > 1) {
+            const int grid = (int)total + ae.n_enc_wgs;
+            if (ae.n_enc_wgs > 0 && lost) attn_cut_kernel<true, true><<<grid, kAttThreads, 0, s>>>(p, ae);
+            else if (ae.n_enc_wgs > 0) attn_cut_kernel<false, true><<<grid, kAttThreads, 0, s>>>(p, ae);
+            else if (lost) attn_cut_kernel<true, false><<<grid, kAttThreads, 0, s>>>(p, ae);
+            else attn_cut_kernel<false, false><<<grid, kAttThreads, 0, s>>>(p, ae);
+            const int rc = launch_status();
+            return rc ? rc : launch_attn_merge(p, s);
+        }
         if (ae.n_enc_wgs > 0) {
             if (lost) attn_bf16_kernel<128, true, true, 2, true><<<(int)total + ae.n_enc_wgs, kAttThreads, 0, s>>>(p, ae);
             else attn_bf16_kernel<128, true, false, 2, true><<<(int)total + ae.n_enc_wgs, kAttThreads, 0, s>>>(p, ae);

@@ -220,7 +220,13 @@ struct AttnParams {
     // nullable: bit (t % 64) of word t / 64 is 1 if non-local token t's codes arrived; a token whose bit is 0 is
     // dropped from the key/value set
     const unsigned long long* valid_bits;
+    // optional scratch for partial results (bf16, 128-wide heads, V transposed): with it the walk of a query block may be cut between workgroups
+    float* part;
+    size_t part_bytes;
+    int32_t n_whole, n_cut;     // set by launch_attention: the first n_whole query blocks of a head are walked whole, the others in n_cut parts (0: none)
 };
+// bytes of `part` that launch_attention makes use of for a launch that carries the n_enc encodes or none of them; 0: it would cut nothing
+size_t attention_part_bytes(int dtype, const AttnParams& p, int head_dim, const EncodeJob* enc, int n_enc);
 // plan_only: validate the launch (shape limits, kernel availability) and launch nothing
 // enc / n_enc / enc_fused: up to two VQ encodes that nothing in the launch depends on, offered to it; *enc_fused tells whether
 // the launch took them (extra workgroups in its tail) or the caller still has to run them

@@ -331,7 +331,24 @@ def test_short_sequences_of_128_wide_heads(n_local, n_nonlocal, hq, hkv, n_cls, 
     _short_sequence(128, n_local, n_nonlocal, hq, hkv, n_cls, causal, lost)
 
 
-def _short_sequence(dh, n_local, n_nonlocal, hq, hkv, n_cls, causal, lost):
+# query and key rows, heads, KV heads, class rows, causal, lost codes; blocks of a head walked whole, parts of the others (as tests/test_launches.py checks)
+CUT_WALKS = [
+    (100, 4096, 4, 4, 0, True, "tiles", 0, 8),      # one block, its last group with four rows; heads that the XCDs do not share evenly
+    (20, 4096, 4, 4, 0, True, "all", 0, 8),         # three groups without a row; seven parts without a key
+    (255, 1900, 4, 4, 1, False, "some", 0, 8),      # a class row, the encode behind the parts
+    (300, 4096, 8, 2, 0, True, None, 0, 8),         # the last part crosses the diagonal; a block of 44 rows
+    (520, 2500, 16, 4, 0, True, "some", 0, 3),      # parts of unequal length, a block of 8 rows
+    (520, 600, 64, 8, 0, True, None, 4, 3),         # whole walks first, the ragged block in parts
+]
+
+
+@pytest.mark.parametrize("n_local,n_nonlocal,hq,hkv,n_cls,causal,lost,whole,parts", CUT_WALKS)
+def test_walks_cut_between_workgroups(n_local, n_nonlocal, hq, hkv, n_cls, causal, lost, whole, parts):
+    """Parts of a walk in scratch and their sum; without the scratch the walks are whole, and the call is taken all the same."""
+    _short_sequence(128, n_local, n_nonlocal, hq, hkv, n_cls, causal, lost, minimal=True)
+
+
+def _short_sequence(dh, n_local, n_nonlocal, hq, hkv, n_cls, causal, lost, minimal=False):
     from gpu_util import LayerOnGpu, compare_codes
     d = 64 * hq
     cfg = wl.LayerConfig("short", "bf16", d, hq, hkv, dh, n_local + n_nonlocal, 1, 16, 256, n_cls=n_cls, causal=causal, seed=71)
@@ -360,3 +377,12 @@ def _short_sequence(dh, n_local, n_nonlocal, hq, hkv, n_cls, causal, lost):
     y, codes = layer.results()
     compare_codes(codes, codes_ref, gap, NEAR_TIE)
     assert np.abs(y - y_ref).max() <= Y_TOL["bf16"]
+    if minimal:
+        eb, dq, dkv, up = 2, hq * dh, hkv * dh, lambda n, m: -(-n // m) * m
+        n_vis, n_q = n_nonlocal, n_cls + n_local
+        smallest = sum(up(n * eb, 256) for n in (n_q * dq, n_q * dkv, up(n_q, 64) * dkv, n_vis * dkv, up(n_vis, 64) * dkv, n_q * dq))
+        assert layer.workspace.numel() > smallest
+        layer.workspace = layer.workspace[:smallest]
+        layer.y.zero_()
+        layer.run(valid_nonlocal=valid)
+        assert np.abs(layer.results()[0] - y_ref).max() <= Y_TOL["bf16"]

@@ -198,3 +198,19 @@ def test_attention_of_short_sequences(tmp_path):
     for c, r in zip(calls[:-1], results):
         assert "attn_short_kernel<128, false, true>" in kernels(r), (c, kernels(r))
     assert "attn_bf16_kernel<128, true, false, 2, true>" in kernels(results[-1])
+
+
+def test_walks_cut_between_workgroups(tmp_path):
+    """The shapes the GPU tests name, and none where whole walks are a round of their own or the call brings no scratch for the parts."""
+    from test_gpu_layer import CUT_WALKS
+    calls = [dict(entry="layer", d=64 * hq, hq=hq, hkv=hkv, dh=128, cls=cls, causal=causal, n_local=t, n_nonlocal=n, groups=16, words=256)
+             for t, n, hq, hkv, cls, causal, _, _, _ in CUT_WALKS]
+    for (t, n, hq, _, cls, _, _, whole, parts), r in zip(CUT_WALKS, record(calls, tmp_path)):
+        blocks = -(-(t + cls) // 128)
+        merge = [(k, g[0]) for k, g, *_ in r["launches"] if k.startswith("attn_merge")]
+        assert merge == [(f"attn_merge_kernel<{parts}>", 4 * hq * (blocks - whole))], (t, n, merge)
+        (grid,) = [g[0] for k, g, *_ in r["launches"] if k.startswith("attn_cut_kernel")]
+        assert grid >= hq * (whole + (blocks - whole) * parts)
+    calls = [dict(LLAMA, entry=e, n_local=t, n_nonlocal=3072, causal=True) for e in ("layer", "kv") for t in (640, 1024)]
+    for r in record(calls, tmp_path):
+        assert not any(k.startswith(("attn_cut", "attn_merge")) for k in kernels(r)), kernels(r)
