@@ -465,9 +465,11 @@ static int layer_forward_impl(const astra_layer_desc* desc, const void* x_local,
     // optional rotary positions (a block's choice, outside the paper): Q and K of the local rows (content row i at n_before + i,
     // class rows untouched) and K-hat of the visible non-local rows (row j at j; the layer is causal, so they all precede the chunk)
     if (rope_base > 0.f) {
-        rc = launch_rope(vq.dtype, Q, pl.dq, pl.Tq, at.n_q_heads, at.head_dim, at.n_cls, 0, 0, at.n_nonlocal_before - at.n_cls, rope_base, s);
-        if (rc == ASTRA_OK) rc = launch_rope(vq.dtype, K, pl.dkv, pl.Tq, at.n_kv_heads, at.head_dim, at.n_cls, 0, 0, at.n_nonlocal_before - at.n_cls, rope_base, s);
-        if (rc == ASTRA_OK) rc = launch_rope(vq.dtype, Kh, pl.dkv, pl.Tn_vis, at.n_kv_heads, at.head_dim, 0, at.n_nonlocal_before, 0, at.n_local, rope_base, s);
+        const int after = at.n_nonlocal_before - at.n_cls;
+        const RopeMat mats[3] = {{Q, pl.dq, pl.Tq, at.n_q_heads, at.n_cls, 0, 0, after},
+                                 {K, pl.dkv, pl.Tq, at.n_kv_heads, at.n_cls, 0, 0, after},
+                                 {Kh, pl.dkv, pl.Tn_vis, at.n_kv_heads, 0, at.n_nonlocal_before, 0, at.n_local}};
+        rc = launch_rope(vq.dtype, mats, 3, at.head_dim, rope_base, s);
         if (rc) return rc;
     }
 

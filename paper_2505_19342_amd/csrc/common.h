@@ -194,10 +194,18 @@ int launch_gemm_batch(int dtype, const GemmProblem* problems, int n_problems, hi
                       bool may_cut = true, double enc_later_us = -1.0);
 size_t gemm_split_workspace_bytes(int dtype, int64_t M, int64_t N, int64_t K);
 
+// Rotary positions of up to three matrices [rows, ld] of n_heads heads, in place (block_kernels.hip)
+struct RopeMat {
+    void* mat;
+    int64_t ld;
+    int32_t rows, n_heads;
+    int32_t skip, split, add_lo, add_hi;     // row r is at position r + (r < split ? add_lo : add_hi); rows below `skip` have none
+};
+constexpr int kMaxRopeMats = 3;
+int launch_rope(int dtype, const RopeMat* mats, int n_mats, int head_dim, float base, hipStream_t s);
+
 // Row-wise LayerNorm (kind 0) / RMSNorm (kind 1) of the fp32 residual stream x [T, D] into the element type of the layer
 // (out [T, D]); gain, bias fp32 [D], nullable.
-int launch_rope(int dtype, void* mat, int64_t ld, int rows, int n_heads, int head_dim, int skip, int split, int add_lo, int add_hi,
-                float base, hipStream_t s);
 int launch_norm(int dtype, int kind, const float* x, int64_t T, int D, float eps, const float* gain, const float* bias, void* out,
                 hipStream_t s);
 // out[t, f] = silu(a[t, f]) * a[t, F + f] for fp32 a [T, 2F]

@@ -214,3 +214,13 @@ def test_walks_cut_between_workgroups(tmp_path):
     calls = [dict(LLAMA, entry=e, n_local=t, n_nonlocal=3072, causal=True) for e in ("layer", "kv") for t in (640, 1024)]
     for r in record(calls, tmp_path):
         assert not any(k.startswith(("attn_cut", "attn_merge")) for k in kernels(r)), kernels(r)
+
+
+def test_rotary_positions_are_one_launch(tmp_path):
+    """Queries, keys and rebuilt keys together; eight heads of a row to a thread, so that 12 heads are two of them; no blocks for a matrix without rows."""
+    block = dict(entry="block", causal=True, norm="rmsnorm", mlp="swiglu", dff=768, rope=10000.0, groups=16, words=256)
+    calls = [dict(block, d=768, hq=12, hkv=12, dh=64, n_local=100, n_nonlocal=n, before=b) for n, b in ((300, 200), (300, 0))]
+    calls.append(dict(block, d=512, hq=4, hkv=2, dh=128, n_local=33, n_nonlocal=66, before=66, dtype="f32"))
+    rows = [(8 * 2 * 100, 8 * 2 * 100, 8 * 2 * 200), (8 * 2 * 100, 8 * 2 * 100), (64 * 33, 64 * 33, 64 * 66)]
+    for c, threads, r in zip(calls, rows, record(calls, tmp_path)):
+        assert [g[0] for k, g, *_ in r["launches"] if k.startswith("rope_kernel")] == [sum(-(-t // 256) for t in threads)], (c, r["launches"])
