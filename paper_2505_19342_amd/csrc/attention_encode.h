@@ -14,7 +14,7 @@ struct AttnEncode {
 };
 
 // bf16, V transposed, a workgroup per 32 query rows; encodes ride on 128-wide heads only
-int launch_attention_short(const AttnParams& p, int head_dim, const AttnEncode& e, hipStream_t s);
+int launch_attention_short(const AttnParams& p, int head_dim, const AttnEncode& e, const Prefetch* fetch, hipStream_t s);
 
 // workgroup idx of those behind the attention's own; cb, cn: LDS for the encode's ring of codebook tiles and their norms
 template <int THREADS>

@@ -962,7 +962,7 @@ size_t attention_part_bytes(int dtype, const AttnParams& p, int head_dim, const 
 }
 
 int launch_attention(int dtype, const AttnParams& p_in, int head_dim, hipStream_t s, bool plan_only, const EncodeJob* enc, int n_enc,
-                     bool* enc_fused) {
+                     bool* enc_fused, const Prefetch* fetch) {
     AttnParams p = p_in;
     if (enc_fused) *enc_fused = false;
     if (p.Tq == 0) return ASTRA_OK;
@@ -1013,7 +1013,7 @@ int launch_attention(int dtype, const AttnParams& p_in, int head_dim, hipStream_
             *enc_fused = true;
         }
         if (plan_only) return ASTRA_OK;
-        if (few) return launch_attention_short(p, head_dim, ae, s);
+        if (few) return launch_attention_short(p, head_dim, ae, fetch, s);
         if (p.n_cut > 1) {
             const int grid = (int)total + ae.n_enc_wgs;
             if (ae.n_enc_wgs > 0 && lost) attn_cut_kernel<true, true><<<grid, kAttThreads, 0, s>>>(p, ae);

@@ -1,6 +1,8 @@
 // Mixed-precision attention of one device (paper Sec. 3.2, Eq. 1) for launches that a few large workgroups cannot fill: short sequences, few heads.
 #include "attention_encode.h"
+#include "prefetch.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace astra {
@@ -25,15 +27,16 @@ namespace astra {
 // 256 + 768 rows 26.0 -> 23.1, 512 + 1024 35.2 -> 31.4.  32 heads of 128 (128 query rows per workgroup before): 17 rows 27.4 -> 24.2, 128 + 384
 // 53.0 -> 47.2, 256 + 4096 149 -> 130.
 //
-// ENC: VQ encodes ride in the launch (AttnEncode).
+// ENC: VQ encodes ride in the launch (AttnEncode).  Units that are left read ahead (prefetch.h).
 // Longer walks and more rows are better off sharing tiles through LDS (launch_attention).
 // ------------------------------------------------------------------------------------------------
 constexpr int kShortThreads = 512;
 constexpr int kShortWaves = kShortThreads / kWave;
 constexpr float kLazyShort = 8.f;     // base-2 units
+constexpr int kShortUnits = 256;      // compute units of the device
 
 template <int DH, bool LOST, bool ENC>
-__global__ __launch_bounds__(kShortThreads) void attn_short_kernel(const AttnParams p, const AttnEncode e) {
+__global__ __launch_bounds__(kShortThreads) void attn_short_kernel(const AttnParams p, const AttnEncode e, const Prefetch f) {
     constexpr int TK = 4096 / DH, NMB = TK / 32, NKS = DH / 16, NDB = DH / 32, NPV = TK / 16, LDP = DH + 4;
     constexpr int KP = DH / 8, VP = TK / 8;    // 16-byte pieces of a row of keys, of values
     constexpr int NT = 8, KR = 64 / KP, VR = 64 / VP;      // transfers of a tile of keys or of values, and their rows
@@ -44,10 +47,18 @@ __global__ __launch_bounds__(kShortThreads) void attn_short_kernel(const AttnPar
     auto part = reinterpret_cast<float(*)[32][LDP]>(&ring[0]);
     if constexpr (ENC) {
         static_assert(sizeof(ring) >= sizeof(u32x4) * kEncBufs * (kEncCbSlots + kEncCnSlots), "the encode's codebook tiles and norms fit");
-        if ((int)blockIdx.x >= e.n_attn_wgs) {
+        if ((int)blockIdx.x >= e.n_attn_wgs && (int)blockIdx.x < e.n_attn_wgs + e.n_enc_wgs) {
             attn_encode_wgs<kShortThreads>(e, (int)blockIdx.x - e.n_attn_wgs, ring, reinterpret_cast<f32x4*>(ring + kEncBufs * kEncCbSlots));
             return;
         }
+    }
+
+    // the arguments arrive together, before the branch on one of them
+    asm volatile("" ::"s"(e.n_attn_wgs), "s"(p.q), "s"(p.k_loc), "s"(p.v_loc), "s"(p.k_hat), "s"(p.v_hat), "s"(p.out), "s"(p.Hq), "s"(p.Hkv), "s"(p.Tq),
+                 "s"(p.Tn_vis), "s"(p.causal), "s"(p.ldv_loc), "s"(p.ldv_hat), "s"(p.scale));
+    if ((int)blockIdx.x >= e.n_attn_wgs) {
+        prefetch_wgs<kShortThreads>(f, blockIdx.x - (uint32_t)(e.n_attn_wgs + e.n_enc_wgs));
+        return;
     }
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -55,7 +66,7 @@ __global__ __launch_bounds__(kShortThreads) void attn_short_kernel(const AttnPar
     const int i32 = lane & 31, h = lane >> 5;
     const int Tq = p.Tq, n_qb = (Tq + 31) / 32;
     // contiguous runs of heads per XCD, so that a KV head's keys and values stay in one L2; later (longer) query blocks first
-    const int total = ENC ? e.n_attn_wgs : (int)gridDim.x, xq = total / 8, xr = total % 8, xcd = blockIdx.x % 8, slot = blockIdx.x / 8;
+    const int total = e.n_attn_wgs, xq = total / 8, xr = total % 8, xcd = blockIdx.x % 8, slot = blockIdx.x / 8;
     const int vid = xcd < xr ? xcd * (xq + 1) + slot : xr * (xq + 1) + (xcd - xr) * xq + slot;
     const int head = vid / n_qb, q0 = (n_qb - 1 - vid % n_qb) * 32;
     const int hk = head / (p.Hq / p.Hkv);
@@ -266,18 +277,22 @@ __global__ __launch_bounds__(kShortThreads) void attn_short_kernel(const AttnPar
     }
 }
 
-int launch_attention_short(const AttnParams& p, int head_dim, const AttnEncode& e, hipStream_t s) {
-    const int grid = (int)(ceil_div(p.Tq, 32) * p.Hq) + e.n_enc_wgs;
+int launch_attention_short(const AttnParams& p, int head_dim, const AttnEncode& e_in, const Prefetch* fetch, hipStream_t s) {
+    AttnEncode e = e_in;
+    e.n_attn_wgs = (int)(ceil_div(p.Tq, 32) * p.Hq);
+    Prefetch f{};
+    if (fetch) f = fetch->on(kShortUnits - e.n_attn_wgs - e.n_enc_wgs, kShortThreads);
+    const int grid = e.n_attn_wgs + e.n_enc_wgs + f.n_wgs;
     const bool lost = p.valid_bits != nullptr;
     if (head_dim == 64) {
-        if (lost) attn_short_kernel<64, true, false><<<grid, kShortThreads, 0, s>>>(p, e);
-        else attn_short_kernel<64, false, false><<<grid, kShortThreads, 0, s>>>(p, e);
+        if (lost) attn_short_kernel<64, true, false><<<grid, kShortThreads, 0, s>>>(p, e, f);
+        else attn_short_kernel<64, false, false><<<grid, kShortThreads, 0, s>>>(p, e, f);
     } else if (e.n_enc_wgs > 0) {
-        if (lost) attn_short_kernel<128, true, true><<<grid, kShortThreads, 0, s>>>(p, e);
-        else attn_short_kernel<128, false, true><<<grid, kShortThreads, 0, s>>>(p, e);
+        if (lost) attn_short_kernel<128, true, true><<<grid, kShortThreads, 0, s>>>(p, e, f);
+        else attn_short_kernel<128, false, true><<<grid, kShortThreads, 0, s>>>(p, e, f);
     } else {
-        if (lost) attn_short_kernel<128, true, false><<<grid, kShortThreads, 0, s>>>(p, e);
-        else attn_short_kernel<128, false, false><<<grid, kShortThreads, 0, s>>>(p, e);
+        if (lost) attn_short_kernel<128, true, false><<<grid, kShortThreads, 0, s>>>(p, e, f);
+        else attn_short_kernel<128, false, false><<<grid, kShortThreads, 0, s>>>(p, e, f);
     }
     return launch_status();
 }

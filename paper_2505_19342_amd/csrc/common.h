@@ -185,6 +185,7 @@ struct GemmProblem {
 };
 constexpr int kMaxGemmProblems = 6;
 struct EncodeJob;
+struct Prefetch;
 // enc / enc_fused (both or neither): offers the VQ encode of the local rows to the launch; *enc_fused tells whether the
 // launch took it (extra workgroups) or the caller still has to run it.  plan_only: decide and validate, launch nothing.
 // enc_later_us: what the encode adds to a later launch that takes it if this one does not; negative: it needs a launch of its own.
@@ -238,9 +239,10 @@ size_t attention_part_bytes(int dtype, const AttnParams& p, int head_dim, const 
 // plan_only: validate the launch (shape limits, kernel availability) and launch nothing
 // enc / n_enc / enc_fused: up to two VQ encodes that nothing in the launch depends on, offered to it; *enc_fused tells whether
 // the launch took them (extra workgroups in its tail) or the caller still has to run them
+// fetch: what the launches after this one read, for the units that it leaves idle (the form on 32 query rows takes it)
 // attention_encode_us: about what one encode adds to the launch (us), negative if the launch would not take it
 int launch_attention(int dtype, const AttnParams& p, int head_dim, hipStream_t s, bool plan_only = false, const EncodeJob* enc = nullptr,
-                     int n_enc = 0, bool* enc_fused = nullptr);
+                     int n_enc = 0, bool* enc_fused = nullptr, const Prefetch* fetch = nullptr);
 double attention_encode_us(const AttnParams& p, int head_dim, const EncodeJob& e);
 int launch_mfma_probe(float* out, int n_blocks, int iters, hipStream_t s);
 

@@ -224,3 +224,17 @@ def test_rotary_positions_are_one_launch(tmp_path):
     rows = [(8 * 2 * 100, 8 * 2 * 100, 8 * 2 * 200), (8 * 2 * 100, 8 * 2 * 100), (64 * 33, 64 * 33, 64 * 66)]
     for c, threads, r in zip(calls, rows, record(calls, tmp_path)):
         assert [g[0] for k, g, *_ in r["launches"] if k.startswith("rope_kernel")] == [sum(-(-t // 256) for t in threads)], (c, r["launches"])
+
+
+def test_reading_ahead_beside_the_attention(tmp_path):
+    """Workgroups behind the 32-row attention of a block read the weights that follow, two lines of 128 bytes a thread, or up to four on the units that are
+    left; none in a layer by itself."""
+    small = dict(SMALL, n_nonlocal=60, causal=True, norm="layernorm", mlp="gelu_tanh", dff=3072)
+    lines = (768 * 768 + 2 * 768 * 3072) * 2 // 128
+    want = [(64, -(-lines // 1024)), (512, 64), (640, 16), (672, 4)]
+    results = record([dict(small, entry="block", n_local=t) for t, _ in want], tmp_path)
+    for (t, wgs), r in zip(want, results):
+        (grid,) = [g[0] for k, g, *_ in r["launches"] if k.startswith("attn_short")]
+        assert grid == -(-t // 32) * 12 + wgs, (t, grid)
+    r = record([dict(SMALL, entry="layer", n_local=64, n_nonlocal=60, causal=True)], tmp_path)[0]
+    assert [g[0] for k, g, *_ in r["launches"] if k.startswith("attn_short")] == [24]
