@@ -2,6 +2,7 @@
 
 #include "common.h"
 #include "prefetch.h"
+#include "vq_decode_body.h"
 #include "vq_encode_body.h"
 
 namespace astra {
@@ -310,7 +311,8 @@ static int layer_forward_impl(const astra_layer_desc* desc, const void* x_local,
                               void* const* ev, int* plan_encode_fused = nullptr, const uint64_t* valid_bits = nullptr,
                               const float* residual = nullptr, const float* pre_k = nullptr, const float* pre_v = nullptr,
                               float rope_base = 0.f, void* part = nullptr, size_t part_bytes = 0,
-                              const Prefetch* behind = nullptr) {      // behind: what the launches after the layer read
+                              const Prefetch* behind = nullptr,        // what the launches after the layer read
+                              bool rebuilt = false) {                  // X-hat is in its place already
     // plan_encode_fused: validate the shapes and report whether the projection launch would carry the encode;
     // nothing is launched and no pointer is dereferenced
     const bool plan_only = plan_encode_fused != nullptr;
@@ -429,7 +431,7 @@ static int layer_forward_impl(const astra_layer_desc* desc, const void* x_local,
     }
     if (rc) return rc;
 
-    if (pl.need_xhat && pl.Tn_vis > 0 && !preprojected) {
+    if (pl.need_xhat && pl.Tn_vis > 0 && !preprojected && !rebuilt) {
         rc = launch_vq_decode(vq, codes_nonlocal, pl.Tn_vis, codebook, Xh, s);
         if (rc) return rc;
     }
@@ -689,6 +691,10 @@ static int block_forward_impl(const astra_block_desc* desc, const astra_block_we
     void* h = h_out ? h_out : (void*)(ws + bp.off_h);
     void* a = ws + bp.off_a;
     const int F = bp.d_ff;
+    // where the peers' rows have to be rebuilt in memory, the launch of the first normalisation takes that along
+    DecodeJob rebuild;
+    const bool rebuilt =
+        pl.need_xhat && vq_decode_job(desc->layer.vq, codes_nonlocal, pl.Tn_vis, w->codebook, ws + pl.off_xhat, &rebuild) && norm_decode_ok(pl.Tq, pl.D, rebuild);
     // every launch of the block is validated before the first one is made
     int fused = 0;
     rc = layer_forward_impl(&desc->layer, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
@@ -727,12 +733,13 @@ static int block_forward_impl(const astra_block_desc* desc, const astra_block_we
     }
 
     // h = norm1(x) in the layer's element type: the tensor that is quantised and projected
-    rc = launch_norm(dtype, desc->norm_kind, x, pl.Tq, pl.D, desc->eps, w->norm1_gain, w->norm1_bias, h, s);
+    rc = rebuilt ? launch_norm_decode(desc->norm_kind, x, pl.Tq, pl.D, desc->eps, w->norm1_gain, w->norm1_bias, h, rebuild, s)
+                 : launch_norm(dtype, desc->norm_kind, x, pl.Tq, pl.D, desc->eps, w->norm1_gain, w->norm1_bias, h, s);
     if (rc) return rc;
     // r = x + layer(h), written to x_out by the output projection's epilogue
     rc = layer_forward_impl(&desc->layer, h, codes_nonlocal, w->codebook, w->cnorm, w->wq, w->wk, w->wv, w->wo, w->bq, w->bk, w->bv,
                             w->bo, x_out, codes_local_out, workspace, pl.total, stream, nullptr, nullptr, valid_nonlocal_bits, x,
-                            nullptr, nullptr, desc->rope_base, ws + bp.total, workspace_bytes - bp.total, read_ahead ? &mlp : nullptr);
+                            nullptr, nullptr, desc->rope_base, ws + bp.total, workspace_bytes - bp.total, read_ahead ? &mlp : nullptr, rebuilt);
     if (rc) return rc;
     rc = launch_norm(dtype, desc->norm_kind, x_out, pl.Tq, pl.D, desc->eps, w->norm2_gain, w->norm2_bias, h2, s);
     if (rc) return rc;

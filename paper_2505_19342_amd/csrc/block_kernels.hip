@@ -2,7 +2,7 @@
 // block normalises, attends with the mixed-precision layer, and runs its position-wise MLP locally): the row-wise
 // normalisation of the fp32 residual stream into the layer's element type, and the gating of the fp32 MLP.
 // Both are bound by HBM traffic: one read of the row, one write of the result.
-#include "common.h"
+#include "vq_decode_body.h"
 
 namespace astra {
 
@@ -33,13 +33,12 @@ __device__ __forceinline__ void store_elem<float>(float* o, float v) { *o = v; }
 template <>
 __device__ __forceinline__ void store_elem<uint16_t>(uint16_t* o, float v) { *o = f32_to_bf16_bits(v); }
 
-// One workgroup per row.  kind 0: (x - mean) / sqrt(var + eps) * gain + bias, biased variance, computed as the mean of
+// One workgroup per row, blockIdx.x.  kind 0: (x - mean) / sqrt(var + eps) * gain + bias, biased variance, computed as the mean of
 // squared deviations (two passes over the registers, no cancellation); kind 1: x / sqrt(mean(x^2) + eps) * gain.
 // VEC: D % 4 == 0 and D <= 8192, the row lives in registers; otherwise the row is re-read (from cache) per pass.
 template <typename OutT, bool VEC>
-__global__ __launch_bounds__(kNormThreads) void norm_kernel(const float* __restrict__ x, int D, int kind, float eps,
-                                                            const float* __restrict__ gain, const float* __restrict__ bias,
-                                                            OutT* __restrict__ out) {
+__device__ __forceinline__ void norm_row(const float* __restrict__ x, int D, int kind, float eps, const float* __restrict__ gain,
+                                         const float* __restrict__ bias, OutT* __restrict__ out) {
     __shared__ float part[2][kNormThreads / kWave];
     const int tid = threadIdx.x;
     const float* __restrict__ row = x + (int64_t)blockIdx.x * D;
@@ -102,11 +101,43 @@ __global__ __launch_bounds__(kNormThreads) void norm_kernel(const float* __restr
     }
 }
 
+template <typename OutT, bool VEC>
+__global__ __launch_bounds__(kNormThreads) void norm_kernel(const float* __restrict__ x, int D, int kind, float eps,
+                                                            const float* __restrict__ gain, const float* __restrict__ bias,
+                                                            OutT* __restrict__ out) {
+    norm_row<OutT, VEC>(x, D, kind, eps, gain, bias, out);
+}
+
+// The normalisation with the decode of the peers' codes behind its rows, where the projections need the rebuilt rows in memory (slices of no whole 16 bytes).
+// The launch lasts what the longer of the two takes, both a few memory latencies for a small model: 6 blocks of 256 + 768 rows, 64 groups of 12, 334.6 us
+// with a launch for the decode, 317.3 now; 512 + 1024 rows 522.8 / 501.0.
+template <typename CodeT>
+__global__ __launch_bounds__(kNormThreads) void norm_decode_kernel(const float* __restrict__ x, int T, int D, int kind, float eps,
+                                                                   const float* __restrict__ gain, const float* __restrict__ bias,
+                                                                   uint16_t* __restrict__ out, const DecodeJob job) {
+    static_assert(kNormThreads == kDecThreads, "one workgroup size for both");
+    if ((int)blockIdx.x < T) norm_row<uint16_t, true>(x, D, kind, eps, gain, bias, out);
+    else vq_decode_run<CodeT>(job, blockIdx.x - (uint32_t)T);
+}
+
+static bool norm_in_registers(int D) { return D % 4 == 0 && D <= kNormThreads * kNormCache * 4; }
+
+bool norm_decode_ok(int64_t T, int D, const DecodeJob& job) { return T > 0 && norm_in_registers(D) && T + job.blocks <= 0x7fffffff; }
+
+int launch_norm_decode(int kind, const float* x, int64_t T, int D, float eps, const float* gain, const float* bias, void* out, const DecodeJob& job,
+                       hipStream_t s) {
+    if (!norm_decode_ok(T, D, job) || (kind != 0 && kind != 1)) return ASTRA_ERR_SHAPE;
+    const int grid = (int)T + job.blocks;
+    if (job.code_bytes == 1) norm_decode_kernel<uint8_t><<<grid, kNormThreads, 0, s>>>(x, (int)T, D, kind, eps, gain, bias, (uint16_t*)out, job);
+    else norm_decode_kernel<uint16_t><<<grid, kNormThreads, 0, s>>>(x, (int)T, D, kind, eps, gain, bias, (uint16_t*)out, job);
+    return launch_status();
+}
+
 int launch_norm(int dtype, int kind, const float* x, int64_t T, int D, float eps, const float* gain, const float* bias, void* out,
                 hipStream_t s) {
     if (T < 0 || D <= 0 || T > 0x7fffffff || (kind != 0 && kind != 1)) return ASTRA_ERR_SHAPE;
     if (T == 0) return ASTRA_OK;
-    const bool vec = D % 4 == 0 && D <= kNormThreads * kNormCache * 4;
+    const bool vec = norm_in_registers(D);
     if (dtype == ASTRA_BF16) {
         if (vec) norm_kernel<uint16_t, true><<<(int)T, kNormThreads, 0, s>>>(x, D, kind, eps, gain, bias, (uint16_t*)out);
         else norm_kernel<uint16_t, false><<<(int)T, kNormThreads, 0, s>>>(x, D, kind, eps, gain, bias, (uint16_t*)out);

@@ -209,6 +209,11 @@ int launch_rope(int dtype, const RopeMat* mats, int n_mats, int head_dim, float 
 // (out [T, D]); gain, bias fp32 [D], nullable.
 int launch_norm(int dtype, int kind, const float* x, int64_t T, int D, float eps, const float* gain, const float* bias, void* out,
                 hipStream_t s);
+struct DecodeJob;
+// bf16; the decode's workgroups behind the rows'
+bool norm_decode_ok(int64_t T, int D, const DecodeJob& job);
+int launch_norm_decode(int kind, const float* x, int64_t T, int D, float eps, const float* gain, const float* bias, void* out, const DecodeJob& job,
+                       hipStream_t s);
 // out[t, f] = silu(a[t, f]) * a[t, F + f] for fp32 a [T, 2F]
 int launch_swiglu_f32(const float* a, int64_t T, int F, float* out, hipStream_t s);
 

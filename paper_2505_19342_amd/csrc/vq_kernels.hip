@@ -3,6 +3,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "vq_decode_body.h"
 #include "vq_encode_body.h"
 #include "vq_encode_f32_body.h"
 
@@ -110,6 +111,19 @@ static bool magic_div(uint32_t d, uint64_t n_max, uint32_t* magic) {
     const uint64_t e = m * d - ((uint64_t)1 << 32);
     if (m > 0xffffffffull || n_max * e >= ((uint64_t)1 << 32)) return false;
     *magic = (uint32_t)m;
+    return true;
+}
+
+bool vq_decode_job(const astra_vq_desc& d, const void* codes, int64_t n_tokens, const void* codebook, void* x_hat, DecodeJob* job) {
+    const int row_bytes = d.d_model / d.n_groups * elem_bytes(d.dtype), per_group = row_bytes / 8, per_token = per_group * d.n_groups;
+    if (row_bytes % 8 != 0 || n_tokens <= 0) return false;
+    const int64_t n = n_tokens * per_token;
+    DecodeJob j{codes, codebook, x_hat, (uint32_t)n, (uint32_t)per_token, (uint32_t)per_group, 0, 0, d.n_groups, d.codebook_size, code_bytes(d.code_type), 0};
+    if (n >= ((int64_t)1 << 31) || (int64_t)d.n_groups * d.codebook_size * per_group >= ((int64_t)1 << 32) ||
+        !magic_div((uint32_t)per_token, (uint64_t)n, &j.magic_token) || !magic_div((uint32_t)per_group, (uint64_t)per_token, &j.magic_group))
+        return false;
+    j.blocks = (int32_t)ceil_div(n, kDecThreads * kDecPieces);
+    *job = j;
     return true;
 }
 

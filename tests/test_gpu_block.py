@@ -248,3 +248,11 @@ def test_block_argument_errors_launch_nothing():
         B.astra_block_forward(blk.desc, w, blk.x, blk.codes_nonlocal, None, blk.x_out, blk.codes_local, blk.h, blk.workspace)
     torch.cuda.synchronize()
     assert bool((blk.x_out == -7.0).all())
+
+
+@pytest.mark.parametrize("words,seq_len", [(256, 420), (1024, 420), (16, 8)])
+def test_slices_of_no_whole_16_bytes(words, seq_len):
+    """64 groups of 12 channels: the peers' rows are rebuilt by the launch of the first normalisation; 8- and 16-bit codes, pieces that fill no whole
+    workgroup, and six rows of peers."""
+    layer = dataclasses.replace(wl.GPT2_SMALL, name="gpt2_64_groups", n_groups=64, codebook_size=words, seq_len=seq_len, seed=81)
+    run_case(dataclasses.replace(wl.GPT2_SMALL_BLOCK, name="gpt2_64_groups_block", layer=layer), 3)

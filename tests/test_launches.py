@@ -238,3 +238,13 @@ def test_reading_ahead_beside_the_attention(tmp_path):
         assert grid == -(-t // 32) * 12 + wgs, (t, grid)
     r = record([dict(SMALL, entry="layer", n_local=64, n_nonlocal=60, causal=True)], tmp_path)[0]
     assert [g[0] for k, g, *_ in r["launches"] if k.startswith("attn_short")] == [24]
+
+
+def test_rebuilt_rows_of_a_block_come_with_its_first_normalisation(tmp_path):
+    """Slices of whole 8 bytes but not 16; a launch of their own for others, and none where the projections fetch codewords themselves."""
+    block = dict(entry="block", d=768, hq=12, hkv=12, dh=64, n_local=100, causal=True, norm="layernorm", mlp="gelu_tanh", dff=3072, words=256)
+    calls = [dict(block, n_nonlocal=300, groups=64), dict(block, n_nonlocal=300, groups=64, before=0), dict(block, n_nonlocal=300, groups=128), dict(block, n_nonlocal=300, groups=32)]
+    with_norm, no_rows, own, none = (kernels(r) for r in record(calls, tmp_path))
+    assert with_norm[0].startswith("norm_decode_kernel") and not any("vq_decode" in k for k in with_norm)
+    assert own[0].startswith("norm_kernel") and any("vq_decode_kernel" in k for k in own)
+    assert not any("decode" in k for k in no_rows + none)
