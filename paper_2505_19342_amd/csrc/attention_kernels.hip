@@ -64,7 +64,7 @@ __device__ __forceinline__ int swz_vt(int r) { return (r >> 1) & 7; }
 // LOST: the caller passed a validity bit per non-local token (an instantiation of its own, so that the code for it does
 // not disturb the register allocation and schedule of the kernel that runs without)
 // ENC: VQ encodes ride in the launch (AttnEncode)
-// CUT: walks may be cut between workgroups (AttnParams::n_whole, n_cut); a part leaves its unnormalised result in AttnParams::part.  Few query blocks leave
+// CUT: the blocks of all heads of an XCD side by side, walks possibly cut between workgroups (AttnParams::n_whole, n_cut); a part leaves its unnormalised result in AttnParams::part.  Few query blocks leave
 // units idle, and a few more than a round of them leave most units idle for a second whole walk.  A part costs 6 us before its first tile and after its
 // last, and its 64 KiB.  Layers 4096 wide, every walk whole / cut (us): 20 + 4096 rows 132.1 / 123.5, 300 + 2565 157.8 / 151.1, 512 + 3584 185.6 / 175.9,
 // 1030 + 2565 261.1 / 251.0, 1400 + 4096 383.6 / 366.2; with K and V quantised after projection 300 + 2100 104.3 / 100.9, 1280 + 3840 276.1 / 261.9.
@@ -894,7 +894,7 @@ static double cut_us(const AttnParams& p, int w, int c, int64_t items, double it
     if (pieces <= kAttCus && pieces + items > kAttCus) us = std::max(us, item + (pieces < kAttCus ? std::min(item, piece_us(per_head - 1)) : piece_us(per_head - 1)));
     if (items > 0) us += 0.25 * item;
     // 16.8 MB of partial results behind a single round: 12 us; behind whole walks they leave while others still run
-    return us + (w == n_qb ? 0.0 : w > 0 ? 3.0 : 4.0) + (w == n_qb ? 0.0 : (w > 0 ? 1.0 : 2.0) * (p.Tq - w * kAttQ) * c * p.Hq * 520.0 / 4.0e6);
+    return us + (w == n_qb ? 0.0 : (w > 0 ? 5.0 : 4.0) + (w > 0 ? 1.0 : 2.0) * (p.Tq - w * kAttQ) * c * p.Hq * 520.0 / 4.0e6);
 }
 
 static size_t cut_bytes(const AttnParams& p, int w, int c) { return (size_t)(ceil_div(p.Tq, kAttQ) - w) * c * p.Hq * kPartFloats * sizeof(float); }
@@ -995,6 +995,13 @@ int launch_attention(int dtype, const AttnParams& p_in, int head_dim, hipStream_
         const AttnCut cut = attention_form(p, head_dim, items, items > 0 ? encode_item_us(enc[0]) : 0.0, p.part ? p.part_bytes : 0, &few);
         p.n_whole = cut.n_whole;
         p.n_cut = cut.n_cut;
+        // Whole walks of unequal length in more than a round: the longest of all heads first, so that the short ones are what the last round is made of.  A
+        // head after the other, the last head's longest blocks start when most are done (us, a head after the other / longest first): layers 4096 wide of
+        // 1531 + 2565 rows 282 / 273, 1531 + 900 226 / 218, 1400 + 4096 344 / 337, with K and V quantised after projection 1531 + 2565 259 / 253.
+        if (p.n_cut == 0 && !few && head_dim == 128 && vt && p.causal && total > kAttCus && p.Hq % kXcdsA == 0 && !p.lse) {
+            p.n_whole = (int)ceil_div(p.Tq, kAttQ);
+            p.n_cut = 1;
+        }
         const bool four = !few && head_dim == 64 && total <= kAttCus / 2;
         if (few || four) total = (int64_t)ceil_div(p.Tq, few ? 32 : kAttQ / 2) * p.Hq;
         if (p.n_cut > 1) total = (p.n_whole + (ceil_div(p.Tq, kAttQ) - p.n_whole) * p.n_cut) * p.Hq;
@@ -1014,14 +1021,14 @@ int launch_attention(int dtype, const AttnParams& p_in, int head_dim, hipStream_
         }
         if (plan_only) return ASTRA_OK;
         if (few) return launch_attention_short(p, head_dim, ae, fetch, s);
-        if (p.n_cut > 1) {
+        if (p.n_cut > 0) {
             const int grid = (int)total + ae.n_enc_wgs;
             if (ae.n_enc_wgs > 0 && lost) attn_cut_kernel<true, true><<<grid, kAttThreads, 0, s>>>(p, ae);
             else if (ae.n_enc_wgs > 0) attn_cut_kernel<false, true><<<grid, kAttThreads, 0, s>>>(p, ae);
             else if (lost) attn_cut_kernel<true, false><<<grid, kAttThreads, 0, s>>>(p, ae);
             else attn_cut_kernel<false, false><<<grid, kAttThreads, 0, s>>>(p, ae);
             const int rc = launch_status();
-            return rc ? rc : launch_attn_merge(p, s);
+            return rc || p.n_cut == 1 ? rc : launch_attn_merge(p, s);
         }
         if (ae.n_enc_wgs > 0) {
             if (lost) attn_bf16_kernel<128, true, true, 2, true><<<(int)total + ae.n_enc_wgs, kAttThreads, 0, s>>>(p, ae);

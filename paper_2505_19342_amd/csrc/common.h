@@ -237,7 +237,7 @@ struct AttnParams {
     // optional scratch for partial results (bf16, 128-wide heads, V transposed): with it the walk of a query block may be cut between workgroups
     float* part;
     size_t part_bytes;
-    int32_t n_whole, n_cut;     // set by launch_attention: the first n_whole query blocks of a head are walked whole, the others in n_cut parts (0: none)
+    int32_t n_whole, n_cut;     // set by launch_attention: the first n_whole query blocks of a head are walked whole, the others in n_cut parts (1: all whole; 0: a head after the other)
 };
 // bytes of `part` that launch_attention makes use of for a launch that carries the n_enc encodes or none of them; 0: it would cut nothing
 size_t attention_part_bytes(int dtype, const AttnParams& p, int head_dim, const EncodeJob* enc, int n_enc);

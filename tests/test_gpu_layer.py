@@ -342,6 +342,12 @@ CUT_WALKS = [
 ]
 
 
+@pytest.mark.parametrize("lost", [None, "some"])
+def test_more_whole_walks_than_units(lost):
+    """320 blocks of 128 rows on 256 units, the longest of all heads first."""
+    _short_sequence(128, 520, 100, 64, 8, 0, True, lost)
+
+
 @pytest.mark.parametrize("n_local,n_nonlocal,hq,hkv,n_cls,causal,lost,whole,parts", CUT_WALKS)
 def test_walks_cut_between_workgroups(n_local, n_nonlocal, hq, hkv, n_cls, causal, lost, whole, parts):
     """Parts of a walk in scratch and their sum; without the scratch the walks are whole, and the call is taken all the same."""

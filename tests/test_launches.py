@@ -216,6 +216,14 @@ def test_walks_cut_between_workgroups(tmp_path):
         assert not any(k.startswith(("attn_cut", "attn_merge")) for k in kernels(r)), kernels(r)
 
 
+def test_more_whole_walks_than_units(tmp_path):
+    """The longest of all heads first where walks differ in length; heads that the XCDs do not share evenly one after the other."""
+    calls = [dict(LLAMA, entry="layer", n_local=1531, n_nonlocal=2565, causal=c) for c in (True, False)]
+    calls.append(dict(entry="layer", d=640, hq=20, hkv=4, dh=128, groups=16, words=256, n_local=1700, n_nonlocal=64, causal=True))
+    for r, name in zip(record(calls, tmp_path), ("attn_cut_kernel", "attn_bf16_kernel", "attn_bf16_kernel")):
+        assert any(k.startswith(name) for k in kernels(r)) and not any(k.startswith("attn_merge") for k in kernels(r)), (name, kernels(r))
+
+
 def test_rotary_positions_are_one_launch(tmp_path):
     """Queries, keys and rebuilt keys together; eight heads of a row to a thread, so that 12 heads are two of them; no blocks for a matrix without rows."""
     block = dict(entry="block", causal=True, norm="rmsnorm", mlp="swiglu", dff=768, rope=10000.0, groups=16, words=256)
