@@ -437,12 +437,10 @@ static int layer_forward_impl(const astra_layer_desc* desc, const void* x_local,
     }
     rc = launch_gemm_batch(vq.dtype, pr, n_pr, s, offer_fused ? &ej : nullptr, offer_fused ? &enc_fused : nullptr, false, nullptr, 0, true, enc_later_us);
     if (rc) return rc;
+    const bool argmin_there = preprojected && pl.Tn_vis > 0 && scores_in_projection_launch;
     if (preprojected && pl.Tn_vis > 0) {
-        rc = launch_preproj_gather(vq.dtype, vq.code_type, codes_nonlocal, pre_k, bk, pl.Tn_vis, vq.n_groups, vq.codebook_size, pl.dkv,
-                                   Kh, pl.dkv, false, s);
-        if (rc) return rc;
-        rc = launch_preproj_gather(vq.dtype, vq.code_type, codes_nonlocal, pre_v, bv, pl.Tn_vis, vq.n_groups, vq.codebook_size, pl.dkv,
-                                   Vh, pl.vt ? pl.ldv_hat : pl.dkv, pl.vt, s);
+        rc = launch_preproj(vq.dtype, vq.code_type, codes_nonlocal, pl.Tn_vis, vq.n_groups, vq.codebook_size, pl.dkv, pre_k, bk, Kh, pre_v, bv, Vh,
+                            pl.vt ? pl.ldv_hat : pl.dkv, argmin_there ? scores : nullptr, cnorm, at.n_local, codes_local_out, s);
         if (rc) return rc;
     }
     mark(1, s);
@@ -457,7 +455,7 @@ static int layer_forward_impl(const astra_layer_desc* desc, const void* x_local,
                 if (rc) return rc;
             }
         }
-        rc = launch_vq_argmin_scores(vq, scores, cnorm, at.n_local, codes_local_out, s);
+        if (!argmin_there) rc = launch_vq_argmin_scores(vq, scores, cnorm, at.n_local, codes_local_out, s);
         if (rc) return rc;
     }
     // an encode the projection launch did not take is offered to the attention launch (extra workgroups in its tail); if

@@ -154,10 +154,11 @@ int launch_vt_pack(const astra_vq_desc& d, const void* src, int64_t ld_src, cons
 int launch_kv_pack(const astra_vq_desc& d, const void* codes_k, const void* codes_v, const void* cb_k, const void* cb_v, const void* v_loc,
                    int T_n, int T_q, int C, void* k_hat, void* v_hat_t, int ldv_hat, void* v_loc_t, int ldv_loc, hipStream_t s);
 
-// out[t, n] = bias[n] + sum_g P[g, codes[t, g], n] with P fp32 [G, K, N]: row-major [T, ld] in the element type, or (transposed,
-// bf16) [N, ld] in the attention kernel's V^T layout
-int launch_preproj_gather(int dtype, int code_type, const void* codes, const float* P, const void* bias, int T, int G, int K, int N,
-                          void* dst, int ld, bool transposed, hipStream_t s);
+// out[t, n] = bias[n] + sum_g P[g, codes[t, g], n] with P fp32 [G, K, N], for K-hat (row-major [T, N] in the element type) and V-hat (the same, or in bf16
+// [N, ld_v] in the attention kernel's V^T layout); with `scores` also codes_out[t, g] = argmin_k cnorm[g, k] - 2 scores[t, g, k] of n_tokens
+int launch_preproj(int dtype, int code_type, const void* codes, int T, int G, int K, int N, const float* pk, const void* bias_k, void* dst_k,
+                   const float* pv, const void* bias_v, void* dst_v, int ld_v, const float* scores, const float* cnorm, int64_t n_tokens, void* codes_out,
+                   hipStream_t s);
 
 // One C[M,N] = A[M,K] . B[N,K]^T (+ bias[N]) problem of a grouped launch.  When `codes` is set the
 // rows of A are not read from `a` but rebuilt on the fly: A[m, g*dg + j] = codebook[g, codes[m, g], j].

@@ -1,7 +1,7 @@
 // Grouped VQ encode (paper Sec. 2, "Vanilla VQ" / "Grouped VQ") for wide groups, compiled with the matrix-core accumulators in the
 // accumulation registers (this file is built without the flag that keeps them in ordinary vector registers): a wavefront
 // holds 64 accumulator values next to two chunks of 20 operand fragments in flight, which only fit that way.
-#include "common.h"
+#include "vq_argmin_body.h"
 #include "vq_encode_body.h"
 
 namespace astra {
@@ -161,29 +161,7 @@ int launch_vq_encode_wide(const astra_vq_desc& d, const void* x, int64_t ldx, in
 template <typename CodeT>
 __global__ __launch_bounds__(256) void vq_argmin_scores_kernel(const float* __restrict__ scores, const float* __restrict__ cnorm,
                                                                CodeT* __restrict__ codes, int64_t n_rows, int G, int K) {
-    const int64_t row = ((int64_t)blockIdx.x * 256 + threadIdx.x) / kWave;        // (token, group)
-    if (row >= n_rows) return;
-    const int lane = lane_id();
-    const int g = (int)(row % G);
-    const float* __restrict__ sr = scores + row * K;
-    const float* __restrict__ cn = cnorm + (int64_t)g * K;
-    float best = INFINITY;
-    int arg = 0x7fffffff;
-    for (int k0 = 4 * lane; k0 < K; k0 += 4 * kWave) {                         // K is a multiple of 4
-        const f32x4 sv = *reinterpret_cast<const f32x4*>(sr + k0);
-        const f32x4 cv = *reinterpret_cast<const f32x4*>(cn + k0);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const float d = fmaf(-2.f, sv[e], cv[e]);
-            if (d < best) { best = d; arg = k0 + e; }
-        }
-    }
-    for (int off = 32; off > 0; off >>= 1) {
-        const float ob = __shfl_xor(best, off);
-        const int oa = __shfl_xor(arg, off);
-        if (ob < best || (ob == best && oa < arg)) { best = ob; arg = oa; }
-    }
-    if (lane == 0) codes[row] = (CodeT)arg;
+    vq_argmin_scores_rows(scores, cnorm, codes, n_rows, G, K, blockIdx.x);
 }
 
 int launch_vq_argmin_scores(const astra_vq_desc& d, const float* scores, const float* cnorm, int64_t n_tokens, void* codes, hipStream_t s) {

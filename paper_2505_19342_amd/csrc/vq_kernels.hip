@@ -3,6 +3,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "vq_argmin_body.h"
 #include "vq_decode_body.h"
 #include "vq_encode_body.h"
 #include "vq_encode_f32_body.h"
@@ -367,11 +368,8 @@ int launch_kv_pack(const astra_vq_desc& d, const void* codes_k, const void* code
 // through LDS into the [N, ld] layout with permuted token positions that the attention kernel reads V in (vt_pack_kernel).
 // ------------------------------------------------------------------------------------------------
 template <typename CodeT, typename ElemT, bool TRANSPOSED>
-__global__ __launch_bounds__(256) void preproj_gather_kernel(const CodeT* __restrict__ codes, const float* __restrict__ P,
-                                                             const ElemT* __restrict__ bias, int T, int G, int K, int N,
-                                                             ElemT* __restrict__ dst, int ld) {
-    __shared__ __attribute__((aligned(16))) uint16_t tile[TRANSPOSED ? 64 * kVtStride : 8];
-    const int t0 = blockIdx.x * 64, c0 = blockIdx.y * 64;
+__device__ __forceinline__ void preproj_gather_tile(const CodeT* __restrict__ codes, const float* __restrict__ P, const ElemT* __restrict__ bias, int T,
+                                                    int G, int K, int N, ElemT* __restrict__ dst, int ld, int t0, int c0, uint16_t* tile) {
     const int tid = threadIdx.x;
 #pragma unroll
     for (int it = 0; it < 2; ++it) {
@@ -437,25 +435,54 @@ __global__ __launch_bounds__(256) void preproj_gather_kernel(const CodeT* __rest
     }
 }
 
-// out [T, ld] row-major in the element type, or (transposed, bf16 only) [N, ld] with ld the padded token count.
-int launch_preproj_gather(int dtype, int code_type, const void* codes, const float* P, const void* bias, int T, int G, int K, int N,
-                          void* dst, int ld, bool transposed, hipStream_t s) {
-    if (T < 0 || G <= 0 || K <= 0 || N <= 0 || N % 8 != 0) return ASTRA_ERR_UNSUPPORTED;
-    if (transposed && (dtype != ASTRA_BF16 || N % 64 != 0 || ld % 64 != 0 || ld < T)) return ASTRA_ERR_UNSUPPORTED;
-    if (!transposed && ld < N) return ASTRA_ERR_SHAPE;
-    const int64_t bt = transposed ? ld / 64 : ceil_div(T, 64);
-    if (bt == 0) return ASTRA_OK;
-    if (bt > 0x7fffffff || ceil_div(N, 64) > 65535) return ASTRA_ERR_SHAPE;
-    const dim3 grid((unsigned)bt, (unsigned)ceil_div(N, 64));
+// One launch for both matrices, and for the argmin of a wide group's encode where its scores came out of the projection launch: the three passes depend on
+// nothing of one another, and each by itself is a launch and two trips to memory (3072 x 1024 from one group, 1024 tokens: 5.4 + 5.4 + 4.9 us and two gaps, together 8.0).
+struct PreprojBatch {
+    const void *codes, *bias_k, *bias_v;
+    const float *pk, *pv;
+    void *dst_k, *dst_v;
+    int32_t T, G, K, N, ld_k, ld_v;
+    int32_t tiles_k, tiles_v;          // workgroups along T
+    const float *scores, *cnorm;       // of the local tokens; n_rows 0: none
+    void* codes_out;
+    int64_t n_rows;
+};
+
+template <typename CodeT, typename ElemT>
+__global__ __launch_bounds__(256) void preproj_kernel(const PreprojBatch b) {
+    constexpr bool VT = sizeof(ElemT) == 2;          // V-hat in the attention's transposed layout
+    __shared__ __attribute__((aligned(16))) uint16_t tile[VT ? 64 * kVtStride : 8];
+    const int cols = (b.N + 63) / 64, n_k = b.tiles_k * cols, n_kv = n_k + b.tiles_v * cols, i = blockIdx.x;
+    if (i < n_k)
+        preproj_gather_tile<CodeT, ElemT, false>((const CodeT*)b.codes, b.pk, (const ElemT*)b.bias_k, b.T, b.G, b.K, b.N, (ElemT*)b.dst_k, b.ld_k,
+                                                 i % b.tiles_k * 64, i / b.tiles_k * 64, tile);
+    else if (i < n_kv)
+        preproj_gather_tile<CodeT, ElemT, VT>((const CodeT*)b.codes, b.pv, (const ElemT*)b.bias_v, b.T, b.G, b.K, b.N, (ElemT*)b.dst_v, b.ld_v,
+                                              (i - n_k) % b.tiles_v * 64, (i - n_k) / b.tiles_v * 64, tile);
+    else
+        vq_argmin_scores_rows(b.scores, b.cnorm, (CodeT*)b.codes_out, b.n_rows, b.G, b.K, i - n_kv);
+}
+
+int launch_preproj(int dtype, int code_type, const void* codes, int T, int G, int K, int N, const float* pk, const void* bias_k, void* dst_k,
+                   const float* pv, const void* bias_v, void* dst_v, int ld_v, const float* scores, const float* cnorm, int64_t n_tokens, void* codes_out,
+                   hipStream_t s) {
+    const bool vt = dtype == ASTRA_BF16;
+    if (T <= 0 || G <= 0 || K <= 0 || N <= 0 || N % 8 != 0) return ASTRA_ERR_UNSUPPORTED;
+    if (vt && (N % 64 != 0 || ld_v % 64 != 0 || ld_v < T)) return ASTRA_ERR_UNSUPPORTED;
+    if (scores && K % 4 != 0) return ASTRA_ERR_UNSUPPORTED;
+    if (ceil_div(N, 64) > 65535) return ASTRA_ERR_SHAPE;
+    PreprojBatch b{codes, bias_k, bias_v, pk, pv, dst_k, dst_v, T, G, K, N, N, ld_v, (int32_t)ceil_div(T, 64), (int32_t)(vt ? ld_v / 64 : ceil_div(T, 64)),
+                   scores, cnorm, codes_out, scores ? n_tokens * G : 0};
+    const int64_t grid = (b.tiles_k + (int64_t)b.tiles_v) * ceil_div(N, 64) + ceil_div(b.n_rows, 4);
+    if (grid > 0x7fffffff) return ASTRA_ERR_SHAPE;
     const bool c16 = code_type == ASTRA_CODE_U16;
-#define ASTRA_GATHER(CT, ET, TR) preproj_gather_kernel<CT, ET, TR><<<grid, 256, 0, s>>>((const CT*)codes, P, (const ET*)bias, T, G, K, N, (ET*)dst, ld)
-    if (dtype == ASTRA_BF16) {
-        if (transposed) { if (c16) ASTRA_GATHER(uint16_t, uint16_t, true); else ASTRA_GATHER(uint8_t, uint16_t, true); }
-        else { if (c16) ASTRA_GATHER(uint16_t, uint16_t, false); else ASTRA_GATHER(uint8_t, uint16_t, false); }
+    if (vt) {
+        if (c16) preproj_kernel<uint16_t, uint16_t><<<(int)grid, 256, 0, s>>>(b);
+        else preproj_kernel<uint8_t, uint16_t><<<(int)grid, 256, 0, s>>>(b);
     } else {
-        if (c16) ASTRA_GATHER(uint16_t, float, false); else ASTRA_GATHER(uint8_t, float, false);
+        if (c16) preproj_kernel<uint16_t, float><<<(int)grid, 256, 0, s>>>(b);
+        else preproj_kernel<uint8_t, float><<<(int)grid, 256, 0, s>>>(b);
     }
-#undef ASTRA_GATHER
     return launch_status();
 }
 
