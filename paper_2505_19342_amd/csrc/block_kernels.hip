@@ -101,6 +101,66 @@ __device__ __forceinline__ void norm_row(const float* __restrict__ x, int D, int
     }
 }
 
+// The same for rows of at most 1024 values with a wavefront per row: what four wavefronts hold and add above, one holds and adds here in the same order, so
+// that the result is theirs bit for bit, without the two barriers.
+constexpr int kNormWaveWidth = 1024;
+template <typename OutT>
+__device__ __forceinline__ void norm_row_wave(const float* __restrict__ x, int64_t r, int D, int kind, float eps, const float* __restrict__ gain,
+                                              const float* __restrict__ bias, OutT* __restrict__ out) {
+    constexpr int W = kNormThreads / kWave;
+    const int lane = lane_id(), n4 = D >> 2;
+    const f32x4* __restrict__ row = reinterpret_cast<const f32x4*>(x + r * D);
+    const float inv_d = 1.f / (float)D;
+    f32x4 c[W], g[W], b[W];
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+        const int i = min(lane + kWave * w, n4 - 1);
+        c[w] = row[i];
+        g[w] = gain ? reinterpret_cast<const f32x4*>(gain)[i] : f32x4{1.f, 1.f, 1.f, 1.f};
+        b[w] = kind == 0 && bias ? reinterpret_cast<const f32x4*>(bias)[i] : f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    auto row_sum = [](const float(&p)[W]) __attribute__((always_inline)) {
+        float t = 0.f;
+#pragma unroll
+        for (int w = 0; w < W; ++w) t += wave_sum(p[w]);
+        return t;
+    };
+    float p[W];
+#pragma unroll
+    for (int w = 0; w < W; ++w) p[w] = lane + kWave * w < n4 ? (c[w].x + c[w].y) + (c[w].z + c[w].w) : 0.f;
+    const float mean = kind == 0 ? row_sum(p) * inv_d : 0.f;
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+        const f32x4 d = c[w] - mean;
+        p[w] = lane + kWave * w < n4 ? (d.x * d.x + d.y * d.y) + (d.z * d.z + d.w * d.w) : 0.f;
+    }
+    const float inv = 1.f / sqrtf(row_sum(p) * inv_d + eps);
+    OutT* __restrict__ orow = out + r * D;
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+        const int i = lane + kWave * w;
+        if (i < n4) {
+            f32x4 v = (c[w] - mean) * inv;
+            if (gain) v *= g[w];
+            if (kind == 0 && bias) v += b[w];
+            if constexpr (sizeof(OutT) == 2) {
+                u32x2 o;
+                o.x = pack_bf16x2(v.x, v.y);
+                o.y = pack_bf16x2(v.z, v.w);
+                reinterpret_cast<u32x2*>(orow)[i] = o;
+            } else {
+                reinterpret_cast<f32x4*>(orow)[i] = v;
+            }
+        }
+    }
+}
+// A wavefront per workgroup (four rows to a workgroup: 12 GPT-2 blocks 608.7 us, 604 now, 614.5 with a workgroup of four wavefronts per row).
+template <typename OutT>
+__global__ __launch_bounds__(kWave) void norm_wave_kernel(const float* __restrict__ x, int D, int kind, float eps, const float* __restrict__ gain,
+                                                          const float* __restrict__ bias, OutT* __restrict__ out) {
+    norm_row_wave<OutT>(x, blockIdx.x, D, kind, eps, gain, bias, out);
+}
+
 template <typename OutT, bool VEC>
 __global__ __launch_bounds__(kNormThreads) void norm_kernel(const float* __restrict__ x, int D, int kind, float eps,
                                                             const float* __restrict__ gain, const float* __restrict__ bias,
@@ -111,15 +171,24 @@ __global__ __launch_bounds__(kNormThreads) void norm_kernel(const float* __restr
 // The normalisation with the decode of the peers' codes behind its rows, where the projections need the rebuilt rows in memory (slices of no whole 16 bytes).
 // The launch lasts what the longer of the two takes, both a few memory latencies for a small model: 6 blocks of 256 + 768 rows, 64 groups of 12, 334.6 us
 // with a launch for the decode, 317.3 now; 512 + 1024 rows 522.8 / 501.0.
-template <typename CodeT>
+template <typename CodeT, bool WAVE>
 __global__ __launch_bounds__(kNormThreads) void norm_decode_kernel(const float* __restrict__ x, int T, int D, int kind, float eps,
                                                                    const float* __restrict__ gain, const float* __restrict__ bias,
                                                                    uint16_t* __restrict__ out, const DecodeJob job) {
     static_assert(kNormThreads == kDecThreads, "one workgroup size for both");
-    if ((int)blockIdx.x < T) norm_row<uint16_t, true>(x, D, kind, eps, gain, bias, out);
-    else vq_decode_run<CodeT>(job, blockIdx.x - (uint32_t)T);
+    constexpr int ROWS = WAVE ? kNormThreads / kWave : 1;
+    const int wgs = (T + ROWS - 1) / ROWS;
+    if ((int)blockIdx.x >= wgs) {
+        vq_decode_run<CodeT>(job, blockIdx.x - (uint32_t)wgs);
+    } else if (WAVE) {
+        const int r = (int)blockIdx.x * ROWS + (int)(threadIdx.x / kWave);
+        if (r < T) norm_row_wave<uint16_t>(x, r, D, kind, eps, gain, bias, out);
+    } else {
+        norm_row<uint16_t, true>(x, D, kind, eps, gain, bias, out);
+    }
 }
 
+static bool norm_by_wave(int D) { return D % 4 == 0 && D <= kNormWaveWidth; }
 static bool norm_in_registers(int D) { return D % 4 == 0 && D <= kNormThreads * kNormCache * 4; }
 
 bool norm_decode_ok(int64_t T, int D, const DecodeJob& job) { return T > 0 && norm_in_registers(D) && T + job.blocks <= 0x7fffffff; }
@@ -127,9 +196,12 @@ bool norm_decode_ok(int64_t T, int D, const DecodeJob& job) { return T > 0 && no
 int launch_norm_decode(int kind, const float* x, int64_t T, int D, float eps, const float* gain, const float* bias, void* out, const DecodeJob& job,
                        hipStream_t s) {
     if (!norm_decode_ok(T, D, job) || (kind != 0 && kind != 1)) return ASTRA_ERR_SHAPE;
-    const int grid = (int)T + job.blocks;
-    if (job.code_bytes == 1) norm_decode_kernel<uint8_t><<<grid, kNormThreads, 0, s>>>(x, (int)T, D, kind, eps, gain, bias, (uint16_t*)out, job);
-    else norm_decode_kernel<uint16_t><<<grid, kNormThreads, 0, s>>>(x, (int)T, D, kind, eps, gain, bias, (uint16_t*)out, job);
+    const bool wave = norm_by_wave(D);
+    const int n = (int)T, grid = (int)ceil_div(n, wave ? kNormThreads / kWave : 1) + job.blocks;
+#define ASTRA_NORM_DECODE(CODE, WAVE) norm_decode_kernel<CODE, WAVE><<<grid, kNormThreads, 0, s>>>(x, n, D, kind, eps, gain, bias, (uint16_t*)out, job)
+    if (job.code_bytes == 1) { if (wave) ASTRA_NORM_DECODE(uint8_t, true); else ASTRA_NORM_DECODE(uint8_t, false); }
+    else { if (wave) ASTRA_NORM_DECODE(uint16_t, true); else ASTRA_NORM_DECODE(uint16_t, false); }
+#undef ASTRA_NORM_DECODE
     return launch_status();
 }
 
@@ -138,6 +210,11 @@ int launch_norm(int dtype, int kind, const float* x, int64_t T, int D, float eps
     if (T < 0 || D <= 0 || T > 0x7fffffff || (kind != 0 && kind != 1)) return ASTRA_ERR_SHAPE;
     if (T == 0) return ASTRA_OK;
     const bool vec = norm_in_registers(D);
+    if (norm_by_wave(D)) {
+        if (dtype == ASTRA_BF16) norm_wave_kernel<uint16_t><<<(int)T, kWave, 0, s>>>(x, D, kind, eps, gain, bias, (uint16_t*)out);
+        else norm_wave_kernel<float><<<(int)T, kWave, 0, s>>>(x, D, kind, eps, gain, bias, (float*)out);
+        return launch_status();
+    }
     if (dtype == ASTRA_BF16) {
         if (vec) norm_kernel<uint16_t, true><<<(int)T, kNormThreads, 0, s>>>(x, D, kind, eps, gain, bias, (uint16_t*)out);
         else norm_kernel<uint16_t, false><<<(int)T, kNormThreads, 0, s>>>(x, D, kind, eps, gain, bias, (uint16_t*)out);

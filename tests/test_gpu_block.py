@@ -256,3 +256,12 @@ def test_slices_of_no_whole_16_bytes(words, seq_len):
     workgroup, and six rows of peers."""
     layer = dataclasses.replace(wl.GPT2_SMALL, name="gpt2_64_groups", n_groups=64, codebook_size=words, seq_len=seq_len, seed=81)
     run_case(dataclasses.replace(wl.GPT2_SMALL_BLOCK, name="gpt2_64_groups_block", layer=layer), 3)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("norm_kind", ["layernorm", "rmsnorm"])
+@pytest.mark.parametrize("d", [64, 832, 1024, 1088])
+def test_widths_of_the_normalisation(d, norm_kind, dtype):
+    """A wavefront per row up to 1024 values (lanes without any, a ragged last quarter, all of them), a workgroup beyond."""
+    layer = wl.LayerConfig("norm_widths", dtype, d, 2, 1, 64, 99, 3, 8, 16, causal=True, seed=82)
+    run_case(wl.BlockConfig("norm_widths_block", layer, norm_kind, "gelu_tanh", 128, 1e-5, norm_kind == "layernorm"), 2)

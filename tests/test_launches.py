@@ -254,5 +254,13 @@ def test_rebuilt_rows_of_a_block_come_with_its_first_normalisation(tmp_path):
     calls = [dict(block, n_nonlocal=300, groups=64), dict(block, n_nonlocal=300, groups=64, before=0), dict(block, n_nonlocal=300, groups=128), dict(block, n_nonlocal=300, groups=32)]
     with_norm, no_rows, own, none = (kernels(r) for r in record(calls, tmp_path))
     assert with_norm[0].startswith("norm_decode_kernel") and not any("vq_decode" in k for k in with_norm)
-    assert own[0].startswith("norm_kernel") and any("vq_decode_kernel" in k for k in own)
+    assert own[0].startswith("norm_wave_kernel") and any("vq_decode_kernel" in k for k in own)
     assert not any("decode" in k for k in no_rows + none)
+
+
+def test_normalisation_by_wavefronts_of_narrow_rows(tmp_path):
+    """Up to 1024 values a wavefront per row, wider ones a workgroup."""
+    block = dict(entry="block", hq=4, hkv=4, dh=64, n_local=33, n_nonlocal=66, causal=True, norm="rmsnorm", mlp="gelu_tanh", dff=256, groups=8, words=16)
+    for d, name in ((64, "norm_wave_kernel"), (1024, "norm_wave_kernel"), (1088, "norm_kernel")):
+        names = kernels(record([dict(block, d=d)], tmp_path)[0])
+        assert sum(k.startswith(name) for k in names) == 2, (d, names)
