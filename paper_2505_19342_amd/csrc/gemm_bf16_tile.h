@@ -19,10 +19,23 @@ struct GemmBatch {
                                            // contracts k in [s * k_split, (s + 1) * k_split) into slice s of an fp32 buffer
 };
 
-__device__ __forceinline__ int find_problem(const GemmBatch& b, int tile) {
-    int p = 0;
-    while (p + 1 < b.n && tile >= b.tile_begin[p + 1]) ++p;
-    return p;
+// The problem a tile belongs to, with the tile's number in it.  The arguments are a memory latency away, and the fields of a problem whose number has to be
+// found first are another: with ONE (launches of one problem) nothing is found, and launches that may be of one (MAYBE_ONE) ask for the first problem's
+// together with the number of problems.  12 GPT-2 blocks, 36 launches of one problem with an epilogue of the MLP: 603.5 us, 583.1 now.
+enum { kOneProblem, kMaybeOneProblem, kManyProblems };
+struct TileProblem {
+    GemmProblem p;
+    int tile, tiles_m;
+};
+template <int MODE>
+__device__ __forceinline__ TileProblem find_problem(const GemmBatch& b, int tile) {
+    if (MODE == kMaybeOneProblem)
+        asm volatile("" ::"s"(b.n), "s"(b.tiles_m[0]), "s"(b.p[0].a), "s"(b.p[0].b), "s"(b.p[0].bias), "s"(b.p[0].c), "s"(b.p[0].M), "s"(b.p[0].N), "s"(b.p[0].K),
+                     "s"(b.p[0].lda), "s"(b.p[0].ldc), "s"(b.p[0].ldb), "s"(b.p[0].c_mode));
+    if (MODE == kOneProblem || (MODE == kMaybeOneProblem && b.n == 1)) return {b.p[0], tile, b.tiles_m[0]};
+    int i = 0;
+    while (i + 1 < b.n && tile >= b.tile_begin[i + 1]) ++i;
+    return {b.p[i], tile - b.tile_begin[i], b.tiles_m[i]};
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -159,10 +172,9 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_nt_bf16_kernel(const GemmBa
         split = vt / tiles;
         vt -= split * tiles;
     }
-    const int pi = find_problem(batch, vt);
-    const GemmProblem& P = batch.p[pi];
-    const int tile = vt - batch.tile_begin[pi];
-    const int tiles_m = batch.tiles_m[pi];
+    const TileProblem tp = find_problem<EPI != kEpiLayer ? kOneProblem : ENC ? kManyProblems : kMaybeOneProblem>(batch, vt);
+    const GemmProblem& P = tp.p;
+    const int tile = tp.tile, tiles_m = tp.tiles_m;
     const int tm = tile % tiles_m, tn = tile / tiles_m;
     const int m0 = tm * BM, n0 = tn * BN;
     const int M = P.M, N = P.N, K = P.K;

@@ -67,10 +67,9 @@ __global__ __launch_bounds__(kWaveThreads) void gemm_wave_kernel(const GemmBatch
     } else {
         vt = xcd_remap(blockIdx.x, gridDim.x);
     }
-    const int pi = find_problem(batch, vt);
-    const GemmProblem& P = batch.p[pi];
-    const int tile = vt - batch.tile_begin[pi];
-    const int tiles_m = batch.tiles_m[pi];
+    const TileProblem tp = find_problem<EPI != kEpiLayer ? kOneProblem : GATHER || ENC ? kManyProblems : kMaybeOneProblem>(batch, vt);
+    const GemmProblem& P = tp.p;
+    const int tile = tp.tile, tiles_m = tp.tiles_m;
     const int m0 = (tile % tiles_m) * BM, tn = tile / tiles_m, n0 = tn * BN;
     const int M = P.M, N = P.N, K = P.K;
 

@@ -14,14 +14,13 @@ namespace astra {
 // As a vector-ALU kernel with two barriers and a latency per 64 of contraction, against now (back to back): 64 x 192 outputs, K = 192 / 768:
 // 8.0 / 23.5 us, now 3.7 / 5.2; 1000 x 1000, K = 1000: 68.7, now 27.4.  Error against fp64 at K = 768: 4.9e-7 of the norm, now 2.5e-7.
 // ------------------------------------------------------------------------------------------------
-template <int T>
+template <int T, bool ONE>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmBatch batch) {
     constexpr int BT = 16 * T, WAVES = 4, PD = 4 / T, LDN = BT + 4;
     __shared__ __align__(16) float red[WAVES * BT * LDN];
-    const int pi = find_problem(batch, blockIdx.x);
-    const GemmProblem& P = batch.p[pi];
-    const int tile = blockIdx.x - batch.tile_begin[pi];
-    const int m0 = tile % batch.tiles_m[pi] * BT, n0 = tile / batch.tiles_m[pi] * BT;
+    const TileProblem tp = find_problem<ONE ? kOneProblem : kManyProblems>(batch, blockIdx.x);
+    const GemmProblem& P = tp.p;
+    const int tile = tp.tile, m0 = tile % tp.tiles_m * BT, n0 = tile / tp.tiles_m * BT;
     const int M = P.M, N = P.N, K = P.K;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -144,13 +143,19 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmBatch batch) {
     }
 }
 
+template <int T>
+static void launch_f32_tiles(int tiles, const GemmBatch& batch, hipStream_t s) {
+    if (batch.n == 1) gemm_f32_kernel<T, true><<<tiles, 256, 0, s>>>(batch);
+    else gemm_f32_kernel<T, false><<<tiles, 256, 0, s>>>(batch);
+}
+
 // the batch was filled for square tiles of 16, 32 or 64
 int launch_gemm_f32(int tile, const GemmBatch& batch, hipStream_t s) {
     const int tiles = batch.tile_begin[batch.n];
     if (tiles == 0) return ASTRA_OK;
-    if (tile == 64) gemm_f32_kernel<4><<<tiles, 256, 0, s>>>(batch);
-    else if (tile == 32) gemm_f32_kernel<2><<<tiles, 256, 0, s>>>(batch);
-    else gemm_f32_kernel<1><<<tiles, 256, 0, s>>>(batch);
+    if (tile == 64) launch_f32_tiles<4>(tiles, batch, s);
+    else if (tile == 32) launch_f32_tiles<2>(tiles, batch, s);
+    else launch_f32_tiles<1>(tiles, batch, s);
     return launch_status();
 }
 
