@@ -533,6 +533,7 @@ typedef float f32x2 __attribute__((ext_vector_type(2), aligned(4)));      // par
 constexpr int kMergeLoads = 8;
 template <typename T, bool BASE2>
 __global__ __launch_bounds__(kDecThreads) void decode_merge_kernel(const DecodeParams p) {
+    asm volatile("" ::"s"(p.part), "s"(p.out), "s"(p.lse), "s"(p.Hq), "s"(p.dh), "s"(p.n_chunks_loc), "s"(p.n_chunks_nl), "s"(gridDim.y));     // all in one trip
     const int h = blockIdx.x, tid = threadIdx.x, lane = lane_id();
     const int n = p.n_chunks_loc + p.n_chunks_nl, last = max(n - 1, 0);
     const int64_t stride = (int64_t)p.Hq * (p.dh + 2);

@@ -77,6 +77,10 @@ __global__ __launch_bounds__(64 * WAVES, 2) void decode_stream_kernel(const Deco
     __shared__ float ml[WAVES][REP][2];
     __shared__ uint16_t stage[NGH > 0 ? WAVES : 1][2][2][32][4];      // codes of a tile: [slot][key | value][token][group]
 
+    // the arguments arrive together; each branch asking for its own is another trip to them
+    asm volatile("" ::"s"(p.q), "s"(p.k_loc), "s"(p.v_loc), "s"(p.codes_k), "s"(p.codes_v), "s"(p.valid_bits), "s"(p.cb_k), "s"(p.cb_v), "s"(p.part), "s"(p.Hq),
+                 "s"(p.Hkv), "s"(p.n_local), "s"(p.n_nonlocal), "s"(p.G), "s"(p.K), "s"(p.dg), "s"(p.code16), "s"(p.n_chunks_loc), "s"(p.n_chunks_nl),
+                 "s"(p.scale));
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = lane & 15, g = lane >> 4;
