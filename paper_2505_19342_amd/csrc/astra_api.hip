@@ -92,7 +92,7 @@ static int make_plan(const astra_layer_desc* desc, LayerPlan* pl) {
     // (with one group the product rides in the projection launch for free; with more it is launches of its own, which pay once
     // a group's codebook has 2^17 elements or more: below that the kernel that streams the codebook per 32 tokens is faster)
     pl->wide_enc = desc->vq.dtype == ASTRA_BF16 && vq_encode_wide_ok(desc->vq.codebook_size, dg, pl->D) && a.n_local > 0 &&
-                   desc->vq.codebook_size % 8 == 0 &&
+                   desc->vq.codebook_size % 8 == 0 && !vq_encode_without_scores(a.n_local, desc->vq.n_groups, desc->vq.codebook_size, dg, pl->D) &&
                    (desc->vq.n_groups == 1 || (int64_t)desc->vq.codebook_size * dg >= (1 << 17)) &&
                    (size_t)a.n_local * desc->vq.n_groups * desc->vq.codebook_size * 4 <= ((size_t)256 << 20);
     pl->off_scores = take(pl->wide_enc ? (size_t)a.n_local * desc->vq.n_groups * desc->vq.codebook_size * 4 : 0);
@@ -249,6 +249,7 @@ int astra_vq_encode_ws(const astra_vq_desc* desc, const void* x, int64_t n_token
     if (!encode_ws_applies(*desc, n_tokens)) return launch_vq_encode(*desc, x, desc->d_model, n_tokens, codebook, cnorm, codes_out, s);
     if (!workspace || workspace_bytes < astra_vq_encode_workspace_bytes(desc, n_tokens)) return ASTRA_ERR_WORKSPACE;
     const int G = desc->n_groups, K = desc->codebook_size, D = desc->d_model, dg = D / G;
+    if (vq_encode_without_scores(n_tokens, G, K, dg, D)) return launch_vq_encode(*desc, x, D, n_tokens, codebook, cnorm, codes_out, s);
     float* scores = (float*)workspace;
     for (int pass = 0; pass < 2; ++pass) {           // every launch is validated before the first one runs
         for (int g0 = 0; g0 < G; g0 += kMaxGemmProblems) {

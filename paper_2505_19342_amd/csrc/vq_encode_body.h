@@ -62,9 +62,14 @@ __device__ __forceinline__ void vq_encode_fast_run_nks(const EncodeJob& job, int
     constexpr int WAVES = THREADS / 64;
     constexpr int TOKENS = WAVES * 32 * TB;             // tokens per item
     constexpr int ITS = kEncCbSlots / THREADS;          // codebook transfers per thread per tile
-    constexpr int NORM_LANES = kEncCnSlots / WAVES;     // lanes per wavefront that fetch 4 norms each
+    // groups of 128 values: tiles of 64 codewords, and an item's tokens are asked for when the one before is done (no registers for two)
+    constexpr bool WIDE = NKS > 4;
+    static_assert(!WIDE || (TB == 2 && NKS == 8), "a tile of 64 codewords is two units of 32");
+    constexpr int CW = WIDE ? kEncCw / 2 : kEncCw;      // codewords of a tile
+    constexpr int PPR = WIDE ? 16 : 8;                  // 16-byte slots of a codeword
+    constexpr int NORM_LANES = CW / 4 / WAVES;          // lanes per wavefront that fetch 4 norms each
     constexpr int DMA = ITS + 1;                        // transfers of a wavefront per tile: "tile s has landed" is a fixed vmcnt threshold
-    constexpr int UNITS = TB == 2 ? 4 : 2, NA = TB == 2 ? 1 : 2;      // units of a tile, codeword blocks of 32 in one
+    constexpr int UNITS = TB == 2 ? CW / 32 : 2, NA = TB == 2 ? 1 : 2;      // units of a tile, codeword blocks of 32 in one
     if (lo >= hi) return;
     const int K = job.K, dg = job.dg, n_tokens = job.n_tokens, n_tb = job.n_tb;
     const int tid = threadIdx.x;
@@ -73,16 +78,17 @@ __device__ __forceinline__ void vq_encode_fast_run_nks(const EncodeJob& job, int
     const int i32 = lane & 31, h = lane >> 5;
     const int n_pieces = dg >> 3;                       // valid 16-byte pieces per codeword
     const uint32_t row_b = (uint32_t)dg * 2u;
-    const int n_tiles = (K + kEncCw - 1) / kEncCw, n_steps = (hi - lo) * n_tiles;
+    const int n_tiles = (K + CW - 1) / CW, n_steps = (hi - lo) * n_tiles;
 
-    // ---- transfers.  Slot c = tid + THREADS*it is (codeword c/8, physical piece c%8) and receives logical piece (c%8) ^ swz(c/8); swz has period 16
-    // codewords and THREADS/8 codewords separate two `it`.  Byte offsets past the group's last codeword are clamped to its row K-1.
-    const int cw_l = tid >> 3;
-    const int piece = (tid & 7) ^ enc_swz(cw_l);
+    // ---- transfers.  Slot c = tid + THREADS*it is (codeword c/PPR, physical piece c%PPR) and receives logical piece (c%PPR) ^ swz(c/PPR); swz has period 16
+    // codewords and THREADS/PPR codewords separate two `it`.  Byte offsets past the group's last codeword are clamped to its row K-1.
+    auto swz_of = [](int r) __attribute__((always_inline)) { return WIDE ? r & 15 : enc_swz(r); };
+    const int cw_l = tid / PPR;
+    const int piece = (tid % PPR) ^ swz_of(cw_l);
     const bool piece_ok = piece < n_pieces;
     uint32_t cb_off[ITS];
 #pragma unroll
-    for (int it = 0; it < ITS; ++it) cb_off[it] = (uint32_t)(cw_l + (THREADS / 8) * it) * row_b + (uint32_t)piece * 16u;
+    for (int it = 0; it < ITS; ++it) cb_off[it] = (uint32_t)(cw_l + (THREADS / PPR) * it) * row_b + (uint32_t)piece * 16u;
     const uint32_t cb_off_max = (uint32_t)(K - 1) * row_b + (uint32_t)piece * 16u;
     const uint32_t cn_off = (uint32_t)(4 * NORM_LANES * wave + 4 * lane) * 4u, cn_off_max = (uint32_t)(K - 4) * 4u;
     int g = lo / n_tb, block = lo - g * n_tb;      // of the item that is worked on
@@ -93,14 +99,14 @@ __device__ __forceinline__ void vq_encode_fast_run_nks(const EncodeJob& job, int
         if (s_step >= n_steps) return;
         const int buf = s_step % kEncBufs;
         const uint32_t base = lds_byte_addr(cb_lds + buf * kEncCbSlots);
-        const uint32_t tile_b = (uint32_t)s_tile * (uint32_t)kEncCw * row_b;
+        const uint32_t tile_b = (uint32_t)s_tile * (uint32_t)CW * row_b;
         if (piece_ok) {
 #pragma unroll
             for (int it = 0; it < ITS; ++it)
                 dma_global_to_lds_16(s_cb, min(cb_off[it] + tile_b, cb_off_max), base + (uint32_t)(64 * (wave + WAVES * it)) * 16u);
         }
-        if (lane < NORM_LANES)                          // 128 norms = WAVES x NORM_LANES lanes x 16 bytes
-            dma_global_to_lds_16(s_cn, min(cn_off + (uint32_t)s_tile * (uint32_t)(kEncCw * 4), cn_off_max),
+        if (lane < NORM_LANES)                          // a tile's norms = WAVES x NORM_LANES lanes x 16 bytes
+            dma_global_to_lds_16(s_cn, min(cn_off + (uint32_t)s_tile * (uint32_t)(CW * 4), cn_off_max),
                                  lds_byte_addr(cn_lds + buf * kEncCnSlots) + (uint32_t)wave * (16u * NORM_LANES));
         ++s_step;
         if (++s_tile == n_tiles) {
@@ -147,7 +153,7 @@ __device__ __forceinline__ void vq_encode_fast_run_nks(const EncodeJob& job, int
     auto read_a = [&](int buf, int u, int ks) __attribute__((always_inline)) {
 #pragma unroll
         for (int n = 0; n < NA; ++n)
-            fa[ks][n] = __builtin_bit_cast(bf16x8, cb_lds[buf * kEncCbSlots + (block_of(u, n) * 32 + i32) * 8 + ((2 * ks + h) ^ enc_swz(i32))]);
+            fa[ks][n] = __builtin_bit_cast(bf16x8, cb_lds[buf * kEncCbSlots + (block_of(u, n) * 32 + i32) * PPR + ((2 * ks + h) ^ swz_of(i32))]);
     };
     auto read_cn = [&](int buf, int u) __attribute__((always_inline)) {
 #pragma unroll
@@ -210,23 +216,23 @@ __device__ __forceinline__ void vq_encode_fast_run_nks(const EncodeJob& job, int
             for (int v = 0; v < 16; ++v) acc[1][j][v] = INFINITY;         // in the place of the unit before the first
         for (int t = 0; t < n_tiles; ++t, ++step) {
             const int buf = step % kEncBufs, next_buf = (step + 1) % kEncBufs;
-            const int lim = K - t * kEncCw;                     // codewords of this tile and beyond
+            const int lim = K - t * CW;                         // codewords of this tile and beyond
 #pragma unroll
             for (int u = 0; u < UNITS; ++u) {
                 if (u == UNITS - 1 && step + 1 < n_steps) {
                     // the next tile has landed (the one after it may be outstanding, and the tokens asked for a tile ago); every wavefront is done with
                     // the tile before this one, whose place takes the one three ahead
                     if (step + 2 < n_steps) {
-                        if (t == t_load + 1 && item + 1 < hi) wait_vmem<DMA + TB * NKS>();
+                        if (!WIDE && t == t_load + 1 && item + 1 < hi) wait_vmem<DMA + TB * NKS>();
                         else wait_vmem<DMA>();
                     } else {
                         wait_vmem_all();
                     }
                     __syncthreads();
-                    if (t == t_load && item + 1 < hi) load_tokens(next_g, next_block);
+                    if (!WIDE && t == t_load && item + 1 < hi) load_tokens(next_g, next_block);
                     send_tile();
                 }
-                if (lim < kEncCw) {                             // codewords past K (the last tile of a K that is no multiple of 128) are infinitely far
+                if (lim < CW) {                                 // codewords past K (the last tile of a K that is no multiple of a tile's) are infinitely far
 #pragma unroll
                     for (int n = 0; n < NA; ++n) {
                         const int left = lim - 32 * block_of(u, n) - 4 * h;
@@ -258,7 +264,7 @@ __device__ __forceinline__ void vq_encode_fast_run_nks(const EncodeJob& job, int
 #pragma unroll
         for (int b = 0; b < TB; ++b) {
             const int e = k0[b] == best[b] ? 0 : k1[b] == best[b] ? 1 : k2[b] == best[b] ? 2 : 3;
-            int arg = til[b] * kEncCw + (grp[b] >> 2) * 32 + (grp[b] & 3) * 8 + 4 * h + e;
+            int arg = til[b] * CW + (grp[b] >> 2) * 32 + (grp[b] & 3) * 8 + 4 * h + e;
             // merge the two half-waves that hold the same token
             const float ob = __shfl_xor(best[b], 32);
             const int oa = __shfl_xor(arg, 32);
@@ -269,6 +275,7 @@ __device__ __forceinline__ void vq_encode_fast_run_nks(const EncodeJob& job, int
                 else ((uint8_t*)job.codes)[at] = (uint8_t)arg;
             }
         }
+        if (WIDE && item + 1 < hi) load_tokens(next_g, next_block);
         if (item + 1 < hi) take_tokens();
         g = next_g;
         block = next_block;
@@ -297,6 +304,18 @@ __device__ __forceinline__ void vq_encode_fast_run(const EncodeJob& job, int lo,
 inline int vq_encode_blocks(const EncodeJob& e, int64_t wgs) {
     const int64_t one = ceil_div(e.n_tokens, (int64_t)256) * e.G, two = ceil_div(e.n_tokens, (int64_t)512) * e.G;
     return 1.6 * (double)ceil_div(two, wgs) < (double)ceil_div(one, wgs) ? 2 : 1;
+}
+
+// Groups of 128 values go through the body in a kernel of its own (64 tokens per wavefront) where the kernel for wide groups, 32 tokens per workgroup, would
+// make more than one round of the units (its rounds are 14 us at K = 1024, where an item of the body's is 21: 128 tokens x 32 groups 13.8 / 21.3 us on it
+// and on the body, 300 28.3 / 22.1, K = 256 6.1 / 9.2 and 10.5 / 10.0, K = 16 4.7 / 6.4 and 7.8 / 7.1; 4000 x 2 groups, K = 1024, 13.5 / 21.9).
+inline bool vq_encode_fast128(int64_t n_tokens, int G, int K, int dg, int64_t ldx) {
+    return dg == 128 && K % 4 == 0 && ldx % 8 == 0 && (int64_t)K * dg * 2 < ((int64_t)1 << 31) && ceil_div(n_tokens, (int64_t)32) * G > 256;
+}
+// Where groups of 128 values are better off without score products: there, and where the products would be more than one launch (32 groups, K = 1024,
+// products and argmin / without: 17 tokens 23.7 / 12.1 us, 1024 78 / 23, 16384 968 / 133; 2 groups, 300 tokens, 8.7 / 12.5).
+inline bool vq_encode_without_scores(int64_t n_tokens, int G, int K, int dg, int64_t ldx) {
+    return vq_encode_fast128(n_tokens, G, K, dg, ldx) || (dg == 128 && G > kMaxGemmProblems);
 }
 
 // true when the fast body handles this configuration

@@ -263,3 +263,16 @@ def test_empty_inputs_and_argument_errors():
         B.astra_vq_prepare(B.VqDesc(B.ASTRA_BF16, B.ASTRA_CODE_U8, 16, 2, 1024), cbd, cn)
     with pytest.raises(B.AstraError):      # NULL output
         B.astra_vq_prepare(B.vq_desc("bf16", 16, 2, 4), cbd, None)
+
+
+@pytest.mark.parametrize("T,G,K", [(257, 32, 1024), (4100, 2, 100), (300, 28, 4), (520, 17, 68), (2100, 64, 64), (600, 32, 256)])
+def test_groups_of_128_values(T, G, K):
+    """64 tokens per wavefront on tiles of 64 codewords (tests/test_launches.py): ragged tiles and token blocks, a codebook of one quad, a single tile, 8- and
+    16-bit codes, workgroups of more than one item whose next tokens are of the next group."""
+    from gpu_util import compare_codes, gpu_vq_encode
+    x, cb = make(40 + T + G, T, G, K, 128, "bf16", "normal")
+    ref, gap = oracle.vq_encode(x, cb, return_gap=True)
+    n_tie = compare_codes(gpu_vq_encode(x, cb, "bf16"), ref, gap, NEAR_TIE)
+    assert n_tie <= max(2, ref.size // 2000)
+    cb[:, K // 2:] = cb[:, :K // 2]                          # every codeword twice: the lower one
+    assert gpu_vq_encode(x, cb, "bf16").max() < K // 2

@@ -264,3 +264,14 @@ def test_normalisation_by_wavefronts_of_narrow_rows(tmp_path):
     for d, name in ((64, "norm_wave_kernel"), (1024, "norm_wave_kernel"), (1088, "norm_kernel")):
         names = kernels(record([dict(block, d=d)], tmp_path)[0])
         assert sum(k.startswith(name) for k in names) == 2, (d, names)
+
+
+def test_encode_of_groups_of_128_values(tmp_path):
+    """The matrix-core body with 64 tokens per wavefront beyond one round of the kernel for wide groups; no score products for more than six groups."""
+    cases = [(256, 32, 1024, "vq_encode_bf16_wide_kernel"), (257, 32, 1024, "vq_encode_bf16_fast128_kernel"), (16384, 32, 16, "vq_encode_bf16_fast128_kernel"),
+             (300, 2, 1024, "gemm"), (4097, 2, 1024, "vq_encode_bf16_fast128_kernel"), (4097, 2, 1022, "vq_encode_bf16_wide_kernel")]
+    results = record([dict(entry="encode", tokens=t, groups=g, words=k, d=128 * g) for t, g, k, _ in cases], tmp_path)
+    for (t, g, k, name), r in zip(cases, results):
+        assert kernels(r)[0].startswith(name), (t, g, k, kernels(r))
+    r = record([dict(entry="layer", d=4096, hq=32, hkv=8, dh=128, causal=True, n_local=700, n_nonlocal=64, groups=32, words=1024)], tmp_path)[0]
+    assert "vq_encode_bf16_fast128_kernel" in kernels(r) and not any("argmin" in k for k in kernels(r)), kernels(r)
