@@ -30,14 +30,14 @@ struct EncodeJob {
 };
 
 // ------------------------------------------------------------------------------------------------
-// Groups of at most 64 values (dg a multiple of 8).  An item is a group and a block of tokens; a workgroup of THREADS threads takes a run of items,
+// Groups of at most 64 values (dg a multiple of 8), and of 128 and 256 on tiles of 64 codewords.  An item is a group and a block of tokens; a workgroup of THREADS threads takes a run of items,
 // 32 TB tokens per wavefront (on the N side of the 32x32x16 MFMA), and walks the group's codebook in tiles of 128 codewords (M side) for each.
 //   - The score is kept as a distance, ||c||^2 - 2 x.c: the token fragments are loaded negated and doubled (exact in bf16), and the accumulation
 //     starts from ||c||^2, so no vector-ALU work is spent on forming the score.
 //   - Codebook tiles and their norms go from global memory straight into a ring of four LDS buffers, two to three tiles ahead, without a break
 //     between items.  Pieces beyond dg are never transferred; the one such slot a contraction step can read (dg an odd multiple of 8) is
 //     zeroed once by the caller (vq_encode_fast_zero_lds, when vq_encode_fast_needs_zero) and meets zero token values.
-//   - A tile is UNITS units of two accumulators (two token blocks against 32 codewords, or one against 64).  While a unit's MFMAs are issued, the
+//   - A tile is UNITS units of two accumulators (two token blocks against 32 codewords, or one against 64; groups of 256: one against 32).  While a unit's MFMAs are issued, the
 //     fragments of the next one are read and the scores of the one before are taken into the running argmin, so that the matrix core, the LDS and
 //     the vector ALU work at the same time whatever the other wavefront of the SIMD does.
 //   - The argmin goes by quads, four consecutive codewords in one lane: the minimum of the best so far and them (two instructions), and where that
@@ -61,15 +61,18 @@ template <int THREADS, int TB, int NKS>
 __device__ __forceinline__ void vq_encode_fast_run_nks(const EncodeJob& job, int lo, int hi, u32x4* cb_lds, f32x4* cn_lds) {
     constexpr int WAVES = THREADS / 64;
     constexpr int TOKENS = WAVES * 32 * TB;             // tokens per item
-    constexpr int ITS = kEncCbSlots / THREADS;          // codebook transfers per thread per tile
-    // groups of 128 values: tiles of 64 codewords, and an item's tokens are asked for when the one before is done (no registers for two)
+    // groups of 128 and 256 values: tiles of 64 codewords, and an item's tokens are asked for when the one before is done (no registers for two);
+    // of 256, a unit is one accumulator, 32 codewords against 32 tokens (none for more either)
     constexpr bool WIDE = NKS > 4;
-    static_assert(!WIDE || (TB == 2 && NKS == 8), "a tile of 64 codewords is two units of 32");
+    static_assert(!WIDE || (TB == 2 && NKS == 8) || (TB == 1 && NKS == 16), "a tile of 64 codewords is two units of 32");
+    constexpr int NB = NKS == 16 ? 1 : 2;               // accumulators of a unit
     constexpr int CW = WIDE ? kEncCw / 2 : kEncCw;      // codewords of a tile
-    constexpr int PPR = WIDE ? 16 : 8;                  // 16-byte slots of a codeword
+    constexpr int PPR = WIDE ? 2 * NKS : 8;             // 16-byte slots of a codeword
+    constexpr int CBS = CW * PPR;                       // slots of a tile
+    constexpr int ITS = CBS / THREADS;                  // codebook transfers per thread per tile
     constexpr int NORM_LANES = CW / 4 / WAVES;          // lanes per wavefront that fetch 4 norms each
     constexpr int DMA = ITS + 1;                        // transfers of a wavefront per tile: "tile s has landed" is a fixed vmcnt threshold
-    constexpr int UNITS = TB == 2 ? CW / 32 : 2, NA = TB == 2 ? 1 : 2;      // units of a tile, codeword blocks of 32 in one
+    constexpr int NA = TB == 2 ? 1 : NB, UNITS = CW / (32 * NA);      // units of a tile, codeword blocks of 32 in one
     if (lo >= hi) return;
     const int K = job.K, dg = job.dg, n_tokens = job.n_tokens, n_tb = job.n_tb;
     const int tid = threadIdx.x;
@@ -98,7 +101,7 @@ __device__ __forceinline__ void vq_encode_fast_run_nks(const EncodeJob& job, int
     auto send_tile = [&]() __attribute__((always_inline)) {
         if (s_step >= n_steps) return;
         const int buf = s_step % kEncBufs;
-        const uint32_t base = lds_byte_addr(cb_lds + buf * kEncCbSlots);
+        const uint32_t base = lds_byte_addr(cb_lds + buf * CBS);
         const uint32_t tile_b = (uint32_t)s_tile * (uint32_t)CW * row_b;
         if (piece_ok) {
 #pragma unroll
@@ -147,13 +150,14 @@ __device__ __forceinline__ void vq_encode_fast_run_nks(const EncodeJob& job, int
     };
 
     // ---- fragments of unit u of the tile in LDS buffer buf: rows 32 mb + lane % 32 (A), norms of rows 32 mb + 8q + 4h .. + 3
-    bf16x8 fa[NKS][NA];
+    constexpr int NR = NKS == 16 ? 8 : NKS;             // of groups of 256, half a unit's fragments are held
+    bf16x8 fa[NR][NA];
     f32x16 cn[NA];
-    auto block_of = [&](int u, int n) { return TB == 2 ? u : 2 * u + n; };
+    auto block_of = [&](int u, int n) { return NA == 1 ? u : 2 * u + n; };
     auto read_a = [&](int buf, int u, int ks) __attribute__((always_inline)) {
 #pragma unroll
         for (int n = 0; n < NA; ++n)
-            fa[ks][n] = __builtin_bit_cast(bf16x8, cb_lds[buf * kEncCbSlots + (block_of(u, n) * 32 + i32) * PPR + ((2 * ks + h) ^ swz_of(i32))]);
+            fa[ks % NR][n] = __builtin_bit_cast(bf16x8, cb_lds[buf * CBS + (block_of(u, n) * 32 + i32) * PPR + ((2 * ks + h) ^ swz_of(i32))]);
     };
     auto read_cn = [&](int buf, int u) __attribute__((always_inline)) {
 #pragma unroll
@@ -169,8 +173,8 @@ __device__ __forceinline__ void vq_encode_fast_run_nks(const EncodeJob& job, int
     // ---- running argmin of this lane's tokens: quad grp (0..15) of tile til, and the quad's first three scores
     float best[TB], best_in[TB], k0[TB], k1[TB], k2[TB];
     int grp[TB], til[TB];
-    f32x16 acc[2][2];
-    auto take_quad = [&](int set, int u, int i) __attribute__((always_inline)) {         // i-th of a unit's eight
+    f32x16 acc[2][NB];
+    auto take_quad = [&](int set, int u, int i) __attribute__((always_inline)) {         // i-th of a unit's 4 NB
         const int j = i >> 2, q = i & 3, b = TB == 2 ? j : 0;
         const float s0 = acc[set][j][4 * q], s1 = acc[set][j][4 * q + 1], s2 = acc[set][j][4 * q + 2], s3 = acc[set][j][4 * q + 3];
         const float m = fminf(fminf(fminf(fminf(best[b], s0), s1), s2), s3);
@@ -198,7 +202,7 @@ __device__ __forceinline__ void vq_encode_fast_run_nks(const EncodeJob& job, int
     __syncthreads();
     read_cn(0, 0);
 #pragma unroll
-    for (int ks = 0; ks < NKS; ++ks) read_a(0, 0, ks);
+    for (int ks = 0; ks < NR; ++ks) read_a(0, 0, ks);
 
     int step = 0;
     for (int item = lo; item < hi; ++item) {
@@ -211,7 +215,7 @@ __device__ __forceinline__ void vq_encode_fast_run_nks(const EncodeJob& job, int
             grp[b] = til[b] = 0;
         }
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < NB; ++j)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[1][j][v] = INFINITY;         // in the place of the unit before the first
         for (int t = 0; t < n_tiles; ++t, ++step) {
@@ -242,13 +246,16 @@ __device__ __forceinline__ void vq_encode_fast_run_nks(const EncodeJob& job, int
                 }
                 const int set = u & 1, rb = u == UNITS - 1 ? next_buf : buf, ru = (u + 1) % UNITS, pu = (u + UNITS - 1) % UNITS;
 #pragma unroll
-                for (int i = 0; i < 2 * NKS; ++i) {
-                    const int ks = i >> 1, j = i & 1;
-                    acc[set][j] = mfma_32x32x16(fa[ks][TB == 2 ? 0 : j], xf[TB == 2 ? j : 0][ks], ks == 0 ? cn[TB == 2 ? 0 : j] : acc[set][j]);
+                for (int i = 0; i < NB * NKS; ++i) {
+                    const int ks = i / NB, j = i % NB;
+                    acc[set][j] = mfma_32x32x16(fa[ks % NR][NA == 1 ? 0 : j], xf[TB == 2 ? j : 0][ks], ks == 0 ? cn[NA == 1 ? 0 : j] : acc[set][j]);
                     if (i == 1) read_cn(rb, ru);
-                    if (j == 1) read_a(rb, ru, ks);
+                    if (j == NB - 1) {
+                        if (ks + NR < NKS) read_a(buf, u, ks + NR);
+                        else read_a(rb, ru, ks + NR - NKS);
+                    }
 #pragma unroll
-                    for (int x = i * 8 / (2 * NKS); x < (i + 1) * 8 / (2 * NKS); ++x) take_quad(set ^ 1, pu, x);
+                    for (int x = i * 4 / NKS; x < (i + 1) * 4 / NKS; ++x) take_quad(set ^ 1, pu, x);
                     __builtin_amdgcn_sched_barrier(0);
                 }
                 if (u == 0) close_tile(t - 1);                  // the quads were those of the tile before
@@ -258,7 +265,7 @@ __device__ __forceinline__ void vq_encode_fast_run_nks(const EncodeJob& job, int
             }
         }
 #pragma unroll
-        for (int x = 0; x < 8; ++x) take_quad(1, UNITS - 1, x);
+        for (int x = 0; x < 4 * NB; ++x) take_quad(1, UNITS - 1, x);
         close_tile(n_tiles - 1);
         const int t0 = block * TOKENS + wave * (32 * TB) + i32;
 #pragma unroll
@@ -306,16 +313,21 @@ inline int vq_encode_blocks(const EncodeJob& e, int64_t wgs) {
     return 1.6 * (double)ceil_div(two, wgs) < (double)ceil_div(one, wgs) ? 2 : 1;
 }
 
-// Groups of 128 values go through the body in a kernel of its own (64 tokens per wavefront) where the kernel for wide groups, 32 tokens per workgroup, would
-// make more than one round of the units (its rounds are 14 us at K = 1024, where an item of the body's is 21: 128 tokens x 32 groups 13.8 / 21.3 us on it
-// and on the body, 300 28.3 / 22.1, K = 256 6.1 / 9.2 and 10.5 / 10.0, K = 16 4.7 / 6.4 and 7.8 / 7.1; 4000 x 2 groups, K = 1024, 13.5 / 21.9).
-inline bool vq_encode_fast128(int64_t n_tokens, int G, int K, int dg, int64_t ldx) {
-    return dg == 128 && K % 4 == 0 && ldx % 8 == 0 && (int64_t)K * dg * 2 < ((int64_t)1 << 31) && ceil_div(n_tokens, (int64_t)32) * G > 256;
+// Groups of 128 and 256 values go through the body in kernels of their own (64 and 32 tokens per wavefront) where the kernel for wide groups, 32 tokens per
+// workgroup, would make more than one round of the units.  At K = 1024 its rounds are 14 and 24 us, where an item of the body's is 21 and 30: 128 tokens x 32
+// groups of 128 13.8 / 21.3 us on it and on the body, 300 28.3 / 22.1, K = 256 6.1 / 9.2 and 10.5 / 10.0, K = 16 4.7 / 6.4 and 7.8 / 7.1; 300 tokens x 16 groups
+// of 256 23.9 / 29.6, 700 43.5 / 30.2, K = 256 8.4 / 13.7 and 15.2 / 13.8, K = 16 5.7 / 9.7 and 9.8 / 9.9.
+inline bool vq_encode_fast_wide(int64_t n_tokens, int G, int K, int dg, int64_t ldx) {
+    return (dg == 128 || dg == 256) && K % 4 == 0 && ldx % 8 == 0 && (int64_t)K * dg * 2 < ((int64_t)1 << 31) &&
+           ceil_div(n_tokens, (int64_t)32) * G > 256;
 }
-// Where groups of 128 values are better off without score products: there, and where the products would be more than one launch (32 groups, K = 1024,
-// products and argmin / without: 17 tokens 23.7 / 12.1 us, 1024 78 / 23, 16384 968 / 133; 2 groups, 300 tokens, 8.7 / 12.5).
+// Where such groups are better off without score products.  Of 128: there, and where the products would be more than one launch (32 groups, K = 1024,
+// products and argmin / without: 17 tokens 23.7 / 12.1 us, 1024 78 / 23, 16384 968 / 133; 2 groups, 300 tokens, 8.7 / 12.5).  Of 256: there, for up to 8
+// groups from one and a half rounds (4096 codewords, 2 groups: 4300 tokens 80 / 93, 6144 96 / 94, 8192 143 / 96; 1024 codewords 26 / 29, 27 / 29, 38 / 30;
+// 8 groups, 1075 tokens 75 / 92 and 32 / 29; 16 groups, 1024 codewords: 700 tokens 42 / 30, 16384 584 / 141; 32 groups, 268 tokens 58 / 30 and 114 / 91).
 inline bool vq_encode_without_scores(int64_t n_tokens, int G, int K, int dg, int64_t ldx) {
-    return vq_encode_fast128(n_tokens, G, K, dg, ldx) || (dg == 128 && G > kMaxGemmProblems);
+    if (dg == 128 && G > kMaxGemmProblems) return true;
+    return vq_encode_fast_wide(n_tokens, G, K, dg, ldx) && (dg == 128 || ceil_div(n_tokens, (int64_t)32) * G > (G > 8 ? 256 : 384));
 }
 
 // true when the fast body handles this configuration

@@ -708,7 +708,7 @@ __global__ __launch_bounds__(256, 2) void vq_encode_bf16_fast_kernel(const Encod
     vq_encode_fast_run_tb<256, TB>(job, min(vid * chunk, items), min((vid + 1) * chunk, items), cb_lds, cn_lds);
 }
 
-// The same body for groups of 128 values (vq_encode_fast128): a codeword fragment serves 64 tokens, and the scores never leave the registers.  16384 tokens
+// The same body for groups of 128 values (vq_encode_fast_wide): a codeword fragment serves 64 tokens, and the scores never leave the registers.  16384 tokens
 // x 32 groups, K = 1024: 133 us (1.03 PFLOP/s), 968 as score products in memory and an argmin over them, 736 with 32 tokens per workgroup; 1024 tokens 23 / 78 / 51.
 __global__ __launch_bounds__(256, 2) void vq_encode_bf16_fast128_kernel(const EncodeJob job, int chunk) {
     __shared__ u32x4 cb_lds[kEncBufs * kEncCbSlots];    // 4 x 16 KiB: [64 codewords][16 pieces of 8 bf16], swizzled
@@ -718,6 +718,19 @@ __global__ __launch_bounds__(256, 2) void vq_encode_bf16_fast128_kernel(const En
     const int vid = xcd < rr ? xcd * (q + 1) + slot : rr * (q + 1) + (xcd - rr) * q + slot;
     const int items = job.G * job.n_tb;
     vq_encode_fast_run_nks<256, 2, 8>(job, min(vid * chunk, items), min((vid + 1) * chunk, items), cb_lds, cn_lds);
+}
+
+// And for groups of 256: 32 tokens per wavefront, eight wavefronts to share a codebook tile.  One workgroup per unit: a tile is
+// 32 KiB.  16384 tokens x 16 groups, K = 1024: 141 us (0.97 PFLOP/s), 584 as score products, 646 with 32 tokens per workgroup; 1024 tokens 30 / 45 / 44.  A
+// codeword fragment serves 32 tokens only, so the LDS reads take as long as the MFMAs; all 16 fragments of a unit held at once spilled (427 us).
+__global__ __launch_bounds__(512, 2) void vq_encode_bf16_fast256_kernel(const EncodeJob job, int chunk) {
+    __shared__ u32x4 cb_lds[kEncBufs * 2 * kEncCbSlots];    // 4 x 32 KiB: [64 codewords][32 pieces of 8 bf16], swizzled
+    __shared__ f32x4 cn_lds[kEncBufs * kEncCnSlots];
+    const int total = gridDim.x;
+    const int q = total / 8, rr = total % 8, xcd = blockIdx.x % 8, slot = blockIdx.x / 8;
+    const int vid = xcd < rr ? xcd * (q + 1) + slot : rr * (q + 1) + (xcd - rr) * q + slot;
+    const int items = job.G * job.n_tb;
+    vq_encode_fast_run_nks<512, 1, 16>(job, min(vid * chunk, items), min((vid + 1) * chunk, items), cb_lds, cn_lds);
 }
 
 int launch_vq_encode(const astra_vq_desc& d, const void* x, int64_t ldx, int64_t n_tokens, const void* codebook,
@@ -747,16 +760,18 @@ int launch_vq_encode(const astra_vq_desc& d, const void* x, int64_t ldx, int64_t
             return launch_status();
         }
         if (G > 65535) return ASTRA_ERR_SHAPE;
-        if (vq_encode_fast128(n_tokens, G, K, dg, ldx)) {
+        if (vq_encode_fast_wide(n_tokens, G, K, dg, ldx)) {
             EncodeJob job{};
             job.x = x; job.codebook = codebook; job.cnorm = cnorm; job.codes = codes; job.ldx = ldx;
             job.n_tokens = (int)n_tokens; job.G = G; job.K = K; job.dg = dg;
             job.code_bytes = d.code_type == ASTRA_CODE_U8 ? 1 : 2;
-            job.tb = 2;
+            job.tb = dg == 128 ? 2 : 1;
             job.n_tb = (int)ceil_div(n_tokens, 2 * kEncTokens);
-            const int64_t items = (int64_t)job.n_tb * G, chunk = ceil_div(items, (int64_t)kEncSlots);
+            const int64_t items = (int64_t)job.n_tb * G, chunk = ceil_div(items, (int64_t)(dg == 128 ? kEncSlots : kEncSlots / 2));
             if (items > 0x7fffffff) return ASTRA_ERR_SHAPE;
-            vq_encode_bf16_fast128_kernel<<<(int)ceil_div(items, chunk), 256, 0, s>>>(job, (int)chunk);
+            const int grid = (int)ceil_div(items, chunk);
+            if (dg == 128) vq_encode_bf16_fast128_kernel<<<grid, 256, 0, s>>>(job, (int)chunk);
+            else vq_encode_bf16_fast256_kernel<<<grid, 512, 0, s>>>(job, (int)chunk);
             return launch_status();
         }
         if (vq_encode_wide_ok(K, dg, ldx)) return launch_vq_encode_wide(d, x, ldx, n_tokens, codebook, cnorm, codes, s);

@@ -276,3 +276,15 @@ def test_groups_of_128_values(T, G, K):
     assert n_tie <= max(2, ref.size // 2000)
     cb[:, K // 2:] = cb[:, :K // 2]                          # every codeword twice: the lower one
     assert gpu_vq_encode(x, cb, "bf16").max() < K // 2
+
+
+@pytest.mark.parametrize("T,G,K", [(513, 16, 1024), (4100, 2, 100), (300, 28, 4), (520, 17, 68), (1100, 40, 64), (700, 16, 256)])
+def test_groups_of_256_values(T, G, K):
+    """32 tokens per wavefront, half a unit's codeword fragments held (tests/test_launches.py): the edges of the groups of 128 above."""
+    from gpu_util import compare_codes, gpu_vq_encode
+    x, cb = make(60 + T + G, T, G, K, 256, "bf16", "normal")
+    ref, gap = oracle.vq_encode(x, cb, return_gap=True)
+    n_tie = compare_codes(gpu_vq_encode(x, cb, "bf16"), ref, gap, NEAR_TIE)
+    assert n_tie <= max(2, ref.size // 2000)
+    cb[:, K // 2:] = cb[:, :K // 2]                          # every codeword twice: the lower one
+    assert gpu_vq_encode(x, cb, "bf16").max() < K // 2

@@ -275,3 +275,15 @@ def test_encode_of_groups_of_128_values(tmp_path):
         assert kernels(r)[0].startswith(name), (t, g, k, kernels(r))
     r = record([dict(entry="layer", d=4096, hq=32, hkv=8, dh=128, causal=True, n_local=700, n_nonlocal=64, groups=32, words=1024)], tmp_path)[0]
     assert "vq_encode_bf16_fast128_kernel" in kernels(r) and not any("argmin" in k for k in kernels(r)), kernels(r)
+
+
+def test_encode_of_groups_of_256_values(tmp_path):
+    """32 tokens per wavefront beyond one round of the kernel for wide groups; beside score products, with few groups, beyond one and a half."""
+    cases = [(512, 16, 1024, "gemm"), (513, 16, 1024, "vq_encode_bf16_fast256_kernel"), (513, 16, 16, "vq_encode_bf16_fast256_kernel"),
+             (512, 16, 16, "vq_encode_bf16_wide_kernel"), (6144, 2, 1024, "gemm"), (6145, 2, 1024, "vq_encode_bf16_fast256_kernel"),
+             (4097, 2, 256, "vq_encode_bf16_fast256_kernel"), (4097, 2, 254, "vq_encode_bf16_wide_kernel")]
+    results = record([dict(entry="encode", tokens=t, groups=g, words=k, d=256 * g) for t, g, k, _ in cases], tmp_path)
+    for (t, g, k, name), r in zip(cases, results):
+        assert kernels(r)[0].startswith(name), (t, g, k, kernels(r))
+    r = record([dict(entry="layer", d=4096, hq=32, hkv=8, dh=128, causal=True, n_local=700, n_nonlocal=64, groups=16, words=1024)], tmp_path)[0]
+    assert "vq_encode_bf16_fast256_kernel" in kernels(r) and not any("argmin" in k for k in kernels(r)), kernels(r)
