@@ -760,7 +760,9 @@ int launch_vq_encode(const astra_vq_desc& d, const void* x, int64_t ldx, int64_t
             return launch_status();
         }
         if (G > 65535) return ASTRA_ERR_SHAPE;
-        if (vq_encode_fast_wide(n_tokens, G, K, dg, ldx)) {
+        // its codebook tiles and norms go to LDS in 16-byte transfers: arrays that start off such a boundary stay with the kernel for wide groups
+        const bool on_16 = ((reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(codebook) | reinterpret_cast<uintptr_t>(cnorm)) & 15) == 0;
+        if (on_16 && vq_encode_fast_wide(n_tokens, G, K, dg, ldx)) {
             EncodeJob job{};
             job.x = x; job.codebook = codebook; job.cnorm = cnorm; job.codes = codes; job.ldx = ldx;
             job.n_tokens = (int)n_tokens; job.G = G; job.K = K; job.dg = dg;

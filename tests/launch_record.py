@@ -111,7 +111,8 @@ def _update(B, c, t):
 def _encode(B, c, t):
     desc = B.vq_desc(c.get("dtype", "bf16"), c["d"], c["groups"], c["words"])
     n = B.astra_vq_encode_workspace_bytes(desc, c["tokens"])
-    B.astra_vq_encode_ws(desc, t(), c["tokens"], t(), t(), t(), _Tensor(n))
+    x, codebook, cnorm = (t(skew=c.get("skew", {}).get(a, 0)) for a in ("x", "codebook", "cnorm"))
+    B.astra_vq_encode_ws(desc, x, c["tokens"], codebook, cnorm, t(), _Tensor(n))
     return n
 
 

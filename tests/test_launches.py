@@ -287,3 +287,13 @@ def test_encode_of_groups_of_256_values(tmp_path):
         assert kernels(r)[0].startswith(name), (t, g, k, kernels(r))
     r = record([dict(entry="layer", d=4096, hq=32, hkv=8, dh=128, causal=True, n_local=700, n_nonlocal=64, groups=16, words=1024)], tmp_path)[0]
     assert "vq_encode_bf16_fast256_kernel" in kernels(r) and not any("argmin" in k for k in kernels(r)), kernels(r)
+
+
+@pytest.mark.parametrize("dg", [128, 256])
+def test_encode_of_wide_groups_off_a_16_byte_boundary(dg, tmp_path):
+    """The body's 16-byte transfers to LDS want x, the codebook and the norms on such a boundary; others keep the kernel for wide groups."""
+    call = dict(entry="encode", tokens=4100, groups=16, words=1024, d=16 * dg)
+    on, *off = record([call] + [dict(call, skew={a: n}) for a, n in (("x", 8), ("codebook", 2), ("cnorm", 4))], tmp_path)
+    assert kernels(on) == [f"vq_encode_bf16_fast{dg}_kernel"]
+    for r in off:
+        assert len(kernels(r)) == 1 and kernels(r)[0].startswith("vq_encode_bf16_wide_kernel"), kernels(r)
