@@ -313,21 +313,32 @@ inline int vq_encode_blocks(const EncodeJob& e, int64_t wgs) {
     return 1.6 * (double)ceil_div(two, wgs) < (double)ceil_div(one, wgs) ? 2 : 1;
 }
 
-// Groups of 128 and 256 values go through the body in kernels of their own (64 and 32 tokens per wavefront) where the kernel for wide groups, 32 tokens per
-// workgroup, would make more than one round of the units.  At K = 1024 its rounds are 14 and 24 us, where an item of the body's is 21 and 30: 128 tokens x 32
-// groups of 128 13.8 / 21.3 us on it and on the body, 300 28.3 / 22.1, K = 256 6.1 / 9.2 and 10.5 / 10.0, K = 16 4.7 / 6.4 and 7.8 / 7.1; 300 tokens x 16 groups
-// of 256 23.9 / 29.6, 700 43.5 / 30.2, K = 256 8.4 / 13.7 and 15.2 / 13.8, K = 16 5.7 / 9.7 and 9.8 / 9.9.
-inline bool vq_encode_fast_wide(int64_t n_tokens, int G, int K, int dg, int64_t ldx) {
-    return (dg == 128 || dg == 256) && K % 4 == 0 && ldx % 8 == 0 && (int64_t)K * dg * 2 < ((int64_t)1 << 31) &&
-           ceil_div(n_tokens, (int64_t)32) * G > 256;
+// Groups of 128, 192 and 256 values are taken by vq_encode_bf16_stream_kernel, 32 tokens per workgroup.  (16 groups of 256 codewords of 256 values stay with
+// vq_encode_bf16_wide_kernel, 8.2 us for one round of it and 8.4 streamed; 128 codewords 6.6 / 6.1, 512 12.4 / 10.1.)
+inline bool vq_encode_stream_ok(int K, int dg, int64_t ldx) {
+    return dg > kEncKt && dg <= 256 && dg % 64 == 0 && K % 4 == 0 && ldx % 8 == 0 && (int64_t)K * dg * 2 < ((int64_t)1 << 31) &&
+           (dg < 256 || K <= 128 || K > 320);
 }
-// Where such groups are better off without score products.  Of 128: there, and where the products would be more than one launch (32 groups, K = 1024,
-// products and argmin / without: 17 tokens 23.7 / 12.1 us, 1024 78 / 23, 16384 968 / 133; 2 groups, 300 tokens, 8.7 / 12.5).  Of 256: there, for up to 8
-// groups from one and a half rounds (4096 codewords, 2 groups: 4300 tokens 80 / 93, 6144 96 / 94, 8192 143 / 96; 1024 codewords 26 / 29, 27 / 29, 38 / 30;
-// 8 groups, 1075 tokens 75 / 92 and 32 / 29; 16 groups, 1024 codewords: 700 tokens 42 / 30, 16384 584 / 141; 32 groups, 268 tokens 58 / 30 and 114 / 91).
+// Beyond that kernel's second round groups of 128 and 256 go through the body in kernels of their own (64 and 32 tokens per wavefront); beyond its first where
+// neither the walk nor the launch is long.  The body's items cost 21 and 30 us at K = 1024, the other's rounds 9.8 and 14.  Streamed / body: 512 tokens x 32 groups
+// of 128 K = 16 6.6 / 7.1, 64 7.1 / 6.9, 256 10.5 / 10.0, 768 16.1 / 18.5, 1024 18.1 / 22.6, 700 tokens 25.6 / 23.1; 1000 x 16 groups of 256 K = 32 7.8 / 9.8,
+// 256 15.8 / 13.9, 512 20.0 / 19.3, 768 23.3 / 24.9, 1024 26.1 / 29.8, 1531 tokens 38.5 / 30.8.
+inline bool vq_encode_fast_wide(int64_t n_tokens, int G, int K, int dg, int64_t ldx) {
+    const int64_t blocks = ceil_div(n_tokens, (int64_t)32) * G;
+    return (dg == 128 || dg == 256) && K % 4 == 0 && ldx % 8 == 0 && (int64_t)K * dg * 2 < ((int64_t)1 << 31) &&
+           (blocks > 512 || (blocks > 256 && K > 32 && K <= 512));
+}
+// Where such groups are better off without score products: of 128 where the products would be more than one launch, of 192 and 256 where they would be
+// three or more, or two with more than 192 tokens (with / without scores: 16 groups of 256, K = 1024, 17 tokens 14.2 / 11.4 us, 128 19.7 / 13.0, 400 35.9 / 13.8; K = 4096 40 tokens 27.6 / 29.4,
+// 250 45.5 / 31.7; 8 groups 100 tokens, K = 768 11.7 / 11.4, 4096 23.3 / 29.3, 500 39.8 / 30.4; 8 of 192, K = 2048 64 tokens 13.9 / 15.8, 500 29.8 / 16.7);
+// and with few groups once all units have a block, of 256 with up to 8 groups one and a half (4096 codewords, 2 groups: 4300 tokens 80 / 93, 8192 143 / 96).
 inline bool vq_encode_without_scores(int64_t n_tokens, int G, int K, int dg, int64_t ldx) {
     if (dg == 128 && G > kMaxGemmProblems) return true;
-    return vq_encode_fast_wide(n_tokens, G, K, dg, ldx) && (dg == 128 || ceil_div(n_tokens, (int64_t)32) * G > (G > 8 ? 256 : 384));
+    if (dg <= kEncKt || dg > 256 || dg % 64 != 0 || K % 4 != 0 || ldx % 8 != 0 || (int64_t)K * dg * 2 >= ((int64_t)1 << 31)) return false;
+    if (G > kMaxGemmProblems && n_tokens > 192) return true;
+    if (G > 2 * kMaxGemmProblems && K <= 1024) return true;
+    const int64_t blocks = ceil_div(n_tokens, (int64_t)32) * G;
+    return dg == 128 ? blocks > 256 : dg == 256 && blocks > (G > 8 ? 256 : 384);
 }
 
 // true when the fast body handles this configuration

@@ -288,3 +288,16 @@ def test_groups_of_256_values(T, G, K):
     assert n_tie <= max(2, ref.size // 2000)
     cb[:, K // 2:] = cb[:, :K // 2]                          # every codeword twice: the lower one
     assert gpu_vq_encode(x, cb, "bf16").max() < K // 2
+
+
+@pytest.mark.parametrize("dg", [128, 192, 256])
+@pytest.mark.parametrize("T,G,K", [(17, 32, 1024), (512, 16, 1024), (33, 7, 4), (700, 20, 32), (100, 9, 100), (64, 3, 260), (300, 13, 2052)])
+def test_streamed_wide_groups(T, G, K, dg):
+    """32 tokens per workgroup, codewords dealt to eight wavefronts in blocks of 32: fewer blocks than wavefronts, ragged blocks, more than a ring of steps."""
+    from gpu_util import compare_codes, gpu_vq_encode
+    x, cb = make(70 + T + G + dg, T, G, K, dg, "bf16", "normal")
+    ref, gap = oracle.vq_encode(x, cb, return_gap=True)
+    n_tie = compare_codes(gpu_vq_encode(x, cb, "bf16"), ref, gap, NEAR_TIE)
+    assert n_tie <= max(2, ref.size // 2000)
+    cb[:, K // 2:] = cb[:, :K // 2]                          # every codeword twice: the lower one
+    assert gpu_vq_encode(x, cb, "bf16").max() < K // 2

@@ -266,27 +266,25 @@ def test_normalisation_by_wavefronts_of_narrow_rows(tmp_path):
         assert sum(k.startswith(name) for k in names) == 2, (d, names)
 
 
-def test_encode_of_groups_of_128_values(tmp_path):
-    """The matrix-core body with 64 tokens per wavefront beyond one round of the kernel for wide groups; no score products for more than six groups."""
-    cases = [(256, 32, 1024, "vq_encode_bf16_wide_kernel"), (257, 32, 1024, "vq_encode_bf16_fast128_kernel"), (16384, 32, 16, "vq_encode_bf16_fast128_kernel"),
-             (300, 2, 1024, "gemm"), (4097, 2, 1024, "vq_encode_bf16_fast128_kernel"), (4097, 2, 1022, "vq_encode_bf16_wide_kernel")]
-    results = record([dict(entry="encode", tokens=t, groups=g, words=k, d=128 * g) for t, g, k, _ in cases], tmp_path)
+@pytest.mark.parametrize("dg", [128, 192, 256])
+def test_encode_of_wide_groups(dg, tmp_path):
+    """32 tokens per workgroup streamed; the matrix-core body where that would make many rounds, or two short ones; score products for few groups."""
+    stream, fast, wide = "vq_encode_bf16_stream_kernel", f"vq_encode_bf16_fast{dg}_kernel", "vq_encode_bf16_wide_kernel"
+    body = fast if dg != 192 else stream
+    few = {128: (4096, 4097), 192: (4096, None), 256: (6144, 6145)}[dg]
+    cases = [(17, 16, 1024, stream), (512, 16, 1024, stream), (1024, 16, 1024, stream), (1025, 16, 1024, body), (513, 16, 512, body), (513, 16, 32, stream),
+             (1025, 16, 16, body), (512, 16, 256, wide if dg == 256 else stream), (512, 16, 128, stream), (17, 16, 1022, wide),
+             (few[0], 2, 1024, "gemm"), (192, 8, 1024, stream if dg == 128 else "gemm"), (193, 8, 1024, stream)]
+    if dg != 192:
+        cases += [(few[1], 2, 1024, stream), (8193, 2, 1024, fast), (4097, 2, 256, fast), (4097, 2, 254, wide)]
+    results = record([dict(entry="encode", tokens=t, groups=g, words=k, d=dg * g) for t, g, k, _ in cases], tmp_path)
     for (t, g, k, name), r in zip(cases, results):
         assert kernels(r)[0].startswith(name), (t, g, k, kernels(r))
-    r = record([dict(entry="layer", d=4096, hq=32, hkv=8, dh=128, causal=True, n_local=700, n_nonlocal=64, groups=32, words=1024)], tmp_path)[0]
-    assert "vq_encode_bf16_fast128_kernel" in kernels(r) and not any("argmin" in k for k in kernels(r)), kernels(r)
-
-
-def test_encode_of_groups_of_256_values(tmp_path):
-    """32 tokens per wavefront beyond one round of the kernel for wide groups; beside score products, with few groups, beyond one and a half."""
-    cases = [(512, 16, 1024, "gemm"), (513, 16, 1024, "vq_encode_bf16_fast256_kernel"), (513, 16, 16, "vq_encode_bf16_fast256_kernel"),
-             (512, 16, 16, "vq_encode_bf16_wide_kernel"), (6144, 2, 1024, "gemm"), (6145, 2, 1024, "vq_encode_bf16_fast256_kernel"),
-             (4097, 2, 256, "vq_encode_bf16_fast256_kernel"), (4097, 2, 254, "vq_encode_bf16_wide_kernel")]
-    results = record([dict(entry="encode", tokens=t, groups=g, words=k, d=256 * g) for t, g, k, _ in cases], tmp_path)
-    for (t, g, k, name), r in zip(cases, results):
-        assert kernels(r)[0].startswith(name), (t, g, k, kernels(r))
-    r = record([dict(entry="layer", d=4096, hq=32, hkv=8, dh=128, causal=True, n_local=700, n_nonlocal=64, groups=16, words=1024)], tmp_path)[0]
-    assert "vq_encode_bf16_fast256_kernel" in kernels(r) and not any("argmin" in k for k in kernels(r)), kernels(r)
+    if dg == 192:
+        return
+    for rows, name in ((17, stream), (700, stream if dg == 256 else fast), (1200, fast)):
+        r = record([dict(entry="layer", d=4096, hq=32, hkv=8, dh=128, causal=True, n_local=rows, n_nonlocal=64, groups=4096 // dg, words=1024)], tmp_path)[0]
+        assert any(k.startswith(name) for k in kernels(r)) and not any("argmin" in k for k in kernels(r)), kernels(r)
 
 
 @pytest.mark.parametrize("dg", [128, 256])
