@@ -1019,6 +1019,20 @@ int launch_attention(int dtype, const AttnParams& p_in, int head_dim, hipStream_
             ae.n_enc_wgs = (int)std::min<int64_t>(items, kAttCus);
             *enc_fused = true;
         }
+        // An encode of wide groups rides beside the short form on units without a query block.  Layers 4096 wide, encode as a launch
+        // of its own / beside: 40 + 120 rows, 16 groups 53.6 / 45.7 us, 32 groups 49.2 / 42.0, 100 + 300 70.2 / 61.1, 66.0 / 57.7.
+        if (items == 0 && few && enc && enc_fused && n_enc == 1 && head_dim == 128 && enc[0].n_tokens > 0 &&
+            vq_encode_stream_fits(enc[0].K, enc[0].dg, enc[0].ldx) && vq_encode_on_16(enc[0].x, enc[0].codebook, enc[0].cnorm)) {
+            const int64_t n_tb = ceil_div(enc[0].n_tokens, kStreamTokens), wgs = n_tb * enc[0].G;
+            if (total + wgs <= kAttCus) {
+                ae.job[0] = enc[0];
+                ae.job[0].n_tb = (int)n_tb;
+                ae.n_jobs = 1;
+                ae.n_attn_wgs = (int)total;
+                ae.n_enc_wgs = (int)wgs;
+                *enc_fused = true;
+            }
+        }
         if (plan_only) return ASTRA_OK;
         if (few) return launch_attention_short(p, head_dim, ae, fetch, s);
         if (p.n_cut > 0) {

@@ -35,8 +35,12 @@ constexpr int kShortWaves = kShortThreads / kWave;
 constexpr float kLazyShort = 8.f;     // base-2 units
 constexpr int kShortUnits = 256;      // compute units of the device
 
-template <int DH, bool LOST, bool ENC>
+// WIDTH: the head's, and in its lowest bit that the encode aboard is one of wide groups (job 0, a workgroup per item), which wants another body.  (The walk as a
+// function shared by two kernels compiled to 60 more instructions, 0.7 % of a layer of 40 rows.)
+constexpr int kStreamed = 1;
+template <int WIDTH, bool LOST, bool ENC>
 __global__ __launch_bounds__(kShortThreads) void attn_short_kernel(const AttnParams p, const AttnEncode e, const Prefetch f) {
+    constexpr int DH = WIDTH & ~kStreamed;
     constexpr int TK = 4096 / DH, NMB = TK / 32, NKS = DH / 16, NDB = DH / 32, NPV = TK / 16, LDP = DH + 4;
     constexpr int KP = DH / 8, VP = TK / 8;    // 16-byte pieces of a row of keys, of values
     constexpr int NT = 8, KR = 64 / KP, VR = 64 / VP;      // transfers of a tile of keys or of values, and their rows
@@ -45,7 +49,18 @@ __global__ __launch_bounds__(kShortThreads) void attn_short_kernel(const AttnPar
     __shared__ __align__(16) u32x4 ring[kPart > kShortWaves * 2 * kTile ? kPart : kShortWaves * 2 * kTile];
     __shared__ float part_m[kShortWaves][32], part_l[kShortWaves][32];
     auto part = reinterpret_cast<float(*)[32][LDP]>(&ring[0]);
-    if constexpr (ENC) {
+    if constexpr (ENC && (WIDTH & kStreamed)) {
+        static_assert(sizeof(ring) >= sizeof(u32x4) * (kStreamSlots + kStreamCnSlots) && kStreamWaves == kShortWaves && kStreamTokens == 32, "the streamed encode's rings fit");
+        const int item = (int)blockIdx.x - e.n_attn_wgs;
+        if (item >= 0 && item < e.n_enc_wgs) {
+            f32x4* cn = reinterpret_cast<f32x4*>(ring + kStreamSlots);
+            auto arg = reinterpret_cast<int(*)[32]>(&part_l[0]);
+            if (e.job[0].dg == 128) vq_encode_stream_run<2>(e.job[0], item, ring, cn, part_m, arg);
+            else if (e.job[0].dg == 192) vq_encode_stream_run<3>(e.job[0], item, ring, cn, part_m, arg);
+            else vq_encode_stream_run<4>(e.job[0], item, ring, cn, part_m, arg);
+            return;
+        }
+    } else if constexpr (ENC) {
         static_assert(sizeof(ring) >= sizeof(u32x4) * kEncBufs * (kEncCbSlots + kEncCnSlots), "the encode's codebook tiles and norms fit");
         if ((int)blockIdx.x >= e.n_attn_wgs && (int)blockIdx.x < e.n_attn_wgs + e.n_enc_wgs) {
             attn_encode_wgs<kShortThreads>(e, (int)blockIdx.x - e.n_attn_wgs, ring, reinterpret_cast<f32x4*>(ring + kEncBufs * kEncCbSlots));
@@ -287,6 +302,9 @@ int launch_attention_short(const AttnParams& p, int head_dim, const AttnEncode& 
     if (head_dim == 64) {
         if (lost) attn_short_kernel<64, true, false><<<grid, kShortThreads, 0, s>>>(p, e, f);
         else attn_short_kernel<64, false, false><<<grid, kShortThreads, 0, s>>>(p, e, f);
+    } else if (e.n_enc_wgs > 0 && e.job[0].dg > kEncKt) {
+        if (lost) attn_short_kernel<128 | kStreamed, true, true><<<grid, kShortThreads, 0, s>>>(p, e, f);
+        else attn_short_kernel<128 | kStreamed, false, true><<<grid, kShortThreads, 0, s>>>(p, e, f);
     } else if (e.n_enc_wgs > 0) {
         if (lost) attn_short_kernel<128, true, true><<<grid, kShortThreads, 0, s>>>(p, e, f);
         else attn_short_kernel<128, false, true><<<grid, kShortThreads, 0, s>>>(p, e, f);

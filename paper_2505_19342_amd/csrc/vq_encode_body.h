@@ -306,6 +306,120 @@ __device__ __forceinline__ void vq_encode_fast_run(const EncodeJob& job, int lo,
     else vq_encode_fast_run_tb<THREADS, 1>(job, lo, hi, cb_lds, cn_lds);
 }
 
+// Groups of 64 NCH values, few tokens: 32 tokens of a group per workgroup, whose eight wavefronts share its codewords, blocks of 32 dealt in turn.  Every
+// wavefront streams its blocks in steps of 64 values through an LDS ring of its own (no barrier in the loop), four steps in flight, in transfers of whole
+// 128-byte lines.  What bounds it: a unit's operand intake (64 B/clk) and the latency before it.  One round at K = 1024, 256 workgroups, against
+// vq_encode_bf16_wide_kernel, which reads 16 bytes of 64 rows with an instruction: groups of 256 13.9 us, 23.8 before (37 as score products), of 128 9.8, 20.0.
+constexpr int kStreamWaves = 8, kStreamRing = 4, kStreamTokens = 32;
+constexpr int kStreamSlots = kStreamWaves * kStreamRing * 32 * 8, kStreamCnSlots = kStreamWaves * kStreamRing * 8;      // 16-byte slots of codewords, of norms
+// item vid (group-major) of the job.  All kStreamWaves wavefronts come here.
+template <int NCH>
+__device__ __forceinline__ void vq_encode_stream_run(const EncodeJob& job, int vid, u32x4* cb_ring, f32x4* cn_ring, float (*m_val)[kStreamTokens],
+                                                     int (*m_arg)[kStreamTokens]) {
+    constexpr int PER = 5;                                          // transfers of a step: four of codewords, one of the block's norms
+    auto cb_lds = reinterpret_cast<u32x4(*)[kStreamRing][32 * 8]>(cb_ring);     // a step: [32 codewords][8 pieces of 8 bf16], swizzled
+    auto cn_lds = reinterpret_cast<f32x4(*)[kStreamRing][8]>(cn_ring);
+    const int g = vid / job.n_tb, t0 = (vid - g * job.n_tb) * kStreamTokens;
+    const int K = job.K, n_tokens = job.n_tokens;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), i32 = lane & 31, h = lane >> 5;
+    constexpr uint32_t row_b = 128u * NCH;
+    const int n_blocks = (K + 31) >> 5, n_mine = (n_blocks - wave + kStreamWaves - 1) / kStreamWaves, n_steps = max(n_mine, 0) * NCH;
+    const char* __restrict__ cb = (const char*)job.codebook + (int64_t)g * K * row_b;
+    const char* __restrict__ cn = (const char*)(job.cnorm + (int64_t)g * K);
+
+    // transfer i of a step: lane l fetches piece (l % 8) ^ (row % 8) of row 8 i + l / 8; rows past K are row K - 1
+    int s_row = 32 * wave, s_ch = 0, s_step = 0;
+    const int l_row = lane >> 3;
+    const uint32_t l_piece = (uint32_t)((lane & 7) ^ l_row) * 16u;
+    auto send = [&]() __attribute__((always_inline)) {
+        if (s_step >= n_steps) return;
+        const int ring = s_step % kStreamRing;
+        const uint32_t base = lds_byte_addr(&cb_lds[wave][ring][0]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            dma_global_to_lds_16(cb, (uint32_t)min(s_row + 8 * i + l_row, K - 1) * row_b + (uint32_t)s_ch * 128u + l_piece, base + 1024u * i);
+        if (lane < 8) dma_global_to_lds_16(cn, (uint32_t)min(s_row + 4 * lane, K - 4) * 4u, lds_byte_addr(&cn_lds[wave][ring][0]));
+        ++s_step;
+        if (++s_ch == NCH) {
+            s_ch = 0;
+            s_row += 32 * kStreamWaves;
+        }
+    };
+#pragma unroll
+    for (int i = 0; i < kStreamRing; ++i) send();
+
+    // the tokens as -2x (exact in bf16): with the norms as the accumulators' start they hold distances
+    bf16x8 xf[4 * NCH];
+    {
+        const uint16_t* xrow = (const uint16_t*)job.x + (int64_t)min(t0 + i32, n_tokens - 1) * job.ldx + (int64_t)g * (64 * NCH) + 8 * h;
+        u32x4 raw[4 * NCH];
+#pragma unroll
+        for (int ks = 0; ks < 4 * NCH; ++ks) raw[ks] = *reinterpret_cast<const u32x4*>(xrow + 16 * ks);
+#pragma unroll
+        for (int ks = 0; ks < 4 * NCH; ++ks) {
+            const bf16x8 xv = __builtin_bit_cast(bf16x8, raw[ks]);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) xf[ks][e] = (__bf16)(-2.f * (float)xv[e]);
+        }
+    }
+    float best = INFINITY;
+    int arg = 0, step = 0;
+    for (int t = 0; t < n_mine; ++t) {
+        f32x16 acc;
+#pragma unroll
+        for (int ch = 0; ch < NCH; ++ch, ++step) {
+            // this step has landed: the three sent after it may be outstanding
+            if (step + kStreamRing <= n_steps) wait_vmem<PER * (kStreamRing - 1)>();
+            else wait_vmem_all();
+            const int ring = step % kStreamRing;
+            bf16x8 fa[4];
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) fa[ks] = __builtin_bit_cast(bf16x8, cb_lds[wave][ring][i32 * 8 + ((2 * ks + h) ^ (i32 & 7))]);
+            if (ch == 0) {
+#pragma unroll
+                for (int p = 0; p < 4; ++p) {
+                    const f32x4 v = cn_lds[wave][ring][2 * p + h];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[4 * p + e] = v[e];
+                }
+            }
+            __builtin_amdgcn_s_waitcnt(0xC07F);              // lgkmcnt 0: the step is in registers, its place is free
+            asm volatile("" ::: "memory");
+            send();
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) acc = mfma_32x32x16(fa[ks], xf[4 * ch + ks], acc);
+        }
+        const int cw0 = 32 * (wave + kStreamWaves * t);
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const int cw = cw0 + acc_row(v, h);
+            const bool better = cw < K && acc[v] < best;
+            best = better ? acc[v] : best;
+            arg = better ? cw : arg;
+        }
+    }
+    {
+        const float ob = __shfl_xor(best, 32);
+        const int oa = __shfl_xor(arg, 32);
+        if (ob < best || (ob == best && oa < arg)) { best = ob; arg = oa; }
+    }
+    if (h == 0) { m_val[wave][i32] = best; m_arg[wave][i32] = arg; }
+    __syncthreads();
+    if (tid < kStreamTokens && t0 + tid < n_tokens) {
+        best = m_val[0][tid];
+        arg = m_arg[0][tid];
+#pragma unroll
+        for (int w = 1; w < kStreamWaves; ++w) {
+            const float ob = m_val[w][tid];
+            const int oa = m_arg[w][tid];
+            if (ob < best || (ob == best && oa < arg)) { best = ob; arg = oa; }
+        }
+        const int64_t at = (int64_t)(t0 + tid) * job.G + g;
+        if (job.code_bytes == 2) ((uint16_t*)job.codes)[at] = (uint16_t)arg;
+        else ((uint8_t*)job.codes)[at] = (uint8_t)arg;
+    }
+}
+
 // Token blocks per wavefront for an encode that `wgs` workgroups of 512 threads share.  Two take 1.6 times as long as one (16384 tokens x 64 groups, K = 1024:
 // 150 us, 185 with one), so they pay where one block each makes more than 1.6 times the rounds.
 inline int vq_encode_blocks(const EncodeJob& e, int64_t wgs) {
@@ -315,9 +429,13 @@ inline int vq_encode_blocks(const EncodeJob& e, int64_t wgs) {
 
 // Groups of 128, 192 and 256 values are taken by vq_encode_bf16_stream_kernel, 32 tokens per workgroup.  (16 groups of 256 codewords of 256 values stay with
 // vq_encode_bf16_wide_kernel, 8.2 us for one round of it and 8.4 streamed; 128 codewords 6.6 / 6.1, 512 12.4 / 10.1.)
-inline bool vq_encode_stream_ok(int K, int dg, int64_t ldx) {
-    return dg > kEncKt && dg <= 256 && dg % 64 == 0 && K % 4 == 0 && ldx % 8 == 0 && (int64_t)K * dg * 2 < ((int64_t)1 << 31) &&
-           (dg < 256 || K <= 128 || K > 320);
+inline bool vq_encode_stream_fits(int K, int dg, int64_t ldx) {
+    return dg > kEncKt && dg <= 256 && dg % 64 == 0 && K % 4 == 0 && ldx % 8 == 0 && (int64_t)K * dg * 2 < ((int64_t)1 << 31);
+}
+inline bool vq_encode_stream_ok(int K, int dg, int64_t ldx) { return vq_encode_stream_fits(K, dg, ldx) && (dg < 256 || K <= 128 || K > 320); }
+// 16-byte transfers to LDS: arrays that start off such a boundary stay with the kernel for wide groups
+inline bool vq_encode_on_16(const void* x, const void* codebook, const void* cnorm) {
+    return ((reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(codebook) | reinterpret_cast<uintptr_t>(cnorm)) & 15) == 0;
 }
 // Beyond that kernel's second round groups of 128 and 256 go through the body in kernels of their own (64 and 32 tokens per wavefront); beyond its first where
 // neither the walk nor the launch is long.  The body's items cost 21 and 30 us at K = 1024, the other's rounds 9.8 and 14.  Streamed / body: 512 tokens x 32 groups
@@ -334,7 +452,7 @@ inline bool vq_encode_fast_wide(int64_t n_tokens, int G, int K, int dg, int64_t 
 // and with few groups once all units have a block, of 256 with up to 8 groups one and a half (4096 codewords, 2 groups: 4300 tokens 80 / 93, 8192 143 / 96).
 inline bool vq_encode_without_scores(int64_t n_tokens, int G, int K, int dg, int64_t ldx) {
     if (dg == 128 && G > kMaxGemmProblems) return true;
-    if (dg <= kEncKt || dg > 256 || dg % 64 != 0 || K % 4 != 0 || ldx % 8 != 0 || (int64_t)K * dg * 2 >= ((int64_t)1 << 31)) return false;
+    if (!vq_encode_stream_fits(K, dg, ldx)) return false;
     if (G > kMaxGemmProblems && n_tokens > 192) return true;
     if (G > 2 * kMaxGemmProblems && K <= 1024) return true;
     const int64_t blocks = ceil_div(n_tokens, (int64_t)32) * G;

@@ -354,10 +354,18 @@ def test_walks_cut_between_workgroups(n_local, n_nonlocal, hq, hkv, n_cls, causa
     _short_sequence(128, n_local, n_nonlocal, hq, hkv, n_cls, causal, lost, minimal=True)
 
 
-def _short_sequence(dh, n_local, n_nonlocal, hq, hkv, n_cls, causal, lost, minimal=False):
+@pytest.mark.parametrize("n_local,n_nonlocal,hq,hkv,n_cls,causal,lost,groups,words", [
+    (17, 60, 8, 2, 0, True, None, 4, 300), (100, 300, 8, 2, 0, True, "some", 2, 256), (65, 64, 12, 4, 1, False, None, 4, 100),
+    (128, 200, 16, 4, 0, True, None, 8, 1024), (33, 0, 8, 8, 0, True, None, 2, 4)])
+def test_encodes_of_wide_groups_beside_the_attention(n_local, n_nonlocal, hq, hkv, n_cls, causal, lost, groups, words):
+    """Groups of 128, 192 and 256 values, streamed by workgroups behind the 32-row attention's (tests/test_launches.py)."""
+    _short_sequence(128, n_local, n_nonlocal, hq, hkv, n_cls, causal, lost, groups=groups, words=words)
+
+
+def _short_sequence(dh, n_local, n_nonlocal, hq, hkv, n_cls, causal, lost, minimal=False, groups=16, words=256):
     from gpu_util import LayerOnGpu, compare_codes
     d = 64 * hq
-    cfg = wl.LayerConfig("short", "bf16", d, hq, hkv, dh, n_local + n_nonlocal, 1, 16, 256, n_cls=n_cls, causal=causal, seed=71)
+    cfg = wl.LayerConfig("short", "bf16", d, hq, hkv, dh, n_local + n_nonlocal, 1, groups, words, n_cls=n_cls, causal=causal, seed=71)
     data = wl.generate(cfg)
     rows = data["x"]
     cls_rows = rows[-n_cls:] if n_cls else rows[:0]
