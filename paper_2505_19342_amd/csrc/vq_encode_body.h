@@ -32,8 +32,9 @@ struct EncodeJob {
 // ------------------------------------------------------------------------------------------------
 // Groups of at most 64 values (dg a multiple of 8), and of 128 and 256 on tiles of 64 codewords.  An item is a group and a block of tokens; a workgroup of THREADS threads takes a run of items,
 // 32 TB tokens per wavefront (on the N side of the 32x32x16 MFMA), and walks the group's codebook in tiles of 128 codewords (M side) for each.
-//   - The score is kept as a distance, ||c||^2 - 2 x.c: the token fragments are loaded negated and doubled (exact in bf16), and the accumulation
-//     starts from ||c||^2, so no vector-ALU work is spent on forming the score.
+//   - The score is kept as a distance, ||c||^2 - 2 x.c: the token fragments are loaded negated and doubled (exact in bf16).  The accumulation of up to four
+//     steps starts from ||c||^2, so no vector-ALU work is spent on forming the score.  That of 8 or 16 steps would round every partial sum at the size of
+//     ||c||^2, about dg: there -2 x.c is summed by itself and ||c||^2 added once, an addition per score.
 //   - Codebook tiles and their norms go from global memory straight into a ring of four LDS buffers, two to three tiles ahead, without a break
 //     between items.  Pieces beyond dg are never transferred; the one such slot a contraction step can read (dg an odd multiple of 8) is
 //     zeroed once by the caller (vq_encode_fast_zero_lds, when vq_encode_fast_needs_zero) and meets zero token values.
@@ -159,24 +160,36 @@ __device__ __forceinline__ void vq_encode_fast_run_nks(const EncodeJob& job, int
         for (int n = 0; n < NA; ++n)
             fa[ks % NR][n] = __builtin_bit_cast(bf16x8, cb_lds[buf * CBS + (block_of(u, n) * 32 + i32) * PPR + ((2 * ks + h) ^ swz_of(i32))]);
     };
+    auto read_cn_quad = [&](int buf, int u, int n, int q) __attribute__((always_inline)) {
+        const f32x4 v = cn_lds[buf * kEncCnSlots + block_of(u, n) * 8 + 2 * q + h];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) cn[n][4 * q + e] = v[e];
+    };
     auto read_cn = [&](int buf, int u) __attribute__((always_inline)) {
 #pragma unroll
         for (int n = 0; n < NA; ++n)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const f32x4 v = cn_lds[buf * kEncCnSlots + block_of(u, n) * 8 + 2 * q + h];
+            for (int q = 0; q < 4; ++q) read_cn_quad(buf, u, n, q);
+    };
+    // codewords past K (the last tile of a K that is no multiple of a tile's; lim: those of the tile and beyond) are infinitely far
+    auto mask_cn = [&](int u, int lim) __attribute__((always_inline)) {
+        if (lim >= CW) return;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) cn[n][4 * q + e] = v[e];
-            }
+        for (int n = 0; n < NA; ++n) {
+            const int left = lim - 32 * block_of(u, n) - 4 * h;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) cn[n][v] = acc_row(v, 0) >= left ? INFINITY : cn[n][v];
+        }
     };
 
     // ---- running argmin of this lane's tokens: quad grp (0..15) of tile til, and the quad's first three scores
     float best[TB], best_in[TB], k0[TB], k1[TB], k2[TB];
     int grp[TB], til[TB];
     f32x16 acc[2][NB];
+    auto score = [&](int set, int j, int v) __attribute__((always_inline)) { return WIDE ? cn[0][v] + acc[set][j][v] : acc[set][j][v]; };
     auto take_quad = [&](int set, int u, int i) __attribute__((always_inline)) {         // i-th of a unit's 4 NB
         const int j = i >> 2, q = i & 3, b = TB == 2 ? j : 0;
-        const float s0 = acc[set][j][4 * q], s1 = acc[set][j][4 * q + 1], s2 = acc[set][j][4 * q + 2], s3 = acc[set][j][4 * q + 3];
+        const float s0 = score(set, j, 4 * q), s1 = score(set, j, 4 * q + 1), s2 = score(set, j, 4 * q + 2), s3 = score(set, j, 4 * q + 3);
         const float m = fminf(fminf(fminf(fminf(best[b], s0), s1), s2), s3);
         const bool better = m < best[b];
         best[b] = m;
@@ -200,7 +213,7 @@ __device__ __forceinline__ void vq_encode_fast_run_nks(const EncodeJob& job, int
     take_tokens();
     wait_vmem_all();
     __syncthreads();
-    read_cn(0, 0);
+    if (!WIDE) read_cn(0, 0);
 #pragma unroll
     for (int ks = 0; ks < NR; ++ks) read_a(0, 0, ks);
 
@@ -218,6 +231,7 @@ __device__ __forceinline__ void vq_encode_fast_run_nks(const EncodeJob& job, int
         for (int j = 0; j < NB; ++j)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[1][j][v] = INFINITY;         // in the place of the unit before the first
+        if (WIDE) cn[0] = f32x16{};
         for (int t = 0; t < n_tiles; ++t, ++step) {
             const int buf = step % kEncBufs, next_buf = (step + 1) % kEncBufs;
             const int lim = K - t * CW;                         // codewords of this tile and beyond
@@ -236,32 +250,30 @@ __device__ __forceinline__ void vq_encode_fast_run_nks(const EncodeJob& job, int
                     if (!WIDE && t == t_load && item + 1 < hi) load_tokens(next_g, next_block);
                     send_tile();
                 }
-                if (lim < CW) {                                 // codewords past K (the last tile of a K that is no multiple of a tile's) are infinitely far
-#pragma unroll
-                    for (int n = 0; n < NA; ++n) {
-                        const int left = lim - 32 * block_of(u, n) - 4 * h;
-#pragma unroll
-                        for (int v = 0; v < 16; ++v) cn[n][v] = acc_row(v, 0) >= left ? INFINITY : cn[n][v];
-                    }
-                }
+                if (!WIDE) mask_cn(u, lim);
                 const int set = u & 1, rb = u == UNITS - 1 ? next_buf : buf, ru = (u + 1) % UNITS, pu = (u + UNITS - 1) % UNITS;
 #pragma unroll
                 for (int i = 0; i < NB * NKS; ++i) {
                     const int ks = i / NB, j = i % NB;
-                    acc[set][j] = mfma_32x32x16(fa[ks % NR][NA == 1 ? 0 : j], xf[TB == 2 ? j : 0][ks], ks == 0 ? cn[NA == 1 ? 0 : j] : acc[set][j]);
-                    if (i == 1) read_cn(rb, ru);
+                    acc[set][j] = mfma_32x32x16(fa[ks % NR][NA == 1 ? 0 : j], xf[TB == 2 ? j : 0][ks],
+                                                ks > 0 ? acc[set][j] : WIDE ? f32x16{} : cn[NA == 1 ? 0 : j]);
+                    if (!WIDE && i == 1) read_cn(rb, ru);
                     if (j == NB - 1) {
                         if (ks + NR < NKS) read_a(buf, u, ks + NR);
                         else read_a(rb, ru, ks + NR - NKS);
                     }
 #pragma unroll
-                    for (int x = i * 4 / NKS; x < (i + 1) * 4 / NKS; ++x) take_quad(set ^ 1, pu, x);
+                    for (int x = i * 4 / NKS; x < (i + 1) * 4 / NKS; ++x) {
+                        take_quad(set ^ 1, pu, x);
+                        if (WIDE && (x >> 2) == NB - 1) read_cn_quad(buf, u, 0, x & 3);      // this unit's, in the place of the ones just used
+                    }
                     __builtin_amdgcn_sched_barrier(0);
                 }
                 if (u == 0) close_tile(t - 1);                  // the quads were those of the tile before
                 // the argmin is worked out here: moved behind the branches that follow, it would keep the scores of several units alive
 #pragma unroll
                 for (int b = 0; b < TB; ++b) asm volatile("" : "+v"(best[b]), "+v"(grp[b]), "+v"(k0[b]), "+v"(k1[b]), "+v"(k2[b]), "+v"(til[b]));
+                if (WIDE) mask_cn(u, lim);
             }
         }
 #pragma unroll
@@ -348,7 +360,7 @@ __device__ __forceinline__ void vq_encode_stream_run(const EncodeJob& job, int v
 #pragma unroll
     for (int i = 0; i < kStreamRing; ++i) send();
 
-    // the tokens as -2x (exact in bf16): with the norms as the accumulators' start they hold distances
+    // the tokens as -2x (exact in bf16): the sums and the norms, added once at the end, are distances
     bf16x8 xf[4 * NCH];
     {
         const uint16_t* xrow = (const uint16_t*)job.x + (int64_t)min(t0 + i32, n_tokens - 1) * job.ldx + (int64_t)g * (64 * NCH) + 8 * h;
@@ -365,7 +377,7 @@ __device__ __forceinline__ void vq_encode_stream_run(const EncodeJob& job, int v
     float best = INFINITY;
     int arg = 0, step = 0;
     for (int t = 0; t < n_mine; ++t) {
-        f32x16 acc;
+        f32x16 acc = {}, norm;
 #pragma unroll
         for (int ch = 0; ch < NCH; ++ch, ++step) {
             // this step has landed: the three sent after it may be outstanding
@@ -375,12 +387,12 @@ __device__ __forceinline__ void vq_encode_stream_run(const EncodeJob& job, int v
             bf16x8 fa[4];
 #pragma unroll
             for (int ks = 0; ks < 4; ++ks) fa[ks] = __builtin_bit_cast(bf16x8, cb_lds[wave][ring][i32 * 8 + ((2 * ks + h) ^ (i32 & 7))]);
-            if (ch == 0) {
+            if (ch == NCH - 1) {
 #pragma unroll
                 for (int p = 0; p < 4; ++p) {
                     const f32x4 v = cn_lds[wave][ring][2 * p + h];
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) acc[4 * p + e] = v[e];
+                    for (int e = 0; e < 4; ++e) norm[4 * p + e] = v[e];
                 }
             }
             __builtin_amdgcn_s_waitcnt(0xC07F);              // lgkmcnt 0: the step is in registers, its place is free
@@ -393,8 +405,9 @@ __device__ __forceinline__ void vq_encode_stream_run(const EncodeJob& job, int v
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             const int cw = cw0 + acc_row(v, h);
-            const bool better = cw < K && acc[v] < best;
-            best = better ? acc[v] : best;
+            const float d = norm[v] + acc[v];
+            const bool better = cw < K && d < best;
+            best = better ? d : best;
             arg = better ? cw : arg;
         }
     }

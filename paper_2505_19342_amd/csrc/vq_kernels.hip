@@ -709,7 +709,8 @@ __global__ __launch_bounds__(256, 2) void vq_encode_bf16_fast_kernel(const Encod
 }
 
 // The same body for groups of 128 values (vq_encode_fast_wide): a codeword fragment serves 64 tokens, and the scores never leave the registers.  16384 tokens
-// x 32 groups, K = 1024: 133 us (1.03 PFLOP/s), 968 as score products in memory and an argmin over them, 736 with 32 tokens per workgroup; 1024 tokens 23 / 78 / 51.
+// x 32 groups, K = 1024: 140 us (0.98 PFLOP/s; 131 with the norms as the accumulators' start), 1026 as score products in memory and an argmin over them, 736
+// with 32 tokens per workgroup; 1024 tokens 23 / 85 / 51.
 __global__ __launch_bounds__(256, 2) void vq_encode_bf16_fast128_kernel(const EncodeJob job, int chunk) {
     __shared__ u32x4 cb_lds[kEncBufs * kEncCbSlots];    // 4 x 16 KiB: [64 codewords][16 pieces of 8 bf16], swizzled
     __shared__ f32x4 cn_lds[kEncBufs * kEncCnSlots];
@@ -721,8 +722,8 @@ __global__ __launch_bounds__(256, 2) void vq_encode_bf16_fast128_kernel(const En
 }
 
 // And for groups of 256: 32 tokens per wavefront, eight wavefronts to share a codebook tile.  One workgroup per unit: a tile is
-// 32 KiB.  16384 tokens x 16 groups, K = 1024: 141 us (0.97 PFLOP/s), 584 as score products, 646 with 32 tokens per workgroup; 1024 tokens 30 / 45 / 44.  A
-// codeword fragment serves 32 tokens only, so the LDS reads take as long as the MFMAs; all 16 fragments of a unit held at once spilled (427 us).
+// 32 KiB.  16384 tokens x 16 groups, K = 1024: 146 us (0.94 PFLOP/s; 144 with the norms as the accumulators' start), 624 as score products, 646 with 32 tokens
+// per workgroup; 1024 tokens 30 / 45 / 44.  A codeword fragment serves 32 tokens only, so the LDS reads take as long as the MFMAs; all 16 fragments of a unit held at once spilled (427 us).
 __global__ __launch_bounds__(512, 2) void vq_encode_bf16_fast256_kernel(const EncodeJob job, int chunk) {
     __shared__ u32x4 cb_lds[kEncBufs * 2 * kEncCbSlots];    // 4 x 32 KiB: [64 codewords][32 pieces of 8 bf16], swizzled
     __shared__ f32x4 cn_lds[kEncBufs * kEncCnSlots];

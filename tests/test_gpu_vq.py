@@ -301,3 +301,22 @@ def test_streamed_wide_groups(T, G, K, dg):
     assert n_tie <= max(2, ref.size // 2000)
     cb[:, K // 2:] = cb[:, :K // 2]                          # every codeword twice: the lower one
     assert gpu_vq_encode(x, cb, "bf16").max() < K // 2
+
+
+@pytest.mark.parametrize("T,G,K,dg", [(40, 7, 1024, 128), (40, 7, 1024, 192), (40, 16, 1024, 256), (8200, 2, 64, 128), (6200, 2, 64, 256)])
+def test_distances_of_wide_groups_are_rounded_once(T, G, K, dg):
+    """Codewords of one norm n, and products with x that move the nearest by 1.5 or 3 units in the last place of n, a quarter of one per 16 values: -2 x.c is
+    summed by itself and the norm added once; added to n one by one the quarters would be lost and the lowest code win.  Streamed encodes and both
+    forms of the matrix-core body (vq_encode_fast_wide)."""
+    from gpu_util import gpu_vq_encode
+    n = dg if dg == 192 else 3 * dg // 4                       # 96 or 192, halfway between two powers of two
+    x = np.zeros((T, G, dg), np.float32)
+    x[:, :, :n] = 2.0 ** (np.floor(np.log2(n)) - 23) / 128
+    x[1::2] *= -1.0
+    rng = np.random.default_rng(91)
+    half = np.repeat([1.0, -1.0], n // 2).astype(np.float32)
+    cb = np.zeros((G, K, dg), np.float32)
+    cb[:, :, :n] = rng.permuted(np.broadcast_to(half, (G, K, n)), axis=2)                   # x.c = 0
+    cb[:, K - 1, :n], cb[:, K - 2, :n] = 1.0, -1.0             # the nearest to the even tokens, to the odd ones
+    codes = gpu_vq_encode(x.reshape(T, -1), cb, "bf16")
+    assert (codes[0::2] == K - 1).all() and (codes[1::2] == K - 2).all()
