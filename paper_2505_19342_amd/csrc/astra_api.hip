@@ -55,7 +55,6 @@ struct LayerPlan {
     bool vt;                 // V, V-hat kept transposed for the attention kernel (bf16)
     int ldv_loc, ldv_hat;    // padded token counts of the transposed V buffers
     size_t off_q, off_k, off_v, off_kh, off_vh, off_o, off_xhat, off_scores, total;
-    size_t part;             // partial results of the attention, behind `total`: a workspace without them is taken, and the attention walks every block whole
 };
 
 static int make_plan(const astra_layer_desc* desc, LayerPlan* pl) {
@@ -97,12 +96,18 @@ static int make_plan(const astra_layer_desc* desc, LayerPlan* pl) {
                    (size_t)a.n_local * desc->vq.n_groups * desc->vq.codebook_size * 4 <= ((size_t)256 << 20);
     pl->off_scores = take(pl->wide_enc ? (size_t)a.n_local * desc->vq.n_groups * desc->vq.codebook_size * 4 : 0);
     pl->total = off > 0 ? off : 256;
-    AttnParams ap = attn_params(a, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
-    ap.v_transposed = pl->vt ? 1 : 0;
-    EncodeJob ej{};
-    ej.n_tokens = a.n_local; ej.G = desc->vq.n_groups; ej.K = desc->vq.codebook_size; ej.dg = dg;
-    pl->part = attention_part_bytes(desc->vq.dtype, ap, a.head_dim, &ej, a.n_local > 0 && vq_encode_fast_ok(ej.K, dg) ? 1 : 0);
     return ASTRA_OK;
+}
+
+// Partial results of the attention, behind LayerPlan::total: asked for by the workspace queries only.  A workspace without them is taken, and the attention
+// walks every block whole.
+static size_t layer_part_bytes(const astra_layer_desc& d, const LayerPlan& pl) {
+    const astra_attn_desc& a = d.attn;
+    AttnParams ap = attn_params(a, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
+    ap.v_transposed = pl.vt ? 1 : 0;
+    EncodeJob ej{};
+    ej.n_tokens = a.n_local; ej.G = d.vq.n_groups; ej.K = d.vq.codebook_size; ej.dg = pl.D / d.vq.n_groups;
+    return attention_part_bytes(d.vq.dtype, ap, a.head_dim, &ej, a.n_local > 0 && vq_encode_fast_ok(ej.K, ej.dg) ? 1 : 0);
 }
 
 struct KvPlan {
@@ -110,7 +115,6 @@ struct KvPlan {
     bool vt;
     int ldv_loc, ldv_hat;
     size_t off_q, off_k, off_v, off_vt, off_kh, off_vh, off_o, total;
-    size_t part;             // as in LayerPlan
 };
 
 static int make_kv_plan(const astra_layer_kv_desc* desc, KvPlan* pl) {
@@ -143,12 +147,16 @@ static int make_kv_plan(const astra_layer_kv_desc* desc, KvPlan* pl) {
     pl->off_vh = take((size_t)(pl->vt ? pl->ldv_hat : pl->Tn_vis) * pl->dkv * eb);
     pl->off_o = take((size_t)pl->Tq * pl->dq * eb);
     pl->total = off > 0 ? off : 256;
-    AttnParams ap = attn_params(a, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
-    ap.v_transposed = pl->vt ? 1 : 0;
-    EncodeJob ej[2] = {};
-    for (EncodeJob& j : ej) { j.n_tokens = a.n_local; j.G = desc->vq.n_groups; j.K = desc->vq.codebook_size; j.dg = pl->dkv / desc->vq.n_groups; }
-    pl->part = attention_part_bytes(dtype, ap, a.head_dim, ej, a.n_local > 0 && vq_encode_fast_ok(ej[0].K, ej[0].dg) ? 2 : 0);
     return ASTRA_OK;
+}
+
+static size_t kv_part_bytes(const astra_layer_kv_desc& d, const KvPlan& pl) {
+    const astra_attn_desc& a = d.attn;
+    AttnParams ap = attn_params(a, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
+    ap.v_transposed = pl.vt ? 1 : 0;
+    EncodeJob ej[2] = {};
+    for (EncodeJob& j : ej) { j.n_tokens = a.n_local; j.G = d.vq.n_groups; j.K = d.vq.codebook_size; j.dg = pl.dkv / d.vq.n_groups; }
+    return attention_part_bytes(d.vq.dtype, ap, a.head_dim, ej, a.n_local > 0 && vq_encode_fast_ok(ej[0].K, ej[0].dg) ? 2 : 0);
 }
 
 struct BlockPlan {
@@ -301,7 +309,7 @@ int astra_mixed_attention_valid(const astra_attn_desc* desc, const void* q, cons
 size_t astra_layer_workspace_bytes(const astra_layer_desc* desc) {
     LayerPlan pl;
     if (make_plan(desc, &pl) != ASTRA_OK) return 0;
-    return pl.total + pl.part;
+    return pl.total + layer_part_bytes(*desc, pl);
 }
 
 static int layer_forward_impl(const astra_layer_desc* desc, const void* x_local, const void* codes_nonlocal,
@@ -407,7 +415,7 @@ static int layer_forward_impl(const astra_layer_desc* desc, const void* x_local,
     ap.ldv_loc = pl.ldv_loc;
     ap.ldv_hat = pl.ldv_hat;
     ap.part = (float*)(part ? part : ws + pl.total);
-    ap.part_bytes = part ? part_bytes : plan_only ? pl.part : workspace_bytes - pl.total;
+    ap.part_bytes = part ? part_bytes : plan_only ? 0 : workspace_bytes - pl.total;
     GemmProblem po = {};
     po.a = O; po.b = wo; po.bias = bo; po.c = y_out; po.M = pl.Tq; po.N = pl.D; po.K = pl.dq; po.lda = pl.dq; po.ldc = pl.D;
     po.c_mode = kCF32;      // y leaves the layer as the fp32 accumulator, for both element types
@@ -572,7 +580,7 @@ int astra_layer_forward_valid(const astra_layer_desc* desc, const void* x_local,
 size_t astra_layer_kv_workspace_bytes(const astra_layer_kv_desc* desc) {
     KvPlan pl;
     if (make_kv_plan(desc, &pl) != ASTRA_OK) return 0;
-    return pl.total + pl.part;
+    return pl.total + kv_part_bytes(*desc, pl);
 }
 
 int astra_layer_forward_kv(const astra_layer_kv_desc* desc, const void* x_local, const void* codes_k_nonlocal,
@@ -667,7 +675,7 @@ int astra_layer_forward_kv(const astra_layer_kv_desc* desc, const void* x_local,
 size_t astra_block_workspace_bytes(const astra_block_desc* desc) {
     BlockPlan bp;
     if (make_block_plan(desc, &bp) != ASTRA_OK) return 0;
-    return bp.total + bp.layer.part;
+    return bp.total + layer_part_bytes(desc->layer, bp.layer);
 }
 
 // validate_only: every check of the call, no launch

@@ -875,42 +875,51 @@ struct AttnCut {
     double us;
 };
 
+// Tiles that a query block of a head walks
+struct Walks {
+    int n_qb, hat, loc;
+    bool causal;
+    explicit Walks(const AttnParams& p)
+        : n_qb((int)ceil_div(p.Tq, kAttQ)), hat((int)ceil_div(p.Tn_vis, kAttKV)), loc((int)ceil_div(p.Tq, kAttKV)), causal(p.causal != 0) {}
+    int tiles(int qb) const { return hat + (causal ? std::min(kAttQ / kAttKV * (qb + 1), loc) : loc); }
+    int64_t all() const {      // of all blocks; only the last one may be short of its two tiles
+        return (int64_t)n_qb * hat + (causal ? (int64_t)(n_qb - 1) * n_qb * (kAttQ / kAttKV) / 2 + loc : (int64_t)n_qb * loc);
+    }
+};
+
 // About how long the launch lasts with the first `w` blocks of a head walked whole and the others in `c` parts (us): the units' mean load, or what the
 // number of pieces leaves of it, and the partial results on their way out and back in.  A tile takes the longer the more units are at it (0.73 us on 32 of
 // them, 0.81 on 96, 1.01 on 256: the clock and the second-level caches are everyone's); 6 us go before the first and after the last.
-static double cut_us(const AttnParams& p, int w, int c, int64_t items, double item) {
-    const int n_qb = (int)ceil_div(p.Tq, kAttQ), hat = (int)ceil_div(p.Tn_vis, kAttKV), per_head = w + (n_qb - w) * c;
-    const double tile = 0.69 + 0.00125 * std::min<int64_t>((int64_t)per_head * p.Hq + items, kAttCus);
-    auto piece_us = [&](int k) {
-        const int qb = k < w ? w - 1 - k : n_qb - 1 - (k - w) / c;
-        const int tiles = hat + (int)ceil_div(p.causal ? std::min(kAttQ * (qb + 1), p.Tq) : p.Tq, kAttKV);
-        return 6.0 + tile * tiles / (k < w ? 1 : c);
-    };
-    double load = 0.0, us = 0.0;
-    for (int k = 0; k < per_head; ++k) load += piece_us(k);
-    for (int64_t j = 0; j * kAttCus < (int64_t)per_head * p.Hq; ++j) us = std::max(us, (j + 1) * piece_us((int)(j * kAttCus / p.Hq)));
-    us = std::max(us, (load * p.Hq + items * item) / kAttCus);
+// `best` or more where the mean load alone says so: the rest, whose cost grows with the rounds, is for the few that are left.
+static double cut_us(const AttnParams& p, const Walks& walks, int w, int c, int64_t items, double item, double best) {
+    const int n_qb = walks.n_qb, per_head = w + (n_qb - w) * c;
     const int64_t pieces = (int64_t)per_head * p.Hq;
-    if (pieces <= kAttCus && pieces + items > kAttCus) us = std::max(us, item + (pieces < kAttCus ? std::min(item, piece_us(per_head - 1)) : piece_us(per_head - 1)));
-    if (items > 0) us += 0.25 * item;
+    const double tile = 0.69 + 0.00125 * std::min<int64_t>(pieces + items, kAttCus);
+    auto piece_us = [&](int k) { return 6.0 + tile * walks.tiles(k < w ? w - 1 - k : n_qb - 1 - (k - w) / c) / (k < w ? 1 : c); };
     // 16.8 MB of partial results behind a single round: 12 us; behind whole walks they leave while others still run
-    return us + (w == n_qb ? 0.0 : (w > 0 ? 5.0 : 4.0) + (w > 0 ? 1.0 : 2.0) * (p.Tq - w * kAttQ) * c * p.Hq * 520.0 / 4.0e6);
+    const double behind = (items > 0 ? 0.25 * item : 0.0) +
+                          (w == n_qb ? 0.0 : (w > 0 ? 5.0 : 4.0) + (w > 0 ? 1.0 : 2.0) * (p.Tq - w * kAttQ) * c * p.Hq * 520.0 / 4.0e6);
+    double us = ((6.0 * per_head + tile * walks.all()) * p.Hq + items * item) / kAttCus;
+    if (us + behind >= best) return us + behind;
+    for (int64_t j = 0; j * kAttCus < pieces; ++j) us = std::max(us, (j + 1) * piece_us((int)(j * kAttCus / p.Hq)));
+    if (pieces <= kAttCus && pieces + items > kAttCus) us = std::max(us, item + (pieces < kAttCus ? std::min(item, piece_us(per_head - 1)) : piece_us(per_head - 1)));
+    return us + behind;
 }
 
 static size_t cut_bytes(const AttnParams& p, int w, int c) { return (size_t)(ceil_div(p.Tq, kAttQ) - w) * c * p.Hq * kPartFloats * sizeof(float); }
 
 static AttnCut attention_cut(const AttnParams& p, int head_dim, int64_t items, double item, size_t part_bytes) {
     AttnCut best = {0, 0, 0.0};
-    const int n_qb = (int)ceil_div(p.Tq, kAttQ);
+    const Walks walks(p);
+    const int n_qb = walks.n_qb;
     if (head_dim != 128 || !p.v_transposed || p.lse || (int64_t)n_qb * p.Hq > 4 * kAttCus) return best;
-    best.us = cut_us(p, n_qb, 1, items, item);
-    const int hat = (int)ceil_div(p.Tn_vis, kAttKV);
+    best.us = cut_us(p, walks, n_qb, 1, items, item, INFINITY);
     for (int j = 0; j * kAttCus / p.Hq < n_qb; ++j) {
         const int w = j * kAttCus / p.Hq;
-        const int pairs = (int)ceil_div(hat + ceil_div(p.causal ? std::min(kAttQ * (w + 1), p.Tq) : p.Tq, kAttKV), 2);     // of the shortest one cut
+        const int pairs = (int)ceil_div(walks.tiles(w), 2);      // of the shortest one cut
         for (int c = 2; c <= kMaxParts && c <= pairs; ++c) {
             if (cut_bytes(p, w, c) > part_bytes) break;
-            const double us = cut_us(p, w, c, items, item);
+            const double us = cut_us(p, walks, w, c, items, item, best.us);
             if (us < best.us) best = {w, c, us};
         }
     }
@@ -991,6 +1000,7 @@ int launch_attention(int dtype, const AttnParams& p_in, int head_dim, hipStream_
         }
         // 64-wide heads otherwise: when 128-row query blocks would leave half of the compute units without a
         // workgroup, 64-row blocks whose tiles are dealt to four wavefronts per query group (half the iterations each)
+        if (plan_only) return ASTRA_OK;
         bool few = false;
         const AttnCut cut = attention_form(p, head_dim, items, items > 0 ? encode_item_us(enc[0]) : 0.0, p.part ? p.part_bytes : 0, &few);
         p.n_whole = cut.n_whole;
@@ -1033,7 +1043,6 @@ int launch_attention(int dtype, const AttnParams& p_in, int head_dim, hipStream_
                 *enc_fused = true;
             }
         }
-        if (plan_only) return ASTRA_OK;
         if (few) return launch_attention_short(p, head_dim, ae, fetch, s);
         if (p.n_cut > 0) {
             const int grid = (int)total + ae.n_enc_wgs;

@@ -5,6 +5,7 @@ import json
 import os
 import subprocess
 import sys
+import time
 import types
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -12,9 +13,9 @@ ROOT = os.path.dirname(HERE)
 
 
 def record(calls, tmp_path):
-    """One dict per call: rc, bytes (of its workspace) and launches, a list of (kernel, grid, block, dynamic LDS bytes, cap on them).
-    A call is a dict of `entry`, its sizes (see the functions below), and optionally `device` (the current device) and
-    `fail_attributes` (the runtime refuses to raise a cap)."""
+    """One dict per call: rc, bytes (of its workspace), launches, a list of (kernel, grid, block, dynamic LDS bytes, cap on them), and us, the shortest time
+    that the entry point took of the host.  A call is a dict of `entry`, its sizes (see the functions below), and optionally `device` (the current device),
+    `fail_attributes` (the runtime refuses to raise a cap) and `repeat`."""
     lib = os.path.join(str(tmp_path), "launch_recorder.so")
     if not os.path.exists(lib):
         subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", os.path.join(HERE, "launch_recorder.cpp"), "-o", lib], check=True)
@@ -74,6 +75,15 @@ def _block(B, c, t):
     return n
 
 
+def _stack(B, c, t):
+    desc = B.block_desc(_layer_desc(B, c), c["norm"], c["mlp"], c["dff"], 1e-5, c.get("rope", 0.0))
+    names = ["codebook", "cnorm", "wq", "wk", "wv", "wo", "w1", "w2", "norm1_gain", "norm2_gain"]
+    n, blocks = B.astra_block_workspace_bytes(desc), range(c["layers"])
+    B.astra_stack_forward(desc, [B.block_weights(**{k: t() for k in names}) for _ in blocks], t(), [t() for _ in blocks], None, t(), [t() for _ in blocks],
+                          _Tensor(n))
+    return n
+
+
 def _kv(B, c, t):
     desc = B.LayerKvDesc(B.vq_desc("bf16", c["hkv"] * c["dh"], c["groups"], c["words"]), _attn_desc(B, c), c["d"])
     n = B.astra_layer_kv_workspace_bytes(desc)
@@ -124,13 +134,26 @@ def _main(recorder):
     from paper_2505_19342_amd import binding as B
     B.load(build_if_missing=False)
     B._stream = lambda: None
-    entries = {"layer": _layer, "block": _block, "kv": _kv, "project": _project, "step": _step, "stats": _stats, "update": _update, "encode": _encode}
+    entries = {"layer": _layer, "block": _block, "stack": _stack, "kv": _kv, "project": _project, "step": _step, "stats": _stats, "update": _update, "encode": _encode}
+    plain = {n: getattr(B, n) for n in ("astra_layer_forward", "astra_layer_forward_kv", "astra_block_forward", "astra_stack_forward")}
+    spent = []
+
+    def timed(f):
+        def g(*a):
+            t = time.perf_counter()
+            f(*a)
+            spent.append(time.perf_counter() - t)
+        return g
+    for n, f in plain.items():
+        setattr(B, n, timed(f))
     out = []
     for c in json.load(sys.stdin):
-        rec.rec_reset(c.get("device", 0), int(c.get("fail_attributes", False)))
+        spent.clear()
         rc, n = "ok", 0
         try:
-            n = entries[c["entry"]](B, c, _Tensor)
+            for _ in range(c.get("repeat", 1)):
+                rec.rec_reset(c.get("device", 0), int(c.get("fail_attributes", False)))
+                n = entries[c["entry"]](B, c, _Tensor)
         except B.AstraError as e:
             rc = str(e)
         launches = []
@@ -140,7 +163,7 @@ def _main(recorder):
             rec.rec_shape(i, grid, block, ctypes.byref(lds), ctypes.byref(cap))
             name = rec.rec_name(i).decode().replace("(anonymous namespace)::", "").replace("void ", "").replace("astra::", "").split("(")[0]
             launches.append((name, list(grid), list(block), lds.value, cap.value))
-        out.append({"rc": rc, "bytes": n, "launches": launches})
+        out.append({"rc": rc, "bytes": n, "launches": launches, "us": min(spent, default=0.0) * 1e6})
     json.dump(out, sys.stdout)
 
 

@@ -298,3 +298,14 @@ def test_encode_of_wide_groups_off_a_16_byte_boundary(dg, tmp_path):
     assert kernels(on) == [f"vq_encode_bf16_fast{dg}_kernel"]
     for r in off:
         assert len(kernels(r)) == 1 and kernels(r)[0].startswith("vq_encode_bf16_wide_kernel"), kernels(r)
+
+
+def test_planning_the_attention_costs_the_host_little(tmp_path):
+    """128-wide heads have walks to plan, 64-wide ones none: 32 blocks of 4096 rows and a layer whose heads have 800 query blocks, within twice the time of those
+    (seen 1.0 - 1.1; a search over all pieces, repeated with every plan of the call, took 25 and 37 times as long)."""
+    layer = dict(entry="layer", d=1024, groups=16, words=1024, causal=True, n_local=100000, n_nonlocal=64, repeat=200)
+    stack = dict(entry="stack", layers=32, d=4096, groups=64, words=1024, causal=True, n_local=4096, n_nonlocal=2565, norm="rmsnorm", mlp="swiglu", dff=14336,
+                 repeat=40)
+    calls = [dict(layer, hq=2, hkv=2, dh=64), dict(layer, hq=1, hkv=1, dh=128), dict(stack, hq=64, hkv=16, dh=64), dict(stack, hq=32, hkv=8, dh=128)]
+    us = [r["us"] for r in record(calls, tmp_path)]
+    assert us[1] < 2 * us[0] and us[3] < 2 * us[2], us
