@@ -99,17 +99,6 @@ static int make_plan(const astra_layer_desc* desc, LayerPlan* pl) {
     return ASTRA_OK;
 }
 
-// Partial results of the attention, behind LayerPlan::total: asked for by the workspace queries only.  A workspace without them is taken, and the attention
-// walks every block whole.
-static size_t layer_part_bytes(const astra_layer_desc& d, const LayerPlan& pl) {
-    const astra_attn_desc& a = d.attn;
-    AttnParams ap = attn_params(a, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
-    ap.v_transposed = pl.vt ? 1 : 0;
-    EncodeJob ej{};
-    ej.n_tokens = a.n_local; ej.G = d.vq.n_groups; ej.K = d.vq.codebook_size; ej.dg = pl.D / d.vq.n_groups;
-    return attention_part_bytes(d.vq.dtype, ap, a.head_dim, &ej, a.n_local > 0 && vq_encode_fast_ok(ej.K, ej.dg) ? 1 : 0);
-}
-
 struct KvPlan {
     int Tq, Tn, Tn_vis, D, dq, dkv;
     bool vt;
@@ -148,15 +137,6 @@ static int make_kv_plan(const astra_layer_kv_desc* desc, KvPlan* pl) {
     pl->off_o = take((size_t)pl->Tq * pl->dq * eb);
     pl->total = off > 0 ? off : 256;
     return ASTRA_OK;
-}
-
-static size_t kv_part_bytes(const astra_layer_kv_desc& d, const KvPlan& pl) {
-    const astra_attn_desc& a = d.attn;
-    AttnParams ap = attn_params(a, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
-    ap.v_transposed = pl.vt ? 1 : 0;
-    EncodeJob ej[2] = {};
-    for (EncodeJob& j : ej) { j.n_tokens = a.n_local; j.G = d.vq.n_groups; j.K = d.vq.codebook_size; j.dg = pl.dkv / d.vq.n_groups; }
-    return attention_part_bytes(d.vq.dtype, ap, a.head_dim, ej, a.n_local > 0 && vq_encode_fast_ok(ej[0].K, ej[0].dg) ? 2 : 0);
 }
 
 struct BlockPlan {
@@ -305,6 +285,8 @@ int astra_mixed_attention_valid(const astra_attn_desc* desc, const void* q, cons
     ap.valid_bits = (const unsigned long long*)valid_bits;
     return launch_attention(desc->dtype, ap, desc->head_dim, (hipStream_t)stream);
 }
+
+static size_t layer_part_bytes(const astra_layer_desc& d, const LayerPlan& pl);
 
 size_t astra_layer_workspace_bytes(const astra_layer_desc* desc) {
     LayerPlan pl;
@@ -507,6 +489,28 @@ static int layer_forward_impl(const astra_layer_desc* desc, const void* x_local,
     return rc;
 }
 
+// Partial results of the attention, behind LayerPlan::total: what the launch of the layer makes use of, or that of the layer with pre-projected codebooks, whose
+// projections may leave the encode to the attention where the others take it.  Worked out by the workspace queries only: a workspace without them is taken, and
+// the attention walks every block whole.
+static size_t layer_part_bytes(const astra_layer_desc& d, const LayerPlan& pl) {
+    const astra_attn_desc& a = d.attn;
+    AttnParams ap = attn_params(a, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
+    ap.v_transposed = pl.vt ? 1 : 0;
+    EncodeJob ej{};
+    ej.n_tokens = a.n_local; ej.G = d.vq.n_groups; ej.K = d.vq.codebook_size; ej.dg = pl.D / d.vq.n_groups;
+    size_t bytes = 0;
+    for (int preprojected = 0; preprojected < 2; ++preprojected) {
+        int fused = 0;
+        const float* table = preprojected ? reinterpret_cast<const float*>(&pl) : nullptr;
+        if (layer_forward_impl(&d, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
+                               nullptr, 0, nullptr, nullptr, &fused, nullptr, nullptr, table, table) != ASTRA_OK)
+            continue;
+        const size_t need = attention_part_bytes(d.vq.dtype, ap, a.head_dim, &ej, fused || pl.wide_enc ? 0 : 1);
+        if (need > bytes) bytes = need;
+    }
+    return bytes;
+}
+
 int astra_vq_project_codebook(const astra_vq_desc* desc, const void* codebook, const void* w, int32_t n_out, float* p_out,
                               void* stream) {
     int rc = check_vq_desc(desc);
@@ -575,6 +579,16 @@ int astra_layer_forward_valid(const astra_layer_desc* desc, const void* x_local,
                               void* y_out, void* codes_local_out, void* workspace, size_t workspace_bytes, void* stream) {
     return layer_forward_impl(desc, x_local, codes_nonlocal, codebook, cnorm, wq, wk, wv, wo, bq, bk, bv, bo, y_out,
                               codes_local_out, workspace, workspace_bytes, stream, nullptr, nullptr, valid_nonlocal_bits);
+}
+
+// as layer_part_bytes; the attention is offered both encodes
+static size_t kv_part_bytes(const astra_layer_kv_desc& d, const KvPlan& pl) {
+    const astra_attn_desc& a = d.attn;
+    AttnParams ap = attn_params(a, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
+    ap.v_transposed = pl.vt ? 1 : 0;
+    EncodeJob ej[2] = {};
+    for (EncodeJob& j : ej) { j.n_tokens = a.n_local; j.G = d.vq.n_groups; j.K = d.vq.codebook_size; j.dg = pl.dkv / d.vq.n_groups; }
+    return attention_part_bytes(d.vq.dtype, ap, a.head_dim, ej, 2);
 }
 
 size_t astra_layer_kv_workspace_bytes(const astra_layer_kv_desc* desc) {

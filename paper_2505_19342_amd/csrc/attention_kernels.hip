@@ -957,17 +957,25 @@ double attention_encode_us(const AttnParams& p, int head_dim, const EncodeJob& e
     return std::max(0.0, with - attention_us(p, attention_short(p, head_dim, 0, 0.0), 0, 0.0));
 }
 
+// Work items of the encodes that the general kernels' launch carries behind its own workgroups (128-wide heads on transposed V: the instantiations built);
+// 0: it does not carry them.
+static int64_t carried_items(const AttnParams& p, int head_dim, const EncodeJob* enc, int n_enc) {
+    if (!enc || n_enc < 1 || n_enc > 2 || head_dim != 128 || !p.v_transposed || ceil_div(p.Tq, kAttQ) * p.Hq + kAttCus > 0x7fffffff) return 0;
+    int64_t items = 0;
+    for (int j = 0; j < n_enc; ++j) {
+        const int64_t n_tb = ceil_div(enc[j].n_tokens, kAttThreads / 2);
+        if (enc[j].n_tokens <= 0 || !vq_encode_fast_ok(enc[j].K, enc[j].dg) || n_tb * enc[j].G > 0x3fffffff || enc[j].dg != enc[0].dg) return 0;
+        items += n_tb * enc[j].G;
+    }
+    return items;
+}
+
 size_t attention_part_bytes(int dtype, const AttnParams& p, int head_dim, const EncodeJob* enc, int n_enc) {
     if (dtype != ASTRA_BF16 || p.Tq == 0) return 0;
-    size_t bytes = 0;
-    for (int with = 0; with < 2; ++with) {               // the encodes may find another place
-        int64_t items = 0;
-        for (int j = 0; j < (with ? n_enc : 0); ++j) items += ceil_div(enc[j].n_tokens, kAttThreads / 2) * enc[j].G;
-        bool few = false;
-        const AttnCut cut = attention_form(p, head_dim, items, items > 0 ? encode_item_us(enc[0]) : 0.0, SIZE_MAX, &few);
-        if (cut.n_cut > 1) bytes = std::max(bytes, cut_bytes(p, cut.n_whole, cut.n_cut));
-    }
-    return bytes;
+    const int64_t items = carried_items(p, head_dim, enc, n_enc);
+    bool few = false;
+    const AttnCut cut = attention_form(p, head_dim, items, items > 0 ? encode_item_us(enc[0]) : 0.0, SIZE_MAX, &few);
+    return cut.n_cut > 1 ? cut_bytes(p, cut.n_whole, cut.n_cut) : 0;
 }
 
 int launch_attention(int dtype, const AttnParams& p_in, int head_dim, hipStream_t s, bool plan_only, const EncodeJob* enc, int n_enc,
@@ -986,18 +994,7 @@ int launch_attention(int dtype, const AttnParams& p_in, int head_dim, hipStream_
         // (head_dim of them, ldv tokens each) and 64 key rows of H_kv * head_dim elements
         if (vt && (int64_t)max(p.ldv_loc, p.ldv_hat) * 2 * head_dim >= (1ll << 32)) return ASTRA_ERR_UNSUPPORTED;
         if ((int64_t)p.Hkv * head_dim * 2 * kAttKV >= (1ll << 32)) return ASTRA_ERR_UNSUPPORTED;
-        // encodes offered by the caller ride in the launch's tail (128-wide heads on transposed V: the instantiations built)
-        int64_t items = 0;
-        if (enc && enc_fused && n_enc >= 1 && n_enc <= 2 && head_dim == 128 && vt && total + kAttCus <= 0x7fffffff) {
-            bool ok = true;
-            for (int j = 0; j < n_enc; ++j) {
-                ok = ok && enc[j].n_tokens > 0 && vq_encode_fast_ok(enc[j].K, enc[j].dg);
-                const int64_t n_tb = ceil_div(enc[j].n_tokens, kAttThreads / 2);
-                ok = ok && n_tb * enc[j].G <= 0x3fffffff && enc[j].dg == enc[0].dg;
-                items += n_tb * enc[j].G;
-            }
-            if (!ok) items = 0;
-        }
+        int64_t items = enc_fused ? carried_items(p, head_dim, enc, n_enc) : 0;      // encodes offered by the caller ride in the launch's tail
         // 64-wide heads otherwise: when 128-row query blocks would leave half of the compute units without a
         // workgroup, 64-row blocks whose tiles are dealt to four wavefronts per query group (half the iterations each)
         if (plan_only) return ASTRA_OK;

@@ -240,7 +240,7 @@ struct AttnParams {
     size_t part_bytes;
     int32_t n_whole, n_cut;     // set by launch_attention: the first n_whole query blocks of a head are walked whole, the others in n_cut parts (1: all whole; 0: a head after the other)
 };
-// bytes of `part` that launch_attention makes use of for a launch that carries the n_enc encodes or none of them; 0: it would cut nothing
+// bytes of `part` that launch_attention makes use of where it is offered the n_enc encodes; 0: it would cut nothing
 size_t attention_part_bytes(int dtype, const AttnParams& p, int head_dim, const EncodeJob* enc, int n_enc);
 // plan_only: validate the launch (shape limits, kernel availability) and launch nothing
 // enc / n_enc / enc_fused: up to two VQ encodes that nothing in the launch depends on, offered to it; *enc_fused tells whether

@@ -61,7 +61,10 @@ def _layer(B, c, t):
     desc = _layer_desc(B, c)
     b = [t() if c.get("bias") else None for _ in range(4)]
     n = B.astra_layer_workspace_bytes(desc)
-    B.astra_layer_forward(desc, t(), t(), t(), t(), *[t() for _ in range(4)], *b, t(), t(), _Tensor(n))
+    if c["entry"] == "preprojected":
+        B.astra_layer_forward_preprojected(desc, t(), t(), None, *[t() for _ in range(8)], *b, t(), t(), _Tensor(n))
+    else:
+        B.astra_layer_forward(desc, t(), t(), t(), t(), *[t() for _ in range(4)], *b, t(), t(), _Tensor(n))
     return n
 
 
@@ -134,7 +137,7 @@ def _main(recorder):
     from paper_2505_19342_amd import binding as B
     B.load(build_if_missing=False)
     B._stream = lambda: None
-    entries = {"layer": _layer, "block": _block, "stack": _stack, "kv": _kv, "project": _project, "step": _step, "stats": _stats, "update": _update, "encode": _encode}
+    entries = {"layer": _layer, "preprojected": _layer, "block": _block, "stack": _stack, "kv": _kv, "project": _project, "step": _step, "stats": _stats, "update": _update, "encode": _encode}
     plain = {n: getattr(B, n) for n in ("astra_layer_forward", "astra_layer_forward_kv", "astra_block_forward", "astra_stack_forward")}
     spent = []
 

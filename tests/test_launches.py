@@ -309,3 +309,29 @@ def test_planning_the_attention_costs_the_host_little(tmp_path):
     calls = [dict(layer, hq=2, hkv=2, dh=64), dict(layer, hq=1, hkv=1, dh=128), dict(stack, hq=64, hkv=16, dh=64), dict(stack, hq=32, hkv=8, dh=128)]
     us = [r["us"] for r in record(calls, tmp_path)]
     assert us[1] < 2 * us[0] and us[3] < 2 * us[2], us
+
+
+def test_scratch_for_the_parts_of_walks_is_what_a_launch_fills(tmp_path):
+    """The layer's workspace is Q, K, V, the peers' K and V and the heads' outputs, and behind them the parts of cut walks (64 KiB and 1 KiB each) of this
+    launch or of that with pre-projected codebooks; none where both walk whole."""
+    def up(n, m):
+        return -(-n // m) * m
+
+    def parts(r):
+        return sum(g[0] // 4 * int(k.split("<")[1][:-1]) for k, g, *_ in r["launches"] if k.startswith("attn_merge"))
+
+    shapes = [dict(LLAMA, n_local=1531, n_nonlocal=2565), dict(LLAMA, n_local=512, n_nonlocal=3584), dict(LLAMA, n_local=1024, n_nonlocal=3072),
+              dict(LLAMA, n_local=185, n_nonlocal=3076, hq=40, d=2560), dict(LLAMA, n_local=5017, n_nonlocal=131, hq=4, hkv=4, d=256, groups=32),
+              dict(LLAMA, n_local=28, n_nonlocal=3182, groups=16), dict(LLAMA, n_local=253, n_nonlocal=6982, hq=16, hkv=2, groups=16)]
+    entries = ("layer", "preprojected", "kv")
+    results = record([dict(c, entry=e, causal=True) for c in shapes for e in entries], tmp_path)
+    some = 0
+    for i, c in enumerate(shapes):
+        q, v, dq, dkv = c["n_local"], c["n_nonlocal"], c["hq"] * 128, c["hkv"] * 128
+        layer = [q * dq, q * dkv, up(q, 64) * dkv, v * dkv, up(v, 64) * dkv, q * dq]
+        for per, sizes in ((results[3 * i:3 * i + 2], layer), (results[3 * i + 2:3 * i + 3], layer + [q * dkv])):
+            n = max(parts(r) for r in per)
+            some += n > 0
+            if c["d"] // c["groups"] <= 64 or len(per) == 1:                 # wide groups keep scores in it, too
+                assert {r["bytes"] for r in per} == {sum(up(2 * s, 256) for s in sizes) + n * (128 * 128 + 256) * 4}, c
+    assert 0 < some < 2 * len(shapes)
