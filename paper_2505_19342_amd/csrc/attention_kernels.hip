@@ -937,14 +937,18 @@ static bool attention_short(const AttnParams& p, int head_dim, int64_t items, do
     return items == 0 || attention_us(p, true, items, item) < attention_us(p, false, items, item);
 }
 
-// The kernel of a launch and where its walks are cut.  The short form gives way where its walk takes longer than parts of one on the kernel above do.
+// The kernel of a launch and where its walks are cut.  The short form gives way where its walk takes longer than parts of one on the kernel above do.  With the
+// encodes of K and V aboard as if they had to wait for the walk's end it gave way too early: layers 4096 wide, 84 + 588 rows, 32 groups of 1024 codewords
+// 45.5 us cut, 41.1 short; 16 groups 40 + 1000 43.5 / 39.2, 200 + 1000 65.0 / 58.8; one encode, 64 groups, 128 + 1000 77.6 / 73.0.
 static AttnCut attention_form(const AttnParams& p, int head_dim, int64_t items, double item, size_t part_bytes, bool* few) {
     *few = attention_short(p, head_dim, items, item);
     const AttnCut cut = attention_cut(p, head_dim, items, item, part_bytes);
     if (!*few || cut.n_cut == 0) return cut;
     const int64_t units = ceil_div(p.Tq, 32) * p.Hq;
     const double walk = 5.0 + std::max(0.37, 0.56 * units / kAttCus) * (p.Tn_vis + p.Tq) / kAttKV;
-    const double behind = (double)std::max<int64_t>(kAttCus - units, 0) * std::floor(walk / std::max(item, 1.0)) >= (double)items ? 0.0 : item;
+    // encodes take turns on the units without a query block, or wait for the walk's end
+    const int64_t idle = kAttCus - units;
+    const double behind = items == 0 ? 0.0 : idle == 0 ? item : std::min(item, std::max(0.0, (double)ceil_div(items, idle) * item - walk));
     *few = walk + behind < cut.us + 1.0;
     return *few ? AttnCut{0, 0, 0.0} : cut;
 }

@@ -335,3 +335,12 @@ def test_scratch_for_the_parts_of_walks_is_what_a_launch_fills(tmp_path):
             if c["d"] // c["groups"] <= 64 or len(per) == 1:                 # wide groups keep scores in it, too
                 assert {r["bytes"] for r in per} == {sum(up(2 * s, 256) for s in sizes) + n * (128 * 128 + 256) * 4}, c
     assert 0 < some < 2 * len(shapes)
+
+
+def test_short_form_keeps_walks_beside_encodes_with_units_of_their_own(tmp_path):
+    """32 query rows per workgroup and the encodes on the units that are left, as long as those are done in about the time of a walk; parts of walks beyond."""
+    short = [("kv", 84, 588, 32), ("kv", 40, 1000, 16), ("kv", 200, 1000, 16), ("layer", 128, 1000, 64)]
+    cut = [("kv", 40, 4096, 16), ("kv", 84, 4096, 32), ("layer", 128, 4096, 64)]
+    results = record([dict(LLAMA, entry=e, n_local=t, n_nonlocal=n, groups=g, causal=True) for e, t, n, g in short + cut], tmp_path)
+    for i, (c, r) in enumerate(zip(short + cut, results)):
+        assert any(k.startswith("attn_short" if i < len(short) else "attn_cut") for k in kernels(r)), (c, kernels(r))
