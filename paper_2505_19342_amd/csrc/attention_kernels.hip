@@ -917,9 +917,13 @@ static AttnCut attention_cut(const AttnParams& p, int head_dim, int64_t items, d
     for (int j = 0; j * kAttCus / p.Hq < n_qb; ++j) {
         const int w = j * kAttCus / p.Hq;
         const int pairs = (int)ceil_div(walks.tiles(w), 2);      // of the shortest one cut
+        // Encodes aboard are work for units that whole walks leave idle, and the estimate of a cut knows little of that: parts of walks of fewer than 16 tiles have to
+        // promise 3 us (17 and 40 + 588 rows, 16 groups, K and V quantised after projection: whole 38.2, 41.5 us, cut 38.8, 42.4 with 1 - 2 promised; 8 heads,
+        // not causal, 20 + 627: 24.5 / 29.1 with 3).
+        const double margin = items > 0 && walks.tiles(n_qb - 1) < 16 ? 3.0 : 0.0;
         for (int c = 2; c <= kMaxParts && c <= pairs; ++c) {
             if (cut_bytes(p, w, c) > part_bytes) break;
-            const double us = cut_us(p, walks, w, c, items, item, best.us);
+            const double us = cut_us(p, walks, w, c, items, item, best.us - margin) + margin;
             if (us < best.us) best = {w, c, us};
         }
     }
@@ -937,19 +941,22 @@ static bool attention_short(const AttnParams& p, int head_dim, int64_t items, do
     return items == 0 || attention_us(p, true, items, item) < attention_us(p, false, items, item);
 }
 
-// The kernel of a launch and where its walks are cut.  The short form gives way where its walk takes longer than parts of one on the kernel above do.  With the
-// encodes of K and V aboard as if they had to wait for the walk's end it gave way too early: layers 4096 wide, 84 + 588 rows, 32 groups of 1024 codewords
-// 45.5 us cut, 41.1 short; 16 groups 40 + 1000 43.5 / 39.2, 200 + 1000 65.0 / 58.8; one encode, 64 groups, 128 + 1000 77.6 / 73.0.
+// The kernel of a launch and where its walks are cut.  The short form gives way where its walk takes longer than parts of one on the kernel above do.  Encodes
+// take turns on the units without a query block; those that are not done within the walk slow all of it a little and end it, at the latest an encode later.
+// Had they to wait for the walk, it would give way too early: layers 4096 wide with the encodes of K and V aboard, 1024 codewords, 84 + 588 rows, 32 groups
+// 45.5 us cut, 41.1 short; 16 groups 40 + 1000 43.5 / 39.2, 200 + 1000 65.0 / 58.8; with one encode, 64 groups, 128 + 1000 77.6 / 73.0.
 static AttnCut attention_form(const AttnParams& p, int head_dim, int64_t items, double item, size_t part_bytes, bool* few) {
     *few = attention_short(p, head_dim, items, item);
     const AttnCut cut = attention_cut(p, head_dim, items, item, part_bytes);
     if (!*few || cut.n_cut == 0) return cut;
-    const int64_t units = ceil_div(p.Tq, 32) * p.Hq;
-    const double walk = 5.0 + std::max(0.37, 0.56 * units / kAttCus) * (p.Tn_vis + p.Tq) / kAttKV;
-    // encodes take turns on the units without a query block, or wait for the walk's end
-    const int64_t idle = kAttCus - units;
-    const double behind = items == 0 ? 0.0 : idle == 0 ? item : std::min(item, std::max(0.0, (double)ceil_div(items, idle) * item - walk));
-    *few = walk + behind < cut.us + 1.0;
+    const int64_t units = ceil_div(p.Tq, 32) * p.Hq, idle = kAttCus - units;
+    const double tiles = (double)(p.Tn_vis + p.Tq) / kAttKV, crowd = 0.56 * units / kAttCus;
+    double us = 5.0 + std::max(0.37, crowd) * tiles;
+    if ((double)idle * std::floor(us / std::max(item, 1.0)) < (double)items) {
+        const double beside = 5.0 + std::max(0.43, crowd) * tiles, waiting = us + item;
+        us = idle > 0 ? std::min(waiting, std::max(beside, (double)ceil_div(items, idle) * item)) : waiting;
+    }
+    *few = us < cut.us + 1.0;
     return *few ? AttnCut{0, 0, 0.0} : cut;
 }
 
