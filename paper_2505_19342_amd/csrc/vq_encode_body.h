@@ -440,12 +440,13 @@ inline int vq_encode_blocks(const EncodeJob& e, int64_t wgs) {
     return 1.6 * (double)ceil_div(two, wgs) < (double)ceil_div(one, wgs) ? 2 : 1;
 }
 
-// Groups of 128, 192 and 256 values are taken by vq_encode_bf16_stream_kernel, 32 tokens per workgroup.  (16 groups of 256 codewords of 256 values stay with
-// vq_encode_bf16_wide_kernel, 8.2 us for one round of it and 8.4 streamed; 128 codewords 6.6 / 6.1, 512 12.4 / 10.1.)
+// Groups of 128, 192 and 256 values are taken by vq_encode_bf16_stream_kernel, 32 tokens per workgroup.  Of 256 values, codebooks of about a block of 32 codewords
+// for each of the eight wavefronts stay with vq_encode_bf16_wide_kernel (wide / streamed, us, 16 groups and 64 tokens, the same within 1 % for 4 to 32 groups and
+// up to 500 tokens: K = 136 6.9 / 6.6, 192 7.2 / 7.0, 224 7.6 / 7.5, 256 7.9 / 8.1, 288 9.0 / 8.3, 320 9.4 / 8.4; 17 tokens 7.6 / 6.9 at 256).
 inline bool vq_encode_stream_fits(int K, int dg, int64_t ldx) {
     return dg > kEncKt && dg <= 256 && dg % 64 == 0 && K % 4 == 0 && ldx % 8 == 0 && (int64_t)K * dg * 2 < ((int64_t)1 << 31);
 }
-inline bool vq_encode_stream_ok(int K, int dg, int64_t ldx) { return vq_encode_stream_fits(K, dg, ldx) && (dg < 256 || K <= 128 || K > 320); }
+inline bool vq_encode_stream_ok(int K, int dg, int64_t ldx) { return vq_encode_stream_fits(K, dg, ldx) && (dg < 256 || K <= 224 || K > 256); }
 // 16-byte transfers to LDS: arrays that start off such a boundary stay with the kernel for wide groups
 inline bool vq_encode_on_16(const void* x, const void* codebook, const void* cnorm) {
     return ((reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(codebook) | reinterpret_cast<uintptr_t>(cnorm)) & 15) == 0;

@@ -344,3 +344,10 @@ def test_short_form_keeps_walks_beside_encodes_with_units_of_their_own(tmp_path)
     results = record([dict(LLAMA, entry=e, n_local=t, n_nonlocal=n, groups=g, causal=True) for e, t, n, g in short + cut], tmp_path)
     for i, (c, r) in enumerate(zip(short + cut, results)):
         assert any(k.startswith("attn_short" if i < len(short) else "attn_cut") for k in kernels(r)), (c, kernels(r))
+
+
+def test_codebooks_of_a_block_per_wavefront(tmp_path):
+    """Groups of 256 values: more than 224 and up to 256 codewords stay with the kernel for wide groups."""
+    sizes = [(132, True), (224, True), (228, False), (256, False), (260, True), (320, True)]
+    for (k, streamed), r in zip(sizes, record([dict(entry="encode", tokens=64, groups=16, words=k, d=4096) for k, _ in sizes], tmp_path)):
+        assert kernels(r)[0].startswith("vq_encode_bf16_stream_kernel" if streamed else "vq_encode_bf16_wide_kernel"), (k, kernels(r))
