@@ -265,3 +265,22 @@ def test_widths_of_the_normalisation(d, norm_kind, dtype):
     """A wavefront per row up to 1024 values (lanes without any, a ragged last quarter, all of them), a workgroup beyond."""
     layer = wl.LayerConfig("norm_widths", dtype, d, 2, 1, 64, 99, 3, 8, 16, causal=True, seed=82)
     run_case(wl.BlockConfig("norm_widths_block", layer, norm_kind, "gelu_tanh", 128, 1e-5, norm_kind == "layernorm"), 2)
+
+
+@pytest.mark.parametrize("words", [256, 300])
+@pytest.mark.parametrize("norm_kind", ["layernorm", "rmsnorm"])
+def test_rebuilt_rows_beside_the_normalisation_of_wide_rows(norm_kind, words):
+    """16 groups of 68 channels: a workgroup per row of 1088 values, the peers' rows in the workgroups behind them; 8- and 16-bit codes."""
+    layer = wl.LayerConfig("wide_decode", "bf16", 1088, 4, 2, 64, 99, 3, 16, words, causal=True, seed=83)
+    run_case(wl.BlockConfig("wide_decode_block", layer, norm_kind, "gelu_tanh", 128, 1e-5, norm_kind == "layernorm"), 2)
+
+
+# heads, tokens, devices: walks in parts (as tests/test_launches.py checks), with the encode behind them and without
+CUT = [(4, 2400, 16), (20, 1600, 4)]
+
+
+@pytest.mark.parametrize("heads,seq_len,n_dev", CUT)
+def test_walks_cut_between_workgroups(heads, seq_len, n_dev):
+    """The parts lie behind everything else that the block keeps in its workspace."""
+    layer = wl.LayerConfig("block_cut", "bf16", 64 * heads, heads, 4, 128, seq_len, n_dev, 16, 256, causal=True, seed=84)
+    run_case(wl.BlockConfig("block_cut", layer, "rmsnorm", "gelu_tanh", 256, 1e-5, False, rope_base=10000.0), n_dev - 1)

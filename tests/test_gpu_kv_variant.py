@@ -116,6 +116,18 @@ def test_short_sequences_of_128_wide_heads(d, hq, hkv, seq_len, groups, words, l
     run_case(cfg, 3, valid=(rng.random(cfg.n_nonlocal) > 0.2).astype(np.uint8) if lost else None)
 
 
+# heads, tokens over sixteen devices: walks in parts with the encodes of K and V behind them (as tests/test_launches.py checks)
+CUT = [(4, 2400), (8, 3200)]
+
+
+@pytest.mark.parametrize("lost", [False, True])
+@pytest.mark.parametrize("heads,seq_len", CUT)
+def test_walks_cut_between_workgroups(heads, seq_len, lost):
+    cfg = wl.LayerConfig("kv_cut", "bf16", 64 * heads, heads, 4, 128, seq_len, 16, 8, 256, causal=True, seed=74)
+    rng = np.random.default_rng(10)
+    run_case(cfg, 15, valid=(rng.random(cfg.n_nonlocal) > 0.2).astype(np.uint8) if lost else None)
+
+
 def test_results_do_not_depend_on_where_k_and_v_are_kept():
     from gpu_util import KvLayerOnGpu
     cfg = wl.GPT2_SMALL

@@ -339,6 +339,14 @@ CUT_WALKS = [
     (300, 4096, 8, 2, 0, True, None, 0, 8),         # the last part crosses the diagonal; a block of 44 rows
     (520, 2500, 16, 4, 0, True, "some", 0, 3),      # parts of unequal length, a block of 8 rows
     (520, 600, 64, 8, 0, True, None, 4, 3),         # whole walks first, the ragged block in parts
+    (520, 600, 64, 8, 0, True, "some", 4, 3),
+    (520, 600, 52, 4, 0, True, "tiles", 4, 3),      # heads that the XCDs do not share evenly
+    (520, 300, 52, 4, 0, True, None, 4, 4),
+    (130, 1500, 52, 4, 0, True, None, 0, 2),        # every other number of parts
+    (70, 4096, 64, 8, 0, True, "some", 0, 4),
+    (130, 4096, 24, 8, 0, True, None, 0, 5),
+    (130, 4096, 20, 4, 0, True, "tiles", 0, 6),
+    (70, 4096, 36, 4, 0, True, None, 0, 7),
 ]
 
 

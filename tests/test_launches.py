@@ -351,3 +351,20 @@ def test_codebooks_of_a_block_per_wavefront(tmp_path):
     sizes = [(132, True), (224, True), (228, False), (256, False), (260, True), (320, True)]
     for (k, streamed), r in zip(sizes, record([dict(entry="encode", tokens=64, groups=16, words=k, d=4096) for k, _ in sizes], tmp_path)):
         assert kernels(r)[0].startswith("vq_encode_bf16_stream_kernel" if streamed else "vq_encode_bf16_wide_kernel"), (k, kernels(r))
+
+
+def test_cut_walks_of_other_entry_points(tmp_path):
+    """The shapes of the GPU tests: the layer that quantises K and V after projection, with both encodes aboard, and blocks."""
+    from test_gpu_block import CUT as BLOCKS
+    from test_gpu_kv_variant import CUT as KV
+    common = dict(dh=128, hkv=4, causal=True, words=256, norm="rmsnorm", mlp="gelu_tanh", dff=256, rope=10000.0)
+    calls = [dict(common, entry="kv", d=64 * h, hq=h, n_local=n // 16, n_nonlocal=n // 16 * 15, groups=8) for h, n in KV]
+    calls += [dict(common, entry="block", d=64 * h, hq=h, n_local=n // d, n_nonlocal=n - n // d, groups=16) for h, n, d in BLOCKS]
+    for aboard, c, r in zip((True, True, True, False), calls, record(calls, tmp_path)):
+        assert any(k.startswith("attn_merge") for k in kernels(r)), (c, kernels(r))
+        assert any(k.startswith("attn_cut_kernel<false, true") for k in kernels(r)) == aboard and not any("vq_encode" in k for k in kernels(r) if aboard), (c, kernels(r))
+
+
+def test_rebuilt_rows_come_with_the_normalisation_of_wide_rows_too(tmp_path):
+    call = dict(entry="block", d=1088, hq=4, hkv=2, dh=64, n_local=33, n_nonlocal=66, causal=True, norm="rmsnorm", mlp="gelu_tanh", dff=128, groups=16, words=256)
+    assert kernels(record([call], tmp_path)[0])[0] == "norm_decode_kernel<unsigned char, false>"
