@@ -42,7 +42,8 @@ typedef enum {
     ASTRA_ERR_NULL = -1,        /* a required pointer is NULL */
     ASTRA_ERR_SHAPE = -2,       /* sizes inconsistent or out of the supported range */
     ASTRA_ERR_DTYPE = -3,       /* unknown dtype / code type, or code type too narrow for K */
-    ASTRA_ERR_WORKSPACE = -4,   /* workspace NULL or smaller than astra_layer_workspace_bytes */
+    ASTRA_ERR_WORKSPACE = -4,   /* workspace NULL or smaller than the call needs (its *_workspace_bytes; for layers
+                                   and blocks see astra_layer_workspace_bytes) */
     ASTRA_ERR_UNSUPPORTED = -5, /* valid request this build has no kernel for */
     ASTRA_ERR_HIP = -6          /* the HIP runtime refused a launch */
 } astra_status;
@@ -98,9 +99,11 @@ int astra_vq_encode(const astra_vq_desc* desc, const void* x, int64_t n_tokens, 
  * groups, down to the vanilla VQ of Sec. 2 with G = 1, the setting of the paper's strongest compression) the distance matrix
  * of a group is a matrix product of its own: scores[t, g, k] = x[t, slice g] . codebook[g, k, :] run on the projection tile
  * kernel into workspace (fp32, n_tokens * G * K * 4 bytes), followed by one pass that picks argmin_k ||c||^2 - 2 score, lowest k
- * on ties (used when a group's codebook has at least 2^17 elements; smaller ones are faster in astra_vq_encode's kernels).
- * Same results as astra_vq_encode under the same near-tie rule; other shapes run astra_vq_encode's kernels and ignore the
- * workspace.  astra_vq_encode_workspace_bytes: the size needed (256 when unused; 0 on an invalid descriptor). */
+ * on ties.  That is asked for where a group's codebook has at least 2^17 elements, and done there unless many groups or many
+ * tokens make it dearer than astra_vq_encode's kernels, as for most shapes of 128 to 256 values per group: those run instead, and
+ * leave the workspace alone.  Same results as astra_vq_encode under the same near-tie rule.
+ * astra_vq_encode_workspace_bytes: the size that the call insists on, n_tokens * G * K * 4 bytes for every wide shape with 2^17
+ * elements or more, whichever way it runs; 256 for other shapes, which ignore the workspace; 0 on an invalid descriptor. */
 size_t astra_vq_encode_workspace_bytes(const astra_vq_desc* desc, int64_t n_tokens);
 int astra_vq_encode_ws(const astra_vq_desc* desc, const void* x, int64_t n_tokens, const void* codebook, const float* cnorm,
                        void* codes_out, void* workspace, size_t workspace_bytes, void* stream);
@@ -132,7 +135,13 @@ int astra_mixed_attention_valid(const astra_attn_desc* desc, const void* q,
                                 const void* k_hat, const void* v_hat, const uint64_t* valid_bits,
                                 void* out, float* lse_out, void* stream);
 
-/* Scratch bytes astra_layer_forward needs for this shape (0 on an invalid descriptor). */
+/* Scratch bytes of astra_layer_forward for this shape (0 on an invalid descriptor).  For bf16 layers on 128-wide heads the last
+ * part of it may be there for partial results of the attention: walks over long contexts are cut between workgroups where
+ * whole ones leave compute units idle.  That part is optional, here and in astra_layer_kv_workspace_bytes and
+ * astra_block_workspace_bytes: a call takes a workspace without it or with some of it, cuts what fits, and is the slower one (by up to
+ * 20 %); ASTRA_ERR_WORKSPACE is for what does not hold the rest.  Its outputs then differ within the accuracy of the element type: cut
+ * or whole, a row's probabilities are rounded to bf16 against another maximum (2e-3 of the norm between the two, 1.8 - 2.0e-3 from 64
+ * bits either way).  With at least the reported size, a result does not depend on the size of the workspace. */
 size_t astra_layer_workspace_bytes(const astra_layer_desc* desc);
 
 /* 1 if astra_layer_forward runs the encode of the local rows inside its projection launch for this shape
@@ -151,7 +160,7 @@ int astra_layer_encode_fused(const astra_layer_desc* desc);
  *   y_out           [T_q, D] fp32 for BOTH element types: the output projection's fp32 accumulator is
  *                   stored unrounded (a bf16 store alone would cost |y| * 2^-9 of accuracy)
  *   codes_local_out [T_l, G]
- *   workspace       at least astra_layer_workspace_bytes(desc) bytes, 256-byte aligned
+ *   workspace       astra_layer_workspace_bytes(desc) bytes, 256-byte aligned
  * No residual, normalisation or positional encoding is applied. */
 int astra_layer_forward(const astra_layer_desc* desc, const void* x_local, const void* codes_nonlocal,
                         const void* codebook, const float* cnorm,

@@ -16,8 +16,9 @@ namespace astra {
 // non-local ones first) for itself: direct transfers bring its keys and values into LDS of its own (8 KiB each, XOR-swizzled pieces), so that the loop has
 // no barrier and no other wavefront to wait for.  A tile's fragments are read into registers whole, and its place takes the wavefront's next tile at once.  The
 // reference maxima start from the ones attn_bf16_kernel would have (its wavefronts' first tiles: a quarter of the 64-key tiles each on 64-wide heads, half on
-// 128-wide ones), exchanged once through LDS: probabilities are then rounded to bf16 on the same scale and a row's output does not depend on which kernel
-// took it but for the order of fp32 sums (layers' outputs then differ by 2e-5 of the norm instead of 2e-3, for 0.5 us of a ViT layer's 23.9).  The
+// 128-wide ones), exchanged once through LDS: probabilities are then rounded to bf16 on the same scale and a row's output does not depend on which of
+// the two took it but for the order of fp32 sums (layers' outputs then differ by 2e-5 of the norm instead of 2e-3, for 0.5 us of a ViT layer's 23.9); where
+// that kernel cuts its walks, every part has maxima of its own, and the outputs differ by 2e-3.  The
 // eight (max, sum, O) triples meet in LDS, and every thread adds four of the workgroup's outputs in wavefront order.
 //
 // What bounds it: a launch, a memory latency at either end, and what the second-level caches give all units together (4 DH bytes a key for every 32
