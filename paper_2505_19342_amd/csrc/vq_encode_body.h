@@ -33,8 +33,10 @@ struct EncodeJob {
 // Groups of at most 64 values (dg a multiple of 8), and of 128 and 256 on tiles of 64 codewords.  An item is a group and a block of tokens; a workgroup of THREADS threads takes a run of items,
 // 32 TB tokens per wavefront (on the N side of the 32x32x16 MFMA), and walks the group's codebook in tiles of 128 codewords (M side) for each.
 //   - The score is kept as a distance, ||c||^2 - 2 x.c: the token fragments are loaded negated and doubled (exact in bf16).  The accumulation of up to four
-//     steps starts from ||c||^2, so no vector-ALU work is spent on forming the score.  That of 8 or 16 steps would round every partial sum at the size of
-//     ||c||^2, about dg: there -2 x.c is summed by itself and ||c||^2 added once, an addition per score.
+//     steps starts from ||c||^2, so no vector-ALU work is spent on forming the score.  That of 8 or 16 steps rounds every partial sum at the size of ||c||^2,
+//     about dg.  Codebooks of 2^17 elements and more, whose score products the body stands in for, are as accurate as those (ONCE): -2 x.c is summed by
+//     itself and ||c||^2 added once, an addition per score.  Smaller ones start from ||c||^2, as in vq_encode_bf16_wide_kernel, which had them before (groups of
+//     128, K = 256, 9901 tokens: 32.6 us, 37.2 with the addition).
 //   - Codebook tiles and their norms go from global memory straight into a ring of four LDS buffers, two to three tiles ahead, without a break
 //     between items.  Pieces beyond dg are never transferred; the one such slot a contraction step can read (dg an odd multiple of 8) is
 //     zeroed once by the caller (vq_encode_fast_zero_lds, when vq_encode_fast_needs_zero) and meets zero token values.
@@ -57,8 +59,8 @@ __device__ __forceinline__ void vq_encode_fast_zero_lds(u32x4* cb_lds) {
 }
 __device__ __forceinline__ bool vq_encode_fast_needs_zero(int dg) { return (dg & 8) != 0; }
 
-// NKS = ceil(dg / 16) contraction steps
-template <int THREADS, int TB, int NKS>
+// NKS = ceil(dg / 16) contraction steps; ONCE: the norm is added to the finished sum
+template <int THREADS, int TB, int NKS, bool ONCE = false>
 __device__ __forceinline__ void vq_encode_fast_run_nks(const EncodeJob& job, int lo, int hi, u32x4* cb_lds, f32x4* cn_lds) {
     constexpr int WAVES = THREADS / 64;
     constexpr int TOKENS = WAVES * 32 * TB;             // tokens per item
@@ -66,6 +68,7 @@ __device__ __forceinline__ void vq_encode_fast_run_nks(const EncodeJob& job, int
     // of 256, a unit is one accumulator, 32 codewords against 32 tokens (none for more either)
     constexpr bool WIDE = NKS > 4;
     static_assert(!WIDE || (TB == 2 && NKS == 8) || (TB == 1 && NKS == 16), "a tile of 64 codewords is two units of 32");
+    static_assert(WIDE || !ONCE, "the norms of one block of codewords are held");
     constexpr int NB = NKS == 16 ? 1 : 2;               // accumulators of a unit
     constexpr int CW = WIDE ? kEncCw / 2 : kEncCw;      // codewords of a tile
     constexpr int PPR = WIDE ? 2 * NKS : 8;             // 16-byte slots of a codeword
@@ -186,7 +189,7 @@ __device__ __forceinline__ void vq_encode_fast_run_nks(const EncodeJob& job, int
     float best[TB], best_in[TB], k0[TB], k1[TB], k2[TB];
     int grp[TB], til[TB];
     f32x16 acc[2][NB];
-    auto score = [&](int set, int j, int v) __attribute__((always_inline)) { return WIDE ? cn[0][v] + acc[set][j][v] : acc[set][j][v]; };
+    auto score = [&](int set, int j, int v) __attribute__((always_inline)) { return ONCE ? cn[0][v] + acc[set][j][v] : acc[set][j][v]; };
     auto take_quad = [&](int set, int u, int i) __attribute__((always_inline)) {         // i-th of a unit's 4 NB
         const int j = i >> 2, q = i & 3, b = TB == 2 ? j : 0;
         const float s0 = score(set, j, 4 * q), s1 = score(set, j, 4 * q + 1), s2 = score(set, j, 4 * q + 2), s3 = score(set, j, 4 * q + 3);
@@ -213,7 +216,7 @@ __device__ __forceinline__ void vq_encode_fast_run_nks(const EncodeJob& job, int
     take_tokens();
     wait_vmem_all();
     __syncthreads();
-    if (!WIDE) read_cn(0, 0);
+    if (!ONCE) read_cn(0, 0);
 #pragma unroll
     for (int ks = 0; ks < NR; ++ks) read_a(0, 0, ks);
 
@@ -231,7 +234,7 @@ __device__ __forceinline__ void vq_encode_fast_run_nks(const EncodeJob& job, int
         for (int j = 0; j < NB; ++j)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[1][j][v] = INFINITY;         // in the place of the unit before the first
-        if (WIDE) cn[0] = f32x16{};
+        if (ONCE) cn[0] = f32x16{};
         for (int t = 0; t < n_tiles; ++t, ++step) {
             const int buf = step % kEncBufs, next_buf = (step + 1) % kEncBufs;
             const int lim = K - t * CW;                         // codewords of this tile and beyond
@@ -250,14 +253,14 @@ __device__ __forceinline__ void vq_encode_fast_run_nks(const EncodeJob& job, int
                     if (!WIDE && t == t_load && item + 1 < hi) load_tokens(next_g, next_block);
                     send_tile();
                 }
-                if (!WIDE) mask_cn(u, lim);
+                if (!ONCE) mask_cn(u, lim);
                 const int set = u & 1, rb = u == UNITS - 1 ? next_buf : buf, ru = (u + 1) % UNITS, pu = (u + UNITS - 1) % UNITS;
 #pragma unroll
                 for (int i = 0; i < NB * NKS; ++i) {
                     const int ks = i / NB, j = i % NB;
                     acc[set][j] = mfma_32x32x16(fa[ks % NR][NA == 1 ? 0 : j], xf[TB == 2 ? j : 0][ks],
-                                                ks > 0 ? acc[set][j] : WIDE ? f32x16{} : cn[NA == 1 ? 0 : j]);
-                    if (!WIDE && i == 1) read_cn(rb, ru);
+                                                ks > 0 ? acc[set][j] : ONCE ? f32x16{} : cn[NA == 1 ? 0 : j]);
+                    if (!ONCE && i == 1) read_cn(rb, ru);
                     if (j == NB - 1) {
                         if (ks + NR < NKS) read_a(buf, u, ks + NR);
                         else read_a(rb, ru, ks + NR - NKS);
@@ -265,7 +268,7 @@ __device__ __forceinline__ void vq_encode_fast_run_nks(const EncodeJob& job, int
 #pragma unroll
                     for (int x = i * 4 / NKS; x < (i + 1) * 4 / NKS; ++x) {
                         take_quad(set ^ 1, pu, x);
-                        if (WIDE && (x >> 2) == NB - 1) read_cn_quad(buf, u, 0, x & 3);      // this unit's, in the place of the ones just used
+                        if (ONCE && (x >> 2) == NB - 1) read_cn_quad(buf, u, 0, x & 3);      // this unit's, in the place of the ones just used
                     }
                     __builtin_amdgcn_sched_barrier(0);
                 }
@@ -273,7 +276,7 @@ __device__ __forceinline__ void vq_encode_fast_run_nks(const EncodeJob& job, int
                 // the argmin is worked out here: moved behind the branches that follow, it would keep the scores of several units alive
 #pragma unroll
                 for (int b = 0; b < TB; ++b) asm volatile("" : "+v"(best[b]), "+v"(grp[b]), "+v"(k0[b]), "+v"(k1[b]), "+v"(k2[b]), "+v"(til[b]));
-                if (WIDE) mask_cn(u, lim);
+                if (ONCE) mask_cn(u, lim);
             }
         }
 #pragma unroll

@@ -711,28 +711,35 @@ __global__ __launch_bounds__(256, 2) void vq_encode_bf16_fast_kernel(const Encod
 // The same body for groups of 128 values (vq_encode_fast_wide): a codeword fragment serves 64 tokens, and the scores never leave the registers.  16384 tokens
 // x 32 groups, K = 1024: 140 us (0.98 PFLOP/s; 131 with the norms as the accumulators' start), 1026 as score products in memory and an argmin over them, 736
 // with 32 tokens per workgroup; 1024 tokens 23 / 85 / 51.
-__global__ __launch_bounds__(256, 2) void vq_encode_bf16_fast128_kernel(const EncodeJob job, int chunk) {
+template <bool ONCE>
+__device__ __forceinline__ void vq_encode_fast128(const EncodeJob& job, int chunk) {
     __shared__ u32x4 cb_lds[kEncBufs * kEncCbSlots];    // 4 x 16 KiB: [64 codewords][16 pieces of 8 bf16], swizzled
     __shared__ f32x4 cn_lds[kEncBufs * kEncCnSlots];
     const int total = gridDim.x;
     const int q = total / 8, rr = total % 8, xcd = blockIdx.x % 8, slot = blockIdx.x / 8;
     const int vid = xcd < rr ? xcd * (q + 1) + slot : rr * (q + 1) + (xcd - rr) * q + slot;
     const int items = job.G * job.n_tb;
-    vq_encode_fast_run_nks<256, 2, 8>(job, min(vid * chunk, items), min((vid + 1) * chunk, items), cb_lds, cn_lds);
+    vq_encode_fast_run_nks<256, 2, 8, ONCE>(job, min(vid * chunk, items), min((vid + 1) * chunk, items), cb_lds, cn_lds);
 }
+__global__ __launch_bounds__(256, 2) void vq_encode_bf16_fast128_kernel(const EncodeJob job, int chunk) { vq_encode_fast128<true>(job, chunk); }
+__global__ __launch_bounds__(256, 2) void vq_encode_bf16_fast128_kernel_small(const EncodeJob job, int chunk) { vq_encode_fast128<false>(job, chunk); }
 
 // And for groups of 256: 32 tokens per wavefront, eight wavefronts to share a codebook tile.  One workgroup per unit: a tile is
 // 32 KiB.  16384 tokens x 16 groups, K = 1024: 146 us (0.94 PFLOP/s; 144 with the norms as the accumulators' start), 624 as score products, 646 with 32 tokens
-// per workgroup; 1024 tokens 30 / 45 / 44.  A codeword fragment serves 32 tokens only, so the LDS reads take as long as the MFMAs; all 16 fragments of a unit held at once spilled (427 us).
-__global__ __launch_bounds__(512, 2) void vq_encode_bf16_fast256_kernel(const EncodeJob job, int chunk) {
+// per workgroup; 1024 tokens 30 / 45 / 44.  A codeword fragment serves 32 tokens only, so the LDS reads take as long as the MFMAs; all 16 fragments of a unit held
+// at once spilled (427 us).
+template <bool ONCE>
+__device__ __forceinline__ void vq_encode_fast256(const EncodeJob& job, int chunk) {
     __shared__ u32x4 cb_lds[kEncBufs * 2 * kEncCbSlots];    // 4 x 32 KiB: [64 codewords][32 pieces of 8 bf16], swizzled
     __shared__ f32x4 cn_lds[kEncBufs * kEncCnSlots];
     const int total = gridDim.x;
     const int q = total / 8, rr = total % 8, xcd = blockIdx.x % 8, slot = blockIdx.x / 8;
     const int vid = xcd < rr ? xcd * (q + 1) + slot : rr * (q + 1) + (xcd - rr) * q + slot;
     const int items = job.G * job.n_tb;
-    vq_encode_fast_run_nks<512, 1, 16>(job, min(vid * chunk, items), min((vid + 1) * chunk, items), cb_lds, cn_lds);
+    vq_encode_fast_run_nks<512, 1, 16, ONCE>(job, min(vid * chunk, items), min((vid + 1) * chunk, items), cb_lds, cn_lds);
 }
+__global__ __launch_bounds__(512, 2) void vq_encode_bf16_fast256_kernel(const EncodeJob job, int chunk) { vq_encode_fast256<true>(job, chunk); }
+__global__ __launch_bounds__(512, 2) void vq_encode_bf16_fast256_kernel_small(const EncodeJob job, int chunk) { vq_encode_fast256<false>(job, chunk); }
 
 // vq_encode_stream_run (vq_encode_body.h) as a kernel of its own
 template <int NCH>
@@ -786,7 +793,10 @@ int launch_vq_encode(const astra_vq_desc& d, const void* x, int64_t ldx, int64_t
             const int64_t items = (int64_t)job.n_tb * G, chunk = ceil_div(items, (int64_t)(dg == 128 ? kEncSlots : kEncSlots / 2));
             if (items > 0x7fffffff) return ASTRA_ERR_SHAPE;
             const int grid = (int)ceil_div(items, chunk);
-            if (dg == 128) vq_encode_bf16_fast128_kernel<<<grid, 256, 0, s>>>(job, (int)chunk);
+            const bool small = (int64_t)K * dg < (1 << 17);
+            if (dg == 128 && small) vq_encode_bf16_fast128_kernel_small<<<grid, 256, 0, s>>>(job, (int)chunk);
+            else if (dg == 128) vq_encode_bf16_fast128_kernel<<<grid, 256, 0, s>>>(job, (int)chunk);
+            else if (small) vq_encode_bf16_fast256_kernel_small<<<grid, 512, 0, s>>>(job, (int)chunk);
             else vq_encode_bf16_fast256_kernel<<<grid, 512, 0, s>>>(job, (int)chunk);
             return launch_status();
         }

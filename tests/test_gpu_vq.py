@@ -303,11 +303,11 @@ def test_streamed_wide_groups(T, G, K, dg):
     assert gpu_vq_encode(x, cb, "bf16").max() < K // 2
 
 
-@pytest.mark.parametrize("T,G,K,dg", [(40, 7, 1024, 128), (40, 7, 1024, 192), (40, 16, 1024, 256), (8200, 2, 64, 128), (6200, 2, 64, 256)])
+@pytest.mark.parametrize("T,G,K,dg", [(40, 7, 1024, 128), (40, 7, 1024, 192), (40, 16, 1024, 256), (8200, 2, 1024, 128), (8200, 2, 512, 256)])
 def test_distances_of_wide_groups_are_rounded_once(T, G, K, dg):
     """Codewords of one norm n, and products with x that move the nearest by 1.5 or 3 units in the last place of n, a quarter of one per 16 values: -2 x.c is
-    summed by itself and the norm added once; added to n one by one the quarters would be lost and the lowest code win.  Streamed encodes and both
-    forms of the matrix-core body (vq_encode_fast_wide)."""
+    summed by itself and the norm added once; added to n one by one the quarters would be lost and the lowest code win.  Streamed encodes, and both
+    forms of the matrix-core body (vq_encode_fast_wide) for codebooks of 2^17 elements, whose score products they stand in for."""
     from gpu_util import gpu_vq_encode
     n = dg if dg == 192 else 3 * dg // 4                       # 96 or 192, halfway between two powers of two
     x = np.zeros((T, G, dg), np.float32)

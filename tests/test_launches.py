@@ -368,3 +368,10 @@ def test_cut_walks_of_other_entry_points(tmp_path):
 def test_rebuilt_rows_come_with_the_normalisation_of_wide_rows_too(tmp_path):
     call = dict(entry="block", d=1088, hq=4, hkv=2, dh=64, n_local=33, n_nonlocal=66, causal=True, norm="rmsnorm", mlp="gelu_tanh", dff=128, groups=16, words=256)
     assert kernels(record([call], tmp_path)[0])[0] == "norm_decode_kernel<unsigned char, false>"
+
+
+def test_encode_bodies_of_wide_groups_by_codebook(tmp_path):
+    """From 2^17 elements on, where score products were used, the norm is added to the finished sum (tests/test_gpu_vq.py)."""
+    sizes = [(128, 1020, "_small"), (128, 1024, ""), (256, 508, "_small"), (256, 512, "")]
+    for (dg, k, form), r in zip(sizes, record([dict(entry="encode", tokens=8200, groups=16, words=k, d=16 * dg) for dg, k, _ in sizes], tmp_path)):
+        assert kernels(r) == [f"vq_encode_bf16_fast{dg}_kernel{form}"], (dg, k, kernels(r))
