@@ -477,7 +477,8 @@ static int layer_forward_impl(const astra_layer_desc* desc, const void* x_local,
                           to_attention ? &enc_in_attention : nullptr, &fetch);
     if (rc) return rc;
     if (enc_pending && !enc_in_attention) {
-        rc = launch_vq_encode(vq, ej.x, pl.D, at.n_local, codebook, cnorm, codes_local_out, s);
+        // one group: its products ride with the projections whatever the codebook's size, where those are not left out for many tokens
+        rc = launch_vq_encode(vq, ej.x, pl.D, at.n_local, codebook, cnorm, codes_local_out, s, vq.n_groups == 1);
         if (rc) return rc;
     }
     mark(2, s);

@@ -136,8 +136,9 @@ int check_attn_desc(const astra_attn_desc* d);
 
 // ---- kernels' host launchers (each returns an astra_status) ---------------------------------
 int launch_vq_prepare(const astra_vq_desc& d, const void* codebook, float* cnorm, hipStream_t s);
+// in_place_of_scores: distances rounded as score products' are, for codebooks of any size
 int launch_vq_encode(const astra_vq_desc& d, const void* x, int64_t ldx, int64_t n_tokens, const void* codebook,
-                     const float* cnorm, void* codes, hipStream_t s);
+                     const float* cnorm, void* codes, hipStream_t s, bool in_place_of_scores = false);
 // wide groups (dg a multiple of 64 above 64), bf16
 bool vq_encode_wide_ok(int K, int dg, int64_t ldx);
 int launch_vq_encode_wide(const astra_vq_desc& d, const void* x, int64_t ldx, int64_t n_tokens, const void* codebook,

@@ -756,7 +756,7 @@ __global__ __launch_bounds__(64 * kStreamWaves) void vq_encode_bf16_stream_kerne
 }
 
 int launch_vq_encode(const astra_vq_desc& d, const void* x, int64_t ldx, int64_t n_tokens, const void* codebook,
-                     const float* cnorm, void* codes, hipStream_t s) {
+                     const float* cnorm, void* codes, hipStream_t s, bool in_place_of_scores) {
     if (n_tokens == 0) return ASTRA_OK;
     const int G = d.n_groups, K = d.codebook_size, dg = d.d_model / G;
     if (n_tokens > 0x7fffffff / 2) return ASTRA_ERR_SHAPE;
@@ -793,7 +793,7 @@ int launch_vq_encode(const astra_vq_desc& d, const void* x, int64_t ldx, int64_t
             const int64_t items = (int64_t)job.n_tb * G, chunk = ceil_div(items, (int64_t)(dg == 128 ? kEncSlots : kEncSlots / 2));
             if (items > 0x7fffffff) return ASTRA_ERR_SHAPE;
             const int grid = (int)ceil_div(items, chunk);
-            const bool small = (int64_t)K * dg < (1 << 17);
+            const bool small = !in_place_of_scores && (int64_t)K * dg < (1 << 17);
             if (dg == 128 && small) vq_encode_bf16_fast128_kernel_small<<<grid, 256, 0, s>>>(job, (int)chunk);
             else if (dg == 128) vq_encode_bf16_fast128_kernel<<<grid, 256, 0, s>>>(job, (int)chunk);
             else if (small) vq_encode_bf16_fast256_kernel_small<<<grid, 512, 0, s>>>(job, (int)chunk);

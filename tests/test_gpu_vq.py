@@ -303,12 +303,9 @@ def test_streamed_wide_groups(T, G, K, dg):
     assert gpu_vq_encode(x, cb, "bf16").max() < K // 2
 
 
-@pytest.mark.parametrize("T,G,K,dg", [(40, 7, 1024, 128), (40, 7, 1024, 192), (40, 16, 1024, 256), (8200, 2, 1024, 128), (8200, 2, 512, 256)])
-def test_distances_of_wide_groups_are_rounded_once(T, G, K, dg):
-    """Codewords of one norm n, and products with x that move the nearest by 1.5 or 3 units in the last place of n, a quarter of one per 16 values: -2 x.c is
-    summed by itself and the norm added once; added to n one by one the quarters would be lost and the lowest code win.  Streamed encodes, and both
-    forms of the matrix-core body (vq_encode_fast_wide) for codebooks of 2^17 elements, whose score products they stand in for."""
-    from gpu_util import gpu_vq_encode
+def distances_of_few_units(T, G, K, dg):
+    """Codewords of one norm n, and products with x that move the nearest by 1.5 or 3 units in the last place of n, a quarter of one per 16 values: added to n
+    one by one the quarters would be lost and the lowest code win.  The nearest to the even tokens is K - 1, to the odd ones K - 2."""
     n = dg if dg == 192 else 3 * dg // 4                       # 96 or 192, halfway between two powers of two
     x = np.zeros((T, G, dg), np.float32)
     x[:, :, :n] = 2.0 ** (np.floor(np.log2(n)) - 23) / 128
@@ -317,6 +314,29 @@ def test_distances_of_wide_groups_are_rounded_once(T, G, K, dg):
     half = np.repeat([1.0, -1.0], n // 2).astype(np.float32)
     cb = np.zeros((G, K, dg), np.float32)
     cb[:, :, :n] = rng.permuted(np.broadcast_to(half, (G, K, n)), axis=2)                   # x.c = 0
-    cb[:, K - 1, :n], cb[:, K - 2, :n] = 1.0, -1.0             # the nearest to the even tokens, to the odd ones
-    codes = gpu_vq_encode(x.reshape(T, -1), cb, "bf16")
+    cb[:, K - 1, :n], cb[:, K - 2, :n] = 1.0, -1.0
+    return x.reshape(T, -1), cb
+
+
+@pytest.mark.parametrize("T,G,K,dg", [(40, 7, 1024, 128), (40, 7, 1024, 192), (40, 16, 1024, 256), (8200, 2, 1024, 128), (8200, 2, 512, 256)])
+def test_distances_of_wide_groups_are_rounded_once(T, G, K, dg):
+    """-2 x.c is summed by itself and the norm added once.  Streamed encodes, and both forms of the matrix-core body (vq_encode_fast_wide) for codebooks of 2^17
+    elements, whose score products they stand in for."""
+    from gpu_util import gpu_vq_encode
+    x, cb = distances_of_few_units(T, G, K, dg)
+    codes = gpu_vq_encode(x, cb, "bf16")
+    assert (codes[0::2] == K - 1).all() and (codes[1::2] == K - 2).all()
+
+
+@pytest.mark.parametrize("T,K,D", [(4000, 512, 128), (12000, 512, 128), (17000, 256, 256)])
+def test_distances_of_one_group_in_a_layer_are_rounded_once(T, K, D):
+    """A codebook of any size: by score products, and by the bodies that stand in for them beside many rows (as tests/test_launches.py checks)."""
+    from gpu_util import LayerOnGpu
+    cfg = wl.LayerConfig("one_group", "bf16", D, D // 64, 2, 64, T, 1, 1, K)
+    x, cb = distances_of_few_units(T, 1, K, D)
+    rng = np.random.default_rng(92)
+    data = {n: wl.round_to_bf16(rng.standard_normal((D, 128 if n in ("wk", "wv") else D), dtype=np.float32)) for n in ("wq", "wk", "wv", "wo")}
+    layer = LayerOnGpu(cfg, dict(data, codebook=cb), x, np.zeros((0, 1), np.int64), 0)
+    layer.run()
+    codes = layer.results()[1]
     assert (codes[0::2] == K - 1).all() and (codes[1::2] == K - 2).all()

@@ -375,3 +375,11 @@ def test_encode_bodies_of_wide_groups_by_codebook(tmp_path):
     sizes = [(128, 1020, "_small"), (128, 1024, ""), (256, 508, "_small"), (256, 512, "")]
     for (dg, k, form), r in zip(sizes, record([dict(entry="encode", tokens=8200, groups=16, words=k, d=16 * dg) for dg, k, _ in sizes], tmp_path)):
         assert kernels(r) == [f"vq_encode_bf16_fast{dg}_kernel{form}"], (dg, k, kernels(r))
+
+
+def test_encode_of_one_group_beside_many_rows(tmp_path):
+    """A layer's single group has score products whatever its codebook's size; the body that replaces them for many rows adds the norm once, as they do."""
+    common = dict(entry="layer", hkv=2, dh=64, groups=1, n_nonlocal=64)
+    layers = [dict(common, d=dg, hq=dg // 64, words=k, n_local=t) for dg, k, t in ((128, 512, 4000), (128, 512, 12000), (256, 256, 17000))]
+    for c, r, enc in zip(layers, record(layers, tmp_path), ("vq_argmin_scores_kernel", "vq_encode_bf16_fast128_kernel", "vq_encode_bf16_fast256_kernel")):
+        assert [k.split("<")[0] for k in kernels(r) if k.startswith("vq_")] == [enc], (c, kernels(r))
