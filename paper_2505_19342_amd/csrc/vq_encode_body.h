@@ -466,7 +466,8 @@ inline bool vq_encode_fast_wide(int64_t n_tokens, int G, int K, int dg, int64_t 
 }
 // Where such groups are better off without score products: of 128 where the products would be more than one launch, of 192 and 256 where they would be
 // three or more, or two with more than 192 tokens (with / without scores: 16 groups of 256, K = 1024, 17 tokens 14.2 / 11.4 us, 128 19.7 / 13.0, 400 35.9 / 13.8; K = 4096 40 tokens 27.6 / 29.4,
-// 250 45.5 / 31.7; 8 groups 100 tokens, K = 768 11.7 / 11.4, 4096 23.3 / 29.3, 500 39.8 / 30.4; 8 of 192, K = 2048 64 tokens 13.9 / 15.8, 500 29.8 / 16.7);
+// 250 45.5 / 31.7; 8 groups 100 tokens, K = 768 11.7 / 11.4, 4096 23.3 / 29.3, 500 39.8 / 30.4; 8 of 192, K = 2048 64 tokens 13.9 / 15.8, 500 29.8 / 16.7,
+// K = 1024 2000 tokens 38.7 / 21.7, 16384 292 / 161);
 // and with few groups once all units have a block, of 256 with up to 8 groups one and a half (4096 codewords, 2 groups: 4300 tokens 80 / 93, 8192 143 / 96).
 inline bool vq_encode_without_scores(int64_t n_tokens, int G, int K, int dg, int64_t ldx) {
     if (dg == 128 && G > kMaxGemmProblems) return true;
