@@ -4,6 +4,23 @@
 
 namespace astra {
 
+// The problem of a tile.  With tiles of 64 its fields are read from the arguments where they are needed: a copy, in one trip, makes 266 registers of 242, one
+// wavefront per SIMD instead of two (700 x 1536 outputs, K = 64: 13.9 us, 20.7 with the copy).  Smaller tiles have the registers for it.
+struct ProblemInPlace {
+    const GemmProblem& p;
+    int tile, tiles_m;
+};
+template <int T, bool ONE>
+__device__ __forceinline__ auto f32_problem(const GemmBatch& b, int tile) {
+    if constexpr (T < 4) {
+        return find_problem<ONE ? kOneProblem : kManyProblems>(b, tile);
+    } else {
+        int i = 0;
+        while (i + 1 < b.n && tile >= b.tile_begin[i + 1]) ++i;
+        return ProblemInPlace{b.p[i], tile - b.tile_begin[i], b.tiles_m[i]};
+    }
+}
+
 // ------------------------------------------------------------------------------------------------
 // fp32, matrix cores (16x16x4: fp32 products, fp32 sums).  A workgroup of four wavefronts owns a 16 T x 16 T output tile, and every wavefront
 // computes all of it over every fourth slice of 16 of the contraction, straight from global memory: lane l holds row l % 16 of each operand, and since
@@ -18,7 +35,7 @@ template <int T, bool ONE>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmBatch batch) {
     constexpr int BT = 16 * T, WAVES = 4, PD = 4 / T, LDN = BT + 4;
     __shared__ __align__(16) float red[WAVES * BT * LDN];
-    const TileProblem tp = find_problem<ONE ? kOneProblem : kManyProblems>(batch, blockIdx.x);
+    const auto tp = f32_problem<T, ONE>(batch, blockIdx.x);
     const GemmProblem& P = tp.p;
     const int tile = tp.tile, m0 = tile % tp.tiles_m * BT, n0 = tile / tp.tiles_m * BT;
     const int M = P.M, N = P.N, K = P.K;
@@ -145,7 +162,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmBatch batch) {
 
 template <int T>
 static void launch_f32_tiles(int tiles, const GemmBatch& batch, hipStream_t s) {
-    if (batch.n == 1) gemm_f32_kernel<T, true><<<tiles, 256, 0, s>>>(batch);
+    if (T < 4 && batch.n == 1) gemm_f32_kernel<T, T < 4><<<tiles, 256, 0, s>>>(batch);
     else gemm_f32_kernel<T, false><<<tiles, 256, 0, s>>>(batch);
 }
 

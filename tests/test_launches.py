@@ -383,3 +383,11 @@ def test_encode_of_one_group_beside_many_rows(tmp_path):
     layers = [dict(common, d=dg, hq=dg // 64, words=k, n_local=t) for dg, k, t in ((128, 512, 4000), (128, 512, 12000), (256, 256, 17000))]
     for c, r, enc in zip(layers, record(layers, tmp_path), ("vq_argmin_scores_kernel", "vq_encode_bf16_fast128_kernel", "vq_encode_bf16_fast256_kernel")):
         assert [k.split("<")[0] for k in kernels(r) if k.startswith("vq_")] == [enc], (c, kernels(r))
+
+
+def test_large_tiles_of_fp32_products_have_one_form(tmp_path):
+    """Tiles of 64 hold too much for the form that copies its one problem's arguments."""
+    call = dict(entry="block", dtype="f32", hq=1, hkv=1, dh=64, n_local=700, n_nonlocal=0, norm="layernorm", mlp="gelu_tanh", dff=64, groups=1, words=16)
+    small, large = (kernels(r) for r in record([dict(call, d=192), dict(call, d=1536)], tmp_path))
+    assert not any(k.startswith("gemm_f32_kernel<4") for k in small) and any(k.endswith(", true>") for k in small if k.startswith("gemm_f32")), small
+    assert [k for k in large if k.startswith("gemm_f32_kernel<4")] == 2 * ["gemm_f32_kernel<4, false>"], large
