@@ -161,10 +161,11 @@ __global__ __launch_bounds__(kWave) void norm_wave_kernel(const float* __restric
     norm_row_wave<OutT>(x, blockIdx.x, D, kind, eps, gain, bias, out);
 }
 
+// Eight wavefronts per SIMD: left to itself the compiler takes 68 registers for bf16 rows, which leaves seven (2000 rows of 8192: 17.2 us, 12000 of 1536: 21.9).
 template <typename OutT, bool VEC>
-__global__ __launch_bounds__(kNormThreads) void norm_kernel(const float* __restrict__ x, int D, int kind, float eps,
-                                                            const float* __restrict__ gain, const float* __restrict__ bias,
-                                                            OutT* __restrict__ out) {
+__global__ __launch_bounds__(kNormThreads, 8) void norm_kernel(const float* __restrict__ x, int D, int kind, float eps,
+                                                               const float* __restrict__ gain, const float* __restrict__ bias,
+                                                               OutT* __restrict__ out) {
     norm_row<OutT, VEC>(x, D, kind, eps, gain, bias, out);
 }
 
